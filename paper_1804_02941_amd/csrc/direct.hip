@@ -20,9 +20,7 @@
 // and an or per dword.  The sign bit of the fp4 code is the activation bit itself, so the
 // accumulators hold -s1 (bit 1 = -1.0); the epilogue multiplies by (beta - alpha) instead.
 //
-// A wavefront computes 64 pixels x 128 filters per tile (or the two 64-filter halves one after
-// the other, which lets the stores of the first half drain under the multiplies of the second),
-// workgroups are persistent and walk over pixel tiles; the loop over tiles has no barrier, the
+// A wavefront computes 64 pixels x 128 filters per tile, workgroups are persistent and walk over pixel tiles; the loop over tiles has no barrier, the
 // wavefronts of a workgroup drift apart and one's stores overlap another's multiplies.
 #include "dab_internal.h"
 #include "mfma_tools.h"
@@ -90,9 +88,6 @@ __device__ __forceinline__ void store_u32(uint32_t* ptr, uint32_t v) {
 }
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store_u32x2(uint32_t* ptr, v2u v) {
-    asm volatile("global_store_dwordx2 %0, %1, off" : : "v"(ptr), "v"(v) : "memory");
-}
 __device__ __forceinline__ void store_u32x4(uint32_t* ptr, v4u v) {
     asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(ptr), "v"(v) : "memory");
 }
@@ -142,7 +137,6 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
                                                              const float* __restrict__ tau_out,
                                                              uint32_t* __restrict__ out_bits) {
     constexpr int NFP = 4;                                         // 32-filter column blocks of a tile
-    constexpr int NPASS = 1;
     extern __shared__ __align__(16) uint4 panel[];                 // [n_ent][4][64 lanes] 16-byte groups; entries from nk on are zero
     __shared__ __align__(16) float sA_lds[8][64];                  // row sums of each wavefront's 64 pixels
     __shared__ __align__(16) float col_lds[3][kDirNTile];                        // beta - alpha, beta, tau of the tile's columns
@@ -160,11 +154,50 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     const int mt_first = blockIdx.x - ntile * g.wg_per_ntile;
     const int f0 = ntile * kDirNTile;
 
+    // the packed activations as a raw buffer: offsets past its end read as zero
+    const uint64_t a_addr = reinterpret_cast<uint64_t>(A);
+    const v4s arsrc = {static_cast<int>(static_cast<uint32_t>(a_addr)), static_cast<int>(static_cast<uint32_t>(a_addr >> 32) & 0xFFFFu),
+                       static_cast<int>(g.a_bytes), 0x00020000};
+    uint32_t base[2], tbits[2];
+    auto locate = [&](int m_base) {
+        // this lane's two pixels (row blocks of 32): byte offset of word h*WH of the window's first tap
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int m = min(m_base + i * 32 + p, g.M - 1);
+            const int b = fdiv(m, g.d_HoWo);
+            const int r = m - b * g.HoWo;
+            const int oy = fdiv(r, g.d_Wo);
+            const int ox = r - oy * g.Wo;
+            const int iy0 = oy * g.sh - g.ph, ix0 = ox * g.sw - g.pw;
+            base[i] = static_cast<uint32_t>(((b * g.H + iy0) * g.W + ix0) * g.pix_bytes + h * g.WH * 4);
+            tbits[i] = 0xFFFFFFFFu;
+            if (PAD) {
+                // bit t: tap t of the window lies inside the image (at most 32 taps, checked on the host): a run
+                // of columns, the same for every window row inside
+                const int x_lo = max(0, -ix0), n_in = min(g.kw, g.W - ix0) - x_lo;
+                const uint32_t cols = n_in > 0 ? (0xFFFFFFFFu >> (32 - n_in)) << x_lo : 0u;
+                uint32_t bitsv = 0;
+                for (int ky = 0; ky < g.kh; ++ky)
+                    bitsv |= (static_cast<unsigned>(iy0 + ky) < static_cast<unsigned>(g.H) ? cols : 0u) << (ky * g.kw);
+                tbits[i] = bitsv;
+            }
+        }
+    };
+    locate((mt_first * waves + wave) * 64);
+    // the first tap's words on their way into the caches while the panel is built (their round trip to
+    // memory would otherwise follow it); the values are not used
+    uint32_t warm[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        warm[i] = __builtin_amdgcn_raw_buffer_load_b32(
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(A), 0, static_cast<int>(g.a_bytes), 0x00020000),
+            static_cast<int>(base[i]), 0, 0);
+
     // ---- the B panel: bits -> fp4, once per workgroup.  Which filter sits in column n of column
     // block j is free to choose.  With fp32 output it is filter 4n + j: a lane then holds four
     // neighbouring filters of an output row in its four blocks and writes them with one 16-byte
     // store, a half-wavefront a whole 512-byte row segment.  With bit output it is filter 32j + n,
-    // so that the ballot of a block is a packed word.  Item = (k-step, half): lane n reads the mask
+    // so that a block's filters are the bits of a packed word.  Item = (k-step, half): lane n reads the mask
     // words of its four filters (fp32 output: sixteen contiguous bytes).
     {
         // five entries of a wavefront at a time: their loads are in flight together (with eight
@@ -218,12 +251,8 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
         const float al = alpha[f], be = beta[f];
         col_lds[0][tid] = be - al;                                 // the accumulators hold -s1
         col_lds[1][tid] = be;
-        col_lds[2][tid] = (BITS && tau_out) ? tau_out[f] : 0.0f;
+        col_lds[2][tid] = f0 + tid >= g.F ? __builtin_nanf("") : (BITS && tau_out) ? tau_out[f] : 0.0f;
     }
-    // the packed activations as a raw buffer: offsets past its end read as zero
-    const uint64_t a_addr = reinterpret_cast<uint64_t>(A);
-    const v4s arsrc = {static_cast<int>(static_cast<uint32_t>(a_addr)), static_cast<int>(static_cast<uint32_t>(a_addr >> 32) & 0xFFFFu),
-                       static_cast<int>(g.a_bytes), 0x00020000};
     // the outputs as raw buffers (stores past their end are dropped)
     auto as_buffer = [](const void* ptr, uint32_t bytes) {
         const uint64_t a = reinterpret_cast<uint64_t>(ptr);
@@ -233,6 +262,7 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     const v4s yrsrc = as_buffer(Y, g.y_bytes);
     const v4s drsrc = as_buffer(dbg_s1, dbg_s1 ? g.y_bytes : 0u);
     __syncthreads();                                               // the panel is complete
+    asm volatile("" : : "v"(warm[0]), "v"(warm[1]));
 
     // the two masks of the expansion in registers (as literals they would split the and-or in two)
     uint32_t k8, k2;
@@ -242,33 +272,9 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     for (int mt = mt_first; mt < g.n_mtiles; mt += g.wg_per_ntile) {
         const int m_base = (mt * waves + wave) * 64;
         if (m_base >= g.M) continue;
-        // this lane's two pixels (row blocks of 32): byte offset of word h*WH of the window's first tap
-        uint32_t base[2], tbits[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int m = min(m_base + i * 32 + p, g.M - 1);
-            const int b = fdiv(m, g.d_HoWo);
-            const int r = m - b * g.HoWo;
-            const int oy = fdiv(r, g.d_Wo);
-            const int ox = r - oy * g.Wo;
-            const int iy0 = oy * g.sh - g.ph, ix0 = ox * g.sw - g.pw;
-            base[i] = static_cast<uint32_t>(((b * g.H + iy0) * g.W + ix0) * g.pix_bytes + h * g.WH * 4);
-            tbits[i] = 0xFFFFFFFFu;
-            if (PAD) {
-                // bit t: tap t of the window lies inside the image (at most 32 taps, checked on the host)
-                uint32_t bitsv = 0;
-                int t = 0;
-                for (int ky = 0; ky < g.kh; ++ky)
-                    for (int kx = 0; kx < g.kw; ++kx, ++t) {
-                        const bool in = static_cast<unsigned>(iy0 + ky) < static_cast<unsigned>(g.H) &&
-                                        static_cast<unsigned>(ix0 + kx) < static_cast<unsigned>(g.W);
-                        bitsv |= (in ? 1u : 0u) << t;
-                    }
-                tbits[i] = bitsv;
-            }
-        }
+        if (mt != mt_first) locate(m_base);
         int ones[2] = {0, 0};
-        for (int pass = 0; pass < NPASS; ++pass) {
+        {
             v16f acc[2][NFP];
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -301,7 +307,7 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
             };
 #pragma unroll
             for (int d = 0; d < PF - 1; ++d) issue(d);
-            const uint4* bptr = bp + pass * NFP * 64;              // B fragments of the round's first k-step
+            const uint4* bptr = bp;                                // B fragments of the round's first k-step
             // B fragments: one register set; a fragment is reloaded for the next k-step right behind the
             // two multiplies that read it, a whole k-step before its next use
             uint4 bq[NFP];
@@ -329,10 +335,8 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
                 // the first group's words: PF - 2 younger groups are in flight
                 wait_words<2 * (PF - 2)>(xq[0][0], xq[0][1]);
                 const uint32_t x0 = word_of<LW>(xq[0][0], 0), x1 = word_of<LW>(xq[0][1], 0);
-                if (pass == 0) {
-                    ones[0] += __builtin_popcount(x0);
-                    ones[1] += __builtin_popcount(x1);
-                }
+                ones[0] += __builtin_popcount(x0);
+                ones[1] += __builtin_popcount(x1);
                 an[0] = expand_a(x0, m8[0], m2[0]);
                 an[1] = expand_a(x1, m8[1], m2[1]);
             }
@@ -343,46 +347,45 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
                     for (int u = 0; u < LW; ++u) {
                         const int q = d * LW + u;                  // k-step of the round
                         const v4i a0 = an[0], a1 = an[1];
-                        // the slot the previous group emptied is refilled PF - 1 groups ahead
-                        if (u == 0) issue((d + PF - 1) % PF);
-                        // the next k-step's A fragments: the next word of this group, or the first
-                        // of the next group (of the next round's first slot at the end of a round)
-                        {
-                            const int un = u + 1 < LW ? u + 1 : 0;
-                            const int dn = u + 1 < LW ? d : (d + 1) % PF;
-                            if (un == 0) {
-                                tap_masks(m8, m2);
-                                wait_words<2 * (PF - 2)>(xq[dn][0], xq[dn][1]);   // PF - 2 younger groups are in flight
-                            }
-                            const uint32_t x0 = word_of<LW>(xq[dn][0], un), x1 = word_of<LW>(xq[dn][1], un);
-                            if (pass == 0) {
-                                ones[0] += __builtin_popcount(x0);
-                                ones[1] += __builtin_popcount(x1);
-                            }
-                            an[0] = expand_a(x0, m8[0], m2[0]);
-                            an[1] = expand_a(x1, m8[1], m2[1]);
-                        }
-#pragma unroll
-                        for (int j = 0; j < NFP; ++j) {
+                        // the next k-step's words: the next word of this group, or the first of the
+                        // next group (of the next round's first slot at the end of a round)
+                        const int un = u + 1 < LW ? u + 1 : 0;
+                        const int dn = u + 1 < LW ? d : (d + 1) % PF;
+                        uint32_t x0 = 0, x1 = 0;
+                        // Two multiplies, the reload of the fragment they have read and a quarter of the
+                        // next step's vector work at a time; nothing moves across the fences between
+                        // them.  (Left to the scheduler's own groups the reload ended up right in front
+                        // of its use and every pair of multiplies waited out an LDS round trip: 28-34 ns
+                        // a multiply instead of 17.)
+                        for_each_column<NFP>([&](auto jc) {
+                            constexpr int j = decltype(jc)::value;
                             const uint4 bu = bq[j];
                             const v4i bv = {static_cast<int>(bu.x), static_cast<int>(bu.y), static_cast<int>(bu.z),
                                             static_cast<int>(bu.w)};
-                            acc[0][j] = mfma_fp4(a0, bv, acc[0][j]);
-                            acc[1][j] = mfma_fp4(a1, bv, acc[1][j]);
+                            // packed signs: the blocks transposed, so that a lane holds one pixel's filters
+                            acc[0][j] = BITS ? mfma_fp4(bv, a0, acc[0][j]) : mfma_fp4(a0, bv, acc[0][j]);
+                            acc[1][j] = BITS ? mfma_fp4(bv, a1, acc[1][j]) : mfma_fp4(a1, bv, acc[1][j]);
                             // (the panel ends with one entry more than the loop multiplies)
                             bq[j] = bptr[(q + 1) * 256 + j * 64];
-                        }
-                        // issue order of the k-step: every LDS read and the vector work of the next
-                        // step's expansion in the shadow of a multiply
-#pragma unroll
-                        for (int j = 0; j < NFP; ++j) {
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one MFMA
-                            // (fewer than a k-step holds, so that no group pulls the next step's work forward)
-                            __builtin_amdgcn_sched_group_barrier(0x002, NFP == 4 ? 2 : 4, 0);   // vector ALU
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one MFMA
-                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                  // one LDS read
-                            __builtin_amdgcn_sched_group_barrier(0x002, NFP == 4 ? 2 : 4, 0);   // vector ALU
-                        }
+                            if constexpr (j == 0) {
+                                // the slot the previous group emptied is refilled PF - 1 groups ahead
+                                if (u == 0) issue((d + PF - 1) % PF);
+                            } else if constexpr (j == 1) {
+                                if (un == 0) {
+                                    tap_masks(m8, m2);
+                                    wait_words<2 * (PF - 2)>(xq[dn][0], xq[dn][1]);   // PF - 2 younger groups are in flight
+                                }
+                                x0 = word_of<LW>(xq[dn][0], un);
+                                x1 = word_of<LW>(xq[dn][1], un);
+                                ones[0] += __builtin_popcount(x0);
+                                ones[1] += __builtin_popcount(x1);
+                            } else if constexpr (j == 2) {
+                                an[0] = expand_a(x0, m8[0], m2[0]);
+                            } else {
+                                an[1] = expand_a(x1, m8[1], m2[1]);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        });
                     }
                 }
             }
@@ -392,91 +395,83 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
 #pragma unroll
             for (int d = 0; d < PF; ++d) asm volatile("s_waitcnt vmcnt(0)" : "+v"(xq[d][0]), "+v"(xq[d][1]));
             // ---- sA of this lane's rows: ones of both halves of a pixel, taps inside the image
-            if (pass == 0) {
+            float sAv[2];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int both = ones[i] + __shfl_xor(ones[i], 32, 64);
-                    const int taps = PAD ? __builtin_popcount(tbits[i]) : g.T;
-                    ones[i] = 2 * both - taps * g.C;
-                }
-                // lane l holds row l of the 64 (row block l / 32, pixel l % 32)
-                sA_lds[wave][lane] = static_cast<float>(h ? ones[1] : ones[0]);
+            for (int i = 0; i < 2; ++i) {
+                const int both = ones[i] + __shfl_xor(ones[i], 32, 64);
+                const int taps = PAD ? __builtin_popcount(tbits[i]) : g.T;
+                sAv[i] = static_cast<float>(2 * both - taps * g.C);
             }
-            // (a wavefront reads back only what it wrote itself: no workgroup barrier needed)
+            // lane l holds row l of the 64 (row block l / 32, pixel l % 32); a wavefront reads back only
+            // what it wrote itself: no workgroup barrier needed
+            if (!BITS) sA_lds[wave][lane] = h ? sAv[1] : sAv[0];
 
             // ---- epilogue.  Register v of a 32x32 block is row (v/4)*8 + (lane/32)*4 + v%4, column
             // lane%32.  y = (beta - alpha)*(-s1) + beta*sA.
-            const int fp0 = f0 + pass * NFP * 32;                  // first filter of this pass
-            float4 s4[2][4];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    s4[i][q] = *reinterpret_cast<const float4*>(&sA_lds[wave][i * 32 + q * 8 + h * 4]);
-            if (BITS) {
-                // Column n of block j is filter 32j + n: the ballot of one accumulator register is the
-                // 32-filter word of two rows (lanes 0..31 and 32..63); lane l collects the words of row
-                // l and stores them side by side.
-                float dcol[NFP], bcol[NFP], tcol[NFP];
+            if constexpr (BITS) {
+                // The blocks are transposed here: register v of block j is filter 32j + (v/4)*8 + (lane/32)*4
+                // + v%4, the lane's pixel is column lane%32, so a lane gathers half of a word's bits by
+                // itself (a compare, a select and an or each) and one exchange with the lane that has the
+                // same pixel's other filters completes the words.  (Pixels in rows, a ballot per
+                // register and two lane writes to drop it into its row took 3.3-4.3 us per tile, more
+                // than a third of the reduction; this form measured 1.6-2.)  Columns past F compare
+                // against NaN.
+                uint32_t half[2][NFP];
 #pragma unroll
                 for (int j = 0; j < NFP; ++j) {
-                    dcol[j] = col_lds[0][(pass * NFP + j) * 32 + p];
-                    bcol[j] = col_lds[1][(pass * NFP + j) * 32 + p];
-                    tcol[j] = col_lds[2][(pass * NFP + j) * 32 + p];
-                }
-                int wb[NFP];
-#pragma unroll
-                for (int j = 0; j < NFP; ++j) wb[j] = 0;
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
+                    half[0][j] = half[1][j] = 0u;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const float sv[4] = {s4[i][q].x, s4[i][q].y, s4[i][q].z, s4[i][q].w};
+                        const int c0 = j * 32 + q * 8 + h * 4;
+                        const float4 d4 = *reinterpret_cast<const float4*>(&col_lds[0][c0]);
+                        const float4 b4 = *reinterpret_cast<const float4*>(&col_lds[1][c0]);
+                        const float4 t4 = *reinterpret_cast<const float4*>(&col_lds[2][c0]);
+                        const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, bv[4] = {b4.x, b4.y, b4.z, b4.w}, tv[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const int r0 = i * 32 + q * 8 + t;         // row of lanes 0..31; lanes 32..63 hold r0 + 4
+                        for (int t = 0; t < 4; ++t)
 #pragma unroll
-                            for (int j = 0; j < NFP; ++j) {
-                                const float y = fmaf(dcol[j], acc[i][j][q * 4 + t], bcol[j] * sv[t]);
-                                const bool bit = fp0 + j * 32 + p < g.F && y >= tcol[j];
-                                const unsigned long long mask = __ballot(bit);
-                                // The mask is written by a vector compare.  On this ISA a vector instruction that reads a scalar
-                                // register needs two wait states behind the vector instruction that wrote it; the compiler
-                                // inserts them for its own instructions but does not look into inline assembly (without them the
-                                // lane write took the register's previous content, the compare before the F mask: bits past F set).
-                                asm volatile("s_nop 1\n\tv_writelane_b32 %0, %1, %2"
-                                             : "+v"(wb[j]) : "s"(static_cast<uint32_t>(mask)), "n"(r0));
-                                asm volatile("v_writelane_b32 %0, %1, %2"
-                                             : "+v"(wb[j]) : "s"(static_cast<uint32_t>(mask >> 32)), "n"(r0 + 4));
+                            for (int i = 0; i < 2; ++i) {
+                                const float y = fmaf(dv[t], acc[i][j][q * 4 + t], bv[t] * sAv[i]);
+                                half[i][j] |= y >= tv[t] ? 1u << (q * 8 + t) : 0u;
                             }
-                        }
                     }
+                }
+                // lane l stores row l of the 64: block i = h of its own pixel
+                uint32_t wb[NFP];
+#pragma unroll
+                for (int j = 0; j < NFP; ++j) {
+                    const uint32_t mine = (h ? half[1][j] : half[0][j]) << (4 * h);
+                    const uint32_t gives = (h ? half[0][j] : half[1][j]) << (4 * h);
+                    wb[j] = mine | static_cast<uint32_t>(__shfl_xor(static_cast<int>(gives), 32, 64));
                 }
                 const int row = m_base + lane;
                 const int Fw = (g.F + 31) >> 5;
                 if (row < g.M) {
-                    uint32_t* dst = out_bits + static_cast<size_t>(row) * Fw + (fp0 >> 5);
-                    if (NFP == 4 && (Fw & 3) == 0) {
-                        store_u32x4(dst, v4u{static_cast<uint32_t>(wb[0]), static_cast<uint32_t>(wb[1]), static_cast<uint32_t>(wb[2]),
-                                             static_cast<uint32_t>(wb[NFP - 1])});
-                    } else if (NFP == 2 && (Fw & 1) == 0) {
-                        store_u32x2(dst, v2u{static_cast<uint32_t>(wb[0]), static_cast<uint32_t>(wb[1])});
+                    uint32_t* dst = out_bits + static_cast<size_t>(row) * Fw + (f0 >> 5);
+                    if ((Fw & 3) == 0) {
+                        store_u32x4(dst, v4u{wb[0], wb[1], wb[2], wb[3]});
                     } else {
 #pragma unroll
                         for (int j = 0; j < NFP; ++j)
-                            if ((fp0 >> 5) + j < Fw) store_u32(dst + j, static_cast<uint32_t>(wb[j]));
+                            if ((f0 >> 5) + j < Fw) store_u32(dst + j, wb[j]);
                     }
                 }
                 continue;
             }
-            // fp32 output (one pass: NFP = 4).  Column n of block j is filter 4n + j, so the four
+            // fp32 output.  Column n of block j is filter 4n + j, so the four
             // blocks of a register index are four neighbouring filters of one output row: one
             // 16-byte store per lane, 512 contiguous bytes per half-wavefront, two rows per
             // instruction.  Y (and the optional integer dump) are raw buffers: the lane's offset
             // (first row of its half, its four filters) plus a scalar row offset; rows past M fall
             // outside the buffer and are dropped by the range check.  When F is not a multiple of
             // four, or for the integer dump, one store per value with columns past F masked.
-            static_assert(BITS || NFP == 4, "the fp32 epilogue stores all four column blocks of a row together");
+            static_assert(NFP == 4, "the epilogues store all four column blocks of a row together");
+            float4 s4[2][4];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    s4[i][q] = *reinterpret_cast<const float4*>(&sA_lds[wave][i * 32 + q * 8 + h * 4]);
             const float4 d4 = *reinterpret_cast<const float4*>(&col_lds[0][4 * p]);
             const float4 b4 = *reinterpret_cast<const float4*>(&col_lds[1][4 * p]);
             const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, bv[4] = {b4.x, b4.y, b4.z, b4.w};
