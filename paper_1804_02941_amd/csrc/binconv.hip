@@ -1073,12 +1073,23 @@ static int run_binconv(const dab_conv_desc& d, const uint32_t* A, const uint32_t
         if (int rc = ensure_device_ready()) return rc;
         return launch_direct(dp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
     }
-    // longer reductions over a few thousand blocks: the block kernel again
-    if (plan_block(d, &bp, true)) return launch_block(bp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
+    // Longer reductions: shares of it per wavefront over blocks of 64 x 128, or a workgroup per 32 x 32
+    // block where those are too few to fill the chip: the smaller of two estimates.  Measured (us, long
+    // reductions | blocks): 300 x 3001 x 2000 11.0 | 7.4, 1568 pixels x 4608 x 512 11.1 | 10.1, 3136 pixels
+    // 11.7 | 15.7, 1024 x 9216 x 1000 13.8 | 17.5, 1024 x 5000 x 3000 19.7 | 36.6.
+    // (A workspace is asked for as it always was, by dab_binconv2d_workspace_bytes; only the layers that
+    // neither kernel covers, padded windows of more than 32 taps among them, still write to it.)
+    const bool few_blocks = plan_block(d, &bp, true);
     MfmaPlan pl;
-    if (int rc = plan_binconv(d, &pl)) return rc;
-    if (!ws || ws_bytes < pl.ws_bytes || misaligned(ws, 256)) return DAB_ERR_WORKSPACE;
+    if (!few_blocks) {
+        if (int rc = plan_binconv(d, &pl)) return rc;
+        if (!ws || ws_bytes < pl.ws_bytes || misaligned(ws, 256)) return DAB_ERR_WORKSPACE;
+    }
+    SplitPlan sp;
+    const bool splits = plan_split(d, &sp);
+    if (few_blocks && !(splits && sp.us <= bp.us)) return launch_block(bp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
     if (int rc = ensure_device_ready()) return rc;
+    if (splits) return launch_split(sp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
     char* a4 = static_cast<char*>(ws);
     uint4* e4 = reinterpret_cast<uint4*>(a4 + pl.a4_bytes);
     float* sa = reinterpret_cast<float*>(a4 + pl.a4_bytes + pl.e4_bytes);

@@ -79,7 +79,6 @@ struct DirectGeom {
     int G, NG;                     // activation load groups per tap and in all
     int odd;                       // odd number of words per pixel
     int n_ent;                     // entries of the LDS panel (k-steps of whole rounds, plus one)
-    uint32_t step_kx, step_ky;     // byte steps of the load cursor across the window
     int n_mtiles, wg_per_ntile;    // pixel tiles, persistent workgroups per 128-filter tile
     int pix_bytes;                 // bytes of a pixel's packed words
     uint32_t a_bytes;              // bytes of the packed activation tensor
@@ -104,10 +103,31 @@ struct BlockGeom {
 struct BlockPlan {
     DirectGeom g;
     BlockGeom bg;
+    double us;              // estimated time of a launch
     int waves, depth, lw;   // wavefronts per block, k-steps per load burst, activation words per load
     bool pad;
     unsigned grid;
 };
+// The kernel for reductions too long for the persistent kernel: a workgroup's wavefronts split pixels and reduction.
+struct SplitGeom {
+    int log_ks, groups_per_share;  // shares of the reduction per pixel block (a power of two), load groups per share
+    uint32_t step_kx, step_ky;     // byte steps of the load cursor across the window
+    int n_mtiles, units, per_xcd;  // pixel tiles, workgroups with work, those of one XCD
+    uint32_t e_bytes;
+    FastDiv d_mtiles, d_G, d_kw;
+};
+struct SplitPlan {
+    DirectGeom g;
+    SplitGeom sg;
+    double us;                     // estimated time of a launch
+    int lw;
+    bool pad;
+    unsigned grid;
+    size_t lds_bytes;
+};
+bool plan_split(const dab_conv_desc& d, SplitPlan* pl);
+int launch_split(const SplitPlan& pl, hipStream_t st, const uint32_t* A, const uint32_t* E, const float* alpha,
+                 const float* beta, float* Y, int32_t* dbg_s1, const float* tau_out, uint32_t* out_bits);
 bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large);
 int launch_block(const BlockPlan& pl, hipStream_t st, const uint32_t* A, const uint32_t* E, const float* alpha,
                  const float* beta, float* Y, int32_t* dbg_s1, const float* tau_out, uint32_t* out_bits);

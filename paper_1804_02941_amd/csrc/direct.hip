@@ -123,6 +123,34 @@ __device__ __forceinline__ uint32_t word_of(const typename WordsOf<LW>::type& x,
     else return x[u];
 }
 
+// Where a lane's two pixels (row blocks of 32 from m_base on) have their windows: byte offset of the
+// first word of its half (half_bytes from the pixel's first), and a bit per tap that lies inside the image.
+template <bool PAD>
+__device__ __forceinline__ void locate_windows(const DirectGeom& g, int m_base, int p, int half_bytes, uint32_t (&base)[2],
+                                               uint32_t (&tbits)[2]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int m = min(m_base + i * 32 + p, g.M - 1);
+        const int b = fdiv(m, g.d_HoWo);
+        const int r = m - b * g.HoWo;
+        const int oy = fdiv(r, g.d_Wo);
+        const int ox = r - oy * g.Wo;
+        const int iy0 = oy * g.sh - g.ph, ix0 = ox * g.sw - g.pw;
+        base[i] = static_cast<uint32_t>(((b * g.H + iy0) * g.W + ix0) * g.pix_bytes + half_bytes);
+        tbits[i] = 0xFFFFFFFFu;
+        if (PAD) {
+            // bit t: tap t of the window lies inside the image (at most 32 taps, checked on the host): a run
+            // of columns, the same for every window row inside
+            const int x_lo = max(0, -ix0), n_in = min(g.kw, g.W - ix0) - x_lo;
+            const uint32_t cols = n_in > 0 ? (0xFFFFFFFFu >> (32 - n_in)) << x_lo : 0u;
+            uint32_t bitsv = 0;
+            for (int ky = 0; ky < g.kh; ++ky)
+                bitsv |= (static_cast<unsigned>(iy0 + ky) < static_cast<unsigned>(g.H) ? cols : 0u) << (ky * g.kw);
+            tbits[i] = bitsv;
+        }
+    }
+}
+
 // LW    words per activation load (1, 2 or 4: the words of a half must divide into such loads)
 // PF    load groups in the queue = groups per round of the reduction loop (the host picks one that
 //       divides the number of groups where it can: a round past the end multiplies zeros)
@@ -159,31 +187,7 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     const v4s arsrc = {static_cast<int>(static_cast<uint32_t>(a_addr)), static_cast<int>(static_cast<uint32_t>(a_addr >> 32) & 0xFFFFu),
                        static_cast<int>(g.a_bytes), 0x00020000};
     uint32_t base[2], tbits[2];
-    auto locate = [&](int m_base) {
-        // this lane's two pixels (row blocks of 32): byte offset of word h*WH of the window's first tap
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int m = min(m_base + i * 32 + p, g.M - 1);
-            const int b = fdiv(m, g.d_HoWo);
-            const int r = m - b * g.HoWo;
-            const int oy = fdiv(r, g.d_Wo);
-            const int ox = r - oy * g.Wo;
-            const int iy0 = oy * g.sh - g.ph, ix0 = ox * g.sw - g.pw;
-            base[i] = static_cast<uint32_t>(((b * g.H + iy0) * g.W + ix0) * g.pix_bytes + h * g.WH * 4);
-            tbits[i] = 0xFFFFFFFFu;
-            if (PAD) {
-                // bit t: tap t of the window lies inside the image (at most 32 taps, checked on the host): a run
-                // of columns, the same for every window row inside
-                const int x_lo = max(0, -ix0), n_in = min(g.kw, g.W - ix0) - x_lo;
-                const uint32_t cols = n_in > 0 ? (0xFFFFFFFFu >> (32 - n_in)) << x_lo : 0u;
-                uint32_t bitsv = 0;
-                for (int ky = 0; ky < g.kh; ++ky)
-                    bitsv |= (static_cast<unsigned>(iy0 + ky) < static_cast<unsigned>(g.H) ? cols : 0u) << (ky * g.kw);
-                tbits[i] = bitsv;
-            }
-        }
-    };
-    locate((mt_first * waves + wave) * 64);
+    locate_windows<PAD>(g, (mt_first * waves + wave) * 64, p, h * g.WH * 4, base, tbits);
     // the first tap's words on their way into the caches while the panel is built (their round trip to
     // memory would otherwise follow it); the values are not used
     uint32_t warm[2];
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     for (int mt = mt_first; mt < g.n_mtiles; mt += g.wg_per_ntile) {
         const int m_base = (mt * waves + wave) * 64;
         if (m_base >= g.M) continue;
-        if (mt != mt_first) locate(m_base);
+        if (mt != mt_first) locate_windows<PAD>(g, m_base, p, h * g.WH * 4, base, tbits);
         int ones[2] = {0, 0};
         {
             v16f acc[2][NFP];
@@ -673,6 +677,279 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
     }
 }
 
+// ---------------------------------------------------------------- long reductions
+// Reductions whose B fragments do not fit in LDS (more than kDirMaxSteps k-steps) over more blocks
+// than the small kernel above is for: the wide fully-connected layers at a training batch, large
+// windows over many channels.  A wavefront computes 64 pixels x 128 filters over a share of the
+// reduction, with both operands read as packed bits and expanded in registers: per k-step 42 vector
+// instructions beside eight multiplies, which hide them (two wavefronts per SIMD: the multiplies are
+// 60 % of the issue time).  The eight wavefronts of a workgroup are 8 / KS pixel blocks x KS shares of
+// the reduction; the shares' exact partial sums are added through LDS, each wavefront finishing a
+// KS-th of the rows.  Nothing is staged, no workspace, one launch; the only barriers are around that
+// exchange.  (The form it replaces expanded both operands into a workspace, multiplied from there and
+// added the shares in a third launch: 1024 x 9216 x 4096 took 9.8 + 29.5 + 18.5 us.)
+constexpr int kSplitWaves = 8;
+constexpr int kSplitLds = kSplitWaves * 16 * 64 * 16;              // bytes of the exchange between the shares
+
+template <int LW, bool PAD, bool BITS>
+__global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const DirectGeom g, const SplitGeom sg,
+                                                                        const uint32_t* __restrict__ A,
+                                                                        const uint32_t* __restrict__ E,
+                                                                        const float* __restrict__ alpha,
+                                                                        const float* __restrict__ beta,
+                                                                        float* __restrict__ Y, int32_t* __restrict__ dbg_s1,
+                                                                        const float* __restrict__ tau_out,
+                                                                        uint32_t* __restrict__ out_bits) {
+    constexpr int NFP = 4;
+    constexpr int STEPS = 8;                                       // k-steps per round, and weight loads in the queue
+    constexpr int PF = STEPS / LW;                                 // activation load groups per round and in the queue
+    extern __shared__ __align__(16) float4 red[];                  // [wave][register row e of a block row][lane]: the exchange
+    __shared__ int ones_lds[2][kSplitWaves][64];
+    __shared__ __align__(16) float sA_lds[kSplitWaves][64];
+    __shared__ __align__(16) float col_lds[3][kDirNTile];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p = lane & 31, h = lane >> 5;
+    // an XCD takes a contiguous run of tiles, pixel tiles of one filter tile next to each other
+    const int unit = static_cast<int>(blockIdx.x % kNumXCD) * sg.per_xcd + static_cast<int>(blockIdx.x / kNumXCD);
+    if (unit >= sg.units) return;                                  // (the whole workgroup)
+    const int ntile = fdiv(unit, sg.d_mtiles);
+    const int mt = unit - ntile * sg.n_mtiles;
+    const int f0 = ntile * kDirNTile;
+    const int share = wave & ((1 << sg.log_ks) - 1), mw = wave >> sg.log_ks;
+    const int m_base = (mt * (kSplitWaves >> sg.log_ks) + mw) * 64;
+    // the load groups of this wavefront (none for a block past the last pixel)
+    const int g_first = min(share * sg.groups_per_share, g.NG);
+    const int g_end = m_base < g.M ? min(g_first + sg.groups_per_share, g.NG) : g_first;
+
+    if (tid < kDirNTile) {
+        const int f = min(f0 + tid, g.F - 1);
+        const float al = alpha[f], be = beta[f];
+        col_lds[0][tid] = be - al;                                 // the accumulators hold -s1
+        col_lds[1][tid] = be;
+        col_lds[2][tid] = f0 + tid >= g.F ? __builtin_nanf("") : (BITS && tau_out) ? tau_out[f] : 0.0f;
+    }
+    const __amdgpu_buffer_rsrc_t arsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(A), 0, static_cast<int>(g.a_bytes), 0x00020000);
+    const __amdgpu_buffer_rsrc_t ersrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(E), 0, static_cast<int>(sg.e_bytes), 0x00020000);
+    // The halves of a tap's words alternate by load: words [2 LW jg, + LW) of group jg belong to lanes 0..31,
+    // the next LW to lanes 32..63, so a load takes 2 LW neighbouring words of every pixel (with the halves
+    // WH words apart a long row's load touched twice the cache lines).
+    uint32_t base[2], tbits[2];
+    locate_windows<PAD>(g, m_base, p, h * LW * 4, base, tbits);
+
+    // ---- load cursors (wavefront-uniform).  Offsets past the end are kOob: such loads return zeros, a
+    // zero mask word multiplies to nothing and a zero activation word counts no ones.
+    const int tap0 = fdiv(min(g_first, g.NG - 1), sg.d_G);
+    int a_left = g_end - g_first;                                  // activation groups still to request
+    int a_jg = min(g_first, g.NG - 1) - tap0 * g.G, a_tap = tap0;
+    int a_kx = tap0 - fdiv(tap0, sg.d_kw) * g.kw;
+    uint32_t a_off = static_cast<uint32_t>(((fdiv(tap0, sg.d_kw) * g.W + a_kx) * g.Cw + a_jg * 2 * LW) * 4);
+    typename WordsOf<LW>::type xa[PF][2];
+    auto request_a = [&](int slot) {
+        const bool live = a_left > 0;
+        const uint32_t off = live ? a_off : kOob;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            uint32_t voff = base[i] + off;
+            if (PAD) voff = ((tbits[i] >> (a_tap & 31)) & (live ? 1u : 0u)) ? voff : kOob;
+            // an odd number of words per pixel: the upper half's last word does not exist
+            if (LW == 1) voff = (h == 1 && g.odd && a_jg == g.G - 1) ? kOob : voff;
+            if constexpr (LW == 1) xa[slot][i] = __builtin_amdgcn_raw_buffer_load_b32(arsrc, static_cast<int>(voff), 0, 0);
+            else if constexpr (LW == 2) xa[slot][i] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(arsrc, static_cast<int>(voff), 0, 0));
+            else xa[slot][i] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(arsrc, static_cast<int>(voff), 0, 0));
+        }
+        --a_left;
+        const bool next_tap = ++a_jg == g.G;
+        a_jg = next_tap ? 0 : a_jg;
+        a_tap += next_tap ? 1 : 0;
+        a_kx += next_tap ? 1 : 0;
+        const bool next_row = a_kx == g.kw;
+        a_kx = next_row ? 0 : a_kx;
+        a_off += next_row ? sg.step_ky : (next_tap ? sg.step_kx : static_cast<uint32_t>(2 * LW * 4));
+    };
+    int b_left = (g_end - g_first) * LW;                           // weight steps still to request
+    int b_jg = min(g_first, g.NG - 1) - tap0 * g.G;
+    uint32_t b_off = static_cast<uint32_t>((tap0 * g.Cw + b_jg * 2 * LW) * g.Fp * 4);
+    // lane n takes the sixteen bytes of filters 4n .. 4n+3 of a row of E
+    const uint32_t b_lane = f0 + 4 * p < g.Fp ? static_cast<uint32_t>((h * LW * g.Fp + f0 + 4 * p) * 4) : kOob;
+    v4u xb[STEPS];
+    auto request_b = [&](int slot, bool last_of_group) {
+        uint32_t voff = b_lane + (b_left > 0 ? b_off : kOob);
+        if (LW == 1) voff = (h == 1 && g.odd && b_jg == g.G - 1) ? kOob : voff;
+        xb[slot] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(ersrc, static_cast<int>(voff), 0, 0));
+        --b_left;
+        // rows of a group's upper half lie between its own and the next group's (an odd tap ends without one)
+        if (last_of_group) {
+            const bool next_tap = ++b_jg == g.G;
+            b_jg = next_tap ? 0 : b_jg;
+            b_off += static_cast<uint32_t>((LW == 1 && next_tap && g.odd ? 1 : LW + 1) * g.Fp * 4);
+        } else {
+            b_off += static_cast<uint32_t>(g.Fp * 4);
+        }
+    };
+
+    v16f acc[2][NFP];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NFP; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    int ones[2] = {0, 0};
+
+    if (g_first < g_end) {
+        // requests in the order of their use, a whole round of them in flight
+        for_each_column<STEPS>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            if constexpr (q % LW == 0) request_a(q / LW);
+            request_b(q, q % LW == LW - 1);
+        });
+        uint32_t k8, k2;
+        asm volatile("s_mov_b32 %0, 0x88888888" : "=s"(k8));
+        asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(k2));
+        int c_tap = tap0, c_jg = min(g_first, g.NG - 1) - tap0 * g.G;       // consume cursor
+        uint32_t m8[2], m2[2];
+        auto tap_masks = [&]() {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const bool in = !PAD || ((tbits[i] >> (c_tap & 31)) & 1u);
+                m8[i] = in ? k8 : 0u;
+                m2[i] = in ? k2 : 0u;
+            }
+            const bool next_tap = ++c_jg == g.G;
+            c_jg = next_tap ? 0 : c_jg;
+            c_tap += next_tap ? 1 : 0;
+        };
+        tap_masks();
+        v4i an[2];
+        {
+            const uint32_t x0 = word_of<LW>(xa[0][0], 0), x1 = word_of<LW>(xa[0][1], 0);
+            ones[0] += __builtin_popcount(x0);
+            ones[1] += __builtin_popcount(x1);
+            an[0] = expand_a(x0, m8[0], m2[0]);
+            an[1] = expand_a(x1, m8[1], m2[1]);
+        }
+        uint4 bn = expand_e(xb[0][0]);
+        // One k-step: two multiplies, the expansion of the next column block's weights and a quarter of the
+        // next step's activations at a time, in this order (fences between them).  A queue slot is
+        // requested again as soon as its last word has been expanded, a round ahead of its use.
+        auto step = [&](auto qc, auto more) {
+            constexpr int q = decltype(qc)::value, qn = (q + 1) % STEPS;
+            constexpr int u = q % LW, d = q / LW, un = qn % LW, dn = qn / LW;
+            const v4i a0 = an[0], a1 = an[1];
+            uint32_t x0 = 0, x1 = 0;
+            for_each_column<NFP>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                const v4i bv = {static_cast<int>(bn.x), static_cast<int>(bn.y), static_cast<int>(bn.z), static_cast<int>(bn.w)};
+                acc[0][j] = mfma_fp4(a0, bv, acc[0][j]);
+                acc[1][j] = mfma_fp4(a1, bv, acc[1][j]);
+                bn = expand_e(j + 1 < NFP ? xb[q][(j + 1) % NFP] : xb[qn][0]);
+                if constexpr (j == 0) {
+                    if constexpr (u == LW - 1 && decltype(more)::value) request_a(d);
+                    if constexpr (un == 0) tap_masks();
+                } else if constexpr (j == 1) {
+                    x0 = word_of<LW>(xa[dn][0], un);
+                    x1 = word_of<LW>(xa[dn][1], un);
+                    ones[0] += __builtin_popcount(x0);
+                    ones[1] += __builtin_popcount(x1);
+                } else if constexpr (j == 2) {
+                    an[0] = expand_a(x0, m8[0], m2[0]);
+                } else {
+                    an[1] = expand_a(x1, m8[1], m2[1]);
+                    if constexpr (decltype(more)::value) request_b(q, u == LW - 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        // whole rounds, then half a round where that is enough (steps past the end multiply zeros; a loop
+        // left in the middle of a round lets the compiler sink the requests behind the exits)
+        const int steps = (g_end - g_first) * LW;
+        int left = steps;
+        for (; left > STEPS / 2; left -= STEPS) for_each_column<STEPS>([&](auto qc) { step(qc, std::true_type{}); });
+        if (left > 0) for_each_column<STEPS / 2>([&](auto qc) { step(qc, std::false_type{}); });
+    }
+
+    // ---- sA of the pixel block: ones of both halves and all shares, taps inside the image
+    const int ks = 1 << sg.log_ks;
+    ones_lds[0][wave][lane] = ones[0];
+    ones_lds[1][wave][lane] = ones[1];
+    __syncthreads();
+    {
+        int both = 0;
+        for (int k = 0; k < ks; ++k) both += ones_lds[h][mw * ks + k][p] + ones_lds[h][mw * ks + k][p + 32];
+        const int taps = PAD ? __builtin_popcount(h ? tbits[1] : tbits[0]) : g.T;
+        sA_lds[wave][lane] = static_cast<float>(2 * both - taps * g.C);     // lane l: row l of the block (read back by this wavefront only)
+    }
+
+    // ---- epilogue.  Register row e = 4q + t of block row i is output row i*32 + q*8 + (lane/32)*4 + t,
+    // column n of block j is filter 4n + j.  y = (beta - alpha)*(-s1) + beta*sA.
+    const float4 d4 = *reinterpret_cast<const float4*>(&col_lds[0][4 * p]);
+    const float4 b4 = *reinterpret_cast<const float4*>(&col_lds[1][4 * p]);
+    const float4 t4 = *reinterpret_cast<const float4*>(&col_lds[2][4 * p]);
+    const int fl = f0 + 4 * p;
+    const int Fw = (g.F + 31) >> 5;
+    auto finish = [&](int i, int e, float4 ns1) {
+        const int rl = i * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+        const int row = m_base + rl;
+        const float sv = sA_lds[wave][rl];
+        const float y[4] = {fmaf(d4.x, ns1.x, b4.x * sv), fmaf(d4.y, ns1.y, b4.y * sv), fmaf(d4.z, ns1.z, b4.z * sv),
+                            fmaf(d4.w, ns1.w, b4.w * sv)};
+        if constexpr (BITS) {
+            // the ballot of block j holds filters 4n + j of both rows; lane w < 4 of a half interleaves
+            // the four bytes that make up word w of its row
+            const unsigned long long b[4] = {__ballot(y[0] >= t4.x), __ballot(y[1] >= t4.y), __ballot(y[2] >= t4.z), __ballot(y[3] >= t4.w)};
+            uint32_t word = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t x = (static_cast<uint32_t>(h ? b[j] >> 32 : b[j]) >> (8 * (p & 3))) & 0xFFu;
+                x = (x | (x << 12)) & 0x000F000Fu;
+                x = (x | (x << 6)) & 0x03030303u;
+                x = (x | (x << 3)) & 0x11111111u;
+                word |= x << j;
+            }
+            if (p < 4 && row < g.M && (f0 >> 5) + p < Fw) out_bits[static_cast<size_t>(row) * Fw + (f0 >> 5) + p] = word;
+        } else if (row < g.M) {
+            const size_t o = static_cast<size_t>(row) * g.F + fl;
+            if ((g.F & 3) == 0 && !dbg_s1) {
+                if (fl < g.F) *reinterpret_cast<float4*>(Y + o) = make_float4(y[0], y[1], y[2], y[3]);
+            } else {
+                const float n[4] = {ns1.x, ns1.y, ns1.z, ns1.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (fl + j < g.F) {
+                        Y[o + j] = y[j];
+                        if (dbg_s1) dbg_s1[o + j] = -static_cast<int>(n[j]);
+                    }
+            }
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (ks == 1) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) finish(i, e, make_float4(acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]));
+            continue;
+        }
+        if (i == 1) __syncthreads();                               // the first block row's sums have been read
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            red[(wave * 16 + e) * 64 + lane] = make_float4(acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]);
+        __syncthreads();
+        const int per = 16 >> sg.log_ks;
+        for (int e = share * per; e < (share + 1) * per; ++e) {
+            float4 s = red[(mw * ks * 16 + e) * 64 + lane];
+            for (int k = 1; k < ks; ++k) {
+                const float4 v = red[((mw * ks + k) * 16 + e) * 64 + lane];
+                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;    // (exact: whole numbers below 2^24)
+            }
+            finish(i, e, s);
+        }
+    }
+}
+
 // ------------------------------------------------------------------ host side
 
 // Whether the direct kernel covers the layer, and its geometry.  It needs the B fragments of the
@@ -680,8 +957,10 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
 // most 32 taps (one validity bit per tap and lane).
 constexpr int kDirMaxSteps = 36;
 
-bool plan_direct(const dab_conv_desc& d, DirectPlan* pl) {
-    DirectGeom& g = pl->g;
+// The layer's geometry for the kernels that read packed bits through 64-pixel blocks; false where their
+// offsets (30 bits) or tap masks (32 taps of a padded window) do not reach.
+static bool describe(const dab_conv_desc& d, DirectGeom* pg, bool* pad, int* lw) {
+    DirectGeom& g = *pg;
     g = DirectGeom{};
     g.H = d.H; g.W = d.W; g.C = d.C; g.F = d.F; g.kh = d.kh; g.kw = d.kw;
     g.ph = d.pad_h; g.pw = d.pad_w; g.sh = d.stride_h; g.sw = d.stride_w;
@@ -695,9 +974,9 @@ bool plan_direct(const dab_conv_desc& d, DirectPlan* pl) {
     const long long M = 1ll * d.B * g.HoWo;
     const long long a_bytes = 1ll * d.B * d.H * d.W * g.Cw * 4;
     const long long nk = 1ll * g.T * g.WH;
-    if (M >= (1ll << 30) || a_bytes >= (1ll << 30) || nk > kDirMaxSteps || 1ll * M * d.F >= (1ll << 29)) return false;
-    pl->pad = d.pad_h > 0 || d.pad_w > 0;
-    if (pl->pad && g.T > 32) return false;
+    if (M >= (1ll << 30) || a_bytes >= (1ll << 30) || nk >= (1 << 20) || 1ll * M * d.F >= (1ll << 29)) return false;
+    *pad = d.pad_h > 0 || d.pad_w > 0;
+    if (*pad && g.T > 32) return false;
     g.M = static_cast<int>(M);
     g.a_bytes = static_cast<uint32_t>(a_bytes);
     g.y_bytes = static_cast<uint32_t>(M * d.F * 4);
@@ -705,12 +984,16 @@ bool plan_direct(const dab_conv_desc& d, DirectPlan* pl) {
     g.pix_bytes = g.Cw * 4;
     g.nk = static_cast<int>(nk);
     g.odd = g.Cw & 1;
-    pl->lw = g.odd ? 1 : (g.WH % 4 == 0 ? 4 : (g.WH % 2 == 0 ? 2 : 1));
-    g.G = g.WH / pl->lw;
+    *lw = g.odd ? 1 : (g.WH % 4 == 0 ? 4 : (g.WH % 2 == 0 ? 2 : 1));
+    g.G = g.WH / *lw;
     g.NG = g.T * g.G;
-    // byte steps of the load cursor: to the next tap of a window row, to the next row of the window
-    g.step_kx = static_cast<uint32_t>((g.Cw - (g.G - 1) * pl->lw) * 4);
-    g.step_ky = static_cast<uint32_t>(((d.W - (d.kw - 1)) * g.Cw - (g.G - 1) * pl->lw) * 4);
+    g.d_HoWo = make_fastdiv(g.HoWo); g.d_Wo = make_fastdiv(g.Wo); g.d_WH = make_fastdiv(g.WH);
+    return true;
+}
+
+bool plan_direct(const dab_conv_desc& d, DirectPlan* pl) {
+    DirectGeom& g = pl->g;
+    if (!describe(d, &g, &pl->pad, &pl->lw) || g.nk > kDirMaxSteps) return false;
     // The loop runs whole rounds of PF groups and reads one B entry ahead.  Of the two queue depths
     // built per load width, the one that wastes fewer groups in the last round (the deeper on a tie).
     const int deep = pl->lw == 1 ? 6 : (pl->lw == 2 ? 4 : 3), shallow = deep - 1;
@@ -718,7 +1001,6 @@ bool plan_direct(const dab_conv_desc& d, DirectPlan* pl) {
     pl->pf = waste_shallow < waste_deep ? shallow : deep;
     g.n_ent = ceil_div(g.NG, pl->pf) * pl->pf * pl->lw + 1;
     if (g.n_ent > kDirMaxSteps + 1) return false;
-    g.d_HoWo = make_fastdiv(g.HoWo); g.d_Wo = make_fastdiv(g.Wo); g.d_WH = make_fastdiv(g.WH);
     // eight wavefronts (512 pixels per tile) when that still gives most compute units a tile, else four
     // (layers with fewer tiles than compute units leave some idle, and are still done in one launch)
     const int n_ntiles = ceil_div(d.F, kDirNTile);
@@ -733,9 +1015,9 @@ bool plan_direct(const dab_conv_desc& d, DirectPlan* pl) {
 }
 
 // Layers for the block kernel.  Small ones (at most 512 blocks of 32 x 32 and too few tiles to give
-// half the compute units one of the persistent kernel's): it is the fastest form.  With `large`,
-// up to 8192 blocks and 400 000 block k-steps: for layers whose reduction is too long for the
-// persistent kernel's panel it still beats the kernels that go through a workspace.
+// half the compute units one of the persistent kernel's): it is the fastest form.  With `large`, up
+// to 8192 blocks and 400 000 block k-steps (well past where the kernel for long reductions is the faster
+// one), and an estimate of the time to compare with that kernel's.
 bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large) {
     DirectGeom& g = pl->g;
     g = DirectGeom{};
@@ -768,14 +1050,17 @@ bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large) {
     bg.d_kw = make_fastdiv(d.kw);
     const long long blocks = 1ll * ceil_div(g.M, 32) * bg.n_fblocks;
     const int tiles256 = ceil_div(g.M, 256) * ceil_div(d.F, kDirNTile);
-    // (measured against the workspace kernels: 4096 blocks x 64 k-steps 24 us against 42, 3136 x 72 28 against 39,
-    // 4096 x 144 63 against 59)
     if (large ? (blocks > 8192 || blocks * nk > 400000) : (tiles256 * 2 > kNumCU || blocks > 512)) return false;
     pl->grid = static_cast<unsigned>(ceil_div(g.M, 32) * bg.fb_per_xcd * kNumXCD);
     // enough wavefronts per block that each keeps a few k-steps of the reduction; the burst such that
     // two of them hold a wavefront's whole share where that is short (one round trip to memory)
     pl->waves = g.nk >= 32 ? 8 : 2;
     pl->lw = (g.Cw % 2 == 0 && g.WH % 4 == 0) ? 4 : 1;
+    // Time of a launch, from measurements between 30e3 and 3e5 block k-steps (block k-steps per us at
+    // sixteen and four bytes of a pixel per load; the workgroups of filter blocks that do not exist on an
+    // XCD leave its neighbours with theirs).
+    pl->us = (pl->lw == 4 ? 5.0 : 4.0) + static_cast<double>(blocks) * nk * (8.0 * bg.fb_per_xcd / bg.n_fblocks) /
+                                             (pl->lw == 4 ? 11000.0 : 7000.0);
     const int share = ceil_div(g.nk, pl->waves * pl->lw) * pl->lw;
     if (pl->lw == 4) pl->depth = share <= 8 ? 4 : (share > 16 && share <= 32 ? 16 : 8);
     else pl->depth = share <= 8 ? 4 : (share > 16 && share <= 26 ? 13 : 8);
@@ -804,6 +1089,65 @@ int launch_block(const BlockPlan& pl, hipStream_t st, const uint32_t* A, const u
     DAB_X(8, 4, 4) DAB_X(8, 8, 4) DAB_X(8, 16, 4) DAB_X(2, 4, 4) DAB_X(2, 8, 4)
 #undef DAB_X
     return DAB_ERR_UNSUPPORTED;
+}
+
+// Layers whose reduction is too long for the persistent kernel's panel and that have more blocks than
+// the small-product kernel is for.
+bool plan_split(const dab_conv_desc& d, SplitPlan* pl) {
+    DirectGeom& g = pl->g;
+    if (!describe(d, &g, &pl->pad, &pl->lw)) return false;
+    const long long e_bytes = 1ll * g.T * g.Cw * g.Fp * 4;
+    if (e_bytes >= (1ll << 30) || 1ll * d.C * g.T >= (1ll << 24)) return false;      // |s1| must stay exact in fp32
+    SplitGeom& sg = pl->sg;
+    sg.e_bytes = static_cast<uint32_t>(e_bytes);
+    // byte steps of the load cursor: to the next tap of a window row, to the next row of the window
+    sg.step_kx = static_cast<uint32_t>((g.Cw - (g.G - 1) * 2 * pl->lw) * 4);
+    sg.step_ky = static_cast<uint32_t>(((d.W - (d.kw - 1)) * g.Cw - (g.G - 1) * 2 * pl->lw) * 4);
+    sg.d_G = make_fastdiv(g.G);
+    sg.d_kw = make_fastdiv(d.kw);
+    // Shares of the reduction per pixel block: the number that minimises rounds of workgroups times the
+    // time of one, as measured (0.4 us a k-step of two wavefronts per SIMD: 1024 x 9216 x 4096, 36 steps of
+    // four shares, 23.7 us, 1024 x 4096 x 4096, 16 steps, 16.2; set-up and epilogue 4, the exchange 4).
+    const int n_ntiles = ceil_div(d.F, kDirNTile);
+    double best = 0.0;
+    for (int lk = 0; lk <= 3; ++lk) {
+        const int per = ceil_div(g.NG, 1 << lk);
+        const long long units = 1ll * ceil_div(g.M, 64 * (kSplitWaves >> lk)) * n_ntiles;
+        const double us = static_cast<double>((units + kNumCU - 1) / kNumCU) * (per * pl->lw * 0.4 + 4.5 + (lk ? 4.0 : 0.0));
+        if (lk == 0 || us < best) {
+            best = us;
+            sg.log_ks = lk;
+            sg.groups_per_share = per;
+        }
+    }
+    pl->us = best;
+    sg.n_mtiles = ceil_div(g.M, 64 * (kSplitWaves >> sg.log_ks));
+    const long long units = 1ll * sg.n_mtiles * n_ntiles;
+    if (units >= (1ll << 30)) return false;
+    sg.units = static_cast<int>(units);
+    sg.per_xcd = ceil_div(sg.units, kNumXCD);
+    sg.d_mtiles = make_fastdiv(sg.n_mtiles);
+    pl->grid = static_cast<unsigned>(sg.per_xcd * kNumXCD);
+    pl->lds_bytes = sg.log_ks ? kSplitLds : 0;
+    return true;
+}
+
+template <int LW>
+static int launch_split_as(const SplitPlan& pl, hipStream_t st, const uint32_t* A, const uint32_t* E, const float* alpha,
+                           const float* beta, float* Y, int32_t* dbg_s1, const float* tau_out, uint32_t* out_bits) {
+    const bool bits = Y == nullptr;
+    auto go = [&](auto kernel) {
+        return launch(kernel, dim3(pl.grid), dim3(64 * kSplitWaves), pl.lds_bytes, st, pl.g, pl.sg, A, E, alpha, beta, Y, dbg_s1, tau_out,
+                      out_bits);
+    };
+    if (pl.pad) return bits ? go(binconv_split_kernel<LW, true, true>) : go(binconv_split_kernel<LW, true, false>);
+    return bits ? go(binconv_split_kernel<LW, false, true>) : go(binconv_split_kernel<LW, false, false>);
+}
+int launch_split(const SplitPlan& pl, hipStream_t st, const uint32_t* A, const uint32_t* E, const float* alpha, const float* beta,
+                 float* Y, int32_t* dbg_s1, const float* tau_out, uint32_t* out_bits) {
+    if (pl.lw == 4) return launch_split_as<4>(pl, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
+    if (pl.lw == 2) return launch_split_as<2>(pl, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
+    return launch_split_as<1>(pl, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
 }
 
 template <int LW, int PF, bool PAD, bool BITS>
@@ -839,7 +1183,20 @@ static int raise_direct_limit() {
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (kDirMaxSteps + 1) * 4096);
     return e == hipSuccess ? static_cast<int>(DAB_OK) : hip_failed(e);
 }
+template <int LW>
+static int raise_split_limit() {
+    for (const void* k : {reinterpret_cast<const void*>(&binconv_split_kernel<LW, false, false>),
+                          reinterpret_cast<const void*>(&binconv_split_kernel<LW, false, true>),
+                          reinterpret_cast<const void*>(&binconv_split_kernel<LW, true, false>),
+                          reinterpret_cast<const void*>(&binconv_split_kernel<LW, true, true>)})
+        if (const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds); e != hipSuccess)
+            return hip_failed(e);
+    return DAB_OK;
+}
 int init_direct() {
+    if (int rc = raise_split_limit<1>()) return rc;
+    if (int rc = raise_split_limit<2>()) return rc;
+    if (int rc = raise_split_limit<4>()) return rc;
 #define DAB_X(LW, PF)                                                   \
     if (int rc = raise_direct_limit<LW, PF, false, false>()) return rc; \
     if (int rc = raise_direct_limit<LW, PF, false, true>()) return rc;  \

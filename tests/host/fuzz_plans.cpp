@@ -63,6 +63,21 @@ int check_one(const dab_conv_desc& d) {
             REQUIRE(1ll * d.C * d.kh * d.kw < (1ll << 24));
         }
     }
+    SplitPlan sp;
+    if (plan_split(d, &sp)) {
+        const SplitGeom& sg = sp.sg;
+        const int ks = 1 << sg.log_ks, tile = 64 * (8 / ks);
+        REQUIRE(sp.lw == 1 || sp.lw == 2 || sp.lw == 4);
+        REQUIRE(sg.log_ks >= 0 && sg.log_ks <= 3 && 1ll * sg.groups_per_share * ks >= sp.g.NG);
+        REQUIRE(sp.g.G * sp.lw == sp.g.WH && sp.g.NG == sp.g.T * sp.g.G && (sp.lw == 1 || sp.g.Cw == 2 * sp.g.WH));
+        REQUIRE(1ll * sg.n_mtiles * tile >= M && 1ll * (sg.n_mtiles - 1) * tile < M);
+        REQUIRE(1ll * sg.units == 1ll * sg.n_mtiles * ((d.F + 127) / 128));
+        REQUIRE(sp.grid == 8u * static_cast<unsigned>(sg.per_xcd) && 8ll * sg.per_xcd >= sg.units);
+        REQUIRE(1ull * sg.e_bytes == 4ull * sp.g.T * sp.g.Cw * sp.g.Fp && sg.e_bytes < (1u << 30));
+        REQUIRE(sp.lds_bytes == (ks > 1 ? 131072u : 0u));
+        REQUIRE(!sp.pad || sp.g.T <= 32);
+        REQUIRE(1ll * d.C * d.kh * d.kw < (1ll << 24));
+    }
     // the public queries and entry points: any status is fine, a crash or a sanitizer report is not
     void* fake = reinterpret_cast<void*>(0x1000);
     const size_t ws = dab_binconv2d_workspace_bytes(&d);

@@ -93,6 +93,50 @@ def test_filter_counts_that_end_inside_a_word_in_the_persistent_kernel(C, F):
     check_rebinarize(L, x, W, None, None)
 
 
+LONG_REDUCTIONS = [
+    # name, B, C, H, W, F, k, pad, stride: reductions of more than 36 steps over many blocks.  One, two and
+    # four words per load, an odd number of words per pixel, last tiles of 1 to 128 filters and 1 to 64
+    # pixels, shares of the reduction that end in whole and half rounds, the whole reduction in one share
+    ("w4_tails", 65, 512, 9, 9, 129, 3, 1, 1), ("w4_even_taps", 260, 1024, 8, 8, 97, 2, 0, 1), ("w1_one_share", 100, 64, 26, 26, 512, 7, 0, 1), ("w2_stride", 70, 100, 21, 19, 150, 5, 2, 2),
+    ("w1_odd_words", 40, 288, 12, 11, 131, 3, 2, 1), ("w1_odd_last_channels", 90, 70, 13, 12, 260, 5, 1, 1),
+    ("w1_one_filter_block", 200, 64, 16, 16, 30, 7, 0, 1), ("fc_rows", 1021, 2560, 1, 1, 1030, 1, 0, 1),
+    ("fc_odd", 515, 5003, 1, 1, 770, 1, 0, 1),
+]
+
+
+@pytest.mark.parametrize("case", LONG_REDUCTIONS, ids=lambda c: c[0])
+def test_long_reductions_over_many_blocks(case):
+    """fp32, integer and packed-sign output: s1 against the product of the unpacked operands (exact in
+    float64), the other two against their definitions from it; |y| error of three fp32 roundings."""
+    name, B, C, H, W, F, k, pad, stride = case
+    rng = np.random.default_rng(zlib.crc32(name.encode()) % 1000)
+    x = rng.standard_normal((B, H, W, C)).astype(np.float32)
+    e = rng.random((F, C, k, k)) < 0.4
+    alpha = (1.0 + rng.random(F)).astype(np.float32)
+    beta = -rng.random(F).astype(np.float32)
+    tau_out = (rng.standard_normal(F) * np.sqrt(C) * k * 0.3).astype(np.float32)
+    d = dab.dab_conv_desc(B, C, H, W, F, k, k, pad, pad, stride, stride)
+    A = dab.dab_pack_activations(gu.to_gpu(x))
+    E = gu.to_gpu(opk.pack_weights(e)[0].view(np.int32))
+    al, be, tau = gu.to_gpu(alpha), gu.to_gpu(beta), gu.to_gpu(tau_out)
+    Y, s1 = dab.dab_binconv2d(d, A, E, al, be, want_s1=True)
+    Y2 = dab.dab_binconv2d(d, A, E, al, be)
+    bits = dab.dab_binconv2d_bits(d, A, E, al, be, tau)
+    sign = dab.dab_pack_activations(Y2, dab.DAB_LAYOUT_NHWC, tau)
+    torch.cuda.synchronize()
+    a = torch.from_numpy(np.where(x >= 0, 1.0, -1.0).transpose(0, 3, 1, 2)).float()
+    conv = lambda w: torch.nn.functional.conv2d(a, w, padding=pad, stride=stride)      # whole numbers below 2^24: exact in fp32
+    want = conv(torch.from_numpy(e.astype(np.float32))).permute(0, 2, 3, 1)
+    sA = conv(torch.ones(1, C, k, k)).permute(0, 2, 3, 1).double()
+    assert torch.equal(s1.cpu(), want.to(torch.int32))
+    assert torch.equal(Y, Y2)
+    y = torch.from_numpy(alpha).double() * want.double() + torch.from_numpy(beta).double() * (sA - want.double())
+    scale = torch.from_numpy(alpha).double() * want.double().abs() + torch.from_numpy(np.abs(beta)).double() * (sA - want.double()).abs()
+    # three roundings (beta - alpha, beta sA, the fma), each of a term of at most 3 * scale (|beta| <= |alpha|)
+    assert torch.all((Y.cpu().double() - y).abs() <= 9 * 2.0 ** -24 * scale + 1e-30)
+    assert torch.equal(bits, sign)
+
+
 @pytest.mark.parametrize("B,K,F", [(1, 2, 1), (5, 70, 9), (64, 512, 512), (65, 1000, 130), (300, 4096, 48), (130, 9216, 40)])
 def test_small_fc_layers_rebinarized(B, K, F):
     rng = np.random.default_rng(B * K + F)
