@@ -110,7 +110,11 @@ __device__ __forceinline__ int job_column(unsigned r, int Fp) {
 // one thread per packed word gathers its 32 channels (stride T), writes the word into column f of E
 // and adds its ones to the tap's count.  (A wavefront per word pair with a ballot is slower: its
 // address arithmetic is per word instead of per lane.)  Columns past F are written as zeros.
-template <int THREADS, int ITEMS>
+// A window of one tap (fully-connected layers, 1 x 1 convolutions) has its channels in the order of the
+// row, so the 64 elements a wavefront holds under one j already are two words: a ballot each, kept by
+// lane j, no LDS.  (Through LDS the 32-byte stride of the gather put 64 lanes on eight banks: 4096 rows of
+// 9216 weights and 4096 of 4096, weight side of both in one call: 175.6 us, 157.6 with the ballots.)
+template <int THREADS, int ITEMS, bool BALLOTS = true>
 __device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitInfo* info, const float (&x)[ITEMS]) {
     __shared__ uint8_t maskb[THREADS * ITEMS];
     __shared__ uint32_t tapcnt[kPackMaxTaps];
@@ -128,6 +132,31 @@ __device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitIn
     const float tv = info->thr_val;
     const int ti = info->thr_idx;
     const bool upper = info->upper != 0;
+    if (BALLOTS && T == 1) {
+        static_assert(ITEMS <= 64 && THREADS / 64 <= kPackMaxTaps, "a lane per j, a count per wavefront");
+        const int lane = tid & 63, wave = tid >> 6;
+        unsigned long long words = 0ull;
+        uint32_t ones = 0;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const int i = tid + j * THREADS;
+            const bool lower = x[j] < tv || (x[j] == tv && i <= ti);
+            const unsigned long long m = __ballot(i < n && lower != upper);
+            ones += static_cast<uint32_t>(__popcll(m));
+            if (lane == j) words = m;
+        }
+        const int r = lane * (THREADS / 32) + wave * 2;
+        if (lane < ITEMS && r < R) E[static_cast<size_t>(r) * Fp + f] = static_cast<uint32_t>(words);
+        if (lane < ITEMS && r + 1 < R) E[static_cast<size_t>(r + 1) * Fp + f] = static_cast<uint32_t>(words >> 32);
+        if (lane == 0) tapcnt[wave] = ones;
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t total = 0;
+            for (int w = 0; w < THREADS / 64; ++w) total += tapcnt[w];
+            ecnt[f] = total;
+        }
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
         const int i = tid + j * THREADS;
@@ -241,7 +270,7 @@ __global__ __launch_bounds__(THREADS) void binarize_sort_kernel(const EstJobs jo
         if (q.E) {
             float x[ITEMS];
             load_row<THREADS, ITEMS>(q.W + static_cast<size_t>(f) * q.n, q.n, x);
-            pack_row<THREADS, ITEMS>(q, f, &info, x);
+            pack_row<THREADS, ITEMS, false>(q, f, &info, x);       // (few rows come here, and the ballots' registers would spill)
         }
         __syncthreads();
     }

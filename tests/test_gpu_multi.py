@@ -71,6 +71,31 @@ def test_binarize_weights_multi_equals_separate_calls_and_runs_without_packing()
         assert torch.equal(E, it["packed"][0]) and torch.equal(ecnt, it["packed"][1])
 
 
+# one tap: masks by ballots.  Rows that end inside a word, with a word or a word pair, at a wavefront's and at the class's last element
+ONE_TAP_ROWS = [2, 31, 33, 64, 65, 100, 255, 257, 2273, 2304, 2305, 4097, 4608, 4609, 9185, 9216, 9217, 13281, 13312]
+
+
+@pytest.mark.parametrize("F", [3, 70, 1540])
+def test_one_tap_rows_of_every_class_equal_the_separate_packing(F):
+    """F: few filters, filters past a word pair of columns, enough for the classes that hand rows over to the sort kernel."""
+    rng = np.random.default_rng(7 * F)
+    rows = ONE_TAP_ROWS if F < 1000 else [100, 2304, 4097]
+    for i in range(0, len(rows), 16):
+        items = []
+        for n in rows[i:i + 16]:
+            W = weight_rows(rng, F, n, "mixture").reshape(F, n, 1, 1)
+            W[F // 2] = 0.25                                      # a constant filter: the sort decides it
+            Wt = gu.to_gpu(W)
+            items.append(dict(W=Wt, est=dab.estimate_outputs(F, Wt.device), packed=dab.pack_weights_outputs(F, n, 1, 1, Wt.device)))
+            for t in items[-1]["packed"][:2]:
+                t.fill_(-1)                                       # every word must be written by the call
+        dab.dab_binarize_weights_multi(dab.weight_jobs(items))
+        for it in items:
+            E, ecnt = dab.dab_pack_weights(it["W"], it["est"]["thr_val"], it["est"]["thr_idx"], it["est"]["alpha_is_upper"])
+            torch.cuda.synchronize()
+            assert torch.equal(E, it["packed"][0]) and torch.equal(ecnt, it["packed"][1]), it["W"].shape
+
+
 def test_binarize_weights_multi_with_previous_split():
     rng = np.random.default_rng(2026)
     shapes = [(24, 64, 3, 3), (10, 700, 3, 3), (16, 128, 5, 5)]
