@@ -113,7 +113,10 @@ __device__ __forceinline__ int job_column(unsigned r, int Fp) {
 // A window of one tap (fully-connected layers, 1 x 1 convolutions) has its channels in the order of the
 // row, so the 64 elements a wavefront holds under one j already are two words: a ballot each, kept by
 // lane j, no LDS.  (Through LDS the 32-byte stride of the gather put 64 lanes on eight banks: 4096 rows of
-// 9216 weights and 4096 of 4096, weight side of both in one call: 175.6 us, 157.6 with the ballots.)
+// 9216 weights and 4096 of 4096, weight side of both in one call: 175.6 us, 157.6 with the ballots.)  Only
+// as many ballots as the row has steps of the workgroup's threads: with all of its class's, short rows were
+// slower than through LDS (16384 rows of 256 weights: LDS 91.0 us, nine ballots 97.5, one 87.8; 4096 of 64:
+// 28.6, 29.4, 27.3; 8192 of 512: 51.5, 53.9, 50.0).
 template <int THREADS, int ITEMS, bool BALLOTS = true>
 __device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitInfo* info, const float (&x)[ITEMS]) {
     __shared__ uint8_t maskb[THREADS * ITEMS];
@@ -140,6 +143,7 @@ __device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitIn
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
             const int i = tid + j * THREADS;
+            if (j * THREADS >= n) break;                           // (the whole workgroup)
             const bool lower = x[j] < tv || (x[j] == tv && i <= ti);
             const unsigned long long m = __ballot(i < n && lower != upper);
             ones += static_cast<uint32_t>(__popcll(m));

@@ -71,8 +71,10 @@ def test_binarize_weights_multi_equals_separate_calls_and_runs_without_packing()
         assert torch.equal(E, it["packed"][0]) and torch.equal(ecnt, it["packed"][1])
 
 
-# one tap: masks by ballots.  Rows that end inside a word, with a word or a word pair, at a wavefront's and at the class's last element
-ONE_TAP_ROWS = [2, 31, 33, 64, 65, 100, 255, 257, 2273, 2304, 2305, 4097, 4608, 4609, 9185, 9216, 9217, 13281, 13312]
+# one tap: masks by ballots.  Rows that end inside a word, with a word or a word pair, at a wavefront's, at a whole step of
+# the workgroup's threads (256, 512, 1024: no ballot past it) and at the class's last element
+ONE_TAP_ROWS = [2, 31, 33, 64, 65, 100, 255, 256, 257, 511, 512, 513, 2048, 2049, 2273, 2304, 2305,
+                4096, 4097, 4608, 4609, 8192, 9185, 9216, 9217, 13281, 13312]
 
 
 @pytest.mark.parametrize("F", [3, 70, 1540])
