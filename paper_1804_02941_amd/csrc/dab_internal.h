@@ -72,6 +72,10 @@ int init_pack();
 int init_estimate(int dev);
 
 // The product kernel that reads both operands as packed bits (direct.hip).
+// (The places of its fields decide how the compiler groups a kernel's scalar loads.  Without the two steps in front of
+// n_mtiles the padded block kernels of two wavefronts come out with 56-72 registers instead of 88-104, one burst of
+// loads waited for before the next: 64 x 192 x 7 x 7 -> 64, 3 x 3, padding 1, 7.7 us with them, 8.1 without; over 90
+// padded layers between 15 % faster and 8 % slower without.)
 struct DirectGeom {
     int H, W, C, Cw, WH, F, Fp, kh, kw, ph, pw, sh, sw;   // WH: words per half of a pixel = ceil(Cw / 2)
     int HoWo, Wo, M, T;
@@ -79,6 +83,7 @@ struct DirectGeom {
     int G, NG;                     // activation load groups per tap and in all
     int odd;                       // odd number of words per pixel
     int n_ent;                     // entries of the LDS panel (k-steps of whole rounds, plus one)
+    uint32_t step_kx, step_ky;     // byte steps of the split kernel's load cursor across the window
     int n_mtiles, wg_per_ntile;    // pixel tiles, persistent workgroups per 128-filter tile
     int pix_bytes;                 // bytes of a pixel's packed words
     uint32_t a_bytes;              // bytes of the packed activation tensor
@@ -111,7 +116,6 @@ struct BlockPlan {
 // The kernel for reductions too long for the persistent kernel: a workgroup's wavefronts split pixels and reduction.
 struct SplitGeom {
     int log_ks, groups_per_share;  // shares of the reduction per pixel block (a power of two), load groups per share
-    uint32_t step_kx, step_ky;     // byte steps of the load cursor across the window
     int n_mtiles, units, per_xcd;  // pixel tiles, workgroups with work, those of one XCD
     uint32_t e_bytes;
     FastDiv d_mtiles, d_G, d_kw;

@@ -123,13 +123,13 @@ __device__ __forceinline__ uint32_t word_of(const typename WordsOf<LW>::type& x,
     else return x[u];
 }
 
-// Where a lane's two pixels (row blocks of 32 from m_base on) have their windows: byte offset of the
+// Where a lane's N pixels (row blocks of 32 from m_base on) have their windows: byte offset of the
 // first word of its half (half_bytes from the pixel's first), and a bit per tap that lies inside the image.
-template <bool PAD>
-__device__ __forceinline__ void locate_windows(const DirectGeom& g, int m_base, int p, int half_bytes, uint32_t (&base)[2],
-                                               uint32_t (&tbits)[2]) {
+template <bool PAD, int N>
+__device__ __forceinline__ void locate_windows(const DirectGeom& g, int m_base, int p, int half_bytes, uint32_t (&base)[N],
+                                               uint32_t (&tbits)[N]) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < N; ++i) {
         const int m = min(m_base + i * 32 + p, g.M - 1);
         const int b = fdiv(m, g.d_HoWo);
         const int r = m - b * g.HoWo;
@@ -546,27 +546,9 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
     if (fb >= bg.n_fblocks) return;                                // (the whole workgroup)
 
     // this lane's pixel: byte offset of word h*WH of the window's first tap, taps inside the image
-    uint32_t base, tbits = 0xFFFFFFFFu;
-    {
-        const int m = min(mb * 32 + p, g.M - 1);
-        const int b = fdiv(m, g.d_HoWo);
-        const int rr = m - b * g.HoWo;
-        const int oy = fdiv(rr, g.d_Wo);
-        const int ox = rr - oy * g.Wo;
-        const int iy0 = oy * g.sh - g.ph, ix0 = ox * g.sw - g.pw;
-        base = static_cast<uint32_t>(((b * g.H + iy0) * g.W + ix0) * g.pix_bytes + h * g.WH * 4);
-        if (PAD) {
-            uint32_t bitsv = 0;
-            int t = 0;
-            for (int ky = 0; ky < g.kh; ++ky)
-                for (int kx = 0; kx < g.kw; ++kx, ++t) {
-                    const bool in = static_cast<unsigned>(iy0 + ky) < static_cast<unsigned>(g.H) &&
-                                    static_cast<unsigned>(ix0 + kx) < static_cast<unsigned>(g.W);
-                    bitsv |= (in ? 1u : 0u) << t;
-                }
-            tbits = bitsv;
-        }
-    }
+    uint32_t base1[1], tbits1[1];
+    locate_windows<PAD>(g, mb * 32, p, h * g.WH * 4, base1, tbits1);
+    const uint32_t base = base1[0], tbits = tbits1[0];
     const __amdgpu_buffer_rsrc_t arsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(A), 0, static_cast<int>(g.a_bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t ersrc =
@@ -768,7 +750,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
         a_kx += next_tap ? 1 : 0;
         const bool next_row = a_kx == g.kw;
         a_kx = next_row ? 0 : a_kx;
-        a_off += next_row ? sg.step_ky : (next_tap ? sg.step_kx : static_cast<uint32_t>(2 * LW * 4));
+        a_off += next_row ? g.step_ky : (next_tap ? g.step_kx : static_cast<uint32_t>(2 * LW * 4));
     };
     int b_left = (g_end - g_first) * LW;                           // weight steps still to request
     int b_jg = min(g_first, g.NG - 1) - tap0 * g.G;
@@ -1101,8 +1083,8 @@ bool plan_split(const dab_conv_desc& d, SplitPlan* pl) {
     SplitGeom& sg = pl->sg;
     sg.e_bytes = static_cast<uint32_t>(e_bytes);
     // byte steps of the load cursor: to the next tap of a window row, to the next row of the window
-    sg.step_kx = static_cast<uint32_t>((g.Cw - (g.G - 1) * 2 * pl->lw) * 4);
-    sg.step_ky = static_cast<uint32_t>(((d.W - (d.kw - 1)) * g.Cw - (g.G - 1) * 2 * pl->lw) * 4);
+    g.step_kx = static_cast<uint32_t>((g.Cw - (g.G - 1) * 2 * pl->lw) * 4);
+    g.step_ky = static_cast<uint32_t>(((d.W - (d.kw - 1)) * g.Cw - (g.G - 1) * 2 * pl->lw) * 4);
     sg.d_G = make_fastdiv(g.G);
     sg.d_kw = make_fastdiv(d.kw);
     // Shares of the reduction per pixel block: the number that minimises rounds of workgroups times the

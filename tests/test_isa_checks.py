@@ -1,6 +1,8 @@
 """The static checks over the ISA of the kernels with inline assembly (hipcc -S, no GPU): every load that
 may be in flight has its registers left alone, and no inline-assembly instruction reads a scalar register
 too soon behind the vector instruction that wrote it."""
+import re
+
 from paper_1804_02941_amd import isa_checks as ic
 
 
@@ -74,3 +76,15 @@ def test_the_read_before_write_check_sees_a_register_set_on_one_path_only():
     (name, lines), = ic.kernels(UNWRITTEN)
     bad = ic.reads_before_any_write(lines)
     assert len(bad) == 1 and bad[0][2] == [2]                      # v2 is set only when the branch is not taken
+
+
+def test_the_padded_block_kernels_hold_both_bursts_of_loads_like_the_plain_ones(tmp_path):
+    """Each burst has registers of its own; a padded form with fewer registers than the plain one waits for one burst before it
+    requests the next (seen with 56 and 72 registers instead of 88 and 104)."""
+    out = str(tmp_path / "direct.s")
+    ic.compile_to_isa("direct.hip", out)
+    regs = dict(re.findall(r"\.amdhsa_kernel \S*binconv_block_kernelI(\w+?)EEv.*?\.amdhsa_next_free_vgpr (\d+)", open(out).read(), re.S))
+    padded = [k for k in regs if k.startswith("Lb1E") and "ELi2E" in k]
+    assert len(padded) == 8
+    for k in padded:
+        assert int(regs[k]) >= int(regs["Lb0E" + k[4:]]), k
