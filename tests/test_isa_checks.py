@@ -3,6 +3,8 @@ may be in flight has its registers left alone, and no inline-assembly instructio
 too soon behind the vector instruction that wrote it."""
 import re
 
+import pytest
+
 from paper_1804_02941_amd import isa_checks as ic
 
 
@@ -78,13 +80,28 @@ def test_the_read_before_write_check_sees_a_register_set_on_one_path_only():
     assert len(bad) == 1 and bad[0][2] == [2]                      # v2 is set only when the branch is not taken
 
 
-def test_the_padded_block_kernels_hold_both_bursts_of_loads_like_the_plain_ones(tmp_path):
+@pytest.fixture(scope="module")
+def direct_isa(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("isa") / "direct.s")
+    ic.compile_to_isa("direct.hip", out)
+    return open(out).read()
+
+
+def test_the_padded_block_kernels_hold_both_bursts_of_loads_like_the_plain_ones(direct_isa):
     """Each burst has registers of its own; a padded form with fewer registers than the plain one waits for one burst before it
     requests the next (seen with 56 and 72 registers instead of 88 and 104)."""
-    out = str(tmp_path / "direct.s")
-    ic.compile_to_isa("direct.hip", out)
-    regs = dict(re.findall(r"\.amdhsa_kernel \S*binconv_block_kernelI(\w+?)EEv.*?\.amdhsa_next_free_vgpr (\d+)", open(out).read(), re.S))
+    regs = dict(re.findall(r"\.amdhsa_kernel \S*binconv_block_kernelI(\w+?)EEv.*?\.amdhsa_next_free_vgpr (\d+)", direct_isa, re.S))
     padded = [k for k in regs if k.startswith("Lb1E") and "ELi2E" in k]
     assert len(padded) == 8
     for k in padded:
         assert int(regs[k]) >= int(regs["Lb0E" + k[4:]]), k
+
+
+def test_the_store_addresses_of_the_persistent_kernel_are_not_worked_out_again_for_every_store(direct_isa):
+    """Scalar stores of the fp32 output (F not a multiple of four): the four offsets of a lane stay in registers.  (Seen otherwise:
+    318 selects between the stores, each into a register that the store before still reads.)"""
+    bodies = re.findall(r"^_ZN\S*binconv_direct_kernelILi\dELi\dELb[01]ELb0EE\S*:(.*?)\.end_amdhsa_kernel", direct_isa, re.S | re.M)
+    assert len(bodies) == 12
+    for b in bodies:
+        stores = b[b.index("buffer_store_dword "):b.rindex("buffer_store_dword ")]
+        assert not re.findall(r"v_cndmask_b32\S* v\d+, v", stores)
