@@ -303,7 +303,8 @@ int dab_prepare_layers(const dab_weight_job* wjobs /* host */, int32_t n_wjobs, 
  *              (NULL to skip); this is what bit-exact tests compare
  *   ws         scratch of at least dab_binconv2d_workspace_bytes(d) bytes, 256-byte
  *              aligned (0 bytes for most layers: the kernels then read the packed bits
- *              directly; long reductions over many rows expand their operands into it);
+ *              directly.  Long reductions over many rows ask for room to expand their
+ *              operands into, also where the kernel then taken does not write to it);
  *              dead when the call's work has completed (DAB_ERR_WORKSPACE if NULL,
  *              too small or misaligned)
  * Padding may reach or exceed the kernel extent (windows entirely in the border give 0).

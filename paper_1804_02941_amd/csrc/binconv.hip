@@ -1060,36 +1060,78 @@ int init_binconv() {
     return raise_lds_limit<4, kOutY, kBf16>();
 }
 
+// Estimated time of the launches that go through the workspace: operands written (a4, e4) at 2.9 TB/s, then per tile of a
+// workgroup the k-steps of eight or four wavefronts, the output at 13.8 TB/s beside the multiplies of others; with the
+// reduction split, the partial sums twice through memory.  (Fitted to the layers that plan_product names; rms error 8 %.)
+static double expanded_us(const MfmaPlan& pl, bool bits) {
+    const MfmaGeom& g = pl.g;
+    const double out = 1.0 * g.M * g.F;
+    const long long units = 1ll * g.n_ntiles * g.n_mtiles * g.ksplit;
+    const long long tiles = pl.split ? (units + kNumCU - 1) / kNumCU
+                                     : 1ll * ceil_div(g.n_mtiles, g.wg_per_ntile) * ceil_div(g.n_ntiles, kNumCU);
+    double us = 8.2 + static_cast<double>(pl.a4_bytes + pl.e4_bytes) / 2.9e6 +
+                static_cast<double>(tiles) * (ceil_div(g.nk, g.ksplit) * (pl.waves == 8 ? 0.31 : 0.207) + 5.3);
+    if (!bits) us += 4.0 * out / 13.8e6;
+    if (pl.split) us += 3.2 + 8.0 * g.ksplit * out / 5.5e6;
+    return us;
+}
+
+// Which kernel computes a layer, with its plan.
+struct ProductPlans {
+    BlockPlan block;
+    DirectPlan direct;
+    SplitPlan split;
+    MfmaPlan expanded;
+    bool needs_ws;          // the caller has to bring the workspace of `expanded`, whichever kernel is taken
+};
+static int plan_product(const dab_conv_desc& d, bool bits, ProductPlans* p, Product* which) {
+    p->needs_ws = false;
+    // layers of a few hundred output blocks: one workgroup per block, straight from the bits, no workspace
+    *which = Product::kBlock;
+    if (plan_block(d, &p->block, false)) return DAB_OK;
+    // a reduction whose B fragments fit in LDS: one launch of the persistent kernel, no workspace
+    *which = Product::kDirect;
+    if (plan_direct(d, &p->direct)) return DAB_OK;
+    // Longer reductions: shares of it per wavefront over blocks of 64 x 128 where that is the faster form.  Otherwise a
+    // workgroup per 32 x 32 block up to a few thousand blocks, and past those the operands expanded into the workspace:
+    // a multiply has less work beside it there (nothing is expanded again for each filter tile and tap), which pays for
+    // the launch and the bytes more on large layers.  Chosen by estimated times.  Over 650 random layers of 37 to 1100
+    // k-steps, both outputs, the estimates are within 9 % rms (split), 8 % (workspace) and 15 % (blocks) of the measured
+    // times, so the split form has to come out a tenth faster; over 300 other layers no choice was then more than 7 %
+    // slower than the form that the layer would take without the split, 11 of 600 more than 3 %.
+    // (us, split | blocks | workspace, fp32 output:) 1024 x 9216 x 4096 21.4 | - | 55.8, 80142 pixels x 144 steps x 33
+    // 52.3 | - | 135, 92 x 10^3 pixels x 400 steps x 512 635 | - | 413, 24480 pixels x 637 steps x 640 310 | - | 216,
+    // 2025 pixels x 108 steps x 384 11.8 | 9.5 | -.
+    // (The workspace is asked for, as dab_binconv2d_workspace_bytes says, whichever of split and workspace is taken.)
+    const bool few_blocks = plan_block(d, &p->block, true);
+    if (!few_blocks) {
+        if (int rc = plan_binconv(d, &p->expanded)) return rc;
+        p->needs_ws = true;
+    }
+    const bool splits = plan_split(d, &p->split);
+    const double other_us = few_blocks ? p->block.us : expanded_us(p->expanded, bits);
+    if (splits && (bits ? p->split.us_bits : p->split.us) < 0.9 * other_us) *which = Product::kSplit;
+    else *which = few_blocks ? Product::kBlock : Product::kExpanded;
+    return DAB_OK;
+}
+int product_of(const dab_conv_desc& d, bool bits, Product* which) {
+    ProductPlans p;
+    return plan_product(d, bits, &p, which);
+}
+
 // Y != nullptr: fp32 output (and optional dbg_s1); Y == nullptr: re-binarized output into out_bits.
 static int run_binconv(const dab_conv_desc& d, const uint32_t* A, const uint32_t* E, const float* alpha,
                        const float* beta, float* Y, int32_t* dbg_s1, const float* tau_out, uint32_t* out_bits,
                        void* ws, size_t ws_bytes, hipStream_t st) {
-    // layers of a few hundred output blocks: one workgroup per block, straight from the bits, no workspace
-    BlockPlan bp;
-    if (plan_block(d, &bp, false)) return launch_block(bp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
-    // a reduction whose B fragments fit in LDS: one launch of the persistent kernel, no workspace
-    DirectPlan dp;
-    if (plan_direct(d, &dp)) {
-        if (int rc = ensure_device_ready()) return rc;
-        return launch_direct(dp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
-    }
-    // Longer reductions: shares of it per wavefront over blocks of 64 x 128, or a workgroup per 32 x 32
-    // block where those are too few to fill the chip: the smaller of two estimates.  Measured (us, long
-    // reductions | blocks): 300 x 3001 x 2000 11.0 | 7.4, 1568 pixels x 4608 x 512 11.1 | 10.1, 3136 pixels
-    // 11.7 | 15.7, 1024 x 9216 x 1000 13.8 | 17.5, 1024 x 5000 x 3000 19.7 | 36.6.
-    // (A workspace is asked for as it always was, by dab_binconv2d_workspace_bytes; only the layers that
-    // neither kernel covers, padded windows of more than 32 taps among them, still write to it.)
-    const bool few_blocks = plan_block(d, &bp, true);
-    MfmaPlan pl;
-    if (!few_blocks) {
-        if (int rc = plan_binconv(d, &pl)) return rc;
-        if (!ws || ws_bytes < pl.ws_bytes || misaligned(ws, 256)) return DAB_ERR_WORKSPACE;
-    }
-    SplitPlan sp;
-    const bool splits = plan_split(d, &sp);
-    if (few_blocks && !(splits && sp.us <= bp.us)) return launch_block(bp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
+    ProductPlans p;
+    Product which;
+    if (int rc = plan_product(d, Y == nullptr, &p, &which)) return rc;
+    const MfmaPlan& pl = p.expanded;
+    if (p.needs_ws && (!ws || ws_bytes < pl.ws_bytes || misaligned(ws, 256))) return DAB_ERR_WORKSPACE;
+    if (which == Product::kBlock) return launch_block(p.block, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
     if (int rc = ensure_device_ready()) return rc;
-    if (splits) return launch_split(sp, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
+    if (which == Product::kDirect) return launch_direct(p.direct, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
+    if (which == Product::kSplit) return launch_split(p.split, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);
     char* a4 = static_cast<char*>(ws);
     uint4* e4 = reinterpret_cast<uint4*>(a4 + pl.a4_bytes);
     float* sa = reinterpret_cast<float*>(a4 + pl.a4_bytes + pl.e4_bytes);

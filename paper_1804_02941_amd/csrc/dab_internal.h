@@ -123,12 +123,16 @@ struct SplitGeom {
 struct SplitPlan {
     DirectGeom g;
     SplitGeom sg;
-    double us;                     // estimated time of a launch
+    double us, us_bits;            // estimated time of a launch with fp32 and with packed-sign output
     int lw;
     bool pad;
     unsigned grid;
     size_t lds_bytes;
 };
+// The kernel a layer's product takes: a workgroup per 32 x 32 block, the persistent kernel, the one for long
+// reductions, or expanded operands in the workspace.
+enum class Product { kBlock, kDirect, kSplit, kExpanded };
+int product_of(const dab_conv_desc& d, bool bits, Product* which);
 bool plan_split(const dab_conv_desc& d, SplitPlan* pl);
 int launch_split(const SplitPlan& pl, hipStream_t st, const uint32_t* A, const uint32_t* E, const float* alpha,
                  const float* beta, float* Y, int32_t* dbg_s1, const float* tau_out, uint32_t* out_bits);

@@ -1,9 +1,11 @@
 // Host-side planning code under AddressSanitizer / UBSan: random layer geometries through the
 // planners of the product kernels and through every workspace-size query and entry point of the C
 // ABI (with placeholder pointers; without a GPU every call ends before a launch).  Checks the
-// invariants the kernels rely on.  Usage: fuzz_plans [cases] [seed]
+// invariants the kernels rely on.  Usage: fuzz_plans [cases] [seed]; or fuzz_plans route followed by the
+// eleven numbers of a layer's descriptor, any number of times: which kernel computes it, fp32 and packed-sign output.
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 
 #include "dab_internal.h"
 
@@ -115,6 +117,20 @@ int check_one(const dab_conv_desc& d) {
 }  // namespace
 
 int main(int argc, char** argv) {
+    if (argc > 1 && std::strcmp(argv[1], "route") == 0) {
+        static const char* const names[] = {"block", "direct", "split", "expanded"};
+        for (int a = 2; a + 11 <= argc; a += 11) {
+            int32_t v[11];
+            for (int i = 0; i < 11; ++i) v[i] = std::atoi(argv[a + i]);
+            const dab_conv_desc d{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10]};
+            for (const bool bits : {false, true}) {
+                dab::Product which;
+                if (dab::product_of(d, bits, &which) != DAB_OK) return 1;
+                std::printf("%s%c", names[static_cast<int>(which)], bits ? '\n' : ' ');
+            }
+        }
+        return 0;
+    }
     const int cases = argc > 1 ? std::atoi(argv[1]) : 20000;
     g_state = argc > 2 ? static_cast<uint64_t>(std::atoll(argv[2])) * 2 + 1 : 1;
     int planned = 0;

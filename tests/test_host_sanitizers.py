@@ -32,3 +32,24 @@ def test_random_geometries_through_the_host_code(fuzz, seed):
     p = subprocess.run([fuzz, "100000", str(seed)], capture_output=True, text=True, timeout=600)
     assert p.returncode == 0, p.stdout[-2000:] + p.stderr[-4000:]
     assert "geometries checked" in p.stdout
+
+
+def routes(fuzz, layers):
+    """[(kernel of the fp32 form, of the packed-sign form)] of layers (B, C, H, W, F, k, pad, stride)."""
+    args = [str(v) for B, C, H, W, F, k, p, s in layers for v in (B, C, H, W, F, k, k, p, p, s, s)]
+    out = subprocess.run([fuzz, "route", *args], capture_output=True, text=True, check=True).stdout
+    return [tuple(line.split()) for line in out.splitlines()]
+
+
+def test_long_reductions_take_the_kernel_that_measured_faster(fuzz):
+    """Layers whose times in the three forms differ by more than a fifth."""
+    layers = [(34, 992, 52, 52, 512, 5, 2, 1), (102, 832, 21, 22, 640, 7, 0, 1), (1, 768, 47, 47, 384, 3, 0, 1),
+              (1024, 9216, 1, 1, 4096, 1, 0, 1), (1024, 4096, 1, 1, 4096, 1, 0, 1)]
+    assert routes(fuzz, layers) == [(r, r) for r in ("expanded", "expanded", "block", "split", "split")]
+
+
+def test_the_gpu_tests_of_the_long_reduction_kernels_reach_them(fuzz):
+    from test_gpu_rebinarize import EXPANDED_LAYERS, SPLIT_LAYERS
+    for layers, kernel in ((SPLIT_LAYERS, "split"), (EXPANDED_LAYERS, "expanded")):
+        for layer, r in zip(layers, routes(fuzz, [c[1:] for c in layers])):
+            assert r == (kernel, kernel), layer[0]
