@@ -63,7 +63,7 @@ def test_host_side_validation_needs_no_gpu(lib):
     assert lib.dab_estimate_workspace_bytes(4, 100) == 0
     assert lib.dab_binfc_workspace_bytes(4, 100, 4) == 0            # small layers run from the bits alone
     assert lib.dab_binfc_workspace_bytes(2048, 64, 512) == 0        # and so do all whose filter bits fit in LDS
-    assert lib.dab_binfc_workspace_bytes(8192, 9216, 512) > 0       # a long reduction over many rows expands its operands
+    assert lib.dab_binfc_workspace_bytes(8192, 9216, 512) > 0       # a long reduction over many rows asks for room to expand its operands
     assert lib.dab_binfc_workspace_bytes(0, 100, 4) == 0
 
 

@@ -109,9 +109,9 @@ EXPANDED_LAYERS = [
     ("odd_words_by_time", 199, 288, 29, 29, 64, 3, 0, 1),
 ]
 LONG_REDUCTIONS = SPLIT_LAYERS + EXPANDED_LAYERS + [
-    # name, B, C, H, W, F, k, pad, stride: reductions of more than 36 steps over many blocks.  One, two and
-    # four words per load, an odd number of words per pixel, last tiles of 1 to 128 filters and 1 to 64
-    # pixels, shares of the reduction that end in whole and half rounds, the whole reduction in one share
+    # name, B, C, H, W, F, k, pad, stride: other reductions of more than 36 steps over many blocks, on whichever
+    # kernel comes out fastest.  One, two and four words per load, an odd number of words per pixel, last tiles of
+    # 1 to 128 filters and 1 to 64 pixels, shares of the reduction that end in whole and half rounds
     ("w4_tails", 65, 512, 9, 9, 129, 3, 1, 1), ("w4_even_taps", 260, 1024, 8, 8, 97, 2, 0, 1), ("w1_one_share", 100, 64, 26, 26, 512, 7, 0, 1), ("w2_stride", 70, 100, 21, 19, 150, 5, 2, 2),
     ("w1_odd_words", 40, 288, 12, 11, 131, 3, 2, 1), ("w1_odd_last_channels", 90, 70, 13, 12, 260, 5, 1, 1),
     ("w1_one_filter_block", 200, 64, 16, 16, 30, 7, 0, 1), ("fc_rows", 1021, 2560, 1, 1, 1030, 1, 0, 1),
@@ -209,7 +209,7 @@ def test_config3_fused_chain_matches_fp32_chain():
 
 
 def test_error_codes_of_the_new_entry_points():
-    d = dab.dab_conv_desc(8192, 9216, 1, 1, 512, 1, 1, 0, 0, 1, 1)   # a long reduction over many rows: operands are expanded into a workspace
+    d = dab.dab_conv_desc(8192, 9216, 1, 1, 512, 1, 1, 0, 0, 1, 1)   # a long reduction over many rows: a workspace is asked for, whichever kernel is taken
     A = torch.zeros((8192, 1, 1, 288), dtype=torch.int32, device="cuda:0")
     E = torch.zeros((288, 512), dtype=torch.int32, device="cuda:0")
     ab = torch.ones(512, dtype=torch.float32, device="cuda:0")

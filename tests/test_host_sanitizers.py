@@ -53,3 +53,10 @@ def test_the_gpu_tests_of_the_long_reduction_kernels_reach_them(fuzz):
     for layers, kernel in ((SPLIT_LAYERS, "split"), (EXPANDED_LAYERS, "expanded")):
         for layer, r in zip(layers, routes(fuzz, [c[1:] for c in layers])):
             assert r == (kernel, kernel), layer[0]
+
+
+def test_the_gpu_tests_of_wide_padding_reach_the_kernels_they_name(fuzz):
+    from test_gpu_parity import BORDER_LAYERS
+    kernels = {"persistent": "direct", "block": "block", "split": "split", "workspace": "expanded"}
+    for layer, r in zip(BORDER_LAYERS, routes(fuzz, [c[1:] for c in BORDER_LAYERS])):
+        assert r == (kernels[layer[0].split()[0]],) * 2, layer[0]
