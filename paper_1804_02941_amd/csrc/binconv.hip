@@ -1061,17 +1061,18 @@ int init_binconv() {
 }
 
 // Estimated time of the launches that go through the workspace: operands written (a4, e4) at 2.9 TB/s, then per tile of a
-// workgroup the k-steps of eight or four wavefronts, the output at 13.8 TB/s beside the multiplies of others; with the
-// reduction split, the partial sums twice through memory.  (Fitted to the layers that plan_product names; rms error 8 %.)
+// workgroup the k-steps of eight or four wavefronts, the output beside the multiplies of others at 14.2 TB/s, or at 6.4
+// where the stores are of single values; with the reduction split, the partial sums twice through memory.  (Fitted to
+// the layers that plan_product names; rms error 7 %.)
 static double expanded_us(const MfmaPlan& pl, bool bits) {
     const MfmaGeom& g = pl.g;
     const double out = 1.0 * g.M * g.F;
     const long long units = 1ll * g.n_ntiles * g.n_mtiles * g.ksplit;
     const long long tiles = pl.split ? (units + kNumCU - 1) / kNumCU
                                      : 1ll * ceil_div(g.n_mtiles, g.wg_per_ntile) * ceil_div(g.n_ntiles, kNumCU);
-    double us = 8.2 + static_cast<double>(pl.a4_bytes + pl.e4_bytes) / 2.9e6 +
+    double us = 9.9 + static_cast<double>(pl.a4_bytes + pl.e4_bytes) / 2.9e6 +
                 static_cast<double>(tiles) * (ceil_div(g.nk, g.ksplit) * (pl.waves == 8 ? 0.31 : 0.207) + 5.3);
-    if (!bits) us += 4.0 * out / 13.8e6;
+    if (!bits) us += 4.0 * out / (g.F % 4 ? 6.4e6 : 14.2e6);
     if (pl.split) us += 3.2 + 8.0 * g.ksplit * out / 5.5e6;
     return us;
 }
@@ -1095,13 +1096,13 @@ static int plan_product(const dab_conv_desc& d, bool bits, ProductPlans* p, Prod
     // Longer reductions: shares of it per wavefront over blocks of 64 x 128 where that is the faster form.  Otherwise a
     // workgroup per 32 x 32 block up to a few thousand blocks, and past those the operands expanded into the workspace:
     // a multiply has less work beside it there (nothing is expanded again for each filter tile and tap), which pays for
-    // the launch and the bytes more on large layers.  Chosen by estimated times.  Over 650 random layers of 37 to 1100
-    // k-steps, both outputs, the estimates are within 9 % rms (split), 8 % (workspace) and 15 % (blocks) of the measured
-    // times, so the split form has to come out a tenth faster; over 300 other layers no choice was then more than 7 %
-    // slower than the form that the layer would take without the split, 11 of 600 more than 3 %.
+    // the launch and the bytes more on large layers.  Chosen by estimated times, which are within 5 % (blocks), 6 %
+    // (split) and 7 % rms (workspace) of the measured ones over 3300 random layers of 37 to 1100 k-steps, both outputs;
+    // over 1750 others the form taken is 0.3 % slower than the faster one in the geometric mean, at most 23 %.  (Split
+    // up to 3 % above the other estimate: of the factors 0.9 to 1.1 this made the fewest choices that cost over 3 %.)
     // (us, split | blocks | workspace, fp32 output:) 1024 x 9216 x 4096 21.4 | - | 55.8, 80142 pixels x 144 steps x 33
     // 52.3 | - | 135, 92 x 10^3 pixels x 400 steps x 512 635 | - | 413, 24480 pixels x 637 steps x 640 310 | - | 216,
-    // 2025 pixels x 108 steps x 384 11.8 | 9.5 | -.
+    // 2025 pixels x 108 steps x 384 11.8 | 9.5 | -, 3136 x 72 x 512 12.1 | 15.2 | -, 789 x 8296 x 928 13.6 | 21.5 | -.
     // (The workspace is asked for, as dab_binconv2d_workspace_bytes says, whichever of split and workspace is taken.)
     const bool few_blocks = plan_block(d, &p->block, true);
     if (!few_blocks) {
@@ -1110,7 +1111,7 @@ static int plan_product(const dab_conv_desc& d, bool bits, ProductPlans* p, Prod
     }
     const bool splits = plan_split(d, &p->split);
     const double other_us = few_blocks ? p->block.us : expanded_us(p->expanded, bits);
-    if (splits && (bits ? p->split.us_bits : p->split.us) < 0.9 * other_us) *which = Product::kSplit;
+    if (splits && (bits ? p->split.us_bits : p->split.us) < 1.03 * other_us) *which = Product::kSplit;
     else *which = few_blocks ? Product::kBlock : Product::kExpanded;
     return DAB_OK;
 }

@@ -1045,13 +1045,15 @@ bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large) {
     // two of them hold a wavefront's whole share where that is short (one round trip to memory)
     pl->waves = g.nk >= 32 ? 8 : 2;
     pl->lw = (g.Cw % 2 == 0 && g.WH % 4 == 0) ? 4 : 1;
-    // Time of a launch, fitted to random layers up to 4e5 block k-steps (block k-steps per us at sixteen and
-    // four bytes of a pixel per load; the workgroups of filter blocks that do not exist on an XCD leave its
-    // neighbours with theirs).
-    pl->us = 4.8 + static_cast<double>(blocks) * nk * (8.0 * bg.fb_per_xcd / bg.n_fblocks) / (pl->lw == 4 ? 15300.0 : 9500.0);
     const int share = ceil_div(g.nk, pl->waves * pl->lw) * pl->lw;
     if (pl->lw == 4) pl->depth = share <= 8 ? 4 : (share > 16 && share <= 32 ? 16 : 8);
     else pl->depth = share <= 8 ? 4 : (share > 16 && share <= 26 ? 13 : 8);
+    // Time of a launch, fitted to 2500 random layers of more than 36 k-steps (rms error 5 %): workgroups per compute
+    // unit of the XCD with the most filter blocks, and in each the k-steps of its wavefronts in whole bursts, at
+    // sixteen and four bytes of a pixel per load; dearer where neighbouring taps share no cache lines.
+    const double per_cu = static_cast<double>(ceil_div(g.M, 32)) * bg.fb_per_xcd * kNumXCD / kNumCU;
+    const double step_us = pl->lw == 4 ? (g.T > 1 ? 0.0081 : 0.0093) : (g.T > 1 ? 0.015 : 0.0165);
+    pl->us = 1.9 + (per_cu + 1.65) * ((pl->pad ? 0.57 : 0.42) + pl->waves * ceil_div(share, pl->depth) * pl->depth * step_us);
     return true;
 }
 
@@ -1111,12 +1113,17 @@ bool plan_split(const dab_conv_desc& d, SplitPlan* pl) {
     sg.n_mtiles = ceil_div(g.M, 64 * (kSplitWaves >> sg.log_ks));
     const long long units = 1ll * sg.n_mtiles * n_ntiles;
     if (units >= (1ll << 30)) return false;
-    // Time of a launch, to compare with the other kernels' (fitted to random layers with the shares chosen above): a
-    // k-step by the words per load, a tenth more with padding, and what the fp32 stores add, more than three times as
-    // much where they are of single values.
-    const double step_us = (pl->lw == 1 ? 0.44 : (pl->lw == 2 ? 0.33 : 0.305)) * (pl->pad ? 1.09 : 1.0);
-    pl->us_bits = 3.0 + static_cast<double>((units + kNumCU - 1) / kNumCU) * (sg.groups_per_share * pl->lw * step_us + 5.2);
-    pl->us = pl->us_bits + (d.F % 4 ? 3.2 : 1.0) * 4.0 * g.M * d.F / 10.0e6;
+    // Time of a launch, to compare with the other kernels' (fitted to 3300 random layers with the shares chosen above,
+    // rms error 6 %): per round of workgroups the k-steps, which come in whole and then half rounds of eight, by the
+    // words per load; dearer with padding, with fewer taps that share their cache lines and with more compute units at
+    // work.  What the fp32 stores add is six times as much where they are of single values.
+    const int steps = sg.groups_per_share * pl->lw;
+    const int steps_run = steps % 8 == 0 ? steps : steps / 8 * 8 + (steps % 8 <= 4 ? 4 : 8);
+    const double rounds = static_cast<double>((units + kNumCU - 1) / kNumCU);
+    const double step_us = (pl->lw == 1 ? 0.324 : (pl->lw == 2 ? 0.241 : 0.21)) *
+                           (1.0 + (pl->pad ? 0.32 : 0.0) + 0.39 / g.T + 0.34 * units / (rounds * kNumCU));
+    pl->us_bits = 2.2 + rounds * (5.9 + steps_run * step_us);
+    pl->us = pl->us_bits + (d.F % 4 ? 2.9 : 0.51) * 4.0 * g.M * d.F / 10.0e6;
     sg.units = static_cast<int>(units);
     sg.per_xcd = ceil_div(sg.units, kNumXCD);
     sg.d_mtiles = make_fastdiv(sg.n_mtiles);

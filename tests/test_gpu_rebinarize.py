@@ -106,7 +106,7 @@ EXPANDED_LAYERS = [
     # name, B, C, H, W, F, k, pad, stride: through the workspace, by a padded window of more than 32 taps and by time
     ("eight_wavefronts", 32, 64, 48, 48, 200, 7, 3, 1), ("four_wavefronts", 16, 64, 48, 48, 200, 7, 3, 1),
     ("split_reduction", 4, 64, 48, 48, 200, 7, 3, 1), ("split_reduction_tails", 5, 70, 41, 37, 131, 7, 3, 1),
-    ("odd_words_by_time", 199, 288, 29, 29, 64, 3, 0, 1),
+    ("odd_words_by_time", 16, 80, 32, 48, 385, 5, 2, 1),
 ]
 LONG_REDUCTIONS = SPLIT_LAYERS + EXPANDED_LAYERS + [
     # name, B, C, H, W, F, k, pad, stride: other reductions of more than 36 steps over many blocks, on whichever
@@ -115,7 +115,7 @@ LONG_REDUCTIONS = SPLIT_LAYERS + EXPANDED_LAYERS + [
     ("w4_tails", 65, 512, 9, 9, 129, 3, 1, 1), ("w4_even_taps", 260, 1024, 8, 8, 97, 2, 0, 1), ("w1_one_share", 100, 64, 26, 26, 512, 7, 0, 1), ("w2_stride", 70, 100, 21, 19, 150, 5, 2, 2),
     ("w1_odd_words", 40, 288, 12, 11, 131, 3, 2, 1), ("w1_odd_last_channels", 90, 70, 13, 12, 260, 5, 1, 1),
     ("w1_one_filter_block", 200, 64, 16, 16, 30, 7, 0, 1), ("fc_rows", 1021, 2560, 1, 1, 1030, 1, 0, 1),
-    ("fc_odd", 515, 5003, 1, 1, 770, 1, 0, 1),
+    ("fc_odd", 515, 5003, 1, 1, 770, 1, 0, 1), ("w1_odd_words_narrow", 199, 288, 29, 29, 64, 3, 0, 1),
 ]
 
 

@@ -43,9 +43,15 @@ def routes(fuzz, layers):
 
 def test_long_reductions_take_the_kernel_that_measured_faster(fuzz):
     """Layers whose times in the three forms differ by more than a fifth."""
-    layers = [(34, 992, 52, 52, 512, 5, 2, 1), (102, 832, 21, 22, 640, 7, 0, 1), (1, 768, 47, 47, 384, 3, 0, 1),
-              (1024, 9216, 1, 1, 4096, 1, 0, 1), (1024, 4096, 1, 1, 4096, 1, 0, 1)]
-    assert routes(fuzz, layers) == [(r, r) for r in ("expanded", "expanded", "block", "split", "split")]
+    layers = {
+        "expanded": [(34, 992, 52, 52, 512, 5, 2, 1), (102, 832, 21, 22, 640, 7, 0, 1)],
+        "block": [(1, 768, 47, 47, 384, 3, 0, 1), (23, 222, 31, 8, 464, 5, 2, 2), (80, 395, 7, 7, 140, 3, 1, 1)],
+        "split": [(1024, 9216, 1, 1, 4096, 1, 0, 1), (1024, 4096, 1, 1, 4096, 1, 0, 1), (64, 512, 7, 7, 512, 3, 1, 1),
+                  (789, 8296, 1, 1, 928, 1, 0, 1), (25, 487, 23, 27, 379, 3, 1, 2), (2, 184, 48, 46, 224, 5, 2, 1),
+                  (112, 720, 54, 10, 74, 7, 0, 1), (64, 138, 48, 10, 816, 7, 0, 1)],
+    }
+    for kernel, ls in layers.items():
+        assert routes(fuzz, ls) == [(kernel, kernel)] * len(ls)
 
 
 def test_the_gpu_tests_of_the_long_reduction_kernels_reach_them(fuzz):
