@@ -105,72 +105,27 @@ __device__ __forceinline__ int job_column(unsigned r, int Fp) {
     return static_cast<int>(r / kNumXCD) < per_xcd ? f : Fp;
 }
 
-// The mask of filter column f as bits (Corollary 1, by stable rank: the split descriptor), by the
-// whole workgroup, from the row as load_row left it in registers: a byte per weight into LDS, then
-// one thread per packed word gathers its 32 channels (stride T), writes the word into column f of E
-// and adds its ones to the tap's count.  (A wavefront per word pair with a ballot is slower: its
-// address arithmetic is per word instead of per lane.)  Columns past F are written as zeros.
-// A window of one tap (fully-connected layers, 1 x 1 convolutions) has its channels in the order of the
-// row, so the 64 elements a wavefront holds under one j already are two words: a ballot each, kept by
-// lane j, no LDS.  (Through LDS the 32-byte stride of the gather put 64 lanes on eight banks: 4096 rows of
-// 9216 weights and 4096 of 4096, weight side of both in one call: 175.6 us, 157.6 with the ballots.)  Only
-// as many ballots as the row has steps of the workgroup's threads: with all of its class's, short rows were
-// slower than through LDS (16384 rows of 256 weights: LDS 91.0 us, nine ballots 97.5, one 87.8; 4096 of 64:
-// 28.6, 29.4, 27.3; 8192 of 512: 51.5, 53.9, 50.0).
-template <int THREADS, int ITEMS, bool BALLOTS = true>
-__device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitInfo* info, const float (&x)[ITEMS]) {
-    __shared__ uint8_t maskb[THREADS * ITEMS];
-    __shared__ uint32_t tapcnt[kPackMaxTaps];
+// v with lane l (the same in every lane) replaced by the scalar s.
+__device__ int amdgcn_writelane(int s, int l, int v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t write_lane(uint32_t v, uint32_t s, int l) {
+    return static_cast<uint32_t>(amdgcn_writelane(static_cast<int>(s), l, static_cast<int>(v)));
+}
+
+// Column f of E and the filter's per-tap counts from the mask, a byte per weight in LDS: one thread per
+// packed word gathers its 32 channels (stride T), writes the word and adds its ones to the tap's count.  (A
+// wavefront per word pair with a ballot is slower: its address arithmetic is per word instead of per lane.)
+template <int THREADS>
+__device__ __forceinline__ void pack_bytes(const EstJob& job, int f, const uint8_t* maskb, uint32_t* tapcnt) {
     const int tid = threadIdx.x;
     // the job's fields by value: behind a reference into the kernel's arguments every store below
     // would make the compiler read them again
     uint32_t* const E = job.E;
     uint32_t* const ecnt = job.ecnt;
-    const int n = job.n, F = job.F, C = job.C, T = job.T, Cw = job.Cw, Fp = job.Fp;
+    const int C = job.C, T = job.T, Cw = job.Cw, Fp = job.Fp;
     const int R = T * Cw;
-    if (f >= F) {
-        for (int r = tid; r < R; r += THREADS) E[static_cast<size_t>(r) * Fp + f] = 0u;
-        return;
-    }
-    const float tv = info->thr_val;
-    const int ti = info->thr_idx;
-    const bool upper = info->upper != 0;
-    if (BALLOTS && T == 1) {
-        static_assert(ITEMS <= 64 && THREADS / 64 <= kPackMaxTaps, "a lane per j, a count per wavefront");
-        const int lane = tid & 63, wave = tid >> 6;
-        unsigned long long words = 0ull;
-        uint32_t ones = 0;
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const int i = tid + j * THREADS;
-            if (j * THREADS >= n) break;                           // (the whole workgroup)
-            const bool lower = x[j] < tv || (x[j] == tv && i <= ti);
-            const unsigned long long m = __ballot(i < n && lower != upper);
-            ones += static_cast<uint32_t>(__popcll(m));
-            if (lane == j) words = m;
-        }
-        const int r = lane * (THREADS / 32) + wave * 2;
-        if (lane < ITEMS && r < R) E[static_cast<size_t>(r) * Fp + f] = static_cast<uint32_t>(words);
-        if (lane < ITEMS && r + 1 < R) E[static_cast<size_t>(r + 1) * Fp + f] = static_cast<uint32_t>(words >> 32);
-        if (lane == 0) tapcnt[wave] = ones;
-        __syncthreads();
-        if (tid == 0) {
-            uint32_t total = 0;
-            for (int w = 0; w < THREADS / 64; ++w) total += tapcnt[w];
-            ecnt[f] = total;
-        }
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int i = tid + j * THREADS;
-        const bool lower = x[j] < tv || (x[j] == tv && i <= ti);
-        if (i < n) maskb[i] = lower != upper ? 1 : 0;
-        if (j % 8 == 7) __builtin_amdgcn_sched_barrier(0);
-    }
     for (int t = tid; t < T; t += THREADS) tapcnt[t] = 0u;
-    __syncthreads();
-    // one thread per packed word: its 32 channels sit T bytes apart (all reads in flight together)
+    lds_barrier();
+    // (all reads of a word in flight together)
     for (int r = tid; r < R; r += THREADS) {
         const int tap = r / Cw, w = r - tap * Cw;
         const int c0 = 32 * w, nc = min(32, C - c0);
@@ -185,14 +140,95 @@ __device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitIn
         E[static_cast<size_t>(r) * Fp + f] = word;
         atomicAdd(&tapcnt[tap], static_cast<uint32_t>(__builtin_popcount(word)));
     }
-    __syncthreads();
+    lds_barrier();
     for (int t = tid; t < T; t += THREADS) ecnt[static_cast<size_t>(f) * T + t] = tapcnt[t];
 }
 
-__device__ __forceinline__ const EstJob& find_job(const EstJobs& jobs, unsigned* blk0) {
+// The mask of filter column f as bits (Corollary 1, by stable rank: the split descriptor), by the
+// whole workgroup, from the row as load_row left it in registers.
+// A window of one tap (fully-connected layers, 1 x 1 convolutions) has its channels in the order of the
+// row, so the 64 elements a wavefront holds under one j already are two words: a ballot each, kept by
+// lane j, no LDS.  (Through LDS the 32-byte stride of the gather put 64 lanes on eight banks: 4096 rows of
+// 9216 weights and 4096 of 4096, weight side of both in one call: 175.6 us, 157.6 with the ballots.)  Only
+// as many ballots as the row has steps of the workgroup's threads: with all of its class's, short rows were
+// slower than through LDS (16384 rows of 256 weights: LDS 91.0 us, nine ballots 97.5, one 87.8; 4096 of 64:
+// 28.6, 29.4, 27.3; 8192 of 512: 51.5, 53.9, 50.0).
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitInfo* info, const float (&x)[ITEMS], uint8_t* maskb) {
+    __shared__ uint32_t tapcnt[kPackMaxTaps];
+    const int tid = threadIdx.x;
+    const int n = job.n;
+    const float tv = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(info->thr_val)));
+    const int ti = __builtin_amdgcn_readfirstlane(info->thr_idx);
+    const bool upper = __builtin_amdgcn_readfirstlane(info->upper) != 0;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // The lower group: w < tv, or w = tv up to index ti, that is w <= tv in a thread's elements up to j_tie and w <= the
+    // float below tv in those behind it.  (Positions past n hold NaN and are in neither group.)
+    const uint32_t tkey = float_to_key(tv);
+    const float below = key_to_float(tkey == 0x80000000u ? tkey - 2u : tkey - 1u);        // (below zero: not -0)
+    const int j_tie = ti < tid ? -1 : (ti - tid) / THREADS;
+    if (job.T == 1) {
+        static_assert(ITEMS <= 64 && THREADS / 64 <= kPackMaxTaps, "a lane per j, a count per wavefront");
+        uint32_t w0 = 0, w1 = 0;
+        uint32_t ones = 0;
+        auto words = [&](auto in_alpha) {
+            for_chunks<ITEMS>([&](auto c, auto e) {
+                if (c * THREADS >= n) return false;                // (the whole workgroup)
+#pragma unroll
+                for (int j = c; j < e; ++j) {
+                    const unsigned long long m = __ballot(in_alpha(x[j], j <= j_tie ? tv : below));
+                    ones += static_cast<uint32_t>(__builtin_popcountll(m));
+                    w0 = write_lane(w0, static_cast<uint32_t>(m), j);
+                    w1 = write_lane(w1, static_cast<uint32_t>(m >> 32), j);
+                }
+                return true;
+            });
+        };
+        if (upper) words([](float v, float t) { return v > t; });
+        else words([](float v, float t) { return v <= t; });
+        uint32_t* const E = job.E;
+        const int R = job.Cw, Fp = job.Fp;
+        const int r = lane * (THREADS / 32) + wave * 2;
+        if (lane < ITEMS && r < R) E[static_cast<size_t>(r) * Fp + f] = w0;
+        if (lane < ITEMS && r + 1 < R) E[static_cast<size_t>(r + 1) * Fp + f] = w1;
+        if (lane == 0) tapcnt[wave] = ones;
+        lds_barrier();
+        if (tid == 0) {
+            uint32_t total = 0;
+            for (int w = 0; w < THREADS / 64; ++w) total += tapcnt[w];
+            job.ecnt[f] = total;
+        }
+        return;
+    }
+    const uint8_t in_lower = upper ? 0 : 1, in_upper = upper ? 1 : 0;
+    for_chunks<ITEMS>([&](auto c, auto e) {
+        if (c * THREADS >= n) return false;
+#pragma unroll
+        for (int j = c; j < e; ++j)                                // (past n: nobody reads it)
+            maskb[tid + j * THREADS] = x[j] <= (j <= j_tie ? tv : below) ? in_lower : in_upper;
+        return true;
+    });
+    pack_bytes<THREADS>(job, f, maskb, tapcnt);
+}
+// The same from the row in memory (rows that were sorted).
+template <int THREADS, int MAX_N>
+__device__ __forceinline__ void pack_row_from(const EstJob& job, int f, const SplitInfo* info, const float* __restrict__ row) {
+    __shared__ uint8_t maskb[MAX_N];
+    __shared__ uint32_t tapcnt[kPackMaxTaps];
+    const float tv = info->thr_val;
+    const int ti = info->thr_idx;
+    const bool upper = info->upper != 0;
+    for (int i = threadIdx.x; i < job.n; i += THREADS) {
+        const float w = row[i];
+        maskb[i] = (w < tv || (w == tv && i <= ti)) != upper ? 1 : 0;
+    }
+    pack_bytes<THREADS>(job, f, maskb, tapcnt);
+}
+
+__device__ __forceinline__ const EstJob& find_job(const EstJobs& jobs, unsigned block, unsigned* blk0) {
     int j = 0;
     *blk0 = 0;
-    while (j + 1 < jobs.n && blockIdx.x >= jobs.job[j].blk_end) *blk0 = jobs.job[j++].blk_end;
+    while (j + 1 < jobs.n && block >= jobs.job[j].blk_end) *blk0 = jobs.job[j++].blk_end;
     return jobs.job[j];
 }
 
@@ -200,18 +236,21 @@ __device__ __forceinline__ const EstJob& find_job(const EstJobs& jobs, unsigned*
 // the row, the sort by the same workgroup (SORT_HERE) or a flag for the sort kernel launched
 // behind; then the packing.
 template <int THREADS, int ITEMS, int NB, int CAP, bool SORT_HERE>
-__device__ __forceinline__ void binarize_row_of_block(const EstJobs& jobs) {
+__device__ __forceinline__ void binarize_row_of_block(const EstJobs& jobs, unsigned block) {
+    using Lds = BucketLds<THREADS, NB, CAP>;
+    constexpr size_t kPool = sizeof(Lds) > THREADS * ITEMS ? sizeof(Lds) : THREADS * ITEMS;
+    __shared__ __align__(16) unsigned char pool[kPool];            // the search's arrays, then the mask, a byte per weight
     __shared__ SplitInfo info;
     unsigned blk0;
-    const EstJob& q = find_job(jobs, &blk0);
-    const int f = job_column(blockIdx.x - blk0, q.Fp);
+    const EstJob& q = find_job(jobs, block, &blk0);
+    const int f = job_column(block - blk0, q.Fp);
     if (f >= q.Fp) return;
     float x[ITEMS];
     bool done = true;
     if (f < q.F) {
         load_row<THREADS, ITEMS>(q.W + static_cast<size_t>(f) * q.n, q.n, x);
-        done = bucket_row<THREADS, ITEMS, NB, CAP>(x, q.n, f, q.alpha, q.beta, q.K, q.thr_val, q.thr_idx, q.aiu, q.K_prev,
-                                                   q.upper_prev, q.max_change, &info);
+        done = bucket_row<THREADS, ITEMS, NB, CAP>(*reinterpret_cast<Lds*>(pool), x, q.n, f, q.alpha, q.beta, q.K, q.thr_val,
+                                                   q.thr_idx, q.aiu, q.K_prev, q.upper_prev, q.max_change, &info);
         if constexpr (SORT_HERE) {
             if (!done) {
                 __syncthreads();
@@ -222,60 +261,59 @@ __device__ __forceinline__ void binarize_row_of_block(const EstJobs& jobs) {
         } else if (threadIdx.x == 0) {
             q.flags[f] = done ? 0 : 1;
         }
-        __syncthreads();
+        lds_barrier();
     }
-    if (q.E && done) {
-        // many elements per thread: read them again (from L2) rather than hold them through the estimation
-        if (ITEMS > 32 && f < q.F) load_row<THREADS, ITEMS>(q.W + static_cast<size_t>(f) * q.n, q.n, x);
-        pack_row<THREADS, ITEMS>(q, f, &info, x);
+    if (q.E && f >= q.F) {
+        const int R = q.T * q.Cw, Fp = q.Fp;
+        uint32_t* const E = q.E;
+        for (int r = threadIdx.x; r < R; r += THREADS) E[static_cast<size_t>(r) * Fp + f] = 0u;
+    } else if (q.E && done) {
+        pack_row<THREADS, ITEMS>(q, f, &info, x, pool);
     }
 }
 
 // The weight side of the layers in `jobs`, and beside it a share of the activation packing in
-// `packs` (none when packs.n == 0).  The two do not depend on each other and load different parts
-// of the chip: the estimation is bound by vector instructions and LDS, the packing by memory, and the
-// workgroups of one launch that share a compute unit are at different points of their work (half of
-// them pack first), so the memory stream of some runs under the arithmetic of the others.
+// `packs`.  The two do not depend on each other and load different parts of the chip: the estimation is
+// bound by vector instructions and LDS, the packing by memory, so the launch's first n_pack workgroups
+// pack and the others take a row each: every compute unit holds wavefronts of both kinds, and the memory
+// stream of the ones runs under the arithmetic of the others.  (Config 3 at batch 256, inputs not in the
+// caches: packing alone 43 us, weight sides alone 35.5, together 56.5; with a row and then a share of the
+// packing in every workgroup, half of them the other way round, 64.3.)
 // Across launches on different streams this overlap does not happen (measured: the times add up).
 template <int THREADS, int ITEMS, int NB, int CAP, bool SORT_HERE, int MIN_WAVES>
 __global__ __launch_bounds__(THREADS, MIN_WAVES) void binarize_rows_kernel(const EstJobs jobs) {
     DAB_RESERVE_VGPRS();
-    binarize_row_of_block<THREADS, ITEMS, NB, CAP, SORT_HERE>(jobs);
+    binarize_row_of_block<THREADS, ITEMS, NB, CAP, SORT_HERE>(jobs, blockIdx.x);
 }
 template <int THREADS, int ITEMS, int NB, int CAP, bool SORT_HERE, int MIN_WAVES>
-__global__ __launch_bounds__(THREADS, MIN_WAVES) void prepare_rows_kernel(const EstJobs jobs, const PackJobs packs) {
+__global__ __launch_bounds__(THREADS, MIN_WAVES) void prepare_rows_kernel(const EstJobs jobs, const PackJobs packs, unsigned n_pack) {
     DAB_RESERVE_VGPRS();
-    // consecutive workgroups go to consecutive XCDs and, inside one, to consecutive compute units:
-    // the workgroups that meet on a compute unit are 256 apart, and every other one of them packs first
-    const bool pack_first = ((blockIdx.x >> 8) & 1u) != 0;
-    if (pack_first) pack_share<THREADS / 64>(packs, blockIdx.x);
-    binarize_row_of_block<THREADS, ITEMS, NB, CAP, SORT_HERE>(jobs);
-    if (!pack_first) pack_share<THREADS / 64>(packs, blockIdx.x);
+    if (blockIdx.x < n_pack) pack_share<THREADS / 64>(packs, blockIdx.x);
+    else binarize_row_of_block<THREADS, ITEMS, NB, CAP, SORT_HERE>(jobs, blockIdx.x - n_pack);
 }
 
-// The rows the kernel above has flagged, kSortRowsPerGroup per workgroup (their flags are one
-// aligned 8-byte read: the flag array of a job is padded to a multiple of 256 bytes).
+// The rows the kernels above have flagged, kSortRowsPerGroup per workgroup.  Their flags are one aligned 8-byte
+// read: the flags of all jobs are one array, each job's part padded to a multiple of 256 bytes.  That read comes
+// first, since as a rule nothing is flagged and the launch is only what it takes to see that.
 template <int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void binarize_sort_kernel(const EstJobs jobs) {
+__global__ __launch_bounds__(THREADS) void binarize_sort_kernel(const uint8_t* flags, const EstJobs jobs) {
     static_assert(kSortRowsPerGroup == 8, "the flags of a workgroup's rows are read as one 64-bit word");
+    unsigned long long fl = reinterpret_cast<const unsigned long long*>(flags)[blockIdx.x];
+    if (fl == 0ull) return;                         // the bucket kernel has finished all of them
     __shared__ SplitInfo info;
     unsigned blk0;
-    const EstJob& q = find_job(jobs, &blk0);
+    const EstJob& q = find_job(jobs, blockIdx.x, &blk0);
     const int f0 = static_cast<int>(blockIdx.x - blk0) * kSortRowsPerGroup;
-    unsigned long long fl = *reinterpret_cast<const unsigned long long*>(q.flags + f0);
+    if (f0 >= q.F) return;                          // (padding: whatever the workspace held)
     if (f0 + kSortRowsPerGroup > q.F) fl &= (1ull << (8 * (q.F - f0))) - 1ull;     // rows past the last one are not ours
-    if (fl == 0ull) return;                         // the bucket kernel has finished all of them
+    if (fl == 0ull) return;
     for (int k = 0; k < kSortRowsPerGroup; ++k) {
         if (((fl >> (8 * k)) & 0xFFull) == 0ull) continue;
         const int f = f0 + k;
         sort_row<THREADS, ITEMS>(q.W, q.n, f, q.alpha, q.beta, q.K, q.thr_val, q.thr_idx, q.aiu, q.K_prev, q.upper_prev,
                                  q.max_change, &info);
         __syncthreads();
-        if (q.E) {
-            float x[ITEMS];
-            load_row<THREADS, ITEMS>(q.W + static_cast<size_t>(f) * q.n, q.n, x);
-            pack_row<THREADS, ITEMS, false>(q, f, &info, x);       // (few rows come here, and the ballots' registers would spill)
-        }
+        if (q.E) pack_row_from<THREADS, THREADS * ITEMS>(q, f, &info, q.W + static_cast<size_t>(f) * q.n);
         __syncthreads();
     }
 }
@@ -336,7 +374,7 @@ __global__ __launch_bounds__(256) void sign_split_kernel(const float* __restrict
 constexpr int kEstimateMaxN = 1024 * 13;
 
 constexpr int kBucketMinN = 4096;        // rows from here on: bucket kernel, then the sort kernel for the rows it flags
-constexpr int kShortMinN = 256;          // rows above this and below kBucketMinN: the one-launch kernel for short rows
+constexpr int kSortMaxN = 192;           // rows up to here, where there are many: the sort kernel
 
 static size_t estimate_ws_bytes(int F, int n) {
     return n >= kBucketMinN ? (static_cast<size_t>(F) + 255) & ~static_cast<size_t>(255) : 0;
@@ -352,18 +390,28 @@ static int dispatch_estimate(const float* W, int F, int n, float* alpha, float* 
     uint8_t* only = nullptr;
     if (n >= kBucketMinN && ws && ws_bytes >= estimate_ws_bytes(F, n)) {
         only = static_cast<uint8_t*>(ws);
-        const int rc = n <= 512 * 16
-            ? launch(estimate_bucket_kernel<512, 16, 2048, 512>, dim3(F), dim3(512), 0, st, W, n, alpha, beta, K, thr_val,
+        // (few long rows: eight wavefronts finish a row sooner, four finish more rows in the same time: 12544 weights, 512 rows
+        // 16.3 us and 17.1, 1024 rows 27.4 and 26.3, 4096 rows 75.8 and 70.5)
+        const int rc = n <= 256 * 18
+            ? launch(estimate_bucket_kernel<256, 18, 1024, 256>, dim3(F), dim3(256), 0, st, W, n, alpha, beta, K, thr_val,
                      thr_idx, aiu, K_prev, upper_prev, max_change, only)
-            : launch(estimate_bucket_kernel<512, 26, 2048, 512>, dim3(F), dim3(512), 0, st, W, n, alpha, beta, K, thr_val,
+            : n <= 256 * 36
+            ? launch(estimate_bucket_kernel<256, 36, 2048, 256>, dim3(F), dim3(256), 0, st, W, n, alpha, beta, K, thr_val,
+                     thr_idx, aiu, K_prev, upper_prev, max_change, only)
+            : F <= 2 * kNumCU
+            ? launch(estimate_bucket_kernel<512, 26, 2048, 512>, dim3(F), dim3(512), 0, st, W, n, alpha, beta, K, thr_val,
+                     thr_idx, aiu, K_prev, upper_prev, max_change, only)
+            : launch(estimate_bucket_kernel<256, 52, 2048, 256>, dim3(F), dim3(256), 0, st, W, n, alpha, beta, K, thr_val,
                      thr_idx, aiu, K_prev, upper_prev, max_change, only);
         if (rc) return rc;
     }
-    // rows between the two: one launch, buckets first and the sort inside the kernel where needed
+    // shorter rows: one launch, buckets first and the sort inside the kernel where needed.  A wavefront per row sorts the
+    // shortest rows; with a workgroup per row the search is faster until the rows fill the chip several times (64 weights:
+    // 64 rows 5.9 us and 8.4 sorted, 512 rows 6.5 and 9.0, 4096 rows 20.2 and 14.0).
 #define DAB_SHORT(T, I, NB) \
     return launch(estimate_short_kernel<T, I, NB, 256>, dim3(F), dim3(T), 0, st, W, n, alpha, beta, K, thr_val, thr_idx, \
                   aiu, K_prev, upper_prev, max_change)
-    if (n > kShortMinN && n < kBucketMinN) {
+    if (n < kBucketMinN && (n > kSortMaxN || F <= 6 * kNumCU)) {
         if (n <= 256 * 3) DAB_SHORT(256, 3, 512);
         if (n <= 256 * 5) DAB_SHORT(256, 5, 1024);
         if (n <= 256 * 7) DAB_SHORT(256, 7, 1024);
@@ -376,13 +424,7 @@ static int dispatch_estimate(const float* W, int F, int n, float* alpha, float* 
 #define DAB_EST(T, I) \
     return launch(estimate_kernel<T, I>, dim3(F), dim3(T), 0, st, W, n, alpha, beta, K, thr_val, thr_idx, aiu, K_prev, \
                   upper_prev, max_change, only)
-    if (n <= 64 * 3) DAB_EST(64, 3);
-    if (n <= 256 * 3) DAB_EST(256, 3);
-    if (n <= 256 * 5) DAB_EST(256, 5);
-    if (n <= 256 * 7) DAB_EST(256, 7);
-    if (n <= 256 * 9) DAB_EST(256, 9);
-    if (n <= 256 * 11) DAB_EST(256, 11);
-    if (n <= 512 * 7) DAB_EST(512, 7);
+    if (n <= kSortMaxN) DAB_EST(64, 3);
     if (n <= 512 * 9) DAB_EST(512, 9);
     if (n <= 512 * 11) DAB_EST(512, 11);
     if (n <= 1024 * 7) DAB_EST(1024, 7);
@@ -435,31 +477,36 @@ static HandOver hand_over_plan(const dab_weight_job* jobs, int n_jobs) {
     return h;
 }
 
+// Hand-over flags of a job with F filters.
+static size_t flag_bytes(int F) { return (static_cast<size_t>(F) + 255) & ~static_cast<size_t>(255); }
+
 static size_t weight_jobs_ws_bytes(const dab_weight_job* jobs, int n_jobs) {
     size_t total = 0;
     const HandOver h = hand_over_plan(jobs, n_jobs);
     for (int i = 0; i < n_jobs; ++i) {
         const long long n = 1ll * jobs[i].C * jobs[i].kh * jobs[i].kw;
         if (n > kShortMaxN || (n > kSmallMaxN ? h.medium : h.small))
-            total += (static_cast<size_t>(jobs[i].F) + 255) & ~static_cast<size_t>(255);
+            total += flag_bytes(jobs[i].F);
     }
     return total;
 }
 
-// Relative duration of a row in its launch (measured on MI355X: 14 ns a row of the 256-thread kernel,
-// 30 of the 512-thread one, 20 + 2.2 per thousand weights of the long rows), for dealing the
-// activation packing out over the launches.
-static double row_cost(int n) {
-    return n <= kSmallMaxN ? 14.0 : (n <= kShortMaxN ? 30.0 : 20.0 + 2.2e-3 * n);
+// Duration of a class's launch by its rows, in us (measured on MI355X over 256 to 4096 rows), for dealing
+// the activation packing out over the launches.
+static double rows_us(int c, long long rows) {
+    constexpr double kLaunch[4] = {6.0, 6.0, 8.0, 8.0}, kRow[4] = {0.0045, 0.0062, 0.0100, 0.0135};
+    return rows > 0 ? kLaunch[c] + kRow[c] * static_cast<double>(rows) : 0.0;
 }
+
+constexpr double kWidePackBytes = 8e7;
 
 static int run_weight_jobs(const dab_weight_job* jobs, int n_jobs, void* ws, size_t ws_bytes, hipStream_t st,
                            const dab_pack_job* packs = nullptr, int n_packs = 0) {
-    // three classes of rows, a launch each where present (a fourth, behind the long rows, for the rows they flag)
+    // four classes of rows, a launch each where present, and one behind them for the rows they flag
     constexpr int kClasses = 4;
     EstJobs cls[kClasses], sortj;
     unsigned end[kClasses] = {0, 0, 0, 0}, sort_end = 0;
-    double cost[kClasses] = {0.0, 0.0, 0.0, 0.0};
+    long long rows[kClasses] = {0, 0, 0, 0};
     for (int c = 0; c < kClasses; ++c) cls[c].n = 0;
     sortj.n = 0;
     uint8_t* flags = static_cast<uint8_t*>(ws);
@@ -476,58 +523,64 @@ static int run_weight_jobs(const dab_weight_job* jobs, int n_jobs, void* ws, siz
         const bool flagged = c >= 2 || (c == 1 ? hand.medium : hand.small);
         if (flagged) {
             q.flags = flags;
-            flags += (static_cast<size_t>(in.F) + 255) & ~static_cast<size_t>(255);
+            flags += flag_bytes(in.F);
         }
         end[c] += columns;
-        cost[c] += row_cost(q.n) * in.F;
+        rows[c] += in.F;
         q.blk_end = end[c];
         cls[c].job[cls[c].n++] = q;
         if (flagged) {
-            sort_end += static_cast<unsigned>(ceil_div(in.F, kSortRowsPerGroup));
+            sort_end += static_cast<unsigned>(flag_bytes(in.F) / kSortRowsPerGroup);
             q.blk_end = sort_end;
             sortj.job[sortj.n++] = q;
         }
     }
     (void)ws_bytes;
     // the activation packing, dealt out over the launches in proportion to their duration: every tensor's
-    // pixels are cut at the same fractions (a launch with fewer workgroups than tensors takes none)
+    // pixels are cut at the same fractions
     PackJobs pk[kClasses];
-    for (int c = 0; c < kClasses; ++c) pk[c].n = 0;
-    if (n_packs > 0) {
-        double total = 0.0;
-        for (int c = 0; c < kClasses; ++c) {
-            if (end[c] < static_cast<unsigned>(n_packs)) cost[c] = 0.0;
-            total += cost[c];
+    unsigned n_pack[kClasses] = {0, 0, 0, 0};
+    double us[kClasses], total = 0.0, pack_bytes = 0.0;
+    for (int c = 0; c < kClasses; ++c) {
+        pk[c].n = 0;
+        us[c] = rows_us(c, rows[c]);
+        total += us[c];
+    }
+    for (int i = 0; i < n_packs; ++i) pack_bytes += 4.0 * packs[i].B * packs[i].H * packs[i].W * packs[i].C;
+    // Rows of 9217 .. 13312 weights: 512 threads finish a row sooner, 256 finish more rows in the same time and leave
+    // room for packing workgroups: 512 rows 18.5 us and 19.3, 1024 rows 30.5 and 28.4, 4096 rows 83.8 and 75.3; the
+    // rows of config 3 with its packing at batch 32 (30 MB) 40.1 and 41.9, at 96 45.6 and 46.0, at 128 (120 MB) 50.7 and
+    // 48.2, at 256 62.7 and 55.8.
+    const bool wide = rows[3] <= 2 * kNumCU && pack_bytes < kWidePackBytes;
+    const int class_waves[kClasses] = {4, hand.medium ? 4 : 8, 4, wide ? 8 : 4};   // (wavefronts of the class's workgroups)
+    double done = 0.0;
+    for (int c = 0; c < kClasses && n_packs > 0; ++c) {
+        if (us[c] <= 0.0) continue;
+        const double lo = done / total, hi = (done + us[c]) / total;
+        done += us[c];
+        for (int i = 0; i < n_packs; ++i) {
+            const long long pixels = 1ll * packs[i].B * packs[i].H * packs[i].W;
+            const long long p0 = static_cast<long long>(lo * static_cast<double>(pixels));
+            const long long p1 = done >= total ? pixels : static_cast<long long>(hi * static_cast<double>(pixels));
+            if (p1 > p0) pk[c].job[pk[c].n++] = make_pack_job(packs[i], p0, p1);
         }
-        if (total <= 0.0) return DAB_ERR_UNSUPPORTED;             // (the caller packs separately then)
-        double done = 0.0;
-        for (int c = 0; c < kClasses; ++c) {
-            if (cost[c] <= 0.0) continue;
-            const double lo = done / total, hi = (done + cost[c]) / total;
-            done += cost[c];
-            for (int i = 0; i < n_packs; ++i) {
-                const long long pixels = 1ll * packs[i].B * packs[i].H * packs[i].W;
-                const long long p0 = static_cast<long long>(lo * static_cast<double>(pixels));
-                const long long p1 = done >= total ? pixels : static_cast<long long>(hi * static_cast<double>(pixels));
-                if (p1 > p0) pk[c].job[pk[c].n++] = make_pack_job(packs[i], p0, p1);
-            }
-            const int class_waves[kClasses] = {4, hand.medium ? 4 : 8, 8, 8};      // (wavefronts of the class's workgroups)
-            if (pk[c].n) share_pack_blocks(&pk[c], end[c], class_waves[c]);
-        }
+        // eight wavefronts of packing per compute unit beside the rows' (four: 59.8 us for config 3 at batch 256, eight 56.5,
+        // twelve 56.4)
+        if (pk[c].n) n_pack[c] = share_pack_blocks(&pk[c], 8 * kNumCU / class_waves[c], class_waves[c]);
     }
 #define DAB_ROWS(C, T, I, NB, CAP, SORT, MINW) \
-    (pk[C].n ? launch(prepare_rows_kernel<T, I, NB, CAP, SORT, MINW>, dim3(end[C]), dim3(T), 0, st, cls[C], pk[C]) \
+    (pk[C].n ? launch(prepare_rows_kernel<T, I, NB, CAP, SORT, MINW>, dim3(end[C] + n_pack[C]), dim3(T), 0, st, cls[C], pk[C], n_pack[C]) \
              : launch(binarize_rows_kernel<T, I, NB, CAP, SORT, MINW>, dim3(end[C]), dim3(T), 0, st, cls[C]))
     if (cls[0].n)
-        if (int rc = hand.small ? DAB_ROWS(0, 256, 9, 512, 256, false, 7) : DAB_ROWS(0, 256, 9, 512, 256, true, 5)) return rc;
+        if (int rc = hand.small ? DAB_ROWS(0, 256, 9, 512, 256, false, 7) : DAB_ROWS(0, 256, 9, 512, 256, true, 4)) return rc;
     if (cls[1].n)
         if (int rc = hand.medium ? DAB_ROWS(1, 256, 18, 1024, 256, false, 6) : DAB_ROWS(1, 512, 9, 2048, 256, true, 4)) return rc;
     if (cls[2].n)
-        if (int rc = DAB_ROWS(2, 512, 18, 2048, 512, false, 6)) return rc;
+        if (int rc = DAB_ROWS(2, 256, 36, 2048, 256, false, 4)) return rc;
     if (cls[3].n)
-        if (int rc = DAB_ROWS(3, 512, 26, 2048, 512, false, 4)) return rc;
+        if (int rc = wide ? DAB_ROWS(3, 512, 26, 2048, 512, false, 4) : DAB_ROWS(3, 256, 52, 2048, 256, false, 3)) return rc;
     if (sortj.n) {
-        if (int rc = launch(binarize_sort_kernel<1024, 13>, dim3(sort_end), dim3(1024), 0, st, sortj)) return rc;
+        if (int rc = launch(binarize_sort_kernel<1024, 13>, dim3(sort_end), dim3(1024), 0, st, static_cast<const uint8_t*>(ws), sortj)) return rc;
     }
 #undef DAB_ROWS
     return DAB_OK;

@@ -6,10 +6,16 @@
 
 #ifndef DAB_HOST_EMULATION
 #include "dab_internal.h"
+#define DAB_RCP_F32(x) __builtin_amdgcn_rcpf(x)
 #define DAB_OPAQUE_F32(x) asm volatile("" : "+v"(x))   // the value as the compiler knows nothing about
+#define DAB_OPAQUE_I32(x) asm volatile("" : "+v"(x))
 #else
+#define DAB_OPAQUE_I32(x) asm volatile("" : "+m"(x))
 #define DAB_OPAQUE_F32(x) asm volatile("" : "+m"(x))
+#define DAB_RCP_F32(x) (1.0f / (x))
 #endif
+
+#include <type_traits>
 
 namespace dab {
 
@@ -97,6 +103,34 @@ __device__ __forceinline__ double wave_max_f64(double v) {                    //
     DAB_DPP_STEPS(DAB_STEP)
 #undef DAB_STEP
     return v;
+}
+__device__ __forceinline__ float wave_max_f32(float v) {                      // result in lane 63
+#define DAB_STEP(C, M) v = fmaxf(v, dpp_from<C, M>(v));
+    DAB_DPP_STEPS(DAB_STEP)
+#undef DAB_STEP
+    return v;
+}
+
+// Set bits of a wavefront mask (the same in every lane) below this lane.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
+#ifndef DAB_HOST_EMULATION
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+#else
+    return static_cast<uint32_t>(__builtin_popcountll(mask & ((1ull << (threadIdx.x & 63u)) - 1ull)));
+#endif
+}
+// A value of lane l (the same l in every lane), as a scalar.
+__device__ __forceinline__ uint32_t lane_of(uint32_t v, int l) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), l));
+}
+__device__ __forceinline__ int lane_of(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ long long lane_of(long long v, int l) {
+    const unsigned long long u = static_cast<unsigned long long>(v);
+    return static_cast<long long>((static_cast<unsigned long long>(lane_of(static_cast<uint32_t>(u >> 32), l)) << 32) |
+                                  lane_of(static_cast<uint32_t>(u), l));
+}
+__device__ __forceinline__ double lane_of(double v, int l) {
+    return __hiloint2double(lane_of(__double2hiint(v), l), lane_of(__double2loint(v), l));
 }
 
 // Candidate split: D = num / den with den > 0; P is the prefix sum at the split.
@@ -322,143 +356,266 @@ __global__ __launch_bounds__(THREADS) void estimate_kernel(const float* __restri
 // The arg-max of D needs the sorted order only near the optimum.  One pass of LDS atomics puts the
 // row into NB value buckets (count and exact fixed-point sum each), a scan gives, for every
 // bucket, the number and sum of all smaller elements, and with them D at the last element of every
-// bucket exactly and an upper bound of D at the positions inside it (the prefix sum there is
-// confined to a convex polygon of the (i, P) plane, and D is largest at one of its vertices).
-// Only buckets whose bound reaches the best bucket-end value can hold the arg-max; their elements
-// (a few dozen for the weight distributions of a network) are ranked exactly, with exact prefix
-// sums, and the split is chosen among them by the same comparison as in the sort.  All copies of
-// a value share a bucket, so the candidates also tell which copy of the split value is the last of
-// the lower group in the order of the row.  A row whose candidates exceed the list (many equal
-// values, a constant row) is left to the sort.
+// bucket and an upper bound of D at the positions inside it.  Only buckets whose bound reaches the
+// best bucket-end value can hold the arg-max; their elements (a few dozen for the weight
+// distributions of a network) are ranked exactly, with exact prefix sums, and the split is chosen
+// among them by the same comparison as in the sort.  All copies of a value share a bucket, and the
+// ranking goes by value and then by index, so the winner's index is the split descriptor's.  A row
+// whose candidates exceed the list (many equal values, a constant row) is left to the sort.
 //
 // Sums are integers: with 2^e > max |w| the values are scaled by 2^(48 - e) and rounded to int64,
 // which is exact for every element within 2^-24 of the row's largest magnitude (smaller ones are
 // rounded at 2^-49 of it), and integer atomics make the result independent of their order.
-constexpr int kFastBigBucket = 96;      // buckets above this size are candidates without a bound
-constexpr int kMaxCandBuckets = 255;    // candidate buckets of a row (more: the row is left to the sort)
+//
+// What bounds this is vector instructions, then LDS atomics, then the latency of the chain of
+// phases.  So an element costs one 64-bit atomic (15 clocks of a compute unit's LDS for a wavefront, whatever the
+// distribution) and five vector instructions in the histogram: the fused multiply-add that rounds it to an integer
+// q >= 0 (counted from the row's minimum) leaves q in the low bits of a double, whose upper word holds the bucket
+// (q >> sh) and gets the count of one put above the 52 bits that are left to the sum of the offsets inside the bucket.
+// A bucket costs about 45 instructions, all but a thread's first in fp32.  No LDS atomic has the address in common
+// among lanes (the compiler turns those into a loop over the lanes).  Search alone, one launch: 4096 rows of 9216
+// weights 47 us (83 with a count and a sum atomic per element, fp64 bounds and a branch per listed element), of 4096
+// 31.6 (46.5), 512 rows of 12544 14.5 (20.3), 1408 of 1800 10.8 (14.0), 256 of 2304 6.7 (9.5).
+constexpr int kBucketChunk = 4;         // elements of a thread handled without a branch between them
+constexpr int kBucketTurns = 12;        // scattered candidate buckets taken one at a time before the row is left to the sort
+
+// f(first element of the chunk, one past its last) over the chunks of ITEMS elements, both as compile-time constants (the
+// elements are registers), until it returns false.
+template <int ITEMS, int C = 0, typename F>
+__device__ __forceinline__ void for_chunks(F&& f) {
+    if constexpr (C < ITEMS) {
+        constexpr int E = C + kBucketChunk < ITEMS ? C + kBucketChunk : ITEMS;
+        if (f(std::integral_constant<int, C>{}, std::integral_constant<int, E>{})) for_chunks<ITEMS, E>(f);
+    }
+}
+
+// A bit per element of a thread.
+template <int ITEMS>
+using mask_t = std::conditional_t<(ITEMS > 32), unsigned long long, uint32_t>;
+// Element j of a thread's registers, j different in every lane.
+template <int LO, int HI, int ITEMS>
+__device__ __forceinline__ float pick(const float (&x)[ITEMS], int j) {
+    if constexpr (HI - LO == 1) {
+        return x[LO];
+    } else {
+        constexpr int P = HI - LO > 32 ? 32 : (HI - LO > 16 ? 16 : (HI - LO > 8 ? 8 : (HI - LO > 4 ? 4 : (HI - LO > 2 ? 2 : 1))));
+        const float a = pick<LO, LO + P>(x, j), b = pick<LO + P, HI>(x, j);
+        return (j & P) ? b : a;
+    }
+}
+
+// A barrier for what the workgroup's threads hand each other in LDS.  (__syncthreads() also waits until every global
+// store so far is acknowledged, which at the end of a row is most of a microsecond of nothing.)
+__device__ __forceinline__ void lds_barrier() {
+#ifndef DAB_HOST_EMULATION
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#else
+    __syncthreads();
+#endif
+}
+
+// The row as a buffer: a load is one instruction with the thread's offset and the element's (a constant), and past the
+// end it gives zero and reads nothing.  (With plain loads every element costs three vector instructions for its address.)
+#ifndef DAB_HOST_EMULATION
+using RowWindow = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ RowWindow row_window(const float* row, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(row), 0, 4 * n, 0x00020000);
+}
+__device__ __forceinline__ float load_from(RowWindow w, int lane_bytes, int step_bytes) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w, lane_bytes, step_bytes, 0));
+}
+#else
+struct RowWindow { const float* row; int n; };
+inline RowWindow row_window(const float* row, int n) { return RowWindow{row, n}; }
+inline float load_from(RowWindow w, int lane_bytes, int step_bytes) {
+    const int i = (lane_bytes + step_bytes) / 4;
+    return i < w.n ? w.row[i] : 0.0f;
+}
+#endif
 
 // The row is read once, every load in flight at once, and stays in registers: element j of thread t
-// is row[t + j * THREADS] (positions past the end repeat the last element).
+// is row[t + j * THREADS]; positions past the end hold NaN, which no comparison below selects.
 template <int THREADS, int ITEMS>
 __device__ __forceinline__ void load_row(const float* __restrict__ row, int n, float (&x)[ITEMS]) {
+    const int tid = threadIdx.x;
+    const RowWindow win = row_window(row, n);
+    for_chunks<ITEMS>([&](auto c, auto e) {
+        if (e * THREADS <= n) {
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) x[j] = row[min(static_cast<int>(threadIdx.x) + j * THREADS, n - 1)];
+            for (int j = c; j < e; ++j) x[j] = load_from(win, tid * 4, j * THREADS * 4);
+        } else {
+#pragma unroll
+            for (int j = c; j < e; ++j) {                          // (the scalar offset is no part of what is checked against the end)
+                const float v = c * THREADS < n ? load_from(win, (tid + j * THREADS) * 4, 0) : 0.0f;
+                x[j] = tid + j * THREADS < n ? v : __uint_as_float(0x7FC00000u);
+            }
+        }
+        return true;
+    });
 }
 
 // THREADS threads with up to ITEMS elements each (as load_row leaves them), NB value buckets, at most
-// CAP candidate elements.  Little LDS is needed and several workgroups share a compute unit:
+// CAP candidate elements at a time.  Little LDS is needed and several workgroups share a compute unit:
 // every phase is a short latency chain between barriers.  The result says whether the row is done
 // (the same for every thread of the workgroup); nothing has been written when it is not.
+struct alignas(16) Listed {
+    uint32_t idx, key, q_lo, q_hi;                                 // index in the row, value as a key, q
+};
+template <int THREADS, int NB, int CAP>
+struct BucketLds {
+    static constexpr int NW = THREADS / 64;
+    alignas(16) unsigned long long hist[NB];                       // a bucket's count (top 12 bits) and the sum of its offsets
+    alignas(16) uint16_t first[NB];                                // elements in lower buckets
+    unsigned long long below[THREADS];                             // sum of q in the buckets below those of a thread
+    Listed list[CAP + 4];                                          // candidates
+    unsigned long long acc_s[CAP];                                 // rank of a candidate and sum up to it
+    uint32_t acc_n[CAP];
+    uint32_t cmask[THREADS];                                       // candidates among a thread's buckets, a bit each
+    float w_min[NW], w_max[NW], w_g[NW];
+    uint32_t w_cnt[NW];
+    long long w_sum[NW];
+    int w_lo[NW], w_hi[NW];                                        // first and last candidate bucket
+    Best wave_best[NW];
+    uint32_t nlist;
+};
 template <int THREADS, int ITEMS, int NB, int CAP>
-__device__ __forceinline__ bool bucket_row(const float (&x)[ITEMS], int n, int f, float* __restrict__ alpha,
-                                           float* __restrict__ beta, int32_t* Kout, float* __restrict__ thr_val,
-                                           int32_t* __restrict__ thr_idx, uint8_t* alpha_is_upper, const int32_t* K_prev,
-                                           const uint8_t* upper_prev, int max_change, SplitInfo* info = nullptr) {
+__device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, const float (&x)[ITEMS], int n, int f,
+                                           float* __restrict__ alpha, float* __restrict__ beta, int32_t* Kout,
+                                           float* __restrict__ thr_val, int32_t* __restrict__ thr_idx, uint8_t* alpha_is_upper,
+                                           const int32_t* K_prev, const uint8_t* upper_prev, int max_change,
+                                           SplitInfo* info = nullptr) {
     constexpr int NW = THREADS / 64;
     constexpr int BPT = NB / THREADS;                              // buckets per thread
-    __shared__ uint32_t cnt[NB + 1];                               // counts, then the exclusive prefix N_b (N_NB = n)
-    __shared__ unsigned long long sum[NB + 1];                     // fixed-point sums, then the exclusive prefix S_b
-    __shared__ uint8_t cand[NB];                                   // 0, or 1 + the bucket's entry of ctab
-    __shared__ uint32_t ctab[kMaxCandBuckets];                     // candidate bucket: first slot of its list segment (low half), elements filed (high half)
-    __shared__ uint32_t lkey[CAP];
-    __shared__ long long lq[CAP];
-    __shared__ uint16_t lb[CAP], lidx[CAP];                         // bucket and index in the row of a candidate
-    __shared__ float w_min[NW], w_max[NW];
-    __shared__ uint32_t w_cnt[NW];
-    __shared__ long long w_sum[NW];
-    __shared__ double w_d[NW];
-    __shared__ Best wave_best[NW];
-    __shared__ uint32_t nlist_s, ncb_s, r_s, wkey_s;
-    __shared__ int cb_lo_s, cb_hi_s;                               // first and last candidate bucket
-    static_assert(CAP <= THREADS && CAP < 1024 && THREADS * ITEMS <= 65536 && ITEMS <= 32,
-                  "a candidate per thread, 10-bit counts, 16-bit indices, a flag bit per element");
+    constexpr int LOG_NB = NB == 512 ? 9 : (NB == 1024 ? 10 : 11);
+    static_assert(NB == 1 << LOG_NB && BPT >= 1 && NB % THREADS == 0 && BPT <= 32, "whole buckets per thread, a bit each");
+    static_assert(THREADS * ITEMS <= 65535 && LOG_NB >= 9, "16-bit counts; the offsets of up to 4095 elements sum to less than 2^52");
+    static_assert(CAP <= THREADS, "a candidate per thread");
+    auto& hist = lds.hist;
+    auto& first = lds.first;
+    auto& below = lds.below;
+    auto& list = lds.list;
+    auto& acc_n = lds.acc_n;
+    auto& acc_s = lds.acc_s;
+    auto& cmask = lds.cmask;
+    auto& w_min = lds.w_min;
+    auto& w_max = lds.w_max;
+    auto& w_g = lds.w_g;
+    auto& w_cnt = lds.w_cnt;
+    auto& w_sum = lds.w_sum;
+    auto& w_lo = lds.w_lo;
+    auto& w_hi = lds.w_hi;
+    auto& wave_best = lds.wave_best;
+    auto& nlist_s = lds.nlist;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // ---- range of the row
-    float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        mn = fminf(mn, x[j]);                                      // (the clamped repeats change nothing)
-        mx = fmaxf(mx, x[j]);
-    }
+    for (int k = 0; k < BPT; ++k) hist[tid + k * THREADS] = 0ull;
+    if (tid < CAP) { acc_n[tid] = 0u; acc_s[tid] = 0ull; }
+    if (tid == 0) nlist_s = 0u;
+    float mn = x[0], mx = x[0];
+    for_chunks<ITEMS>([&](auto c, auto e) {
+        if (c * THREADS >= n) return false;                        // (the whole workgroup, here and below)
+#pragma unroll
+        for (int j = c; j < e; ++j) {
+            mn = fminf(mn, x[j]);
+            mx = fmaxf(mx, x[j]);
+        }
+        return true;
+    });
     wave_min_max_f32(mn, mx);
     if (lane == 63) { w_min[wave] = mn; w_max[wave] = mx; }
-    for (int b = tid; b < NB; b += THREADS) { cnt[b] = 0u; sum[b] = 0ull; cand[b] = 0; }
-    if (tid == 0) { nlist_s = 0u; ncb_s = 0u; cb_lo_s = NB; cb_hi_s = -1; }
-    __syncthreads();
-    for (int w = 0; w < NW; ++w) { mn = fminf(mn, w_min[w]); mx = fmaxf(mx, w_max[w]); }
+    lds_barrier();
+    mn = w_min[0];
+    mx = w_max[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) { mn = fminf(mn, w_min[w]); mx = fmaxf(mx, w_max[w]); }
+    mn = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mn)));
+    mx = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mx)));
     if (!(mx > mn) || !(fabsf(mn) < INFINITY) || !(fabsf(mx) < INFINITY)) return false;   // constant row (or not finite)
     const float M = fmaxf(fabsf(mn), fabsf(mx));
     const int ex = static_cast<int>((__float_as_uint(M) >> 23) & 0xFFu) - 126;     // M < 2^ex
-    const double scale = ldexp(1.0, 48 - ex);
-    const double vmin = static_cast<double>(mn);
-    // bucket of a value: fp32 arithmetic, monotone in the value (subtraction, multiplication by a
-    // positive constant and truncation all are); the rounding moves a value by less than 1e-3 of
-    // a bucket, which the bounds below allow for
-    const float bscalef = static_cast<float>(NB * (1.0 - 1.0 / 4096.0) / (static_cast<double>(mx) - vmin));
-    const double bwidth = 1.0 / static_cast<double>(bscalef);     // value units per bucket
-    auto bucket_of = [&](float x) -> int { return max(min(static_cast<int>((x - mn) * bscalef), NB - 1), 0); };
-    // x * 2^(48 - ex) rounded to an integer (|.| < 2^48): added to 1.5 * 2^52, the integer sits in
-    // the low bits of the double
-    auto fixed_of = [&](float x) -> long long {
-        return __double_as_longlong(fma(static_cast<double>(x), scale, 6755399441055744.0)) - 0x4338000000000000ll;
-    };
+    const double scale = ldexp(1.0, 48 - ex), unscale = ldexp(1.0, ex - 48);
+    // x 2^(48 - ex) rounded to an integer (|.| < 2^48): added to 1.5 * 2^52, the integer sits in the low bits of the double;
+    // q = that integer + off >= 0 (off even, so that ties round the same way), in the low bits of the double near 2^52
+    const long long fmin_i = __double_as_longlong(fma(static_cast<double>(mn), scale, 6755399441055744.0)) - 0x4338000000000000ll;
+    const long long off = -fmin_i + (fmin_i & 1);
+    const double magic = 4503599627370496.0 + static_cast<double>(off);
+    auto q_of = [&](float v) -> double { return fma(static_cast<double>(v), scale, magic); };
+    // bucket = q >> sh, at least half of the buckets in use (a row whose range is below an eighth of its largest magnitude
+    // uses fewer); 35 <= sh <= 49 - LOG_NB, so buckets are decided in the upper word alone
+    const uint32_t qmax_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(__double2hiint(q_of(mx)))) & 0xFFFFFu;
+    const int sh = max(35, 64 - __builtin_clz(qmax_hi | 1u) - LOG_NB);
+    const uint32_t in_bucket = (1u << (sh - 32)) - 1u;             // upper word: offset inside the bucket
+    const int to_addr = sh - 35;
 
-    // ---- histogram: count and exact sum per bucket
+    // ---- histogram: count and exact sum of offsets per bucket
     {
+        auto add = [&](float v) {
+            const double q = q_of(v);
+            const uint32_t hi = static_cast<uint32_t>(__double2hiint(q)), lo = static_cast<uint32_t>(__double2loint(q));
+            unsigned long long* cell = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(hist) +
+                                                                            ((hi >> to_addr) & ((NB - 1u) << 3)));
+            atomicAdd(cell, (static_cast<unsigned long long>((hi & in_bucket) | 0x100000u) << 32) | lo);
+        };
+        for_chunks<ITEMS>([&](auto c, auto e) {
+            if (c * THREADS >= n) return false;
+            if (e * THREADS <= n) {
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            if (tid + j * THREADS < n) {
-                const int b = bucket_of(x[j]);
-                atomicAdd(&cnt[b], 1u);
-                atomicAdd(&sum[b], static_cast<unsigned long long>(fixed_of(x[j])));
+                for (int j = c; j < e; ++j) add(x[j]);
+            } else {
+#pragma unroll
+                for (int j = c; j < e; ++j)
+                    if (tid + j * THREADS < n) add(x[j]);
             }
-            if (j % 8 == 7) __builtin_amdgcn_sched_barrier(0);
-        }
+            return true;
+        });
     }
-    __syncthreads();
+    lds_barrier();
 
-    // ---- exclusive prefixes over the buckets (thread t scans buckets t*BPT ..)
+    // ---- prefixes over the buckets (thread t has buckets t*BPT ..).  A bucket with 4096 elements or more spoils
+    // the counts: their sum is then not n, and the row is left to the sort.
+    uint32_t bc[BPT];                                              // counts
+    float bf[BPT];                                                 // the offsets' sum in buckets' widths
+    uint32_t crun = 0, cb = 0;
+    unsigned long long srun = 0;
     {
-        uint32_t c[BPT], crun = 0;
-        long long sv[BPT], srun = 0;
+        const float per_width = __uint_as_float(static_cast<uint32_t>(127 + 24 - sh) << 23);   // 2^(24 - sh)
+        unsigned long long cell[BPT];
+#pragma unroll
+        for (int k = 0; k < BPT; ++k) cell[k] = hist[tid * BPT + k];
 #pragma unroll
         for (int k = 0; k < BPT; ++k) {
-            c[k] = cnt[tid * BPT + k];
-            sv[k] = static_cast<long long>(sum[tid * BPT + k]);
+            const uint32_t hi = static_cast<uint32_t>(cell[k] >> 32), lo = static_cast<uint32_t>(cell[k]);
+            bc[k] = hi >> 20;
+            bf[k] = static_cast<float>(((hi & 0xFFFFFu) << 8) | (lo >> 24)) * per_width;
+            crun += bc[k];
+            cb += bc[k] * static_cast<uint32_t>(tid * BPT + k);
+            srun += cell[k] & 0xFFFFFFFFFFFFFull;
         }
-#pragma unroll
-        for (int k = 0; k < BPT; ++k) {
-            const uint32_t tc = c[k];
-            const long long ts = sv[k];
-            c[k] = crun;
-            sv[k] = srun;
-            crun += tc;
-            srun += ts;
-        }
-        const uint32_t cinc = wave_inclusive_scan_u32(crun);
-        const long long sinc = wave_inclusive_scan_i64(srun);
-        if (lane == 63) { w_cnt[wave] = cinc; w_sum[wave] = sinc; }
-        __syncthreads();
-        uint32_t cbase = cinc - crun;
-        long long sbase = sinc - srun, total = 0;
-        for (int w = 0; w < NW; ++w) {
-            if (w < wave) { cbase += w_cnt[w]; sbase += w_sum[w]; }
-            total += w_sum[w];
-        }
-#pragma unroll
-        for (int k = 0; k < BPT; ++k) {
-            cnt[tid * BPT + k] = c[k] + cbase;
-            sum[tid * BPT + k] = static_cast<unsigned long long>(sv[k] + sbase);
-        }
-        if (tid == 0) {
-            cnt[NB] = static_cast<uint32_t>(n);
-            sum[NB] = static_cast<unsigned long long>(total);
-        }
+        srun += static_cast<unsigned long long>(cb) << sh;
     }
-    __syncthreads();
-    const double T = static_cast<double>(static_cast<long long>(sum[NB]));
+    const uint32_t cinc = wave_inclusive_scan_u32(crun);
+    const unsigned long long sinc = static_cast<unsigned long long>(wave_inclusive_scan_i64(static_cast<long long>(srun)));
+    if (lane == 63) { w_cnt[wave] = cinc; w_sum[wave] = static_cast<long long>(sinc); }
+    lds_barrier();
+    // (the wavefronts' totals: a lane each, scanned like the rest)
+    uint32_t wc = w_cnt[NW == 1 ? 0 : lane & (NW - 1)];
+    long long wsum = w_sum[NW == 1 ? 0 : lane & (NW - 1)];
+    if (NW > 1) { wc = dpp_add<0x111, 0xf>(wc); wsum = dpp_add<0x111, 0xf>(wsum); }
+    if (NW > 2) { wc = dpp_add<0x112, 0xf>(wc); wsum = dpp_add<0x112, 0xf>(wsum); }
+    if (NW > 4) { wc = dpp_add<0x114, 0xf>(wc); wsum = dpp_add<0x114, 0xf>(wsum); }
+    if (NW > 8) { wc = dpp_add<0x118, 0xf>(wc); wsum = dpp_add<0x118, 0xf>(wsum); }
+    if (lane_of(wc, NW - 1) != static_cast<uint32_t>(n)) return false;
+    const unsigned long long s_all = static_cast<unsigned long long>(lane_of(wsum, NW - 1));
+    uint32_t i_run = cinc - crun + (wave ? lane_of(wc, wave - 1) : 0u);
+    const unsigned long long s_base = sinc - srun + (wave ? static_cast<unsigned long long>(lane_of(wsum, wave - 1)) : 0ull);
+    const long long T_fix = static_cast<long long>(s_all) - static_cast<long long>(n) * off;    // the row's sum
+    below[tid] = s_base;
 
     // ---- allowed splits: 1 .. n-1, or the window around the previous split
     int wlo = 1, whi = n - 1;
@@ -470,212 +627,262 @@ __device__ __forceinline__ bool bucket_row(const float (&x)[ITEMS], int n, int f
         whi = min(n - 1, ip + d);
     }
 
-    // ---- D at the end of every bucket (the hardware reciprocal is accurate far beyond the margin
-    // used below).  Buckets are dealt out round robin: the populated ones are neighbours.
-    const double dn = static_cast<double>(n);
-    auto score = [&](double P, double i) -> double {              // D at a (real) position i with prefix sum P
-        const double rest = T - P;
-        return P * P * __builtin_amdgcn_rcp(i) + rest * rest * __builtin_amdgcn_rcp(dn - i);
-    };
-    double dend = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < BPT; ++k) {
-        const int b = tid + k * THREADS;
-        const int i0 = static_cast<int>(cnt[b]), iend = static_cast<int>(cnt[b + 1]);
-        if (iend > i0 && iend >= wlo && iend <= whi)
-            dend = fmax(dend, score(static_cast<double>(static_cast<long long>(sum[b + 1])), static_cast<double>(iend)));
-    }
-    dend = wave_max_f64(dend);
-    if (lane == 63) w_d[wave] = dend;
-    __syncthreads();
-    for (int w = 0; w < NW; ++w) dend = fmax(dend, w_d[w]);
-    const double need = dend - 1e-6 * fabs(dend);
-
-    // ---- candidates: buckets that can hold a split reaching `need`.  With j elements of the bucket
-    // below the split, P lies between L(j) = max(S_b + j lo, S_e - (c-j) hi) and
-    // U(j) = min(S_b + j hi, S_e - (c-j) lo): a convex region of the (i, P) plane, and D (a sum of
-    // squares over linear terms) is jointly convex there, so it is largest at a vertex: at the two
-    // ends of the j range or where the two lines of L or of U cross.
-#pragma unroll
-    for (int k = 0; k < BPT; ++k) {
-        const int b = tid + k * THREADS;
-        const int i0 = static_cast<int>(cnt[b]), iend = static_cast<int>(cnt[b + 1]);
-        const int c = iend - i0;
-        if (c == 0) continue;
-        const double Sb = static_cast<double>(static_cast<long long>(sum[b]));
-        const double Se = static_cast<double>(static_cast<long long>(sum[b + 1]));
-        // D(i, P) >= need without a division: both sides times i (n - i) > 0
-        auto reaches = [&](double P, double i) -> bool {
-            const double rest = T - P, r = dn - i;
-            return P * P * r + rest * rest * i >= need * (i * r);
-        };
-        bool is_cand = false;
-        if (iend >= wlo && iend <= whi) is_cand = reaches(Se, static_cast<double>(iend));
-        const int jlo = max(1, wlo - i0), jhi = min(c - 1, whi - i0);
-        if (!is_cand && jlo <= jhi) {
-            if (c > kFastBigBucket) {
-                is_cand = true;
-            } else {
-                // value range of the bucket, widened against the rounding of the bucket index
-                const double lov = vmin + (static_cast<double>(b) - 2e-3) * bwidth;
-                const double hiv = vmin + (static_cast<double>(b) + 1.0 + 2e-3) * bwidth;
-                // Cheap test first (most buckets end here): with values of one sign, P inside the bucket
-                // lies between the prefix sums at its two ends, so D is at most the larger P^2 over the
-                // smallest i plus the larger (T - P)^2 over the smallest n - i.
-                if (lov >= 0.0 || hiv <= 0.0) {
-                    const double il = static_cast<double>(i0 + jlo), rr = static_cast<double>(n - i0 - jhi);
-                    const double rb = T - Sb, re = T - Se;
-                    if (fmax(Sb * Sb, Se * Se) * rr + fmax(rb * rb, re * re) * il < need * (il * rr)) continue;
-                }
-                const double lo = lov * scale - 1.0, hi = hiv * scale + 1.0;    // in fixed-point units
-                const double dc = static_cast<double>(c), ja = static_cast<double>(jlo), jb = static_cast<double>(jhi);
-                auto L = [&](double j) { return fmax(Sb + j * lo, Se - (dc - j) * hi); };
-                auto U = [&](double j) { return fmin(Sb + j * hi, Se - (dc - j) * lo); };
-                const double inv = __builtin_amdgcn_rcp(hi - lo);
-                const double jl = fmin(fmax((Sb - Se + dc * hi) * inv, ja), jb);    // the lines of L cross here
-                const double ju = fmin(fmax((Se - Sb - dc * lo) * inv, ja), jb);    // the lines of U cross here
-                const double di0 = static_cast<double>(i0);
-                is_cand = reaches(L(ja), di0 + ja) || reaches(U(ja), di0 + ja) || reaches(L(jb), di0 + jb) ||
-                          reaches(U(jb), di0 + jb) || reaches(L(jl), di0 + jl) || reaches(U(ju), di0 + ju);
-            }
-        }
-        if (is_cand) {
-            // the bucket's elements get a segment of the list to themselves
-            const uint32_t entry = atomicAdd(&ncb_s, 1u);
-            const uint32_t start = atomicAdd(&nlist_s, static_cast<uint32_t>(c));
-            if (entry < kMaxCandBuckets) {
-                cand[b] = static_cast<uint8_t>(entry + 1u);
-                ctab[entry] = min(start, 0xFFFFu);
-            }
-            atomicMin(&cb_lo_s, b);
-            atomicMax(&cb_hi_s, b);
-        }
-    }
-    __syncthreads();
-    const uint32_t nc = nlist_s;
-    if (nc > CAP || nc == 0 || ncb_s > kMaxCandBuckets) return false;
-
-    // ---- the candidates' elements, filed into the segment of their bucket.  The candidates are
-    // neighbours as a rule, so every thread first flags the elements whose bucket lies between the
-    // first and the last candidate (two compares on the bucket coordinate: for t >= 0 the
-    // truncation is the floor, so lo <= int(t) <= hi is lo <= t < hi + 1), then looks up the few
-    // it has flagged and files those whose bucket is a candidate
+    // ---- D at the end of every bucket and a bound inside it.  D = T^2/n + n (P - i T/n)^2 / (i (n - i)), and the
+    // second term does not change when every value is shifted, so it is taken of the q; P - i T/n is at most 0 for
+    // ascending values, so D is the larger the smaller P is.  With j of the bucket's c elements below the split,
+    // P is at least L(j) = max(S_b + j lo, S_e - (c - j) hi), lo and hi the bucket's limits, and D is convex along
+    // both lines: it is at most the largest of its values at the bucket's start, at its end and where the two
+    // lines cross, at c - (sum of the offsets / width).  In units of a bucket's width and in fp32, from differences
+    // formed in fp64 at a thread's first bucket.
+    const double mean = static_cast<double>(s_all) / static_cast<double>(n);
+    const float nf = static_cast<float>(n);
+    float ub[BPT];                                                 // bound over the bucket
+    float gbest = -1.0f;                                           // largest value at an allowed end
     {
-        const float tlo = static_cast<float>(cb_lo_s);
-        const float thi = cb_hi_s >= NB - 1 ? INFINITY : static_cast<float>(cb_hi_s + 1);   // (the last bucket also takes what rounds past it)
-        uint32_t flags = 0;
+        auto spread = [&](float Q, float i) -> float { return Q * Q * DAB_RCP_F32(fmaxf(i * (nf - i), 0.5f)); };
+        float Q0 = static_cast<float>(ldexp(static_cast<double>(s_base) - static_cast<double>(i_run) * mean, -sh));
+        float i0 = static_cast<float>(i_run), g0 = spread(Q0, i0);
+        float dist = static_cast<float>(static_cast<double>(tid * BPT) - ldexp(mean, -sh));     // bucket's lower limit - mean
+        uint32_t i = i_run, pair = 0;
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            float xv = x[j];
-            DAB_OPAQUE_F32(xv);                                    // (the coordinate is computed again, not kept since the histogram)
-            const float t = (xv - mn) * bscalef;
-            if (tid + j * THREADS < n && t >= tlo && t < thi) flags |= 1u << j;
+        for (int k = 0; k < BPT; ++k) {
+            if (BPT == 1) first[tid] = static_cast<uint16_t>(i);
+            else if (k % 2 == 0) pair = i;
+            else reinterpret_cast<uint32_t*>(first)[tid * (BPT / 2) + k / 2] = pair | (i << 16);
+            const int start = static_cast<int>(i);
+            i += bc[k];
+            const int end = static_cast<int>(i);
+            const float c = static_cast<float>(bc[k]), js = c - bf[k], i1 = static_cast<float>(i);
+            const float Q1 = Q0 + fmaf(c, dist, bf[k]);
+            const float g1 = spread(Q1, i1), gs = spread(fmaf(js, dist, Q0), i0 + js);
+            float bound = fmaxf(fmaxf(g0, g1), gs), at_end = g1;
+            DAB_OPAQUE_F32(bound);                                 // (evaluated here, not in branches on the conditions below)
+            DAB_OPAQUE_F32(at_end);
+            ub[k] = ((bc[k] != 0u) & (end >= wlo) & (start < whi)) ? bound : -INFINITY;
+            gbest = ((bc[k] != 0u) & (end >= wlo) & (end <= whi)) ? fmaxf(gbest, at_end) : gbest;
+            Q0 = Q1;
+            i0 = i1;
+            g0 = g1;
+            dist += 1.0f;
         }
+    }
+    gbest = wave_max_f32(gbest);
+    if (lane == 63) w_g[wave] = gbest;
+    lds_barrier();
+    gbest = w_g[0];
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            if ((flags >> j) & 1u) {
-                const int b = bucket_of(x[j]);
-                const uint32_t cb = cand[b];
-                if (cb) {
-                    const uint32_t old = atomicAdd(&ctab[cb - 1], 1u << 16);
-                    const uint32_t slot = (old & 0xFFFFu) + (old >> 16);
-                    lkey[slot] = float_to_key(x[j]);
-                    lq[slot] = fixed_of(x[j]);
-                    lb[slot] = static_cast<uint16_t>(b);
-                    lidx[slot] = static_cast<uint16_t>(tid + j * THREADS);
+    for (int w = 1; w < NW; ++w) gbest = fmaxf(gbest, w_g[w]);
+    // a margin of 4e-6 of D (the fp32 evaluation is good to 1e-6); no allowed end: every bucket of the window
+    const float mean_f = static_cast<float>(ldexp(mean - static_cast<double>(off), -sh));
+    const float need = gbest < 0.0f ? -3.0e38f : gbest - 4e-6f * (gbest + mean_f * mean_f);
+
+    // ---- candidates: buckets that can hold a split reaching `need`
+    {
+        uint32_t mask = 0;
+#pragma unroll
+        for (int k = 0; k < BPT; ++k) mask |= ub[k] >= need ? 1u << k : 0u;
+        cmask[tid] = mask;
+        const unsigned long long any = __ballot(mask != 0u);
+        int lo = NB, hi = -1;
+        if (any != 0ull) {
+            const int l0 = __builtin_ctzll(any), l1 = 63 - __builtin_clzll(any);
+            lo = (wave * 64 + l0) * BPT + __builtin_ctz(lane_of(mask, l0));
+            hi = (wave * 64 + l1) * BPT + 31 - __builtin_clz(lane_of(mask, l1));
+        }
+        if (lane == 0) { w_lo[wave] = lo; w_hi[wave] = hi; }
+    }
+    lds_barrier();
+    int lo = w_lo[0], hi = w_hi[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) { lo = min(lo, w_lo[w]); hi = max(hi, w_hi[w]); }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    const int last = __builtin_amdgcn_readfirstlane(hi);
+    if (last < 0) return false;                                    // no bucket in the window: not expected
+
+    // ---- the candidates are neighbours as a rule: everything between the first and the last of them is taken
+    // at once.  Where that is too much (D has two maxima of nearly the same height) one bucket is taken at a time.
+    auto elements_below = [&](int b) -> int {
+        return __builtin_amdgcn_readfirstlane(b < NB ? static_cast<int>(first[b]) : n);
+    };
+    Best best{-1.0, 1.0, 0.0, 0};                                  // of this thread's candidates
+    uint32_t my_key = 0, my_idx = 0;
+    int nblk = 0;                                                  // wavefronts that had candidates
+    hi = last;
+    for (int turns = 1;; ++turns) {
+        const int n_lo = elements_below(lo);
+        if (elements_below(hi + 1) - n_lo > CAP) hi = lo;
+        const int in_reach = elements_below(hi + 1) - n_lo;
+        if (in_reach > CAP || turns > kBucketTurns) return false;
+
+        // the candidates' elements.  q >= A (even) says x 2^(48 - ex) + off >= A - 1/2, so the elements of
+        // buckets lo .. hi are those from the smallest float at or above one value to below another.
+        {
+            auto at_least = [&](int b) -> float {
+                const double t = (ldexp(static_cast<double>(b), sh) - 0.5 - static_cast<double>(off)) * unscale;   // (exact)
+                const float v = static_cast<float>(t);
+                return key_to_float(float_to_key(v) + (static_cast<double>(v) < t ? 1u : 0u));
+            };
+            const float xlo = at_least(lo), xhi = at_least(hi + 1);
+            // A thread notes its elements in a mask, then the wavefront takes places in the list together and every thread
+            // files its few, each selected from the registers by a tree of selects: a branch per element costs more than
+            // that, and ten times the code.
+            uint32_t part[(ITEMS + 31) / 32] = {};
+            for_chunks<ITEMS>([&](auto c, auto e) {
+                if (c * THREADS >= n) return false;
+                uint32_t four = 0;
+#pragma unroll
+                for (int j = c; j < e; ++j) four |= ((x[j] >= xlo) & (x[j] < xhi)) ? 1u << (j - c) : 0u;
+                part[c / 32] |= four << (c % 32);
+                return true;
+            });
+            mask_t<ITEMS> mine = part[0];
+            if constexpr (ITEMS > 32) mine |= static_cast<mask_t<ITEMS>>(part[1]) << 32;
+            const uint32_t have = static_cast<uint32_t>(__builtin_popcountll(mine));
+            const uint32_t upto = wave_inclusive_scan_u32(have), count = lane_of(upto, 63);
+            if (count != 0u) {
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&nlist_s, count);
+                uint32_t slot = lane_of(base, 0) + upto - have;
+                while (mine) {
+                    const int j = __builtin_ctzll(mine);
+                    mine &= mine - 1;
+                    const float v = pick<0, ITEMS>(x, j);
+                    const double q = q_of(v);
+                    if (slot < static_cast<uint32_t>(CAP))
+                        list[slot] = Listed{static_cast<uint32_t>(tid + j * THREADS), float_to_key(v),
+                                            static_cast<uint32_t>(__double2loint(q)),
+                                            static_cast<uint32_t>(__double2hiint(q)) & 0xFFFFFu};
+                    ++slot;
                 }
             }
         }
-    }
-    __syncthreads();
+        lds_barrier();
+        const int nc = __builtin_amdgcn_readfirstlane(static_cast<int>(nlist_s));
+        if (nc != in_reach) return false;                          // (not expected: the counts said otherwise)
 
-    // ---- exact position and prefix sum of every candidate (thread e has the e-th entry of the
-    // list): the elements of its bucket that precede it, which are the entries of its segment
-    // (among equal values the earlier entry precedes; the count of equal values that come first in
-    // the row serves the split descriptor below).  Counts are packed, 10 bits each.
-    const int e = tid;
-    const bool has = e < static_cast<int>(nc);
-    Best best{-1.0, 1.0, 0.0, 0};
-    uint32_t my_key = 0, my_less = 0, my_first = 0, my_idx = 0;
-    if (has) {
-        const uint32_t key = lkey[e];
-        const int b = lb[e];
-        my_idx = lidx[e];
-        const int q0 = static_cast<int>(ctab[cand[b] - 1] & 0xFFFFu);
-        const int q1 = q0 + static_cast<int>(cnt[b + 1] - cnt[b]);
-        uint32_t counts = 0;
-        long long ps = 0;
-        // four entries per trip, their reads in flight together (a trip is one LDS round trip)
-        for (int q = q0; q < q1; q += 4) {
-            uint32_t kq[4], iq[4];
-            long long vq[4];
+        // exact rank and prefix sum of every candidate: the listed elements up to it in the order of value, then
+        // index.  The wavefronts share the list out.
+        const int nb = (nc + 63) >> 6;
+        {
+            const int per = (nc + NW - 1) / NW;
+            const int q0 = wave * per, q1 = min(q0 + per, nc);
+            for (int v = 0; v < nb; ++v) {
+                const int e = v * 64 + lane;
+                const Listed& me = list[min(e, nc - 1)];
+                const unsigned long long key = (static_cast<unsigned long long>(me.key) << 32) | me.idx;
+                uint32_t cnt = 0;
+                unsigned long long sum = 0;
+                for (int q = q0; q < q1; q += 4) {
+                    Listed o[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int qq = min(q + u, q1 - 1);
-                kq[u] = lkey[qq];
-                iq[u] = lidx[qq];
-                vq[u] = lq[qq];
-            }
+                    for (int u = 0; u < 4; ++u) o[u] = list[q + u];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool in = q + u < q1;
-                const bool lt = in && kq[u] < key;
-                const bool eq = in && kq[u] == key;
-                const bool le = lt || (eq && q + u <= e);
-                counts += (le ? 1u : 0u) + (lt ? 1u << 10 : 0u) + ((eq && iq[u] < my_idx) ? 1u << 20 : 0u);
-                ps += le ? vq[u] : 0ll;
+                    for (int u = 0; u < 4; ++u) DAB_OPAQUE_I32(o[u].q_lo);   // (read with the rest, not behind the comparison)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const bool le = (q + u < q1) & (((static_cast<unsigned long long>(o[u].key) << 32) | o[u].idx) <= key);
+                        cnt += le ? 1u : 0u;
+                        sum += le ? (static_cast<unsigned long long>(o[u].q_hi) << 32) | o[u].q_lo : 0ull;
+                    }
+                }
+                if (e < nc) {
+                    atomicAdd(&acc_n[e], cnt);
+                    atomicAdd(&acc_s[e], sum);
+                }
             }
         }
-        const uint32_t within = counts & 1023u, less = (counts >> 10) & 1023u;
-        my_key = key;
-        my_less = cnt[b] + less;
-        my_first = counts >> 20;
-        const int i = static_cast<int>(cnt[b] + within);
-        if (i >= wlo && i <= whi) {
-            const double Pi = static_cast<double>(static_cast<long long>(sum[b]) + ps);
-            const double rest = T - Pi;
-            const double fi = static_cast<double>(i), fr = static_cast<double>(n - i);
-            best = Best{Pi * Pi * fr + rest * rest * fi, fi * fr, Pi, i};
+        lds_barrier();
+        // the split behind it
+        if (tid < nc) {
+            unsigned long long sum = below[lo / BPT] + acc_s[tid];
+#pragma unroll
+            for (int k = 0; k < BPT - 1; ++k) {
+                const int b = lo / BPT * BPT + k;
+                const unsigned long long cell = hist[b];
+                const unsigned long long in = (cell & 0xFFFFFFFFFFFFFull) +
+                                              (static_cast<unsigned long long>(static_cast<uint32_t>(cell >> 52) * static_cast<uint32_t>(b)) << sh);
+                sum += b < lo ? in : 0ull;
+            }
+            const int i = n_lo + static_cast<int>(acc_n[tid]);
+            if (i >= wlo && i <= whi) {
+                const double T = static_cast<double>(T_fix);
+                const double Pi = static_cast<double>(static_cast<long long>(sum) - static_cast<long long>(i) * off);
+                const double rest = T - Pi;
+                const double fi = static_cast<double>(i), fr = static_cast<double>(n - i);
+                const Best c{Pi * Pi * fr + rest * rest * fi, fi * fr, Pi, i};
+                if (better(c, best)) { best = c; my_key = list[tid].key; my_idx = list[tid].idx; }
+            }
         }
+        nblk = max(nblk, nb);
+        if (hi >= last) break;
+        // the next candidate bucket; the list and its sums start again
+        int next = NB;
+        for (int w = hi / BPT / 64; w < NW && next == NB; ++w) {
+            uint32_t mask = cmask[w * 64 + lane];
+            const int b0 = (w * 64 + lane) * BPT;                  // (a thread's bucket k counts if b0 + k > hi)
+            if (hi >= b0) mask = hi - b0 >= 31 ? 0u : mask & ~((2u << (hi - b0)) - 1u);
+            const unsigned long long any = __ballot(mask != 0u);
+            if (any != 0ull) {
+                const int l0 = __builtin_ctzll(any);
+                next = (w * 64 + l0) * BPT + __builtin_ctz(lane_of(mask, l0));
+            }
+        }
+        lo = next;
+        hi = last;
+        lds_barrier();
+        if (tid < CAP) { acc_n[tid] = 0u; acc_s[tid] = 0ull; }
+        if (tid == 0) nlist_s = 0u;
+        lds_barrier();
     }
-    const int my_i = best.i;
-    // only the wavefronts that hold candidates (the first one, as a rule) reduce
-    const int nwr = min(NW, static_cast<int>(nc + 63) >> 6);
-    if (wave < nwr) {
-        const Best wb = wave_best_of(best);
-        if (lane == 63) wave_best[wave] = wb;
+
+    int won;                                                       // the winning position
+    if (nblk == 1) {
+        // one wavefront holds them all: those within rounding of the largest quotient, one as a rule
+        if (wave != 0) return true;
+        const double d = best.num / best.den;
+        const double dmax = lane_of(wave_max_f64(d), 63);
+        unsigned long long top = __ballot(d >= dmax * (1.0 - 1e-13));
+        Best bb{-1.0, 1.0, 0.0, 0};
+        for (; top != 0ull; top &= top - 1ull) {
+            const int l = __builtin_ctzll(top);
+            const Best o{lane_of(best.num, l), lane_of(best.den, l), 0.0, lane_of(best.i, l)};
+            if (better(o, bb)) bb = o;
+        }
+        won = bb.i;
+    } else {
+        if (wave < nblk) {
+            const Best wb = wave_best_of(best);
+            if (lane == 63) wave_best[wave] = wb;
+        }
+        lds_barrier();
+        Best bb = wave_best[0];
+        for (int w = 1; w < nblk; ++w)
+            if (better(wave_best[w], bb)) bb = wave_best[w];
+        won = bb.i;
     }
-    __syncthreads();
-    Best bb = wave_best[0];
-    for (int w = 1; w < nwr; ++w)
-        if (better(wave_best[w], bb)) bb = wave_best[w];
-    if (bb.i < 1) return false;                                    // no candidate inside the window: not expected
-    if (my_i == bb.i) {                                            // exactly one thread holds the winning position
-        wkey_s = my_key;
-        r_s = static_cast<uint32_t>(bb.i) - my_less;               // copies of the value in the lower group
-    }
-    __syncthreads();
-    const uint32_t wkey = wkey_s;
-    if (tid == 0) {
-        const int is = bb.i;
-        const double mu_lower = bb.P / static_cast<double>(is) / scale;
-        const double mu_upper = (T - bb.P) / static_cast<double>(n - is) / scale;
+    if (best.i == won) {                                           // exactly one thread holds the winning position
+        const double T = static_cast<double>(T_fix);
+        const double mu_lower = best.P / static_cast<double>(won) * unscale;
+        const double mu_upper = (T - best.P) / static_cast<double>(n - won) * unscale;
         const bool upper = fabs(mu_upper) >= fabs(mu_lower);
+        if (info) { info->thr_val = key_to_float(my_key); info->thr_idx = static_cast<int>(my_idx); info->upper = upper ? 1 : 0; }
         alpha[f] = static_cast<float>(upper ? mu_upper : mu_lower);
         beta[f] = static_cast<float>(upper ? mu_lower : mu_upper);
-        Kout[f] = upper ? n - is : is;
+        Kout[f] = upper ? n - won : won;
         alpha_is_upper[f] = upper ? 1 : 0;
-        thr_val[f] = key_to_float(wkey);
-        if (info) { info->thr_val = key_to_float(wkey); info->upper = upper ? 1 : 0; }
-    }
-
-    // ---- the split descriptor's index: the r-th copy of the split value in the order of the row.
-    // Every copy is a candidate (equal values share a bucket) and knows how many copies precede it.
-    if (has && my_key == wkey && my_first + 1 == r_s) {
+        thr_val[f] = key_to_float(my_key);
         thr_idx[f] = static_cast<int32_t>(my_idx);
-        if (info) info->thr_idx = static_cast<int>(my_idx);
     }
     return true;
+}
+template <int THREADS, int ITEMS, int NB, int CAP>
+__device__ __forceinline__ bool bucket_row(const float (&x)[ITEMS], int n, int f, float* __restrict__ alpha,
+                                           float* __restrict__ beta, int32_t* Kout, float* __restrict__ thr_val,
+                                           int32_t* __restrict__ thr_idx, uint8_t* alpha_is_upper, const int32_t* K_prev,
+                                           const uint8_t* upper_prev, int max_change) {
+    __shared__ BucketLds<THREADS, NB, CAP> lds;
+    return bucket_row<THREADS, ITEMS, NB, CAP>(lds, x, n, f, alpha, beta, Kout, thr_val, thr_idx, alpha_is_upper, K_prev,
+                                               upper_prev, max_change);
 }
 
 }  // namespace dab

@@ -3,7 +3,7 @@
 // static here) that one thread writes and another reads or writes without a barrier between them;
 // built with -fsanitize=address,undefined every LDS index out of bounds.  Usage:
 //     emulate_rows <case> [seed]       case: sort64x3 sort256x7 sort512x7 sort1024x7 sort1024x13
-//                                            bucket256x9 bucket512x9 bucket512x26
+//                                            bucket256x9 bucket512x9 bucket512x26 bucket256x36
 #include "hip_emu.h"
 
 #include <string>
@@ -138,6 +138,7 @@ int main(int argc, char** argv) {
     else if (which == "bucket256x9") n = 2304;
     else if (which == "bucket512x9") n = 4000;
     else if (which == "bucket512x26") n = 12544;
+    else if (which == "bucket256x36") n = 9001;
     else { std::fprintf(stderr, "unknown case %s\n", which.c_str()); return 2; }
     // rows: a Gaussian one, a skewed two-cluster one, one with few distinct values, a ragged shorter one is a second run
     const int F = 4;
@@ -156,7 +157,8 @@ int main(int argc, char** argv) {
     else if (which == "sort1024x13") run_sort<1024, 13>(W, F, n, o);
     else if (which == "bucket256x9") run_bucket<256, 9, 512, 256>(W, F, n, o);
     else if (which == "bucket512x9") run_bucket<512, 9, 2048, 256>(W, F, n, o);
-    else run_bucket<512, 26, 2048, 512>(W, F, n, o);
+    else if (which == "bucket512x26") run_bucket<512, 26, 2048, 512>(W, F, n, o);
+    else run_bucket<256, 36, 2048, 256>(W, F, n, o);
 #ifdef EMU_POISON_LDS
     std::printf("LDS section marked uninitialised before every workgroup: %zu bytes\n", static_cast<size_t>(__stop_emu_lds - __start_emu_lds));
 #endif

@@ -17,7 +17,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 EMU = os.path.join(ROOT, "tests", "emu")
 CSRC = os.path.join(ROOT, "paper_1804_02941_amd", "csrc")
 CLANG = "/opt/rocm/llvm/bin/clang++"
-CASES = ["sort64x3", "sort256x7", "sort512x7", "sort1024x7", "sort1024x13", "bucket256x9", "bucket512x9", "bucket512x26"]
+CASES = ["sort64x3", "sort256x7", "sort512x7", "sort1024x7", "sort1024x13", "bucket256x9", "bucket512x9", "bucket512x26", "bucket256x36"]
 
 
 def build(tmp, name, compiler, flags):
