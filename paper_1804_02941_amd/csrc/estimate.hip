@@ -34,6 +34,7 @@
 
 #include "estimate_rows.h"
 #include "pack_act.h"
+#include "pack_mask.h"
 
 namespace dab {
 
@@ -81,149 +82,19 @@ __global__ __launch_bounds__(THREADS) void estimate_short_kernel(const float* __
 // read from memory once, and a network's weight side is two or three launches whatever its depth.
 constexpr int kMaxEstJobs = 16;
 constexpr int kSortRowsPerGroup = 8;               // rows a workgroup of the sort kernel looks after
-constexpr int kPackMaxTaps = 128;
 struct EstJob {
     const float* W;
     float* alpha; float* beta; int32_t* K; float* thr_val; int32_t* thr_idx; uint8_t* aiu;
     const int32_t* K_prev; const uint8_t* upper_prev;
-    uint32_t* E; uint32_t* ecnt;                   // packed mask [T*Cw][Fp] and per-tap counts [F][T], or both nullptr
+    MaskShape mask;                                // where the packed mask goes (E and ecnt nullptr: nowhere)
     uint8_t* flags;                                // long rows: one hand-over flag per filter
-    int n, F, C, T, Cw, Fp, max_change;
+    int n, F, max_change;
     unsigned blk_end;                              // first workgroup past this job's range
 };
 struct EstJobs {
     int n;
     EstJob job[kMaxEstJobs];
 };
-
-// Workgroup r of a job takes filter column f: consecutive workgroups go to consecutive XCDs, and a
-// column of E is one 4-byte word per row, so an XCD gets a contiguous range of columns and the
-// partial lines of neighbouring filters merge in one L2.
-__device__ __forceinline__ int job_column(unsigned r, int Fp) {
-    const int per_xcd = (Fp + kNumXCD - 1) / kNumXCD;
-    const int f = static_cast<int>(r % kNumXCD) * per_xcd + static_cast<int>(r / kNumXCD);
-    return static_cast<int>(r / kNumXCD) < per_xcd ? f : Fp;
-}
-
-// v with lane l (the same in every lane) replaced by the scalar s.
-__device__ int amdgcn_writelane(int s, int l, int v) __asm("llvm.amdgcn.writelane.i32");
-__device__ __forceinline__ uint32_t write_lane(uint32_t v, uint32_t s, int l) {
-    return static_cast<uint32_t>(amdgcn_writelane(static_cast<int>(s), l, static_cast<int>(v)));
-}
-
-// Column f of E and the filter's per-tap counts from the mask, a byte per weight in LDS: one thread per
-// packed word gathers its 32 channels (stride T), writes the word and adds its ones to the tap's count.  (A
-// wavefront per word pair with a ballot is slower: its address arithmetic is per word instead of per lane.)
-template <int THREADS>
-__device__ __forceinline__ void pack_bytes(const EstJob& job, int f, const uint8_t* maskb, uint32_t* tapcnt) {
-    const int tid = threadIdx.x;
-    // the job's fields by value: behind a reference into the kernel's arguments every store below
-    // would make the compiler read them again
-    uint32_t* const E = job.E;
-    uint32_t* const ecnt = job.ecnt;
-    const int C = job.C, T = job.T, Cw = job.Cw, Fp = job.Fp;
-    const int R = T * Cw;
-    for (int t = tid; t < T; t += THREADS) tapcnt[t] = 0u;
-    lds_barrier();
-    // (all reads of a word in flight together)
-    for (int r = tid; r < R; r += THREADS) {
-        const int tap = r / Cw, w = r - tap * Cw;
-        const int c0 = 32 * w, nc = min(32, C - c0);
-        const uint8_t* src = maskb + c0 * T + tap;
-        uint32_t word = 0;
-        if (nc == 32) {
-#pragma unroll
-            for (int k = 0; k < 32; ++k) word |= static_cast<uint32_t>(src[k * T]) << k;
-        } else {
-            for (int k = 0; k < nc; ++k) word |= static_cast<uint32_t>(src[k * T]) << k;
-        }
-        E[static_cast<size_t>(r) * Fp + f] = word;
-        atomicAdd(&tapcnt[tap], static_cast<uint32_t>(__builtin_popcount(word)));
-    }
-    lds_barrier();
-    for (int t = tid; t < T; t += THREADS) ecnt[static_cast<size_t>(f) * T + t] = tapcnt[t];
-}
-
-// The mask of filter column f as bits (Corollary 1, by stable rank: the split descriptor), by the
-// whole workgroup, from the row as load_row left it in registers.
-// A window of one tap (fully-connected layers, 1 x 1 convolutions) has its channels in the order of the
-// row, so the 64 elements a wavefront holds under one j already are two words: a ballot each, kept by
-// lane j, no LDS.  (Through LDS the 32-byte stride of the gather put 64 lanes on eight banks: 4096 rows of
-// 9216 weights and 4096 of 4096, weight side of both in one call: 175.6 us, 157.6 with the ballots.)  Only
-// as many ballots as the row has steps of the workgroup's threads: with all of its class's, short rows were
-// slower than through LDS (16384 rows of 256 weights: LDS 91.0 us, nine ballots 97.5, one 87.8; 4096 of 64:
-// 28.6, 29.4, 27.3; 8192 of 512: 51.5, 53.9, 50.0).
-template <int THREADS, int ITEMS>
-__device__ __forceinline__ void pack_row(const EstJob& job, int f, const SplitInfo* info, const float (&x)[ITEMS], uint8_t* maskb) {
-    __shared__ uint32_t tapcnt[kPackMaxTaps];
-    const int tid = threadIdx.x;
-    const int n = job.n;
-    const float tv = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(info->thr_val)));
-    const int ti = __builtin_amdgcn_readfirstlane(info->thr_idx);
-    const bool upper = __builtin_amdgcn_readfirstlane(info->upper) != 0;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // The lower group: w < tv, or w = tv up to index ti, that is w <= tv in a thread's elements up to j_tie and w <= the
-    // float below tv in those behind it.  (Positions past n hold NaN and are in neither group.)
-    const uint32_t tkey = float_to_key(tv);
-    const float below = key_to_float(tkey == 0x80000000u ? tkey - 2u : tkey - 1u);        // (below zero: not -0)
-    const int j_tie = ti < tid ? -1 : (ti - tid) / THREADS;
-    if (job.T == 1) {
-        static_assert(ITEMS <= 64 && THREADS / 64 <= kPackMaxTaps, "a lane per j, a count per wavefront");
-        uint32_t w0 = 0, w1 = 0;
-        uint32_t ones = 0;
-        auto words = [&](auto in_alpha) {
-            for_chunks<ITEMS>([&](auto c, auto e) {
-                if (c * THREADS >= n) return false;                // (the whole workgroup)
-#pragma unroll
-                for (int j = c; j < e; ++j) {
-                    const unsigned long long m = __ballot(in_alpha(x[j], j <= j_tie ? tv : below));
-                    ones += static_cast<uint32_t>(__builtin_popcountll(m));
-                    w0 = write_lane(w0, static_cast<uint32_t>(m), j);
-                    w1 = write_lane(w1, static_cast<uint32_t>(m >> 32), j);
-                }
-                return true;
-            });
-        };
-        if (upper) words([](float v, float t) { return v > t; });
-        else words([](float v, float t) { return v <= t; });
-        uint32_t* const E = job.E;
-        const int R = job.Cw, Fp = job.Fp;
-        const int r = lane * (THREADS / 32) + wave * 2;
-        if (lane < ITEMS && r < R) E[static_cast<size_t>(r) * Fp + f] = w0;
-        if (lane < ITEMS && r + 1 < R) E[static_cast<size_t>(r + 1) * Fp + f] = w1;
-        if (lane == 0) tapcnt[wave] = ones;
-        lds_barrier();
-        if (tid == 0) {
-            uint32_t total = 0;
-            for (int w = 0; w < THREADS / 64; ++w) total += tapcnt[w];
-            job.ecnt[f] = total;
-        }
-        return;
-    }
-    const uint8_t in_lower = upper ? 0 : 1, in_upper = upper ? 1 : 0;
-    for_chunks<ITEMS>([&](auto c, auto e) {
-        if (c * THREADS >= n) return false;
-#pragma unroll
-        for (int j = c; j < e; ++j)                                // (past n: nobody reads it)
-            maskb[tid + j * THREADS] = x[j] <= (j <= j_tie ? tv : below) ? in_lower : in_upper;
-        return true;
-    });
-    pack_bytes<THREADS>(job, f, maskb, tapcnt);
-}
-// The same from the row in memory (rows that were sorted).
-template <int THREADS, int MAX_N>
-__device__ __forceinline__ void pack_row_from(const EstJob& job, int f, const SplitInfo* info, const float* __restrict__ row) {
-    __shared__ uint8_t maskb[MAX_N];
-    __shared__ uint32_t tapcnt[kPackMaxTaps];
-    const float tv = info->thr_val;
-    const int ti = info->thr_idx;
-    const bool upper = info->upper != 0;
-    for (int i = threadIdx.x; i < job.n; i += THREADS) {
-        const float w = row[i];
-        maskb[i] = (w < tv || (w == tv && i <= ti)) != upper ? 1 : 0;
-    }
-    pack_bytes<THREADS>(job, f, maskb, tapcnt);
-}
 
 __device__ __forceinline__ const EstJob& find_job(const EstJobs& jobs, unsigned block, unsigned* blk0) {
     int j = 0;
@@ -243,8 +114,8 @@ __device__ __forceinline__ void binarize_row_of_block(const EstJobs& jobs, unsig
     __shared__ SplitInfo info;
     unsigned blk0;
     const EstJob& q = find_job(jobs, block, &blk0);
-    const int f = job_column(block - blk0, q.Fp);
-    if (f >= q.Fp) return;
+    const int f = column_of_block(block - blk0, q.mask.Fp);
+    if (f >= q.mask.Fp) return;
     float x[ITEMS];
     bool done = true;
     if (f < q.F) {
@@ -263,12 +134,10 @@ __device__ __forceinline__ void binarize_row_of_block(const EstJobs& jobs, unsig
         }
         lds_barrier();
     }
-    if (q.E && f >= q.F) {
-        const int R = q.T * q.Cw, Fp = q.Fp;
-        uint32_t* const E = q.E;
-        for (int r = threadIdx.x; r < R; r += THREADS) E[static_cast<size_t>(r) * Fp + f] = 0u;
-    } else if (q.E && done) {
-        pack_row<THREADS, ITEMS>(q, f, &info, x, pool);
+    if (q.mask.E && f >= q.F) {
+        pack_padding<THREADS>(q.mask, f);
+    } else if (q.mask.E && done) {
+        pack_row<THREADS, ITEMS>(q.mask, f, info, x, pool);
     }
 }
 
@@ -313,7 +182,7 @@ __global__ __launch_bounds__(THREADS) void binarize_sort_kernel(const uint8_t* f
         sort_row<THREADS, ITEMS>(q.W, q.n, f, q.alpha, q.beta, q.K, q.thr_val, q.thr_idx, q.aiu, q.K_prev, q.upper_prev,
                                  q.max_change, &info);
         __syncthreads();
-        if (q.E) pack_row_from<THREADS, THREADS * ITEMS>(q, f, &info, q.W + static_cast<size_t>(f) * q.n);
+        if (q.mask.E) pack_row_from<THREADS, THREADS * ITEMS>(q.mask, f, info, q.W + static_cast<size_t>(f) * q.n);
         __syncthreads();
     }
 }
@@ -516,9 +385,10 @@ static int run_weight_jobs(const dab_weight_job* jobs, int n_jobs, void* ws, siz
         EstJob q{};
         q.W = in.W; q.alpha = in.alpha; q.beta = in.beta; q.K = in.K; q.thr_val = in.thr_val; q.thr_idx = in.thr_idx;
         q.aiu = in.alpha_is_upper; q.K_prev = in.K_prev; q.upper_prev = in.alpha_is_upper_prev; q.max_change = in.max_change;
-        q.E = in.E_packed; q.ecnt = in.ecnt;
-        q.F = in.F; q.C = in.C; q.T = in.kh * in.kw; q.n = in.C * q.T; q.Cw = ceil_div(in.C, 32); q.Fp = 64 * ceil_div(in.F, 64);
-        const unsigned columns = static_cast<unsigned>(kNumXCD * ceil_div(q.Fp, kNumXCD));
+        q.F = in.F;
+        q.mask = make_mask_shape(in.E_packed, in.ecnt, in.F, in.C, in.kh * in.kw);
+        q.n = q.mask.n;
+        const unsigned columns = static_cast<unsigned>(kNumXCD * ceil_div(q.mask.Fp, kNumXCD));
         const int c = q.n <= kSmallMaxN ? 0 : (q.n <= kShortMaxN ? 1 : (q.n <= kMidMaxN ? 2 : 3));
         const bool flagged = c >= 2 || (c == 1 ? hand.medium : hand.small);
         if (flagged) {

@@ -6,6 +6,7 @@
 // split descriptor of the estimator, i.e. by stable rank and not by the sign of the value.
 #include "dab_internal.h"
 #include "pack_act.h"
+#include "pack_mask.h"
 
 namespace dab {
 
@@ -62,6 +63,28 @@ __global__ __launch_bounds__(256) void pack_act_nchw_kernel(const float* __restr
 }
 
 // ---------------------------------------------------------------- weights
+// One workgroup per (padded) filter column, the filter read once into registers (every load in flight together), its
+// mask formed there and packed as the estimators pack theirs.
+template <int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void pack_weights_row_kernel(const float* __restrict__ Wt, const float* __restrict__ thr_val,
+                                                                   const int32_t* __restrict__ thr_idx,
+                                                                   const uint8_t* __restrict__ alpha_is_upper, const MaskShape mask,
+                                                                   int F) {
+    DAB_RESERVE_VGPRS();
+    __shared__ uint8_t bytes[THREADS * ITEMS];
+    const int f = column_of_block(blockIdx.x, mask.Fp);
+    if (f >= mask.Fp) return;
+    if (f >= F) {
+        pack_padding<THREADS>(mask, f);
+        return;
+    }
+    float x[ITEMS];
+    load_row<THREADS, ITEMS>(Wt + static_cast<size_t>(f) * mask.n, mask.n, x);
+    const SplitInfo info{thr_val[f], thr_idx[f], alpha_is_upper[f]};
+    pack_row<THREADS, ITEMS>(mask, f, info, x, bytes);
+}
+
+// Filters of more weights or taps than those kernels hold.
 // One workgroup per (padded) filter column.  The filter is brought into LDS with coalesced
 // reads, a slab of whole channels at a time; a wavefront then takes one tap and four groups
 // of 64 consecutive channels at a time: gathered from LDS with stride kh*kw (four reads in
@@ -292,6 +315,21 @@ int dab_pack_weights(const float* W, int32_t F, int32_t C, int32_t kh, int32_t k
     if (T > kWeightMaxTaps || 1ll * C * T >= (1ll << 31)) return DAB_ERR_UNSUPPORTED;
     const int Cw = ceil_div(C, 32);
     const int Fp = 64 * ceil_div(F, 64);
+    const dim3 columns(kNumXCD * ceil_div(Fp, kNumXCD));
+    // filters that fit in a workgroup's registers (through LDS and a ballot per 64 weights, below, the filters of config 3 take
+    // 5.6, 4.8, 5.6, 5.6, 11.2 and 4.0 us; in these kernels 3.6, 3.7, 3.6, 3.7, 8.4 and 3.3)
+    if (T <= kPackMaxTaps && C * T <= 512 * 26) {
+        const MaskShape mask = make_mask_shape(E_packed, ecnt, F, C, T);
+        hipStream_t st = static_cast<hipStream_t>(stream);
+#define DAB_PACK_ROWS(N, I) \
+    return launch(pack_weights_row_kernel<N, I>, columns, dim3(N), 0, st, W, thr_val, thr_idx, alpha_is_upper, mask, F)
+        if (C * T <= 256 * 4) DAB_PACK_ROWS(256, 4);
+        if (C * T <= 256 * 9) DAB_PACK_ROWS(256, 9);
+        if (C * T <= 512 * 9) DAB_PACK_ROWS(512, 9);
+        if (C * T <= 512 * 18) DAB_PACK_ROWS(512, 18);
+        DAB_PACK_ROWS(512, 26);
+#undef DAB_PACK_ROWS
+    }
     int slab_c = (kWeightSlabFloats / T) & ~63;             // whole 64-channel groups per slab
     if (slab_c < 64) return DAB_ERR_UNSUPPORTED;
     if (slab_c > C) slab_c = 64 * ceil_div(C, 64);
@@ -301,7 +339,7 @@ int dab_pack_weights(const float* W, int32_t F, int32_t C, int32_t kh, int32_t k
     // the (tap, 64-channel group) items of a filter are spread over the wavefronts of its workgroup:
     // long filters get sixteen of them
     const int threads = 1ll * C * T >= 8192 ? 1024 : 256;
-    return launch(pack_weights_kernel, dim3(kNumXCD * ceil_div(Fp, kNumXCD)), dim3(threads), lds,
+    return launch(pack_weights_kernel, columns, dim3(threads), lds,
                   static_cast<hipStream_t>(stream), W, thr_val, thr_idx, alpha_is_upper, E_packed, ecnt, F, C, T, Cw, Fp, slab_c);
 }
 
