@@ -3,18 +3,21 @@
     python -m paper_1804_02941_amd.build
 
 hipcc cross-compiles without a GPU.  The library is written next to the sources
-(``paper_1804_02941_amd/libdab_hip.so``); nothing is installed.
+(``paper_1804_02941_amd/libdab_hip.so``), and so is the native half of the Python
+binding (``_dab_call.so``, host code only); nothing is installed.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libdab_hip.so")
+CALL = os.path.join(PKG, "_dab_call.so")
 SOURCES = ("api.hip", "binconv.hip", "direct.hip", "pack.hip", "estimate.hip", "training.hip", "probe.hip")
 
 FLAGS = [
@@ -74,6 +77,23 @@ def _without_remarks(text: str) -> str:
     return "\n".join(keep)
 
 
+def build_call() -> str:
+    """Compile _dab_call.so, the native half of the Python binding, against the built library and torch."""
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-isystem", os.path.join(tdir, "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "binding_call.cpp"),
+           "-o", CALL + ".tmp", "-L", PKG, "-l:libdab_hip.so", "-L", os.path.join(tdir, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("compiling the binding failed:\n" + proc.stdout)
+    os.replace(CALL + ".tmp", CALL)
+    return CALL
+
+
 def build(verbose: bool = False) -> str:
     """Compile every HIP translation unit and link libdab_hip.so; returns its path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -97,6 +117,7 @@ def build(verbose: bool = False) -> str:
                   f"LDS {r.get('LDS Size [bytes/block]')} scratch {r.get('ScratchSize [bytes/lane]')} "
                   f"waves/SIMD {r.get('Occupancy [waves/SIMD]')}", flush=True)
     os.replace(LIB + ".tmp", LIB)
+    build_call()
     return LIB
 
 
