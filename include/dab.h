@@ -377,8 +377,8 @@ int dab_pool_bits(const uint32_t* A_packed, int32_t B, int32_t C, int32_t H, int
  *   E_packed, alpha, beta   as for dab_binconv2d (the outputs of dab_pack_weights / the estimator)
  *   Y          fp32 NHWC [B][Ho][Wo][F] out (dab_wbin_fc: [B][F])
  *   ws         workspace of dab_wbin_conv2d_workspace_bytes(d) bytes (dab_wbin_fc_workspace_bytes),
- *              256-byte aligned: the bf16 pieces (6 bytes per input element, with the padding
- *              halo), the expanded masks, per-pixel input sums
+ *              256-byte aligned.  (The operands are expanded on the way into the matrix cores, so nothing is
+ *              written there; the size is still asked for, and a call that brings less refused.)
  * Accuracy: fp32 accumulation of exact terms; the error is bounded by about (3*n/16 + T) * 2^-24
  * times sum_i |x_i| |w~_i| (n = C*kh*kw, T = kh*kw) and is typically a few 1e-7 of that scale.
  * Errors as for dab_binconv2d.

@@ -18,7 +18,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libdab_hip.so")
 CALL = os.path.join(PKG, "_dab_call.so")
-SOURCES = ("api.hip", "binconv.hip", "direct.hip", "pack.hip", "estimate.hip", "training.hip", "probe.hip")
+SOURCES = ("api.hip", "binconv.hip", "direct.hip", "wbin.hip", "pack.hip", "estimate.hip", "training.hip", "probe.hip")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

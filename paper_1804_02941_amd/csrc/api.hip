@@ -1,5 +1,6 @@
 // Status text, error bookkeeping and the one-time device set-up of the C ABI.
 #include "dab_internal.h"
+#include "wbin.h"
 
 #include <atomic>
 #include <mutex>
@@ -26,6 +27,7 @@ int ensure_device_ready(int* dev_out) {
     if (g_ready[dev].load(std::memory_order_relaxed)) return DAB_OK;
     if (int rc = init_binconv()) return rc;
     if (int rc = init_direct()) return rc;
+    if (int rc = init_wbin()) return rc;
     if (int rc = init_pack()) return rc;
     if (int rc = init_estimate(dev)) return rc;
     g_ready[dev].store(1, std::memory_order_release);

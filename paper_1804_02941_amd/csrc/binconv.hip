@@ -36,13 +36,9 @@
 //   finish    (split launches only) adds the partials, y = (alpha-beta)*s1 + beta*sA.
 // Layers with at most 512 output blocks of 32 x 32 skip main and finish for the small-product
 // kernel further down (one workgroup per block, no partial sums in memory).
-//
-// The weights-only layer (Section 5.1's WBin: real inputs, binarized weights) runs through the
-// same main and small kernels with bf16 operands: wbin_prepare_kernel splits every fp32 input
-// exactly into three bf16 pieces laid out like the fp4 planes, the masks become bf16 0 / 1, and
-// v_mfma_f32_32x32x16_bf16 takes the place of the fp4 instruction (products exact, fp32 sums).
 #include "dab_internal.h"
 #include "mfma_tools.h"
+#include "wbin.h"
 
 namespace dab {
 
@@ -64,8 +60,7 @@ struct MfmaGeom {
     int act_p, act_w, act_wt;      // prepare: pixels x words of a transpose tile (product 256), word tiles
     int sum_shift;                 // prepare: log2 of the lanes that share one pixel's row sum
     int n_fblocks;                 // 32-filter column blocks (small products)
-    int wbin, C16, nb;             // weights-only layer: flag, 16-channel groups per tap, B steps per filter tile (fp4: nb = nk)
-    FastDiv d_HoWo, d_Wo, d_Wp, d_HpWp, d_nk, d_mtiles, d_ksplit, d_T, d_kw, d_act_wt, d_Cw, d_fblocks, d_3;
+    FastDiv d_HoWo, d_Wo, d_Wp, d_HpWp, d_nk, d_mtiles, d_ksplit, d_T, d_kw, d_act_wt, d_Cw, d_fblocks;
     // block ranges of the prepare kernel
     unsigned blk_act, blk_wgt, blk_sum, blk_tab, blk_sa;
 };
@@ -228,193 +223,13 @@ __global__ __launch_bounds__(256) void binconv_prepare_kernel(const MfmaGeom g, 
     }
 }
 
-// ---------------------------------------------------------------- prepare (weights-only layer)
-// fp32 -> bf16 with round-to-nearest-even (finite inputs).
-__device__ __forceinline__ uint32_t bf16_bits(float x) {
-    const uint32_t u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ float bf16_value(uint32_t b) { return __uint_as_float(b << 16); }
-
-// The weights-only layer keeps the real inputs: x is split into three bf16 pieces, x = p0 + p1 + p2
-// exactly (each remainder is computed exactly in fp32 and has at most 16, then 8 significant bits),
-// the masks become bf16 0 / 1, and every product p * e is exact, so the fp32 accumulators of the
-// MFMAs see exactly the terms x_i e_i, eight bits at a time.  Layout of the pieces: planes
-// [(16-channel group * 3 + piece) * 2 + half][padded pixel][8 bf16], zero halo, zero past C;
-// weights: fragments [128-filter tile][16-channel group * T + tap][4][2][32][8 bf16].
-__global__ __launch_bounds__(256) void wbin_prepare_kernel(const MfmaGeom g, const float* __restrict__ X,
-                                                           const uint32_t* __restrict__ E, uint4* __restrict__ A16,
-                                                           uint4* __restrict__ E16, float* __restrict__ pixsum,
-                                                           int32_t* __restrict__ ktab, float* __restrict__ sA) {
-    DAB_RESERVE_VGPRS();
-    __shared__ float xt[32][65];                                   // 32 pixels x 64 channels, padded rows
-    unsigned blk = blockIdx.x;
-    if (blk < g.blk_act) {
-        // A block takes 32 padded pixels x 64 channels.  Its threads read the fp32 values along the
-        // channels (256 contiguous bytes per pixel), turn the tile through LDS, and write the bf16
-        // pieces along the pixels (512 contiguous bytes per plane and half-wavefront).
-        const int n_ct = (g.C16 + 3) >> 2;                          // 64-channel tiles
-        const int pt = static_cast<int>(blk) / n_ct;
-        const int ct = static_cast<int>(blk) - pt * n_ct;
-        const int tid = threadIdx.x;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int e = tid + k * 256;                            // element of the tile: pixel e / 64, channel e % 64
-            const int pl = e >> 6, cl = e & 63;
-            const int pp = pt * 32 + pl, c = ct * 64 + cl;
-            float v = 0.0f;
-            if (pp < g.npix && c < g.C) {
-                const int b = fdiv(pp, g.d_HpWp);
-                const int r = pp - b * g.Hp * g.Wp;
-                const int yp = fdiv(r, g.d_Wp);
-                const int y = yp - g.ph, x = r - yp * g.Wp - g.pw;
-                if (y >= 0 && y < g.H && x >= 0 && x < g.W) v = X[((static_cast<size_t>(b) * g.H + y) * g.W + x) * g.C + c];
-            }
-            xt[pl][cl] = v;
-        }
-        __syncthreads();
-        const int pl = tid & 31, gl = tid >> 5;                     // pixel of the tile, 8-channel group of the tile
-        const int pp = pt * 32 + pl, g8 = ct * 8 + gl;
-        if (pp >= g.npix || g8 >= 2 * g.C16) return;
-        uint32_t piece[3][8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            float rest = xt[pl][gl * 8 + c];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                piece[p][c] = bf16_bits(rest);
-                rest -= bf16_value(piece[p][c]);                     // exact
-            }
-        }
-        const int c16 = g8 >> 1, half = g8 & 1;
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const size_t q = static_cast<size_t>((c16 * 3 + p) * 2 + half);
-            A16[q * g.npix + pp] = make_uint4(piece[p][0] | (piece[p][1] << 16), piece[p][2] | (piece[p][3] << 16),
-                                              piece[p][4] | (piece[p][5] << 16), piece[p][6] | (piece[p][7] << 16));
-        }
-        return;
-    }
-    blk -= g.blk_act;
-    if (blk < g.blk_wgt) {
-        const long long i = 1ll * blk * 256 + threadIdx.x;
-        if (i >= 1ll * g.n_ntiles * g.nb * 256) return;
-        const int e = static_cast<int>(i & 255);
-        const int tk = static_cast<int>(i >> 8);                    // filter tile * nb + B step
-        const int nt = tk / g.nb;
-        const int bs = tk - nt * g.nb;
-        const int c16 = fdiv(bs, g.d_T);
-        const int tap = bs - c16 * g.T;
-        const int j = e >> 6, half = (e >> 5) & 1, f = nt * kNTile + j * 32 + (e & 31);
-        uint32_t bits = 0;
-        if (f < g.Fp) bits = (E[(static_cast<size_t>(tap) * g.Cw + (c16 >> 1)) * g.Fp + f] >> ((c16 & 1) * 16 + half * 8)) & 0xFFu;
-        uint32_t w[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            w[k] = ((bits >> (2 * k)) & 1u ? 0x3F80u : 0u) | ((bits >> (2 * k + 1)) & 1u ? 0x3F800000u : 0u);
-        E16[i] = make_uint4(w[0], w[1], w[2], w[3]);
-        return;
-    }
-    blk -= g.blk_wgt;
-    if (blk < g.blk_sum) {
-        // sum of the real inputs of every padded pixel (0 in the halo), double accumulation;
-        // 2^sum_shift neighbouring lanes share a pixel (about sixteen channels each)
-        const unsigned t = blk * 256 + threadIdx.x;
-        const int pp = static_cast<int>(t >> g.sum_shift);
-        const int sub = static_cast<int>(t & ((1u << g.sum_shift) - 1));
-        const int ppc = min(pp, g.npix - 1);                       // every lane stays in the shuffles
-        const int b = fdiv(ppc, g.d_HpWp);
-        const int r = ppc - b * g.Hp * g.Wp;
-        const int yp = fdiv(r, g.d_Wp);
-        const int y = yp - g.ph, x = r - yp * g.Wp - g.pw;
-        double sum = 0.0;
-        if (y >= 0 && y < g.H && x >= 0 && x < g.W) {
-            const float* src = X + ((static_cast<size_t>(b) * g.H + y) * g.W + x) * g.C;
-            for (int c = sub; c < g.C; c += 1 << g.sum_shift) sum += static_cast<double>(src[c]);
-        }
-        for (int d = 1; d < (1 << g.sum_shift); d <<= 1) sum += __shfl_xor(sum, d, 64);
-        if (pp < g.npix && sub == 0) pixsum[pp] = static_cast<float>(sum);
-        return;
-    }
-    blk -= g.blk_sum;
-    if (blk < g.blk_tab) {
-        // byte offset of every k-step: steps run (16-channel group, tap, piece), pieces fastest, so
-        // three consecutive steps share one B fragment; then the window's pixel offsets (times 16)
-        const int i = static_cast<int>(blk * 256 + threadIdx.x);
-        if (i >= g.nk + kTabPad + g.T) return;
-        if (i >= g.nk + kTabPad) {
-            const int tap = i - (g.nk + kTabPad);
-            const int ky = fdiv(tap, g.d_kw);
-            ktab[i] = (ky * g.Wp + (tap - ky * g.kw)) * 16;
-            return;
-        }
-        const int ks = min(i, g.nk - 1);
-        const int bs = fdiv(ks, g.d_3);
-        const int piece = ks - 3 * bs;
-        const int c16 = fdiv(bs, g.d_T);
-        const int tap = bs - c16 * g.T;
-        const int ky = fdiv(tap, g.d_kw);
-        const int kx = tap - ky * g.kw;
-        ktab[i] = (c16 * 3 + piece) * 2 * g.plane + (ky * g.Wp + kx) * 16;
-        return;
-    }
-    blk -= g.blk_tab;
-    {
-        // small layers only: the window sum of every output pixel, one workgroup per pixel; a row of
-        // the window is kw*C contiguous values, read four batches deep
-        __shared__ double part[4];
-        const int m = static_cast<int>(blk);
-        const int tid = threadIdx.x;
-        const int b = fdiv(m, g.d_HoWo);
-        const int r = m - b * g.HoWo;
-        const int oy = fdiv(r, g.d_Wo);
-        const int ox = r - oy * g.Wo;
-        const int x0 = max(ox * g.sw - g.pw, 0), x1 = min(ox * g.sw - g.pw + g.kw, g.W);
-        const int len = (x1 - x0) * g.C;
-        double acc = 0.0;
-        for (int ky = 0; ky < g.kh; ++ky) {
-            const int y = oy * g.sh - g.ph + ky;
-            if (y < 0 || y >= g.H) continue;
-            const float* src = X + ((static_cast<size_t>(b) * g.H + y) * g.W + x0) * g.C;
-            for (int i0 = tid; i0 < len; i0 += 4 * 256) {
-                float v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = src[min(i0 + u * 256, len - 1)];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc += i0 + u * 256 < len ? static_cast<double>(v[u]) : 0.0;
-            }
-        }
-        for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
-        if ((tid & 63) == 0) part[tid >> 6] = acc;
-        __syncthreads();
-        if (tid == 0) sA[m] = static_cast<float>((part[0] + part[1]) + (part[2] + part[3]));
-    }
-}
-
 // ---------------------------------------------------------------- main
-// Operand kinds of the main kernel: bits expanded to fp4 (the binarized layer), or bf16 (the
-// weights-only layer: fp32 inputs split into three bf16 pieces, masks as 0 / 1).
-enum { kFp4 = 0, kBf16 = 1 };
-
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
-template <int KIND>
-__device__ __forceinline__ v16f mfma_step(v4i a, v4i b, v16f c) {
-    if constexpr (KIND == kFp4) {
-        return mfma_fp4(a, b, c);
-    } else {
-        // 32x32x16: lane l holds row (column) l % 32 and the eight k of half l / 32
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-    }
-}
-
-
 // One group of the k-step schedule: an MFMA, then at most one LDS read or one buffer load in its shadow.
 #define DAB_SLOT_DS()   do { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); } while (0)
 #define DAB_SLOT_VMEM() do { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); __builtin_amdgcn_sched_group_barrier(0x020, 1, 0); } while (0)
 #define DAB_SLOT_NONE() do { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); } while (0)
 
-template <int WAVES, int MODE, int KIND = kFp4>
+template <int WAVES, int MODE>
 __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom g, const char* __restrict__ A4,
                                                                   const uint4* __restrict__ E4,
                                                                   const float* __restrict__ alpha,
@@ -427,11 +242,6 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
                                                                   uint32_t* __restrict__ out_bits) {
     constexpr int THREADS = 64 * WAVES;
     constexpr int MTILE = 64 * WAVES;
-    // k-steps per B step: the three bf16 pieces of an input share the fragments of their 16-channel
-    // group and tap, so a panel entry serves three consecutive k-steps; depth of the A queue
-    constexpr int PIECES = KIND == kBf16 ? 3 : 1;
-    constexpr int QD = KIND == kBf16 ? 6 : kPrefetch;
-    constexpr int EPQ = QD / PIECES;                               // panel entries per queue round
     extern __shared__ __align__(16) uint4 panel[];                 // [kchunk][4][64 lanes] 16-byte groups
     __shared__ __align__(16) float sA_lds[WAVES][64];              // row sums of each wavefront's 64 pixels
 
@@ -452,10 +262,10 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
         mt_first = blockIdx.x - ntile * g.wg_per_ntile;
         mt_step = g.wg_per_ntile;
         kbeg = 0;
-        kend = g.nb;                                               // chunks are counted in B steps (fp4: nb = nk)
+        kend = g.nk;
     }
     const int f0 = ntile * kNTile;
-    const uint4* Epanel = E4 + static_cast<size_t>(ntile) * g.nb * 256;
+    const uint4* Epanel = E4 + static_cast<size_t>(ntile) * g.nk * 256;
     const int nchunks = (kend - kbeg + g.kchunk - 1) / g.kchunk;
     // A4 as a buffer resource: the per-lane pixel offset rides in a VGPR, the k-step offset in an SGPR
     const __amdgpu_buffer_rsrc_t a4rsrc =
@@ -490,7 +300,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
     // A reduction that fits in LDS is staged once, and its copies are issued first of all so that
     // they fly while the first tile's addresses and row sums are worked out.
     bool staged = false;
-    if (nchunks == 1 && mt_first < g.n_mtiles) stage_panel(kbeg, kend, (kend - kbeg + EPQ - 1) / EPQ * EPQ);
+    if (nchunks == 1 && mt_first < g.n_mtiles) stage_panel(kbeg, kend, (kend - kbeg + kPrefetch - 1) / kPrefetch * kPrefetch);
     for (int mt = mt_first; mt < g.n_mtiles; mt += mt_step) {
         const int m_base = mt * MTILE + wave * 64;
         int pixoff[2], mypix = 0;
@@ -509,18 +319,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
         // entries of the k-step table are the window's pixel offsets, times 16).  Thirty-two loads at a
         // time (a 5x5 window is one round trip); the result is needed only after the reduction loop.
         float rowsum = 0.0f;
-        if (KIND == kBf16) {
-            // weights-only layer: the per-pixel sums are fp32 sums of the real inputs
-            const float* psum = reinterpret_cast<const float*>(pixsum);
-            const int32_t* wtab = ktab + g.nk + kTabPad;            // the window's pixel offsets, times 16
-            for (int t0 = 0; t0 < g.T; t0 += 32) {
-                float v[32];
-#pragma unroll
-                for (int u = 0; u < 32; ++u) v[u] = psum[mypix + (wtab[min(t0 + u, g.T - 1)] >> 4)];
-#pragma unroll
-                for (int u = 0; u < 32; ++u) rowsum += t0 + u < g.T ? v[u] : 0.0f;
-            }
-        } else if (MODE != kOutSplit) {
+        if (MODE != kOutSplit) {
             int sum = 0;
             for (int t0 = 0; t0 < g.T; t0 += 32) {
                 int v[32];
@@ -544,13 +343,12 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
             const int ks1 = min(kend, ks0 + g.kchunk);
             // panel entries of this chunk rounded up to a queue round; the extra k-steps multiply
             // zero B fragments (and read some valid A fragment), so the loop has no tail
-            const int ent = (ks1 - ks0 + EPQ - 1) / EPQ * EPQ;
-            const int steps = ent * PIECES;
+            const int steps = (ks1 - ks0 + kPrefetch - 1) / kPrefetch * kPrefetch;
             if (nchunks > 1) {
                 __syncthreads();                                   // previous users of the panel are done
-                stage_panel(ks0, ks1, ent);
+                stage_panel(ks0, ks1, steps);
             }
-            // A fragments: a queue of QD k-steps per row block, refilled as it drains.  The byte
+            // A fragments: a queue of kPrefetch k-steps per row block, refilled as it drains.  The byte
             // offset of a k-step comes from the table the prepare kernel wrote (four per scalar
             // load); steps past the end read a valid fragment against zero B fragments.
             auto load_a = [&](int i, int poff) -> v4i {
@@ -558,13 +356,13 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
                 return v4i{static_cast<int>(v[0]), static_cast<int>(v[1]), static_cast<int>(v[2]), static_cast<int>(v[3])};
             };
             // Slot d of the queue holds the fragments of step st + d; the slot emptied by the previous
-            // step is refilled during this one (QD - 1 steps ahead), so a register is never live as
+            // step is refilled during this one (kPrefetch - 1 steps ahead), so a register is never live as
             // both a pending load and an operand and the loop carries no copies.  The first
             // fragments are requested before the wait for the panel, so both latencies overlap.
-            const int* kt = ktab + ks0 * PIECES;
-            v4i abuf[QD][2];
+            const int* kt = ktab + ks0;
+            v4i abuf[kPrefetch][2];
 #pragma unroll
-            for (int d = 0; d < QD - 1; ++d) {
+            for (int d = 0; d < kPrefetch - 1; ++d) {
                 const int p = kt[d];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) abuf[d][i] = load_a(i, p);
@@ -582,35 +380,27 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
             uint4 bq[2][4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) bq[0][j] = bp[j * 64];
-            int e0 = 0;                                            // panel entry of step st
-            for (int st = 0; st < steps; st += QD, e0 += EPQ) {
+            for (int st = 0; st < steps; st += kPrefetch) {
 #pragma unroll
-                for (int d = 0; d < QD; ++d) {
-                    constexpr int kAhead = QD - 1;
-                    const int eb = d / PIECES;                     // entry of this step within the round
-                    if (d % PIECES == 0) {
-                        // B fragments of the next entry are read while this one multiplies
-                        const uint4* bn = bp + static_cast<size_t>(min(e0 + eb + 1, ent - 1)) * 256;
+                for (int d = 0; d < kPrefetch; ++d) {
+                    constexpr int kAhead = kPrefetch - 1;
+                    // B fragments of the next step are read while this one multiplies
+                    const uint4* bn = bp + static_cast<size_t>(min(st + d + 1, steps - 1)) * 256;
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) bq[(eb + 1) & 1][j] = bn[j * 64];
-                    }
+                    for (int j = 0; j < 4; ++j) bq[(d + 1) & 1][j] = bn[j * 64];
                     const int p = kt[st + d + kAhead];
-                    abuf[(d + kAhead) % QD][0] = load_a(0, p);
-                    abuf[(d + kAhead) % QD][1] = load_a(1, p);
+                    abuf[(d + kAhead) % kPrefetch][0] = load_a(0, p);
+                    abuf[(d + kAhead) % kPrefetch][1] = load_a(1, p);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const uint4 bu = bq[eb & 1][j];
+                        const uint4 bu = bq[d & 1][j];
                         const v4i bv = {static_cast<int>(bu.x), static_cast<int>(bu.y), static_cast<int>(bu.z),
                                         static_cast<int>(bu.w)};
-                        acc[0][j] = mfma_step<KIND>(abuf[d][0], bv, acc[0][j]);
-                        acc[1][j] = mfma_step<KIND>(abuf[d][1], bv, acc[1][j]);
+                        acc[0][j] = mfma_fp4(abuf[d][0], bv, acc[0][j]);
+                        acc[1][j] = mfma_fp4(abuf[d][1], bv, acc[1][j]);
                     }
                     // issue order of this k-step: every memory instruction in the shadow of an MFMA
-                    if (d % PIECES == 0) {
-                        DAB_SLOT_DS(); DAB_SLOT_DS(); DAB_SLOT_DS(); DAB_SLOT_DS();
-                    } else {
-                        DAB_SLOT_NONE(); DAB_SLOT_NONE(); DAB_SLOT_NONE(); DAB_SLOT_NONE();
-                    }
+                    DAB_SLOT_DS(); DAB_SLOT_DS(); DAB_SLOT_DS(); DAB_SLOT_DS();
                     DAB_SLOT_VMEM(); DAB_SLOT_NONE(); DAB_SLOT_VMEM(); DAB_SLOT_NONE();
                 }
             }
@@ -735,7 +525,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_mfma_kernel(const MfmaGeom
 // sA comes from the prepare kernel's per-pixel pass.
 constexpr int kSmallDepth = 8;
 
-template <int MODE, int WAVES, int KIND = kFp4>
+template <int MODE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void binconv_small_kernel(
     const MfmaGeom g, const char* __restrict__ A4, const uint4* __restrict__ E4, const float* __restrict__ alpha,
     const float* __restrict__ beta, float* __restrict__ Y, int32_t* __restrict__ dbg_s1, const float* __restrict__ sA,
@@ -745,22 +535,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_small_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int mb = fdiv(blockIdx.x, g.d_fblocks);
     const int fb = blockIdx.x - mb * g.n_fblocks;                   // neighbouring workgroups share the pixel rows
-    const uint4* Eb = E4 + static_cast<size_t>(fb >> 2) * g.nb * 256 + (fb & 3) * 64 + lane;
-    // This kernel walks the reduction with the taps of one plane fastest (neighbouring taps share
-    // cache lines).  For fp4 that is the order of the offset table; the weights-only layer's table
-    // runs (16-channel group, tap, piece), so its step s = (group * 3 + piece) * T + tap is mapped
-    // to the table entry and to the B fragment the three pieces share.
-    auto table_step = [&](int s) -> int {
-        if (KIND == kFp4) return s;
-        const int kbp = fdiv(s, g.d_T);
-        const int c16 = fdiv(kbp, g.d_3);
-        return (c16 * g.T + (s - kbp * g.T)) * 3 + (kbp - 3 * c16);
-    };
-    auto b_step = [&](int s) -> int {
-        if (KIND == kFp4) return s;
-        const int kbp = fdiv(s, g.d_T);
-        return fdiv(kbp, g.d_3) * g.T + (s - kbp * g.T);
-    };
+    const uint4* Eb = E4 + static_cast<size_t>(fb >> 2) * g.nk * 256 + (fb & 3) * 64 + lane;
     const __amdgpu_buffer_rsrc_t a4rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(A4), 0, 2 * g.KB * g.plane, 0x00020000);
     int pixoff;
@@ -797,9 +572,9 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_small_kernel(
     uint4 bq[2][kSmallDepth];
     auto fetch = [&](int set, int first) {
 #pragma unroll
-        for (int d = 0; d < kSmallDepth; ++d) aq[set][d] = load_a(ktab[table_step(min(first + d, klast))]);
+        for (int d = 0; d < kSmallDepth; ++d) aq[set][d] = load_a(ktab[min(first + d, klast)]);
 #pragma unroll
-        for (int d = 0; d < kSmallDepth; ++d) bq[set][d] = Eb[static_cast<size_t>(b_step(min(first + d, klast))) * 256];
+        for (int d = 0; d < kSmallDepth; ++d) bq[set][d] = Eb[static_cast<size_t>(min(first + d, klast)) * 256];
     };
     auto multiply = [&](int set, int first) {
 #pragma unroll
@@ -808,7 +583,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_small_kernel(
                 const uint4 bu = bq[set][d];
                 const v4i bv = {static_cast<int>(bu.x), static_cast<int>(bu.y), static_cast<int>(bu.z),
                                 static_cast<int>(bu.w)};
-                acc = mfma_step<KIND>(aq[set][d], bv, acc);
+                acc = mfma_fp4(aq[set][d], bv, acc);
             }
         }
     };
@@ -926,15 +701,14 @@ struct MfmaPlan {
 
 static size_t round256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
-static int plan_binconv(const dab_conv_desc& d, MfmaPlan* pl, bool wbin = false) {
+static int plan_binconv(const dab_conv_desc& d, MfmaPlan* pl) {
     MfmaGeom& g = pl->g;
     g = MfmaGeom{};
     g.B = d.B; g.H = d.H; g.W = d.W; g.F = d.F; g.kh = d.kh; g.kw = d.kw;
     g.ph = d.pad_h; g.pw = d.pad_w; g.sh = d.stride_h; g.sw = d.stride_w;
     g.C = d.C; g.Cw = ceil_div(d.C, 32);
-    // k-blocks per tap: 64 channels of fp4, or (weights-only layer) 16 channels of bf16 times three pieces
-    g.wbin = wbin ? 1 : 0; g.C16 = ceil_div(d.C, 16);
-    g.KB = wbin ? 3 * g.C16 : ceil_div(d.C, 64);
+    // k-blocks per tap: 64 channels of fp4
+    g.KB = ceil_div(d.C, 64);
     g.Ho = (d.H + 2 * d.pad_h - d.kh) / d.stride_h + 1;
     g.Wo = (d.W + 2 * d.pad_w - d.kw) / d.stride_w + 1;
     g.HoWo = g.Ho * g.Wo;
@@ -944,10 +718,9 @@ static int plan_binconv(const dab_conv_desc& d, MfmaPlan* pl, bool wbin = false)
     const long long a4 = 1ll * d.B * g.Hp * g.Wp * g.KB * 32;
     const long long nk = 1ll * d.kh * d.kw * g.KB;
     if (M >= (1ll << 30) || a4 >= (1ll << 31) || nk >= (1 << 20) || 1ll * M * d.F >= (1ll << 40)) return DAB_ERR_UNSUPPORTED;
-    if (!wbin && 1ll * d.C * d.kh * d.kw >= (1ll << 24)) return DAB_ERR_UNSUPPORTED;   // |s1| must stay exact in fp32
+    if (1ll * d.C * d.kh * d.kw >= (1ll << 24)) return DAB_ERR_UNSUPPORTED;   // |s1| must stay exact in fp32
     g.M = static_cast<int>(M);
     g.nk = static_cast<int>(nk);
-    g.nb = wbin ? d.kh * d.kw * g.C16 : g.nk;
     g.n_ntiles = ceil_div(d.F, kNTile);
     if (1ll * g.n_ntiles * g.nk >= (1ll << 22)) return DAB_ERR_UNSUPPORTED;
 
@@ -958,7 +731,7 @@ static int plan_binconv(const dab_conv_desc& d, MfmaPlan* pl, bool wbin = false)
     const int tiles256 = ceil_div(g.M, 256) * g.n_ntiles;
     pl->waves = 1ll * ceil_div(g.M, 512) * g.n_ntiles >= kNumCU * 3 / 4 ? 8 : 4;
     g.ksplit = 1;
-    if (!wbin && tiles256 * 2 <= kNumCU) {                       // (the weights-only layer runs unsplit)
+    if (tiles256 * 2 <= kNumCU) {
         g.ksplit = kNumCU / tiles256;
         const int max_split = g.nk / (2 * kPrefetch);              // at least two prefetch groups per split
         if (g.ksplit > max_split) g.ksplit = max_split;
@@ -978,11 +751,10 @@ static int plan_binconv(const dab_conv_desc& d, MfmaPlan* pl, bool wbin = false)
         g.ksplit = 1;
         g.split_steps = g.nk;
     }
-    // chunks of the LDS panel, in B steps (the weights-only layer has a third as many as k-steps)
-    const int span = pl->split ? g.split_steps : g.nb;
+    // chunks of the LDS panel
+    const int span = pl->split ? g.split_steps : g.nk;
     const int nchunks = ceil_div(span, kMaxChunk);
-    const int round = wbin ? 2 : kPrefetch;                        // panel entries per round of the A queue
-    g.kchunk = ceil_div(ceil_div(span, nchunks), round) * round;
+    g.kchunk = ceil_div(ceil_div(span, nchunks), kPrefetch) * kPrefetch;
     g.n_mtiles = ceil_div(g.M, 64 * pl->waves);
     g.wg_per_ntile = kNumCU / g.n_ntiles;
     if (g.wg_per_ntile < 1) g.wg_per_ntile = 1;
@@ -994,11 +766,10 @@ static int plan_binconv(const dab_conv_desc& d, MfmaPlan* pl, bool wbin = false)
     g.d_HoWo = make_fastdiv(g.HoWo); g.d_Wo = make_fastdiv(g.Wo);
     g.d_Wp = make_fastdiv(g.Wp); g.d_HpWp = make_fastdiv(g.Hp * g.Wp);
     g.d_T = make_fastdiv(g.T); g.d_kw = make_fastdiv(g.kw); g.d_Cw = make_fastdiv(g.Cw);
-    g.d_3 = make_fastdiv(3);
     g.d_nk = make_fastdiv(g.nk); g.d_mtiles = make_fastdiv(g.n_mtiles); g.d_ksplit = make_fastdiv(g.ksplit);
 
     pl->a4_bytes = round256(static_cast<size_t>(a4));
-    pl->e4_bytes = static_cast<size_t>(g.n_ntiles) * g.nb * 4096;
+    pl->e4_bytes = static_cast<size_t>(g.n_ntiles) * g.nk * 4096;
     pl->sa_bytes = round256(static_cast<size_t>(g.M) * 4) + round256(static_cast<size_t>(g.npix) * 4) +
                    round256(static_cast<size_t>(g.nk + kTabPad + g.T) * 4);
     pl->s1_bytes = pl->split ? round256(static_cast<size_t>(g.ksplit) * g.M * d.F * 4) : 0;
@@ -1017,47 +788,33 @@ static int plan_binconv(const dab_conv_desc& d, MfmaPlan* pl, bool wbin = false)
     g.blk_sum = static_cast<unsigned>((1ll * g.npix * (1 << g.sum_shift) + 255) / 256);
     g.blk_tab = static_cast<unsigned>((g.nk + kTabPad + 255) / 256);
     g.blk_sa = (pl->split || pl->small) ? static_cast<unsigned>((g.M + 3) / 4) : 0u;
-    if (wbin) {
-        // block ranges of wbin_prepare_kernel: a block per 32 pixels x 64 channels, a thread per 16-byte
-        // weight fragment, lanes per padded pixel, a thread per table entry, a block per output pixel
-        g.blk_act = static_cast<unsigned>(ceil_div(g.npix, 32)) * static_cast<unsigned>(ceil_div(g.C16, 4));
-        g.blk_wgt = static_cast<unsigned>((1ll * g.n_ntiles * g.nb * 256 + 255) / 256);
-        g.sum_shift = 0;
-        while (g.sum_shift < 6 && (16 << g.sum_shift) < d.C) ++g.sum_shift;
-        // the small kernel takes the window sums of the sA pass, not the per-pixel sums
-        g.blk_tab = static_cast<unsigned>((g.nk + kTabPad + g.T + 255) / 256);
-        g.blk_sum = pl->small ? 0u : static_cast<unsigned>((1ll * g.npix * (1 << g.sum_shift) + 255) / 256);
-        g.blk_sa = pl->small ? static_cast<unsigned>(g.M) : 0u;
-    }
     return DAB_OK;
 }
 
-template <int WAVES, int MODE, int KIND = kFp4>
+template <int WAVES, int MODE>
 static int launch_main(const MfmaPlan& pl, hipStream_t st, const char* a4, const uint4* e4, float* sa,
                        const float* alpha, const float* beta, float* Y, int32_t* dbg_s1, float* ws_s1,
                        const int32_t* pixsum, const int32_t* ktab, const float* tau_out, uint32_t* out_bits) {
-    return launch(binconv_mfma_kernel<WAVES, MODE, KIND>, dim3(pl.grid), dim3(64 * WAVES), pl.lds_bytes, st, pl.g, a4, e4,
+    return launch(binconv_mfma_kernel<WAVES, MODE>, dim3(pl.grid), dim3(64 * WAVES), pl.lds_bytes, st, pl.g, a4, e4,
                   alpha, beta, Y, dbg_s1, ws_s1, sa, pixsum, ktab, tau_out, out_bits);
 }
 
 // One-time set-up on the current device: the panel of the main kernel takes up to kMaxChunk * 4 KB
 // of dynamic LDS, above the default limit of a launch.
-template <int WAVES, int MODE, int KIND>
+template <int WAVES, int MODE>
 static int raise_lds_limit() {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&binconv_mfma_kernel<WAVES, MODE, KIND>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&binconv_mfma_kernel<WAVES, MODE>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, kMaxChunk * 4096);
     return e == hipSuccess ? static_cast<int>(DAB_OK) : hip_failed(e);
 }
 int init_binconv() {
-    if (int rc = raise_lds_limit<8, kOutY, kFp4>()) return rc;
-    if (int rc = raise_lds_limit<8, kOutYDebug, kFp4>()) return rc;
-    if (int rc = raise_lds_limit<8, kOutBits, kFp4>()) return rc;
-    if (int rc = raise_lds_limit<4, kOutY, kFp4>()) return rc;
-    if (int rc = raise_lds_limit<4, kOutYDebug, kFp4>()) return rc;
-    if (int rc = raise_lds_limit<4, kOutBits, kFp4>()) return rc;
-    if (int rc = raise_lds_limit<4, kOutSplit, kFp4>()) return rc;
-    if (int rc = raise_lds_limit<8, kOutY, kBf16>()) return rc;
-    return raise_lds_limit<4, kOutY, kBf16>();
+    if (int rc = raise_lds_limit<8, kOutY>()) return rc;
+    if (int rc = raise_lds_limit<8, kOutYDebug>()) return rc;
+    if (int rc = raise_lds_limit<8, kOutBits>()) return rc;
+    if (int rc = raise_lds_limit<4, kOutY>()) return rc;
+    if (int rc = raise_lds_limit<4, kOutYDebug>()) return rc;
+    if (int rc = raise_lds_limit<4, kOutBits>()) return rc;
+    return raise_lds_limit<4, kOutSplit>();
 }
 
 // Estimated time of the launches that go through the workspace: operands written (a4, e4) at 2.9 TB/s, then per tile of a
@@ -1182,35 +939,16 @@ static int run_binconv(const dab_conv_desc& d, const uint32_t* A, const uint32_t
                   : launch_main<4, kOutY>(pl, st, a4, e4, sa, alpha, beta, Y, dbg_s1, s1, pixsum, ktab, tau_out, out_bits);
 }
 
-// The weights-only layer: same main kernel on bf16 operands, fp32 output only.
+// The weights-only layer (wbin.hip).
 static int run_wbin(const dab_conv_desc& d, const float* X, const uint32_t* E, const float* alpha, const float* beta,
                     float* Y, void* ws, size_t ws_bytes, hipStream_t st) {
-    MfmaPlan pl;
-    if (int rc = plan_binconv(d, &pl, true)) return rc;
-    if (!ws || ws_bytes < pl.ws_bytes || misaligned(ws, 256)) return DAB_ERR_WORKSPACE;
+    size_t need = 0;
+    if (int rc = wbin_workspace(d, &need)) return rc;
+    if (!ws || ws_bytes < need || misaligned(ws, 256)) return DAB_ERR_WORKSPACE;
     if (int rc = ensure_device_ready()) return rc;
-    char* a16 = static_cast<char*>(ws);
-    uint4* e16 = reinterpret_cast<uint4*>(a16 + pl.a4_bytes);
-    float* sa = reinterpret_cast<float*>(a16 + pl.a4_bytes + pl.e4_bytes);
-    const MfmaGeom& g = pl.g;
-    float* pixsum = reinterpret_cast<float*>(reinterpret_cast<char*>(sa) + round256(static_cast<size_t>(g.M) * 4));
-    int32_t* ktab = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(pixsum) + round256(static_cast<size_t>(g.npix) * 4));
-    if (int rc = launch(wbin_prepare_kernel, dim3(g.blk_act + g.blk_wgt + g.blk_sum + g.blk_tab + g.blk_sa), dim3(256), 0, st,
-                        g, X, E, reinterpret_cast<uint4*>(a16), e16, pixsum, ktab, sa))
-        return rc;
-    if (pl.small) {
-        const unsigned blocks = static_cast<unsigned>(ceil_div(g.M, 32) * g.n_fblocks);
-        if (g.nk >= 32)
-            return launch(binconv_small_kernel<kOutY, 8, kBf16>, dim3(blocks), dim3(512), 0, st, g, a16, e16, alpha, beta, Y,
-                          nullptr, sa, ktab, nullptr, nullptr);
-        return launch(binconv_small_kernel<kOutY, 2, kBf16>, dim3(blocks), dim3(128), 0, st, g, a16, e16, alpha, beta, Y,
-                      nullptr, sa, ktab, nullptr, nullptr);
-    }
-    const int32_t* psum = reinterpret_cast<const int32_t*>(pixsum);
-    return pl.waves == 8 ? launch_main<8, kOutY, kBf16>(pl, st, a16, e16, sa, alpha, beta, Y, nullptr, nullptr, psum, ktab,
-                                                        nullptr, nullptr)
-                         : launch_main<4, kOutY, kBf16>(pl, st, a16, e16, sa, alpha, beta, Y, nullptr, nullptr, psum, ktab,
-                                                        nullptr, nullptr);
+    WbinPlan pl;
+    plan_wbin(d, &pl);
+    return launch_wbin(pl, st, X, E, alpha, beta, Y);
 }
 
 static int check_common(const void* A, const void* E, const void* alpha, const void* beta, const void* Y,
@@ -1273,9 +1011,8 @@ int dab_binfc(int32_t B, int32_t Kin, int32_t F, const uint32_t* A_packed, const
 }
 
 size_t dab_wbin_conv2d_workspace_bytes(const dab_conv_desc* d) {
-    dab::MfmaPlan pl;
-    if (!d || dab::check_desc(d) != DAB_OK || dab::plan_binconv(*d, &pl, true) != DAB_OK) return 0;
-    return pl.ws_bytes;
+    size_t need = 0;
+    return d && dab::check_desc(d) == DAB_OK && dab::wbin_workspace(*d, &need) == DAB_OK ? need : 0;
 }
 
 size_t dab_wbin_fc_workspace_bytes(int32_t B, int32_t Kin, int32_t F) {

@@ -2,12 +2,14 @@
 // planners of the product kernels and through every workspace-size query and entry point of the C
 // ABI (with placeholder pointers; without a GPU every call ends before a launch).  Checks the
 // invariants the kernels rely on.  Usage: fuzz_plans [cases] [seed]; or fuzz_plans route followed by the
-// eleven numbers of a layer's descriptor, any number of times: which kernel computes it, fp32 and packed-sign output.
+// eleven numbers of a layer's descriptor, any number of times: which kernel computes it, fp32 and packed-sign output;
+// or wbin and the same numbers: the form of the weights-only layer.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 
 #include "dab_internal.h"
+#include "wbin.h"
 
 namespace {
 
@@ -80,6 +82,32 @@ int check_one(const dab_conv_desc& d) {
         REQUIRE(!sp.pad || sp.g.T <= 32);
         REQUIRE(1ll * d.C * d.kh * d.kw < (1ll << 24));
     }
+    size_t wneed = 0;
+    if (wbin_workspace(d, &wneed) == DAB_OK) {
+        WbinPlan wp;
+        plan_wbin(d, &wp);
+        const WbinGeom& g = wp.g;
+        const int pixels = wp.form.rows ? wp.form.rows * 8 / wp.form.v : 32 * wp.form.v;
+        const int filters = wp.form.rows ? wp.form.rows * wp.form.nb : 32 * wp.form.nb * (4 / wp.form.v);
+        REQUIRE(g.M == M && wp.lds_bytes <= static_cast<size_t>(kWbinMaxLds));
+        REQUIRE(g.n_ntiles == (d.F + filters - 1) / filters && 1ll * g.units == (M + pixels - 1) / pixels * g.n_ntiles);
+        REQUIRE(wp.grid == 8u * static_cast<unsigned>(g.per_xcd) && 8ll * g.per_xcd >= g.units);
+        REQUIRE(1ull * g.x_bytes == 4ull * d.B * d.H * d.W * d.C && g.x_bytes < (1u << 31));
+        REQUIRE(1ull * g.e_bytes == 4ull * g.T * g.Cw * g.Fp && g.e_bytes < (1u << 31));
+        if (wp.form.rows == 0) {
+            // every tile's pixels fit the patch (tiles near image ends and a few hundred others)
+            const long long tiles = (M + pixels - 1) / pixels, step = tiles > 300 ? tiles / 300 : 1;
+            auto padded = [&](long long m) {
+                const long long b = m / g.HoWo, r = m % g.HoWo;
+                return (b * g.Hp + r / g.Wo * g.sh) * g.Wp + r % g.Wo * g.sw;
+            };
+            for (long long t = 0; t < tiles; t += step) {
+                const long long last = t * pixels + pixels < M ? t * pixels + pixels : M;
+                const long long np = padded(last - 1) + 1ll * (g.kh - 1) * g.Wp + g.kw - padded(t * pixels);
+                REQUIRE(np <= 64 * kPatchSlots && 8 * 64 * kPatchSlots + 4 * pixels <= 96 * 64 * kPatchSlots);
+            }
+        }
+    }
     // the public queries and entry points: any status is fine, a crash or a sanitizer report is not
     void* fake = reinterpret_cast<void*>(0x1000);
     const size_t ws = dab_binconv2d_workspace_bytes(&d);
@@ -117,6 +145,16 @@ int check_one(const dab_conv_desc& d) {
 }  // namespace
 
 int main(int argc, char** argv) {
+    if (argc > 1 && std::strcmp(argv[1], "wbin") == 0) {
+        for (int a = 2; a + 11 <= argc; a += 11) {
+            int32_t v[11];
+            for (int i = 0; i < 11; ++i) v[i] = std::atoi(argv[a + i]);
+            dab::WbinPlan p;
+            dab::plan_wbin(dab_conv_desc{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10]}, &p);
+            std::printf("%d,%d,%d\n", p.form.rows, p.form.nb, p.form.v);
+        }
+        return 0;
+    }
     if (argc > 1 && std::strcmp(argv[1], "route") == 0) {
         static const char* const names[] = {"block", "direct", "split", "expanded"};
         for (int a = 2; a + 11 <= argc; a += 11) {

@@ -66,3 +66,11 @@ def test_the_gpu_tests_of_wide_padding_reach_the_kernels_they_name(fuzz):
     kernels = {"persistent": "direct", "block": "block", "split": "split", "workspace": "expanded"}
     for layer, r in zip(BORDER_LAYERS, routes(fuzz, [c[1:] for c in BORDER_LAYERS])):
         assert r == (kernels[layer[0].split()[0]],) * 2, layer[0]
+
+
+def test_the_gpu_tests_of_the_weights_only_layer_reach_the_forms_they_name(fuzz):
+    from test_gpu_wbin_forms import LAYERS
+    args = [str(v) for _, (B, C, H, W, F, k, p, s) in LAYERS for v in (B, C, H, W, F, k, k, p, p, s, s)]
+    out = subprocess.run([fuzz, "wbin", *args], capture_output=True, text=True, check=True).stdout.split()
+    for (form, layer), got in zip(LAYERS, out, strict=True):
+        assert tuple(int(v) for v in got.split(",")) == form, layer
