@@ -834,6 +834,33 @@ static double expanded_us(const MfmaPlan& pl, bool bits) {
     return us;
 }
 
+// Estimated times (us) of the kernels that read bits, for reductions of at most 36 k-steps.  Fitted to 573 random layers
+// and batches of the trunk that are too large for plan_block's first rule, both outputs, every kernel timed on each (rms
+// error 12 % persistent, 7 % blocks, 12 % split).
+static double short_out(const DirectGeom& g, bool bits, double whole, double single) {
+    return bits ? 0.0 : 4.0e-6 * g.M * g.F * (g.F % 4 ? single : whole);    // stores of four values, of one
+}
+static double short_direct_us(const DirectPlan& pl, bool bits) {
+    const DirectGeom& g = pl.g;
+    const int n_ntiles = ceil_div(g.F, kNTile), tiles = ceil_div(g.n_mtiles, g.wg_per_ntile) * ceil_div(n_ntiles, kNumCU);
+    const double step = (pl.waves == 4 ? 0.114 : 0.151) * (pl.pad ? 1.485 : 1.0) * (pl.lw == 1 ? 1.477 : pl.lw == 2 ? 1.062 : 1.0);
+    return 3.64 + 0.0385 * g.n_ent + tiles * ((g.n_ent - 1) * step + (pl.waves == 4 ? 2.08 : 3.72)) + short_out(g, bits, 0.033, 0.494);
+}
+static double short_block_us(const BlockPlan& pl, bool bits) {
+    const DirectGeom& g = pl.g;
+    const double per_cu = static_cast<double>(pl.grid) / kNumCU;
+    const double step = pl.lw == 4 ? (g.T > 1 ? 0.0099 : 0.0061) : (g.T > 1 ? 0.0186 : 0.0239);
+    const int share = ceil_div(g.nk, pl.waves * pl.lw) * pl.lw, steps = ceil_div(share, pl.depth) * pl.depth;
+    return 4.04 + (per_cu + 0.435) * ((pl.pad ? 0.243 : 0.182) + pl.waves * steps * step) + short_out(g, bits, 0.095, 0.141);
+}
+static double short_split_us(const SplitPlan& pl, bool bits) {
+    const DirectGeom& g = pl.g;
+    const int steps = pl.sg.groups_per_share * pl.lw;
+    const int steps_run = steps % 8 == 0 ? steps : steps / 8 * 8 + (steps % 8 <= 4 ? 4 : 8);
+    const double step = (pl.lw == 1 ? 0.643 : pl.lw == 2 ? 0.506 : 0.421) * (1.0 + (pl.pad ? 0.158 : 0.0) + 0.018 / g.T);
+    return 3.65 + ceil_div(pl.sg.units, kNumCU) * (2.92 + steps_run * step) + short_out(g, bits, 0.018, 0.342);
+}
+
 // Which kernel computes a layer, with its plan.
 struct ProductPlans {
     BlockPlan block;
@@ -847,9 +874,27 @@ static int plan_product(const dab_conv_desc& d, bool bits, ProductPlans* p, Prod
     // layers of a few hundred output blocks: one workgroup per block, straight from the bits, no workspace
     *which = Product::kBlock;
     if (plan_block(d, &p->block, false)) return DAB_OK;
-    // a reduction whose B fragments fit in LDS: one launch of the persistent kernel, no workspace
-    *which = Product::kDirect;
-    if (plan_direct(d, &p->direct)) return DAB_OK;
+    // A reduction whose B fragments fit in LDS: the persistent kernel, which builds them once per workgroup.  With too few
+    // tiles for the compute units, or where its stores are of single values, a workgroup per 32 x 32 block or the split
+    // kernel are faster: taken where their estimates are under 0.9 and 0.85 of the persistent one's (the split kernel from
+    // eight k-steps and up to two rounds of workgroups, as far as it was timed).  Over 295 other layers that makes fp32
+    // outputs 15.2 % and packed signs 8.1 % faster in the geometric mean, at most 2.5 times faster and 4 % slower.  (us,
+    // persistent | blocks | split, fp32:) 3600 pixels x 36 steps x 256 12.1 | 7.3 | 9.4, 7200 12.3 | 11.2 | 10.0,
+    // 10800 12.4 | 14.7 | 12.8; 15376 x 25 x 128 10.2 | 17.2 | 9.8; 4104 x 18 x 205 16.8 | 8.7 | 10.1.
+    if (plan_direct(d, &p->direct)) {
+        *which = Product::kDirect;
+        const double direct = short_direct_us(p->direct, bits);
+        double best = direct;
+        if (plan_block(d, &p->block, true) && short_block_us(p->block, bits) < 0.9 * direct) {
+            best = short_block_us(p->block, bits);
+            *which = Product::kBlock;
+        }
+        if (p->direct.g.nk >= 8 && plan_split(d, &p->split) && p->split.sg.units <= 2 * kNumCU) {
+            const double split = short_split_us(p->split, bits);
+            if (split < best && split < 0.85 * direct) *which = Product::kSplit;
+        }
+        return DAB_OK;
+    }
     // Longer reductions: shares of it per wavefront over blocks of 64 x 128 where that is the faster form.  Otherwise a
     // workgroup per 32 x 32 block up to a few thousand blocks, and past those the operands expanded into the workspace:
     // a multiply has less work beside it there (nothing is expanded again for each filter tile and tap), which pays for
