@@ -15,7 +15,7 @@ __global__ __launch_bounds__(256) void pack_act_nhwc_kernel(const float* __restr
                                                             uint32_t* __restrict__ A, int n_items,
                                                             int C, int Cw, int Cw64, FastDiv d_Cw64) {
     DAB_RESERVE_VGPRS();
-    pack_act_nhwc<PERIODIC>(X, tau, A, n_items, C, Cw, Cw64, d_Cw64,
+    pack_act_nhwc<PERIODIC, true>(X, tau, A, n_items, C, Cw, Cw64, d_Cw64,
                             static_cast<int>(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)),
                             static_cast<int>(gridDim.x * (blockDim.x >> 6)));
 }
@@ -253,19 +253,20 @@ int dab_pack_activations(const float* X, int32_t layout, int32_t B, int32_t C, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (layout == DAB_LAYOUT_NHWC) {
         const int Cw64 = ceil_div(C, 64);
-        const long long n_items = pixels * Cw64;
-        if (n_items >= (1ll << 30)) return DAB_ERR_UNSUPPORTED;
+        if (pixels * Cw64 >= (1ll << 30)) return DAB_ERR_UNSUPPORTED;
+        const bool flat = packs_flat(tau, C, pixels);
+        const long long n_items = flat ? pixels * C / 64 : pixels * Cw64;
         const long long waves = (n_items + kItemsPerWave - 1) / kItemsPerWave;
         long long blocks = (waves + 3) / 4;
         if (blocks > 4ll * kNumCU) blocks = 4ll * kNumCU;           // four wavefronts per SIMD, then loop
         // sixteen consecutive items start at a multiple of sixteen, so the channel group of item u
         // of a batch is u mod Cw64 whenever Cw64 divides sixteen
         const bool periodic = Cw64 <= kItemsPerWave && (Cw64 & (Cw64 - 1)) == 0;
-        if (periodic && C % 64 == 0) {
+        if (flat || (periodic && C % 64 == 0)) {
 #define DAB_PACK_ALIGNED(N)                                                                                      \
     return launch(pack_act_nhwc_aligned_kernel<N>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, X, tau, \
                   A_packed, static_cast<int>(n_items))
-            switch (Cw64) {
+            switch (flat ? 1 : Cw64) {
                 case 1: DAB_PACK_ALIGNED(1);
                 case 2: DAB_PACK_ALIGNED(2);
                 case 4: DAB_PACK_ALIGNED(4);
