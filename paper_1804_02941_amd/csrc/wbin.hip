@@ -3,9 +3,10 @@
 //   y = (alpha - beta) * sum x e + beta * sum x   (taps inside the image).
 // Every fp32 input is split exactly into three bf16 pieces of eight significant bits, the mask bits become
 // bf16 0 / 1, and v_mfma_f32_32x32x16_bf16 multiplies them: products exact, fp32 sums.  sum x is accumulated
-// in double.  The first pieces have accumulators of their own: added to the same ones, the other two, hundreds
-// of times smaller, lose bits at every step (against 64 bits, of the norm: 8.6e-8 over 1600 terms instead of
-// 5.6e-7, 1.0e-7 over 4096 instead of 2.9e-7; over 24 random layers 6e-8 to 1.2e-7 instead of 1.0e-7 to 7.5e-7).
+// in double.  The instruction loses low bits of products much smaller than the accumulator, so the pieces are
+// summed in one of two ways: rounded pieces (signs of their own, the losses cancel) in one accumulator, or cut
+// pieces with a second accumulator for the last two.  Error against 64 bits, of the norm, over 1600 terms 5.5e-7
+// and 8.6e-8 (cut pieces in one accumulator: 1.0e-6); over 4096 terms in eight shares 2.9e-7 and 1.0e-7.
 //
 // Both kernels read the fp32 input and the packed masks as they lie.
 //   patch   layers of several taps: a workgroup owns 32 * NB consecutive output pixels x 128 filters.  The
@@ -35,6 +36,16 @@ __device__ __forceinline__ uint32_t take_piece(float& a, float& b) {
     const uint32_t p = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
     a -= __uint_as_float(__float_as_uint(a) & 0xFFFF0000u);
     b -= __uint_as_float(__float_as_uint(b) & 0xFFFF0000u);
+    return p;
+}
+
+// The same with a and b rounded to bf16 (to nearest even).
+__device__ __forceinline__ uint32_t take_rounded_piece(float& a, float& b) {
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    const uint32_t p = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{a, b}, v2bf));
+    a -= __uint_as_float(p << 16);
+    b -= __uint_as_float(p & 0xFFFF0000u);
     return p;
 }
 
@@ -138,13 +149,11 @@ __global__ __launch_bounds__(256, 2) void wbin_patch_kernel(const WbinGeom g, co
     double sum[SLOTS];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) sum[s] = 0.0;
-    v16f acc[2][NB];                                     // the first pieces' sums, the other two's
+    v16f acc[NB];                                        // (a second set would leave no register free)
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[p][j][v] = 0.0f;
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
 
     for (int grp = 0; grp < g.C16; ++grp) {
         if (grp) wbin_lds_barrier();                     // the previous group's readers are done
@@ -157,8 +166,8 @@ __global__ __launch_bounds__(256, 2) void wbin_patch_kernel(const WbinGeom g, co
             char* const dst = lds + ((q >> 1) * kPix + s * 64 + (tid >> 2)) * 16 + (q & 1) * 8;
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
-                const uint32_t lo = take_piece(v[0], v[1]);
-                *reinterpret_cast<uint2*>(dst + p * 2 * kPix * 16) = make_uint2(lo, take_piece(v[2], v[3]));
+                const uint32_t lo = take_rounded_piece(v[0], v[1]);
+                *reinterpret_cast<uint2*>(dst + p * 2 * kPix * 16) = make_uint2(lo, take_rounded_piece(v[2], v[3]));
             }
         }
         __builtin_amdgcn_s_waitcnt(0);                   // the mask words have landed too (issued before these pixels)
@@ -195,8 +204,7 @@ __global__ __launch_bounds__(256, 2) void wbin_patch_kernel(const WbinGeom g, co
             for (int p = 0; p < 3; ++p) {
 #pragma unroll
                 for (int j = 0; j < NB; ++j)
-                    acc[p > 0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[set][p]), b[set][j],
-                                                                            acc[p > 0][j], 0, 0, 0);
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[set][p]), b[set][j], acc[j], 0, 0, 0);
             }
 #pragma unroll
             for (int j = 0; j < NB; ++j) b[set ^ 1][j] = expand_mask(bits[set ^ 1][j]);
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(256, 2) void wbin_patch_kernel(const WbinGeom g, co
 #pragma unroll
         for (int j = 0; j < NB; ++j)
             if (whole || (m0 + r < g.M && fl + j * 32 < g.F))
-                store_y(y + j * 32, fmaf(dcol[j], acc[0][j][v] + acc[1][j][v], bcol[j] * sx), g.stream_out);
+                store_y(y + j * 32, fmaf(dcol[j], acc[j][v], bcol[j] * sx), g.stream_out);
     }
 }
 
