@@ -484,7 +484,7 @@ def weights_only_products(states, dab, torch):
         out[L.name] = {"ms": round(us * 1e-3, 4), "bf16_tflops": round(6 * s.macs / (us * 1e-6) / 1e12, 1),
                        "frac_of_mfma_bf16_peak": round(6 * s.macs / (us * 1e-6) / MFMA_BF16_FLOPS, 4)}
         del ws, Y
-    return {"what": "dab_wbin_conv2d / dab_wbin_fc (prepare + product) per layer, fp32 inputs as three bf16 pieces, "
+    return {"what": "dab_wbin_conv2d / dab_wbin_fc (one launch) per layer, fp32 inputs as three bf16 pieces, "
                     "each call alone on the chip",
             "ms_per_step": round(total_us * 1e-3, 4), "macs_per_s": total_macs / (total_us * 1e-6), "per_layer": out}
 
