@@ -541,9 +541,11 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     const int ex = static_cast<int>((__float_as_uint(M) >> 23) & 0xFFu) - 126;     // M < 2^ex
     const double scale = ldexp(1.0, 48 - ex), unscale = ldexp(1.0, ex - 48);
     // x 2^(48 - ex) rounded to an integer (|.| < 2^48): added to 1.5 * 2^52, the integer sits in the low bits of the double;
-    // q = that integer + off >= 0 (off even, so that ties round the same way), in the low bits of the double near 2^52
+    // q = that integer + off, in the low bits of the double near 2^52: off is even, so that ties round the same way, and leaves q
+    // at 2 or more before the rounding (below 2^52 doubles are half as far apart: a smallest weight of which the scaling leaves a
+    // fraction, one below 2^-24 of the largest, would round to 2^52 - 1/2 there if it could reach it, into the last bucket)
     const long long fmin_i = __double_as_longlong(fma(static_cast<double>(mn), scale, 6755399441055744.0)) - 0x4338000000000000ll;
-    const long long off = -fmin_i + (fmin_i & 1);
+    const long long off = 2 - fmin_i + (fmin_i & 1);
     const double magic = 4503599627370496.0 + static_cast<double>(off);
     auto q_of = [&](float v) -> double { return fma(static_cast<double>(v), scale, magic); };
     // bucket = q >> sh, at least half of the buckets in use (a row whose range is below an eighth of its largest magnitude

@@ -2,8 +2,8 @@
 // plain sorted reference.  Built with -fsanitize=thread it reports every LDS word (a function-local
 // static here) that one thread writes and another reads or writes without a barrier between them;
 // built with -fsanitize=address,undefined every LDS index out of bounds.  Usage:
-//     emulate_rows <case> [seed]       case: sort64x3 sort256x7 sort512x7 sort1024x7 sort1024x13
-//                                            bucket256x9 bucket512x9 bucket512x26 bucket256x36
+//     emulate_rows <case> [seed] [rows] [n]    case: sort<threads>x<weights per thread>, bucket<...> as in kCases;
+//                                              rows: a name in fill(); n: weights of a row instead of the case's own
 #include "hip_emu.h"
 
 #include <string>
@@ -123,42 +123,80 @@ double uniform() {
 }
 double gaussian() { return std::sqrt(-2.0 * std::log(uniform() + 1e-300)) * std::cos(6.283185307179586 * uniform()); }
 
+// Rows of n weights; returns how many.
+int fill(const std::string& kind, int n, std::vector<float>& W) {
+    auto row = [&]() { W.resize(W.size() + static_cast<size_t>(n)); return W.data() + W.size() - n; };
+    if (kind == "mixed") {
+        // a Gaussian row, a skewed two-cluster one, one with few distinct values, a one-sided one
+        for (int k = 0; k < 4; ++k) row();
+        for (int j = 0; j < n; ++j) {
+            W[static_cast<size_t>(j)] = static_cast<float>(0.05 * gaussian() + 0.01);
+            W[static_cast<size_t>(n + j)] = static_cast<float>(uniform() < 0.2 ? 0.5 + 0.1 * gaussian() : -0.1 + 0.05 * gaussian());
+            W[static_cast<size_t>(2 * n + j)] = static_cast<float>(static_cast<int>(uniform() * 7) - 3) * 0.25f;
+            W[static_cast<size_t>(3 * n + j)] = static_cast<float>(std::fabs(gaussian()));
+        }
+        return 4;
+    }
+    if (kind == "tiny_minimum") {
+        // One-sided rows whose smallest weight is k times 2^(e - 48), 2^e the power of two above the largest magnitude: the
+        // only weights that are rounded when the row is scaled to integers.  Both parities, every quarter of the fraction.
+        const double ks[] = {0.3, 0.6, 1.4, 1.5, 281.4, 281.5, 281.6, 282.6, 1e-30};
+        int F = 0;
+        for (double k : ks)
+            for (int sign = -1; sign <= 1; sign += 2, ++F) {
+                float* w = row();
+                float top = 0.0f;
+                for (int j = 0; j < n; ++j) {
+                    w[j] = static_cast<float>(0.1 * std::fabs(gaussian()) + 0.01);
+                    top = std::max(top, w[j]);
+                }
+                int e;
+                std::frexp(top, &e);
+                w[n / 3] = static_cast<float>(sign * k * std::ldexp(1.0, e - 48));
+            }
+        return F;
+    }
+    return 0;
+}
+
+struct Case {
+    const char* name;
+    int n;
+    void (*run)(const std::vector<float>&, int, int, Out&);
+};
+// (rows shorter than the case's thread count times its weights per thread: positions past the end take part)
+const Case kCases[] = {
+    {"sort64x3", 150, run_sort<64, 3>},
+    {"sort256x7", 1600, run_sort<256, 7>},
+    {"sort512x7", 3500, run_sort<512, 7>},
+    {"sort1024x7", 7000, run_sort<1024, 7>},
+    {"sort1024x13", 12544, run_sort<1024, 13>},
+    {"bucket256x3", 300, run_bucket<256, 3, 512, 256>},
+    {"bucket256x7", 1600, run_bucket<256, 7, 1024, 256>},
+    {"bucket256x9", 2304, run_bucket<256, 9, 512, 256>},
+    {"bucket512x9", 4000, run_bucket<512, 9, 2048, 256>},
+    {"bucket256x18", 4600, run_bucket<256, 18, 1024, 256>},
+    {"bucket512x26", 12544, run_bucket<512, 26, 2048, 512>},
+    {"bucket256x36", 9001, run_bucket<256, 36, 2048, 256>},
+    {"bucket256x52", 13000, run_bucket<256, 52, 2048, 256>},
+};
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string which = argc > 1 ? argv[1] : "sort256x7";
     if (const char* e = std::getenv("EMU_SKIP_BARRIER")) emu::g_skip_barrier = std::atoi(e);
     g_state = argc > 2 ? static_cast<uint64_t>(std::atoll(argv[2])) * 2 + 1 : 1;
-    int n = 0;
-    if (which == "sort64x3") n = 150;
-    else if (which == "sort256x7") n = 1600;
-    else if (which == "sort512x7") n = 3500;
-    else if (which == "sort1024x7") n = 7000;
-    else if (which == "sort1024x13") n = 12544;
-    else if (which == "bucket256x9") n = 2304;
-    else if (which == "bucket512x9") n = 4000;
-    else if (which == "bucket512x26") n = 12544;
-    else if (which == "bucket256x36") n = 9001;
-    else { std::fprintf(stderr, "unknown case %s\n", which.c_str()); return 2; }
-    // rows: a Gaussian one, a skewed two-cluster one, one with few distinct values, a ragged shorter one is a second run
-    const int F = 4;
-    std::vector<float> W(static_cast<size_t>(F) * n);
-    for (int j = 0; j < n; ++j) {
-        W[static_cast<size_t>(j)] = static_cast<float>(0.05 * gaussian() + 0.01);
-        W[static_cast<size_t>(n + j)] = static_cast<float>(uniform() < 0.2 ? 0.5 + 0.1 * gaussian() : -0.1 + 0.05 * gaussian());
-        W[static_cast<size_t>(2 * n + j)] = static_cast<float>(static_cast<int>(uniform() * 7) - 3) * 0.25f;
-        W[static_cast<size_t>(3 * n + j)] = static_cast<float>(std::fabs(gaussian()));
-    }
+    const Case* c = nullptr;
+    for (const Case& k : kCases)
+        if (which == k.name) c = &k;
+    const std::string kind = argc > 3 ? argv[3] : "mixed";
+    const int n = argc > 4 ? std::atoi(argv[4]) : (c ? c->n : 0);
+    std::vector<float> W;
+    const int F = c ? fill(kind, n, W) : 0;
+    if (F == 0) { std::fprintf(stderr, "unknown case %s or rows %s\n", which.c_str(), kind.c_str()); return 2; }
     Out o(F);
-    if (which == "sort64x3") run_sort<64, 3>(W, F, n, o);
-    else if (which == "sort256x7") run_sort<256, 7>(W, F, n, o);
-    else if (which == "sort512x7") run_sort<512, 7>(W, F, n, o);
-    else if (which == "sort1024x7") run_sort<1024, 7>(W, F, n, o);
-    else if (which == "sort1024x13") run_sort<1024, 13>(W, F, n, o);
-    else if (which == "bucket256x9") run_bucket<256, 9, 512, 256>(W, F, n, o);
-    else if (which == "bucket512x9") run_bucket<512, 9, 2048, 256>(W, F, n, o);
-    else if (which == "bucket512x26") run_bucket<512, 26, 2048, 512>(W, F, n, o);
-    else run_bucket<256, 36, 2048, 256>(W, F, n, o);
+    c->run(W, F, n, o);
 #ifdef EMU_POISON_LDS
     std::printf("LDS section marked uninitialised before every workgroup: %zu bytes\n", static_cast<size_t>(__stop_emu_lds - __start_emu_lds));
 #endif

@@ -38,10 +38,15 @@ def builds(tmp_path_factory):
     return out
 
 
-def run(exe, case, seed=1, env=None):
+@pytest.fixture(scope="module")
+def plain(tmp_path_factory):
+    return build(str(tmp_path_factory.mktemp("emu_plain")), "emu", "g++", ["-O2"])
+
+
+def run(exe, case, seed=1, env=None, rows="mixed"):
     e = dict(os.environ, TSAN_OPTIONS="halt_on_error=0 exitcode=66")
     e.update(env or {})
-    return subprocess.run([exe, case, str(seed)], capture_output=True, text=True, env=e, timeout=900)
+    return subprocess.run([exe, case, str(seed), rows], capture_output=True, text=True, env=e, timeout=900)
 
 
 @pytest.mark.parametrize("case", CASES)
@@ -66,6 +71,14 @@ def test_no_read_of_unwritten_memory(builds, case):
     p = run(builds["msan"], case)
     assert "MemorySanitizer" not in p.stderr and p.returncode == 0, p.stdout[-2000:] + p.stderr[-3000:]
     assert "LDS section marked uninitialised" in p.stdout
+
+
+@pytest.mark.parametrize("case", ["bucket256x3", "bucket256x7", "bucket256x9", "bucket512x9", "bucket256x18", "bucket256x36",
+                                  "bucket512x26", "bucket256x52"])
+def test_smallest_weight_below_the_others_last_bit(plain, case):
+    """A row's only weights that are rounded when it is scaled to integers; at the row's minimum the rounding decides its bucket."""
+    p = run(plain, case, rows="tiny_minimum")
+    assert p.returncode == 0 and p.stdout.count("identical") == 18, p.stdout
 
 
 def test_the_checker_sees_a_missing_barrier(builds):

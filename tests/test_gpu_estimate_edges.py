@@ -1,7 +1,8 @@
 """Rows on which the value-bucket search has to take its rarer branches, and sizes at the edges of its kernels: two maxima of D of
 nearly the same height (candidate buckets far apart, taken one at a time), buckets of more elements than a cell counts, more
 equal values at the split than the list holds, a range far below the largest magnitude, an outlier that leaves one bucket for
-all the rest, ties that the index decides.  Every row against the oracle, through the separate and the grouped calls."""
+all the rest, ties that the index decides, a smallest weight that is rounded away beside the largest.  Every row
+against the oracle, through the separate and the grouped calls."""
 import numpy as np
 import pytest
 import torch
@@ -32,12 +33,16 @@ def rows(rng, F, n, kind):
         w[:, n // 3] = 300.0
     elif kind == "grid":                                          # values on a coarse grid: ties everywhere, zeros of both signs
         w = np.round(g * 8) / 8 * np.where(rng.random((F, n)) < 0.5, 1.0, -1.0)
+    elif kind == "tiny_minimum":                                  # one weight below 2^-24 of the others, the row's minimum
+        w = np.abs(g).astype(np.float32) * np.float32(0.1) + np.float32(0.01)
+        k = np.resize([0.6, -0.3, 281.4, 281.6, 282.6, 1e-30], F)
+        w[:, n // 3] = np.ldexp(k, np.frexp(w.max(axis=1))[1] - 48)
     else:
         w = g
     return np.ascontiguousarray(w, dtype=np.float32)
 
 
-KINDS = ["two_maxima", "pruned", "spike", "far_mean", "outlier", "grid", "gauss"]
+KINDS = ["two_maxima", "pruned", "spike", "far_mean", "outlier", "grid", "gauss", "tiny_minimum"]
 # chunk edges (four elements of 256 or 512 threads), class limits, rows of a few weights
 SIZES = [5, 63, 191, 193, 255, 1023, 1025, 2303, 3071, 3584, 4095, 4608, 4609, 6145, 9215, 9216, 9217, 12544, 13312]
 
@@ -58,6 +63,8 @@ def check_multi(W, shape):
 def test_rows_of_every_size_and_kind(kind):
     rng = np.random.default_rng(KINDS.index(kind) + 50)
     for n in SIZES:
+        if kind == "tiny_minimum" and n < 63:                     # (a group of the rounded weight alone)
+            continue
         W = rows(rng, 6, n, kind)
         got, _ = gu.gpu_estimate(W)
         gu.check_estimate(W, got)
