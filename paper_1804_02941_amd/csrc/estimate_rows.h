@@ -377,6 +377,7 @@ __global__ __launch_bounds__(THREADS) void estimate_kernel(const float* __restri
 // weights 47 us (83 with a count and a sum atomic per element, fp64 bounds and a branch per listed element), of 4096
 // 31.6 (46.5), 512 rows of 12544 14.5 (20.3), 1408 of 1800 10.8 (14.0), 256 of 2304 6.7 (9.5).
 constexpr int kBucketChunk = 4;         // elements of a thread handled without a branch between them
+constexpr int kExactN = 256;            // rows up to here: sums without any rounding
 constexpr int kBucketTurns = 12;        // scattered candidate buckets taken one at a time before the row is left to the sort
 
 // f(first element of the chunk, one past its last) over the chunks of ITEMS elements, both as compile-time constants (the
@@ -556,8 +557,13 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     const int to_addr = sh - 35;
 
     // ---- histogram: count and exact sum of offsets per bucket
+    // Rows of up to kExactN weights keep all their digits, as the sort does: a group of such a row may be a weight or two,
+    // its mean as small as the weight.  One that is rounded is not counted, and the row is left to the sort.
+    constexpr bool kExact = THREADS * ITEMS <= 3 * kExactN;
+    const float rounded = kExact && n <= kExactN ? ldexpf(1.0f, ex - 25) : 0.0f;
     {
         auto add = [&](float v) {
+            if (kExact && (v != 0.0f) & (fabsf(v) < rounded)) return;
             const double q = q_of(v);
             const uint32_t hi = static_cast<uint32_t>(__double2hiint(q)), lo = static_cast<uint32_t>(__double2loint(q));
             unsigned long long* cell = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(hist) +

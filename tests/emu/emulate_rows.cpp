@@ -140,7 +140,7 @@ int fill(const std::string& kind, int n, std::vector<float>& W) {
     if (kind == "tiny_minimum") {
         // One-sided rows whose smallest weight is k times 2^(e - 48), 2^e the power of two above the largest magnitude: the
         // only weights that are rounded when the row is scaled to integers.  Both parities, every quarter of the fraction.
-        const double ks[] = {0.3, 0.6, 1.4, 1.5, 281.4, 281.5, 281.6, 282.6, 1e-30};
+        const double ks[] = {0.3, 0.6, 1.4, 1.5, 281.4, 281.5, 281.6, 282.6, 1e-26};
         int F = 0;
         for (double k : ks)
             for (int sign = -1; sign <= 1; sign += 2, ++F) {

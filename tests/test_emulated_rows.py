@@ -43,10 +43,10 @@ def plain(tmp_path_factory):
     return build(str(tmp_path_factory.mktemp("emu_plain")), "emu", "g++", ["-O2"])
 
 
-def run(exe, case, seed=1, env=None, rows="mixed"):
+def run(exe, case, seed=1, env=None, rows="mixed", n=0):
     e = dict(os.environ, TSAN_OPTIONS="halt_on_error=0 exitcode=66")
     e.update(env or {})
-    return subprocess.run([exe, case, str(seed), rows], capture_output=True, text=True, env=e, timeout=900)
+    return subprocess.run([exe, case, str(seed), rows] + ([str(n)] if n else []), capture_output=True, text=True, env=e, timeout=900)
 
 
 @pytest.mark.parametrize("case", CASES)
@@ -79,6 +79,14 @@ def test_smallest_weight_below_the_others_last_bit(plain, case):
     """A row's only weights that are rounded when it is scaled to integers; at the row's minimum the rounding decides its bucket."""
     p = run(plain, case, rows="tiny_minimum")
     assert p.returncode == 0 and p.stdout.count("identical") == 18, p.stdout
+
+
+@pytest.mark.parametrize("n,left", [(5, 18), (256, 18), (257, 0)])
+def test_short_rows_are_not_rounded(plain, n, left):
+    """Up to 256 weights a row that the scaling would round is sorted instead."""
+    p = run(plain, "bucket256x3", rows="tiny_minimum", n=n)
+    assert p.returncode == 0 and p.stdout.count("left to the sort") == left, p.stdout
+    assert run(plain, "bucket256x3", n=n).stdout.count("identical") >= 3
 
 
 def test_the_checker_sees_a_missing_barrier(builds):
