@@ -61,10 +61,11 @@ __device__ __forceinline__ v8bf expand_mask(uint32_t bits) {
     return __builtin_bit_cast(v8bf, w);
 }
 
-// Four consecutive channels of one pixel (off: their byte offset without the group's, or kOutside).  Offsets are
-// multiples of four, and a buffer load is checked per dword, so any channel count will do.
-__device__ __forceinline__ float4 load_channels(__amdgpu_buffer_rsrc_t x, uint32_t off, uint32_t group) {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(x, off, group, 0);
+// Four consecutive channels of one pixel (off: their byte offset, or kOutside or a little more).  Offsets are multiples
+// of four, and a buffer load is checked per dword, so any channel count will do: the last pixel's channels past C lie past
+// the end and read as zeros.  The whole offset is the vector one: the scalar offset is no part of what is checked.
+__device__ __forceinline__ float4 load_channels(__amdgpu_buffer_rsrc_t x, uint32_t off) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(x, off, 0, 0);
     return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
 }
 // Zeros in place of the n channels of v from c that lie past C (they are the next pixel's).
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(256, 2) void wbin_patch_kernel(const WbinGeom g, co
     float4 stage[SLOTS];
     auto load_group = [&](int grp) {
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) stage[s] = load_channels(xr, off[s], 64 * grp);
+        for (int s = 0; s < SLOTS; ++s) stage[s] = load_channels(xr, off[s] + 64 * grp);
     };
     // The mask words of 32 channels go straight into LDS, 1 KB (kMaskTaps taps) per wavefront instruction; filters past
     // the padded count and taps past the last repeat a valid word (nothing of them is used).
@@ -343,9 +344,9 @@ __global__ __launch_bounds__(512, ROWS * NB < 64 ? 4 : 2) void wbin_direct_kerne
     for (int j = 0; j < NB; ++j) fcol[j] = 4 * min(f0 + j * ROWS + col, g.Fp - 1);
     auto fetch = [&](int slot) {
         // steps past the share read zeros (and some valid mask word)
-        const uint32_t o = next < k1 ? off : kOutside;
-        xq[slot][0] = load_channels(xr, o, 4 * kChan * cg);
-        xq[slot][1] = load_channels(xr, o + 16, 4 * kChan * cg);
+        const uint32_t o = (next < k1 ? off : kOutside) + 4 * kChan * cg;
+        xq[slot][0] = load_channels(xr, o);
+        xq[slot][1] = load_channels(xr, o + 16);
         const int row = (tap * g.Cw + cg * kChan / 32) * g.Fp * 4;
 #pragma unroll
         for (int j = 0; j < NB; ++j) bq[slot][j] = __builtin_amdgcn_raw_buffer_load_b32(er, fcol[j], row, 0);

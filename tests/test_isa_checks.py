@@ -105,3 +105,12 @@ def test_the_store_addresses_of_the_persistent_kernel_are_not_worked_out_again_f
     for b in bodies:
         stores = b[b.index("buffer_store_dword "):b.rindex("buffer_store_dword ")]
         assert not re.findall(r"v_cndmask_b32\S* v\d+, v", stores)
+
+
+def test_the_input_of_the_weights_only_layer_is_read_with_checked_offsets(tmp_path):
+    """The last channels of the last pixel may lie past the end of the input: a buffer load reads zeros there only where the vector
+    offset says so, the scalar one (third operand) is no part of the check."""
+    out = str(tmp_path / "wbin.s")
+    ic.compile_to_isa("wbin.hip", out)
+    loads = re.findall(r"buffer_load_dwordx4 \S+ (\S+), s\[\d+:\d+\], (\w+) offen", open(out).read())
+    assert len(loads) > 50 and all(scalar == "0" for _, scalar in loads)
