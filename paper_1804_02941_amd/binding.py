@@ -128,7 +128,7 @@ def native():
             from . import _dab_call
         except ImportError as e:
             raise RuntimeError(f"_dab_call.so is missing or unusable ({e}): run `python -m paper_1804_02941_amd.build` first") from e
-        _dab_call.setup(_pointer, _check, dab_conv_desc, ctypes.ArgumentError)
+        _dab_call.setup(_pointer, _check, _number, dab_conv_desc, ctypes.ArgumentError)
         _native = _dab_call
     return _native
 
@@ -156,6 +156,25 @@ _KINDS = {"f": torch.float32, "i": torch.int32, "b": torch.uint8}
 def _pointer(t, kind, name):
     """What native code does not take at a glance: the address of tensor t (kind "v", or no name: unchecked)."""
     return t.data_ptr() if name is None or kind == "v" else _ptr(t, _KINDS[kind], name)
+
+
+_NUMBERS = {"i": c_int32, "z": c_size_t, "f": ctypes.c_float}
+
+
+def _number(value, kind):
+    """What native code takes for no number at a glance, as ctypes converts it for a C argument."""
+    ctype = _NUMBERS[kind]
+    try:
+        ctype.from_param(value)                                     # (its result does not show the number)
+    except (TypeError, AttributeError) as e:
+        raise ctypes.ArgumentError(str(e)) from None
+    while True:
+        if isinstance(value, ctype):
+            return value.value
+        try:
+            return ctype(value).value
+        except TypeError:
+            value = value._as_parameter_
 
 
 def _stream():

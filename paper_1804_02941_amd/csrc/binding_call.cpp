@@ -7,9 +7,10 @@
 //   float* / int32_t* / uint8_t*    an fp32 / int32 / uint8 tensor on the GPU, contiguous, or None
 //   void*                           any tensor or None (a workspace); the last one is the stream
 //   const dab_conv_desc*            the binding's structure of that name
-//   int32_t, size_t, float          numbers, converted as ctypes does
-// What is not plainly right (another type, a subclass of Tensor, an active torch-function mode) is left
-// to the binding's own Python check, which either returns the address or raises.
+//   int32_t, size_t, float          numbers
+// What is not plainly right is left to the binding's own Python: a tensor of another type, a subclass of
+// Tensor or an active torch-function mode to its check, which either returns the address or raises, and
+// what is no Python int or float (a scalar of numpy, a tensor of one element) to ctypes' conversion.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -28,6 +29,7 @@ namespace {
 
 PyObject* g_pointer;         // (object, kind, name) -> address or None, or raises
 PyObject* g_failed;          // (name, status): raises
+PyObject* g_number;          // (object, kind) -> int or float as ctypes converts it, or raises
 PyObject* g_desc_type;       // the binding's dab_conv_desc
 PyObject* g_argument_error;  // ctypes.ArgumentError
 
@@ -72,6 +74,14 @@ bool wrong_type() {
     return false;
 }
 
+// A Python int or float.
+template <typename T>
+bool number(PyObject* o, T* out) {
+    if constexpr (std::is_floating_point_v<T>) *out = static_cast<T>(PyFloat_AsDouble(o));
+    else *out = static_cast<T>(PyLong_AsUnsignedLongLongMask(o));
+    return !PyErr_Occurred();
+}
+
 template <typename T>
 bool convert(PyObject* o, const char* name, T* out) {
     if constexpr (std::is_same_v<T, const dab_conv_desc*>) {
@@ -86,14 +96,16 @@ bool convert(PyObject* o, const char* name, T* out) {
         if (!pointer(o, kind_of<std::remove_pointer_t<T>>(), name, &p)) return false;
         *out = static_cast<T>(p);
         return true;
-    } else if constexpr (std::is_floating_point_v<T>) {
-        if (!PyFloat_Check(o) && !PyLong_Check(o)) return wrong_type();
-        *out = static_cast<T>(PyFloat_AsDouble(o));
-        return !PyErr_Occurred();
     } else {
-        if (!PyLong_Check(o)) return wrong_type();
-        *out = static_cast<T>(PyLong_AsUnsignedLongLongMask(o));
-        return !PyErr_Occurred();
+        constexpr bool kFloat = std::is_floating_point_v<T>;
+        if (!PyLong_Check(o) && !(kFloat && PyFloat_Check(o))) {
+            PyObject* r = PyObject_CallFunction(g_number, "OC", o, kFloat ? 'f' : sizeof(T) == 8 ? 'z' : 'i');
+            if (r == nullptr) return false;
+            const bool ok = number(r, out);
+            Py_DECREF(r);
+            return ok;
+        }
+        return number(o, out);
     }
 }
 
@@ -149,10 +161,10 @@ struct Entry<Fn> {
 };
 
 PyObject* setup(PyObject*, PyObject* args) {
-    PyObject *pointer_fn, *failed_fn, *desc, *error;
-    if (!PyArg_ParseTuple(args, "OOOO", &pointer_fn, &failed_fn, &desc, &error)) return nullptr;
-    Py_INCREF(pointer_fn), Py_INCREF(failed_fn), Py_INCREF(desc), Py_INCREF(error);
-    g_pointer = pointer_fn, g_failed = failed_fn, g_desc_type = desc, g_argument_error = error;
+    PyObject *pointer_fn, *failed_fn, *number_fn, *desc, *error;
+    if (!PyArg_ParseTuple(args, "OOOOO", &pointer_fn, &failed_fn, &number_fn, &desc, &error)) return nullptr;
+    Py_INCREF(pointer_fn), Py_INCREF(failed_fn), Py_INCREF(number_fn), Py_INCREF(desc), Py_INCREF(error);
+    g_pointer = pointer_fn, g_failed = failed_fn, g_number = number_fn, g_desc_type = desc, g_argument_error = error;
     Py_RETURN_NONE;
 }
 

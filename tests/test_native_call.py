@@ -1,7 +1,9 @@
 """The binding's native calls: they refuse what the Python checks refuse, and convert numbers as ctypes does."""
 import ctypes
 import os
+from fractions import Fraction
 
+import numpy as np
 import pytest
 import torch
 
@@ -33,6 +35,33 @@ def test_sizes_and_numbers(call):
             call.dab_binfc_workspace_bytes(*bad)
     with pytest.raises(ctypes.ArgumentError):
         call.dab_binconv2d_workspace_bytes(bytes(44))
+
+
+class Sized:
+    _as_parameter_ = 9216
+
+
+@pytest.mark.parametrize("n", [np.int64(9216), np.int32(9216), np.uint8(64), torch.tensor(9216), torch.tensor([9216]), np.array(9216),
+                               ctypes.c_int32(9216), Sized(), np.float32(9216.0), torch.tensor(9216.0), np.array([9216, 1]), 9216j,
+                               Fraction(9216)])
+def test_numbers_of_other_types_are_taken_and_refused_as_ctypes_does(call, n):
+    def result(f, *a):
+        try:
+            return f(*a)
+        except ctypes.ArgumentError:
+            return "refused"
+    for args in ((8192, n, 512), (n, 9216, 512)):
+        assert result(call.dab_binfc_workspace_bytes, *args) == result(binding.lib().dab_binfc_workspace_bytes, *args)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lo", [np.float32(-0.5), np.float64(-0.5), Fraction(-1, 2), torch.tensor(-0.5), ctypes.c_float(-0.5)])
+def test_limits_of_other_types(lo):
+    W = torch.randn(4, 3, 3, 3, device="cuda:0")
+    ref = binding.dab_mean_center_clamp(W, lo=-0.5, hi=1.0)
+    assert torch.equal(binding.dab_mean_center_clamp(W, lo=lo, hi=np.int32(1)), ref)
+    with pytest.raises(ctypes.ArgumentError):
+        binding.dab_mean_center_clamp(W, lo="-0.5")
 
 
 @pytest.mark.parametrize("X", [torch.zeros(2, 64), torch.nn.Parameter(torch.zeros(2, 64)), [[0.0] * 64] * 2])
