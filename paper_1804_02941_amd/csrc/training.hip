@@ -163,9 +163,9 @@ __global__ __launch_bounds__(THREADS) void gradient_row_kernel(const float* W, i
     for (int j = 0; j < N; ++j) {
         const int i = x.index(j);
         const bool in = (i < n) & in_alpha_group(x.v[j], i, tv, ti, upper);
-        const float a = fabsf(x.v[j]), aa = in ? a : 0.0f;             // (zero past the end)
-        s[0] += static_cast<double>(aa);
-        s[1] += static_cast<double>(a - aa);
+        const float a = fabsf(x.v[j]);                                 // (zero past the end)
+        s[0] += static_cast<double>(in ? a : 0.0f);
+        s[1] += static_cast<double>(in ? 0.0f : a);                    // (no difference: an infinite weight stays with its group)
         member |= in ? 1u << j : 0u;
     }
     count = static_cast<uint32_t>(__popc(member));

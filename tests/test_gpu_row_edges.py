@@ -88,3 +88,20 @@ def test_packed_masks_at_class_edges(F):
         dab.dab_pack_weights(gu.to_gpu(W.reshape(F, C, kh, kw)), gu.to_gpu(tv), gu.to_gpu(ti), gu.to_gpu(upper), out=(E, ecnt))
         E_ref, ecnt_ref = opk.pack_weights(e)
         assert np.array_equal(gu.u32(E), E_ref) and np.array_equal(gu.u32(ecnt), ecnt_ref), (C, kh, kw)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_the_gradient_of_a_group_does_not_see_the_other_groups_infinity(bad):
+    rng = np.random.default_rng(5)
+    for n in (300, 1024, 4097, 16384, 20000):
+        W = (0.7 * rng.standard_normal((2, n))).astype(np.float32)
+        W[:, n // 2] = bad
+        upper = np.array([1, 0], np.uint8)                        # the alpha group, then the other one, holds +inf and NaN
+        lower = W < 0.25
+        d = [gu.to_gpu(np.full(2, 0.25, np.float32)), gu.to_gpu(np.full(2, -1, np.int32)), gu.to_gpu(upper)]
+        got = dab.dab_weight_gradient(gu.to_gpu(W), *d).cpu().numpy()
+        for f in range(2):
+            rest = lower[f] if bad != -np.inf else ~lower[f]      # the group without it
+            w = W[f][rest].astype(np.float64)
+            ref = 1 / rest.sum() + np.abs(w).sum() / rest.sum() * np.where(np.abs(w) <= 1, w, 0)
+            assert np.allclose(got[f][rest], ref, rtol=RTOL, atol=0), (n, f)
