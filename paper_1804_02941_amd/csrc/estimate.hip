@@ -68,7 +68,7 @@ __global__ __launch_bounds__(THREADS) void estimate_short_kernel(const float* __
     const int f = static_cast<int>(blockIdx.x);
     float x[ITEMS];
     load_row<THREADS, ITEMS>(Wt + static_cast<size_t>(f) * n, n, x);
-    if (bucket_row<THREADS, ITEMS, NB, CAP>(x, n, f, alpha, beta, Kout, thr_val, thr_idx, alpha_is_upper, K_prev, upper_prev,
+    if (bucket_row<THREADS, ITEMS, NB, CAP, 1>(x, n, f, alpha, beta, Kout, thr_val, thr_idx, alpha_is_upper, K_prev, upper_prev,
                                             max_change))
         return;
     __syncthreads();
@@ -120,7 +120,7 @@ __device__ __forceinline__ void binarize_row_of_block(const EstJobs& jobs, unsig
     bool done = true;
     if (f < q.F) {
         load_row<THREADS, ITEMS>(q.W + static_cast<size_t>(f) * q.n, q.n, x);
-        done = bucket_row<THREADS, ITEMS, NB, CAP>(*reinterpret_cast<Lds*>(pool), x, q.n, f, q.alpha, q.beta, q.K, q.thr_val,
+        done = bucket_row<THREADS, ITEMS, NB, CAP, SORT_HERE ? 1 : kMaxLists>(*reinterpret_cast<Lds*>(pool), x, q.n, f, q.alpha, q.beta, q.K, q.thr_val,
                                                    q.thr_idx, q.aiu, q.K_prev, q.upper_prev, q.max_change, &info);
         if constexpr (SORT_HERE) {
             if (!done) {

@@ -378,6 +378,10 @@ __global__ __launch_bounds__(THREADS) void estimate_kernel(const float* __restri
 // 31.6 (46.5), 512 rows of 12544 14.5 (20.3), 1408 of 1800 10.8 (14.0), 256 of 2304 6.7 (9.5).
 constexpr int kBucketChunk = 4;         // elements of a thread handled without a branch between them
 constexpr int kExactN = 256;            // rows up to here: sums without any rounding
+constexpr int kNarrow = 128;            // candidates, and what lies between them, up to here are compared each with each
+constexpr uint32_t kParts = 64;         // buckets with a part of a list
+constexpr int kMaxLists = 4;            // of candidates; a row with more is left to the sort
+constexpr int kPartedRow = 2304;        // rows of the classes up to here: a part of the list for every bucket where there are many
 constexpr int kBucketTurns = 12;        // scattered candidate buckets taken one at a time before the row is left to the sort
 
 // f(first element of the chunk, one past its last) over the chunks of ITEMS elements, both as compile-time constants (the
@@ -462,7 +466,7 @@ __device__ __forceinline__ void load_row(const float* __restrict__ row, int n, f
 // every phase is a short latency chain between barriers.  The result says whether the row is done
 // (the same for every thread of the workgroup); nothing has been written when it is not.
 struct alignas(16) Listed {
-    uint32_t idx, key, q_lo, q_hi;                                 // index in the row, value as a key, q
+    uint32_t idx, key, q_lo, q_hi;                                 // index in the row, above it where its part of the list starts; value as a key; q
 };
 template <int THREADS, int NB, int CAP>
 struct BucketLds {
@@ -473,15 +477,17 @@ struct BucketLds {
     Listed list[CAP + 4];                                          // candidates
     unsigned long long acc_s[CAP];                                 // rank of a candidate and sum up to it
     uint32_t acc_n[CAP];
-    uint32_t cmask[THREADS];                                       // candidates among a thread's buckets, a bit each
+    uint32_t cmask[THREADS];                                       // candidates among a thread's buckets, a bit each: still to be listed, listed now; their first entry
+    uint32_t seg[kParts];                                           // of a listed bucket: start of its part of the list, elements there
     float w_min[NW], w_max[NW], w_g[NW];
     uint32_t w_cnt[NW];
     long long w_sum[NW];
     int w_lo[NW], w_hi[NW];                                        // first and last candidate bucket
     Best wave_best[NW];
-    uint32_t nlist;
+    uint32_t nlist;                                                // places asked for, entries asked for
+    uint32_t ncand, listed;                                        // elements in candidate buckets, in the list
 };
-template <int THREADS, int ITEMS, int NB, int CAP>
+template <int THREADS, int ITEMS, int NB, int CAP, int LISTS = kMaxLists>
 __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, const float (&x)[ITEMS], int n, int f,
                                            float* __restrict__ alpha, float* __restrict__ beta, int32_t* Kout,
                                            float* __restrict__ thr_val, int32_t* __restrict__ thr_idx, uint8_t* alpha_is_upper,
@@ -490,7 +496,7 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     constexpr int NW = THREADS / 64;
     constexpr int BPT = NB / THREADS;                              // buckets per thread
     constexpr int LOG_NB = NB == 512 ? 9 : (NB == 1024 ? 10 : 11);
-    static_assert(NB == 1 << LOG_NB && BPT >= 1 && NB % THREADS == 0 && BPT <= 32, "whole buckets per thread, a bit each");
+    static_assert(NB == 1 << LOG_NB && BPT >= 1 && NB % THREADS == 0 && BPT <= 8, "whole buckets per thread, a bit each");
     static_assert(THREADS * ITEMS <= 65535 && LOG_NB >= 9, "16-bit counts; the offsets of up to 4095 elements sum to less than 2^52");
     static_assert(CAP <= THREADS, "a candidate per thread");
     auto& hist = lds.hist;
@@ -500,6 +506,7 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     auto& acc_n = lds.acc_n;
     auto& acc_s = lds.acc_s;
     auto& cmask = lds.cmask;
+    auto& seg = lds.seg;
     auto& w_min = lds.w_min;
     auto& w_max = lds.w_max;
     auto& w_g = lds.w_g;
@@ -509,6 +516,8 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     auto& w_hi = lds.w_hi;
     auto& wave_best = lds.wave_best;
     auto& nlist_s = lds.nlist;
+    auto& ncand_s = lds.ncand;
+    auto& listed_s = lds.listed;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -517,7 +526,7 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
 #pragma unroll
     for (int k = 0; k < BPT; ++k) hist[tid + k * THREADS] = 0ull;
     if (tid < CAP) { acc_n[tid] = 0u; acc_s[tid] = 0ull; }
-    if (tid == 0) nlist_s = 0u;
+    if (tid == 0) { nlist_s = 0u; ncand_s = 0u; listed_s = 0u; seg[0] = 0u; }
     float mn = x[0], mx = x[0];
     for_chunks<ITEMS>([&](auto c, auto e) {
         if (c * THREADS >= n) return false;                        // (the whole workgroup, here and below)
@@ -555,6 +564,7 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     const int sh = max(35, 64 - __builtin_clz(qmax_hi | 1u) - LOG_NB);
     const uint32_t in_bucket = (1u << (sh - 32)) - 1u;             // upper word: offset inside the bucket
     const int to_addr = sh - 35;
+    auto bucket_of = [&](uint32_t hi) -> int { return static_cast<int>((hi & 0xFFFFFu) >> (sh - 32)); };   // from a q's upper word
 
     // ---- histogram: count and exact sum of offsets per bucket
     // Rows of up to kExactN weights keep all their digits, as the sort does: a group of such a row may be a weight or two,
@@ -623,6 +633,7 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     uint32_t i_run = cinc - crun + (wave ? lane_of(wc, wave - 1) : 0u);
     const unsigned long long s_base = sinc - srun + (wave ? static_cast<unsigned long long>(lane_of(wsum, wave - 1)) : 0ull);
     const long long T_fix = static_cast<long long>(s_all) - static_cast<long long>(n) * off;    // the row's sum
+
     below[tid] = s_base;
 
     // ---- allowed splits: 1 .. n-1, or the window around the previous split
@@ -685,11 +696,24 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     const float need = gbest < 0.0f ? -3.0e38f : gbest - 4e-6f * (gbest + mean_f * mean_f);
 
     // ---- candidates: buckets that can hold a split reaching `need`
+    constexpr bool kParted = THREADS * ITEMS <= kPartedRow;
+    // (an atomic whose address is known to be the same in all lanes becomes a scan over them)
+    auto no_offset = []() -> int {
+        int zero = 0;
+        DAB_OPAQUE_I32(zero);
+        return zero;
+    };
     {
         uint32_t mask = 0;
 #pragma unroll
         for (int k = 0; k < BPT; ++k) mask |= ub[k] >= need ? 1u << k : 0u;
         cmask[tid] = mask;
+        if (mask && kParted) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int k = 0; k < BPT; ++k) c += (mask >> k) & 1u ? bc[k] : 0u;
+            atomicAdd(&ncand_s + no_offset(), c);
+        }
         const unsigned long long any = __ballot(mask != 0u);
         int lo = NB, hi = -1;
         if (any != 0ull) {
@@ -707,140 +731,302 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     const int last = __builtin_amdgcn_readfirstlane(hi);
     if (last < 0) return false;                                    // no bucket in the window: not expected
 
-    // ---- the candidates are neighbours as a rule: everything between the first and the last of them is taken
-    // at once.  Where that is too much (D has two maxima of nearly the same height) one bucket is taken at a time.
-    auto elements_below = [&](int b) -> int {
-        return __builtin_amdgcn_readfirstlane(b < NB ? static_cast<int>(first[b]) : n);
-    };
     Best best{-1.0, 1.0, 0.0, 0};                                  // of this thread's candidates
     uint32_t my_key = 0, my_idx = 0;
     int nblk = 0;                                                  // wavefronts that had candidates
-    hi = last;
-    for (int turns = 1;; ++turns) {
-        const int n_lo = elements_below(lo);
-        if (elements_below(hi + 1) - n_lo > CAP) hi = lo;
-        const int in_reach = elements_below(hi + 1) - n_lo;
-        if (in_reach > CAP || turns > kBucketTurns) return false;
-
-        // the candidates' elements.  q >= A (even) says x 2^(48 - ex) + off >= A - 1/2, so the elements of
-        // buckets lo .. hi are those from the smallest float at or above one value to below another.
-        {
-            auto at_least = [&](int b) -> float {
-                const double t = (ldexp(static_cast<double>(b), sh) - 0.5 - static_cast<double>(off)) * unscale;   // (exact)
-                const float v = static_cast<float>(t);
-                return key_to_float(float_to_key(v) + (static_cast<double>(v) < t ? 1u : 0u));
-            };
-            const float xlo = at_least(lo), xhi = at_least(hi + 1);
-            // A thread notes its elements in a mask, then the wavefront takes places in the list together and every thread
-            // files its few, each selected from the registers by a tree of selects: a branch per element costs more than
-            // that, and ten times the code.
-            uint32_t part[(ITEMS + 31) / 32] = {};
-            for_chunks<ITEMS>([&](auto c, auto e) {
-                if (c * THREADS >= n) return false;
-                uint32_t four = 0;
+    auto elements_below = [&](int b) -> int { return b < NB ? static_cast<int>(first[b]) : n; };
+    auto uniform = [](int v) -> int { return __builtin_amdgcn_readfirstlane(v); };
+    if constexpr (kParted) {
+        // Most rows have few candidates, neighbours: one list, every element compared with every other.  Heavy tails put
+        // hundreds of elements into a few buckets, or buckets that are no candidates between them: then every bucket gets a
+        // part of the list to itself and its elements are compared with each other only, in as many lists as it takes (one
+        // where the workgroup itself sorts what is left, which takes less than a second list).  us, weight sides, all between
+        // the first and the last candidate in one list | now: the 128 x 1600 Laplacian weights of configuration 2 17.7 | 11.5,
+        // other Laplacian ones 128 x 1600 12.9 | 10.5, 256 x 2304 23.1 | 19.0, 1024 x 1152 19.5 | 13.9; Gaussian ones
+        // 256 x 2304 9.05 | 9.3, the others within 1 %.  In the classes of longer rows the registers for it cost a wavefront
+        // per SIMD (4096 Gaussian rows of 9216 57.0 | 61.5): they keep the other form below.
+        const int total = __builtin_amdgcn_readfirstlane(static_cast<int>(ncand_s));
+        const int span = __builtin_amdgcn_readfirstlane(elements_below(last + 1) - elements_below(lo));
+        const bool narrow = span <= kNarrow;
+        if (!narrow && total > LISTS * CAP) return false;
+        // the parts of as many of this thread's candidate buckets as the list still holds
+        auto take_places = [&]() {
+            const uint32_t mask = cmask[tid] & 0xFFu;
+            uint32_t m = 0, entry = 0;
+            if (mask) {
+                auto count = [&](int k) -> uint32_t {
+                    return static_cast<uint32_t>(elements_below(tid * BPT + k + 1) - static_cast<int>(first[tid * BPT + k]));
+                };
+                uint32_t whole = 0;
 #pragma unroll
-                for (int j = c; j < e; ++j) four |= ((x[j] >= xlo) & (x[j] < xhi)) ? 1u << (j - c) : 0u;
-                part[c / 32] |= four << (c % 32);
-                return true;
-            });
-            mask_t<ITEMS> mine = part[0];
-            if constexpr (ITEMS > 32) mine |= static_cast<mask_t<ITEMS>>(part[1]) << 32;
-            const uint32_t have = static_cast<uint32_t>(__builtin_popcountll(mine));
-            const uint32_t upto = wave_inclusive_scan_u32(have), count = lane_of(upto, 63);
-            if (count != 0u) {
-                uint32_t base = 0;
-                if (lane == 0) base = atomicAdd(&nlist_s, count);
-                uint32_t slot = lane_of(base, 0) + upto - have;
+                for (int k = 0; k < BPT; ++k) whole += (mask >> k) & 1u ? count(k) : 0u;
+                m = whole <= CAP ? mask : mask & (~mask + 1u);         // (too many for one list: the lowest bucket's)
+                const uint32_t c = whole <= CAP ? whole : count(__builtin_ctz(mask));
+                const uint32_t taken = atomicAdd(&nlist_s + no_offset(), (static_cast<uint32_t>(__builtin_popcount(m)) << 16) | c);
+                uint32_t at = taken & 0xFFFFu, e = taken >> 16;
+                entry = e;
+                if (at + c <= CAP && e + static_cast<uint32_t>(__builtin_popcount(m)) <= kParts) atomicAdd(&listed_s + no_offset(), c);
+                else m = 0;
+#pragma unroll
+                for (int k = 0; k < BPT; ++k)
+                    if ((m >> k) & 1u) {
+                        seg[e++] = at;
+                        at += count(k);
+                    }
+            }
+            cmask[tid] = (mask & ~m) | (m << 8) | (entry << 16);
+        };
+        // q >= A (even) says x 2^(48 - ex) + off >= A - 1/2, so the elements of buckets lo .. last are those from the smallest
+        // float at or above one value to below another
+        auto at_least = [&](int b) -> float {
+            const double t = (ldexp(static_cast<double>(b), sh) - 0.5 - static_cast<double>(off)) * unscale;   // (exact)
+            const float v = static_cast<float>(t);
+            return __int_as_float(__builtin_amdgcn_readfirstlane(
+                __float_as_int(key_to_float(float_to_key(v) + (static_cast<double>(v) < t ? 1u : 0u)))));
+        };
+        const float xlo = at_least(lo), xhi = at_least(last + 1);
+        int left = narrow ? span : total;
+        for (;;) {
+            int nc = left;
+            if (!narrow) {
+                take_places();
+                lds_barrier();
+                nc = __builtin_amdgcn_readfirstlane(static_cast<int>(listed_s));
+                if (nc == 0) return false;                             // (a bucket alone is too much for the list)
+            }
+            {
+                // A thread notes its elements in a mask, then files its few, each selected from the registers by a tree of
+                // selects: a branch per element costs more than that, and ten times the code.
+                uint32_t part[(ITEMS + 31) / 32] = {};
+                for_chunks<ITEMS>([&](auto c, auto e) {
+                    if (c * THREADS >= n) return false;
+                    uint32_t four = 0;
+#pragma unroll
+                    for (int j = c; j < e; ++j) four |= ((x[j] >= xlo) & (x[j] < xhi)) ? 1u << (j - c) : 0u;
+                    part[c / 32] |= four << (c % 32);
+                    return true;
+                });
+                mask_t<ITEMS> mine = part[0];
+                if constexpr (ITEMS > 32) mine |= static_cast<mask_t<ITEMS>>(part[1]) << 32;
                 while (mine) {
                     const int j = __builtin_ctzll(mine);
                     mine &= mine - 1;
                     const float v = pick<0, ITEMS>(x, j);
                     const double q = q_of(v);
-                    if (slot < static_cast<uint32_t>(CAP))
-                        list[slot] = Listed{static_cast<uint32_t>(tid + j * THREADS), float_to_key(v),
-                                            static_cast<uint32_t>(__double2loint(q)),
-                                            static_cast<uint32_t>(__double2hiint(q)) & 0xFFFFFu};
-                    ++slot;
+                    const uint32_t q_hi = static_cast<uint32_t>(__double2hiint(q)) & 0xFFFFFu;
+                    uint32_t entry = 0;
+                    if (!narrow) {
+                        const int b = bucket_of(q_hi);
+                        const uint32_t m = cmask[b / BPT];
+                        if (!((m >> (8 + b % BPT)) & 1u)) continue;    // (not a candidate, or not in this list)
+                        entry = (m >> 16) + static_cast<uint32_t>(__builtin_popcount((m >> 8) & ((1u << (b % BPT)) - 1u)));
+                    }
+                    const uint32_t old = atomicAdd(&seg[entry] + no_offset(), 1u << 16), start = old & 0xFFFFu;
+                    list[start + (old >> 16)] = Listed{(start << 16) | static_cast<uint32_t>(tid + j * THREADS), float_to_key(v),
+                                                       static_cast<uint32_t>(__double2loint(q)), q_hi};
                 }
             }
-        }
-        lds_barrier();
-        const int nc = __builtin_amdgcn_readfirstlane(static_cast<int>(nlist_s));
-        if (nc != in_reach) return false;                          // (not expected: the counts said otherwise)
+            lds_barrier();
+            if (tid == 0) { nlist_s = 0u; listed_s = 0u; }             // (for the next list)
+            left -= nc;
 
-        // exact rank and prefix sum of every candidate: the listed elements up to it in the order of value, then
-        // index.  The wavefronts share the list out.
-        const int nb = (nc + 63) >> 6;
-        {
-            const int per = (nc + NW - 1) / NW;
-            const int q0 = wave * per, q1 = min(q0 + per, nc);
-            for (int v = 0; v < nb; ++v) {
-                const int e = v * 64 + lane;
-                const Listed& me = list[min(e, nc - 1)];
-                const unsigned long long key = (static_cast<unsigned long long>(me.key) << 32) | me.idx;
-                uint32_t cnt = 0;
-                unsigned long long sum = 0;
-                for (int q = q0; q < q1; q += 4) {
-                    Listed o[4];
+            // exact rank and prefix sum of every candidate in its part of the list: the elements up to it in the order of
+            // value, then index.  The wavefronts share every part out.
+            constexpr int kTrip = 2;                               // entries read together, as many as the classes have registers for
+            const int nb = (nc + 63) >> 6;
+            {
+                for (int v = 0; v < nb; ++v) {
+                    const int e = v * 64 + lane;
+                    const Listed& me = list[min(e, nc - 1)];
+                    const unsigned long long key = (static_cast<unsigned long long>(me.key) << 32) | me.idx;
+                    uint32_t cnt = 0;
+                    unsigned long long sum = 0;
+                    auto compare_with = [&](int q0, int q1) {
+                        for (int q = q0; q < q1; q += kTrip) {
+                            Listed o[kTrip];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) o[u] = list[q + u];
+                            for (int u = 0; u < kTrip; ++u) o[u] = list[q + u];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) DAB_OPAQUE_I32(o[u].q_lo);   // (read with the rest, not behind the comparison)
+                            for (int u = 0; u < kTrip; ++u) DAB_OPAQUE_I32(o[u].q_lo);   // (read with the rest, not behind the comparison)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const bool le = (q + u < q1) & (((static_cast<unsigned long long>(o[u].key) << 32) | o[u].idx) <= key);
-                        cnt += le ? 1u : 0u;
-                        sum += le ? (static_cast<unsigned long long>(o[u].q_hi) << 32) | o[u].q_lo : 0ull;
+                            for (int u = 0; u < kTrip; ++u) {
+                                const bool le = (q + u < q1) & (((static_cast<unsigned long long>(o[u].key) << 32) | o[u].idx) <= key);
+                                cnt += le ? 1u : 0u;
+                                sum += le ? (static_cast<unsigned long long>(o[u].q_hi) << 32) | o[u].q_lo : 0ull;
+                            }
+                        }
+                    };
+                    if (narrow) {                                      // (the same entries in every lane)
+                        const int per = (nc + NW - 1) / NW, q0 = wave * per;
+                        compare_with(q0, min(q0 + per, nc));
+                    } else {
+                        const int b = bucket_of(me.q_hi), start = static_cast<int>(me.idx >> 16);
+                        const int size = elements_below(b + 1) - elements_below(b), per = (size + NW - 1) / NW, q0 = start + wave * per;
+                        compare_with(q0, min(q0 + per, start + size));
+                    }
+                    if (e < nc) {
+                        atomicAdd(&acc_n[e], cnt);
+                        atomicAdd(&acc_s[e], sum);
                     }
                 }
-                if (e < nc) {
-                    atomicAdd(&acc_n[e], cnt);
-                    atomicAdd(&acc_s[e], sum);
+            }
+            lds_barrier();
+            // the split behind it
+            if (tid < nc) {
+                const int b = narrow ? lo : bucket_of(list[tid].q_hi), b0 = b / BPT * BPT;   // the lowest bucket of the part
+                unsigned long long sum = below[b / BPT] + acc_s[tid];
+#pragma unroll
+                for (int k = 0; k < BPT - 1; ++k) {
+                    const unsigned long long cell = hist[b0 + k];
+                    const unsigned long long in = (cell & 0xFFFFFFFFFFFFFull) +
+                                                  (static_cast<unsigned long long>(static_cast<uint32_t>(cell >> 52) * static_cast<uint32_t>(b0 + k)) << sh);
+                    sum += b0 + k < b ? in : 0ull;
+                }
+                const int i = static_cast<int>(first[b]) + static_cast<int>(acc_n[tid]);
+                acc_s[tid] = 0ull;
+                acc_n[tid] = 0u;
+                if (i >= wlo && i <= whi) {
+                    const double T = static_cast<double>(T_fix);
+                    const double Pi = static_cast<double>(static_cast<long long>(sum) - static_cast<long long>(i) * off);
+                    const double rest = T - Pi;
+                    const double fi = static_cast<double>(i), fr = static_cast<double>(n - i);
+                    const Best c{Pi * Pi * fr + rest * rest * fi, fi * fr, Pi, i};
+                    if (better(c, best)) { best = c; my_key = list[tid].key; my_idx = list[tid].idx & 0xFFFFu; }
                 }
             }
+            nblk = max(nblk, nb);
+            if (left == 0) break;
         }
-        lds_barrier();
-        // the split behind it
-        if (tid < nc) {
-            unsigned long long sum = below[lo / BPT] + acc_s[tid];
-#pragma unroll
-            for (int k = 0; k < BPT - 1; ++k) {
-                const int b = lo / BPT * BPT + k;
-                const unsigned long long cell = hist[b];
-                const unsigned long long in = (cell & 0xFFFFFFFFFFFFFull) +
-                                              (static_cast<unsigned long long>(static_cast<uint32_t>(cell >> 52) * static_cast<uint32_t>(b)) << sh);
-                sum += b < lo ? in : 0ull;
-            }
-            const int i = n_lo + static_cast<int>(acc_n[tid]);
-            if (i >= wlo && i <= whi) {
-                const double T = static_cast<double>(T_fix);
-                const double Pi = static_cast<double>(static_cast<long long>(sum) - static_cast<long long>(i) * off);
-                const double rest = T - Pi;
-                const double fi = static_cast<double>(i), fr = static_cast<double>(n - i);
-                const Best c{Pi * Pi * fr + rest * rest * fi, fi * fr, Pi, i};
-                if (better(c, best)) { best = c; my_key = list[tid].key; my_idx = list[tid].idx; }
-            }
-        }
-        nblk = max(nblk, nb);
-        if (hi >= last) break;
-        // the next candidate bucket; the list and its sums start again
-        int next = NB;
-        for (int w = hi / BPT / 64; w < NW && next == NB; ++w) {
-            uint32_t mask = cmask[w * 64 + lane];
-            const int b0 = (w * 64 + lane) * BPT;                  // (a thread's bucket k counts if b0 + k > hi)
-            if (hi >= b0) mask = hi - b0 >= 31 ? 0u : mask & ~((2u << (hi - b0)) - 1u);
-            const unsigned long long any = __ballot(mask != 0u);
-            if (any != 0ull) {
-                const int l0 = __builtin_ctzll(any);
-                next = (w * 64 + l0) * BPT + __builtin_ctz(lane_of(mask, l0));
-            }
-        }
-        lo = next;
+    } else {
+        // ---- the candidates are neighbours as a rule: everything between the first and the last of them is taken
+        // at once.  Where that is too much (D has two maxima of nearly the same height) one bucket is taken at a time.
         hi = last;
-        lds_barrier();
-        if (tid < CAP) { acc_n[tid] = 0u; acc_s[tid] = 0ull; }
-        if (tid == 0) nlist_s = 0u;
-        lds_barrier();
+        for (int turns = 1;; ++turns) {
+            const int n_lo = uniform(elements_below(lo));
+            if (uniform(elements_below(hi + 1)) - n_lo > CAP) hi = lo;
+            const int in_reach = uniform(elements_below(hi + 1)) - n_lo;
+            if (in_reach > CAP || turns > kBucketTurns) return false;
+
+            // the candidates' elements.  q >= A (even) says x 2^(48 - ex) + off >= A - 1/2, so the elements of
+            // buckets lo .. hi are those from the smallest float at or above one value to below another.
+            {
+                auto at_least = [&](int b) -> float {
+                    const double t = (ldexp(static_cast<double>(b), sh) - 0.5 - static_cast<double>(off)) * unscale;   // (exact)
+                    const float v = static_cast<float>(t);
+                    return key_to_float(float_to_key(v) + (static_cast<double>(v) < t ? 1u : 0u));
+                };
+                const float xlo = at_least(lo), xhi = at_least(hi + 1);
+                // A thread notes its elements in a mask, then the wavefront takes places in the list together and every thread
+                // files its few, each selected from the registers by a tree of selects: a branch per element costs more than
+                // that, and ten times the code.
+                uint32_t part[(ITEMS + 31) / 32] = {};
+                for_chunks<ITEMS>([&](auto c, auto e) {
+                    if (c * THREADS >= n) return false;
+                    uint32_t four = 0;
+#pragma unroll
+                    for (int j = c; j < e; ++j) four |= ((x[j] >= xlo) & (x[j] < xhi)) ? 1u << (j - c) : 0u;
+                    part[c / 32] |= four << (c % 32);
+                    return true;
+                });
+                mask_t<ITEMS> mine = part[0];
+                if constexpr (ITEMS > 32) mine |= static_cast<mask_t<ITEMS>>(part[1]) << 32;
+                const uint32_t have = static_cast<uint32_t>(__builtin_popcountll(mine));
+                const uint32_t upto = wave_inclusive_scan_u32(have), count = lane_of(upto, 63);
+                if (count != 0u) {
+                    uint32_t base = 0;
+                    if (lane == 0) base = atomicAdd(&nlist_s, count);
+                    uint32_t slot = lane_of(base, 0) + upto - have;
+                    while (mine) {
+                        const int j = __builtin_ctzll(mine);
+                        mine &= mine - 1;
+                        const float v = pick<0, ITEMS>(x, j);
+                        const double q = q_of(v);
+                        if (slot < static_cast<uint32_t>(CAP))
+                            list[slot] = Listed{static_cast<uint32_t>(tid + j * THREADS), float_to_key(v),
+                                                static_cast<uint32_t>(__double2loint(q)),
+                                                static_cast<uint32_t>(__double2hiint(q)) & 0xFFFFFu};
+                        ++slot;
+                    }
+                }
+            }
+            lds_barrier();
+            const int nc = __builtin_amdgcn_readfirstlane(static_cast<int>(nlist_s));
+            if (nc != in_reach) return false;                          // (not expected: the counts said otherwise)
+
+            // exact rank and prefix sum of every candidate: the listed elements up to it in the order of value, then
+            // index.  The wavefronts share the list out.
+            const int nb = (nc + 63) >> 6;
+            {
+                const int per = (nc + NW - 1) / NW;
+                const int q0 = wave * per, q1 = min(q0 + per, nc);
+                for (int v = 0; v < nb; ++v) {
+                    const int e = v * 64 + lane;
+                    const Listed& me = list[min(e, nc - 1)];
+                    const unsigned long long key = (static_cast<unsigned long long>(me.key) << 32) | me.idx;
+                    uint32_t cnt = 0;
+                    unsigned long long sum = 0;
+                    for (int q = q0; q < q1; q += 4) {
+                        Listed o[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) o[u] = list[q + u];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) DAB_OPAQUE_I32(o[u].q_lo);   // (read with the rest, not behind the comparison)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const bool le = (q + u < q1) & (((static_cast<unsigned long long>(o[u].key) << 32) | o[u].idx) <= key);
+                            cnt += le ? 1u : 0u;
+                            sum += le ? (static_cast<unsigned long long>(o[u].q_hi) << 32) | o[u].q_lo : 0ull;
+                        }
+                    }
+                    if (e < nc) {
+                        atomicAdd(&acc_n[e], cnt);
+                        atomicAdd(&acc_s[e], sum);
+                    }
+                }
+            }
+            lds_barrier();
+            // the split behind it
+            if (tid < nc) {
+                unsigned long long sum = below[lo / BPT] + acc_s[tid];
+#pragma unroll
+                for (int k = 0; k < BPT - 1; ++k) {
+                    const int b = lo / BPT * BPT + k;
+                    const unsigned long long cell = hist[b];
+                    const unsigned long long in = (cell & 0xFFFFFFFFFFFFFull) +
+                                                  (static_cast<unsigned long long>(static_cast<uint32_t>(cell >> 52) * static_cast<uint32_t>(b)) << sh);
+                    sum += b < lo ? in : 0ull;
+                }
+                const int i = n_lo + static_cast<int>(acc_n[tid]);
+                if (i >= wlo && i <= whi) {
+                    const double T = static_cast<double>(T_fix);
+                    const double Pi = static_cast<double>(static_cast<long long>(sum) - static_cast<long long>(i) * off);
+                    const double rest = T - Pi;
+                    const double fi = static_cast<double>(i), fr = static_cast<double>(n - i);
+                    const Best c{Pi * Pi * fr + rest * rest * fi, fi * fr, Pi, i};
+                    if (better(c, best)) { best = c; my_key = list[tid].key; my_idx = list[tid].idx; }
+                }
+            }
+            nblk = max(nblk, nb);
+            if (hi >= last) break;
+            // the next candidate bucket; the list and its sums start again
+            int next = NB;
+            for (int w = hi / BPT / 64; w < NW && next == NB; ++w) {
+                uint32_t mask = cmask[w * 64 + lane];
+                const int b0 = (w * 64 + lane) * BPT;                  // (a thread's bucket k counts if b0 + k > hi)
+                if (hi >= b0) mask = hi - b0 >= 31 ? 0u : mask & ~((2u << (hi - b0)) - 1u);
+                const unsigned long long any = __ballot(mask != 0u);
+                if (any != 0ull) {
+                    const int l0 = __builtin_ctzll(any);
+                    next = (w * 64 + l0) * BPT + __builtin_ctz(lane_of(mask, l0));
+                }
+            }
+            lo = next;
+            hi = last;
+            lds_barrier();
+            if (tid < CAP) { acc_n[tid] = 0u; acc_s[tid] = 0ull; }
+            if (tid == 0) nlist_s = 0u;
+            lds_barrier();
+        }
     }
 
     int won;                                                       // the winning position
@@ -883,13 +1069,13 @@ __device__ __forceinline__ bool bucket_row(BucketLds<THREADS, NB, CAP>& lds, con
     }
     return true;
 }
-template <int THREADS, int ITEMS, int NB, int CAP>
+template <int THREADS, int ITEMS, int NB, int CAP, int LISTS = kMaxLists>
 __device__ __forceinline__ bool bucket_row(const float (&x)[ITEMS], int n, int f, float* __restrict__ alpha,
                                            float* __restrict__ beta, int32_t* Kout, float* __restrict__ thr_val,
                                            int32_t* __restrict__ thr_idx, uint8_t* alpha_is_upper, const int32_t* K_prev,
                                            const uint8_t* upper_prev, int max_change) {
     __shared__ BucketLds<THREADS, NB, CAP> lds;
-    return bucket_row<THREADS, ITEMS, NB, CAP>(lds, x, n, f, alpha, beta, Kout, thr_val, thr_idx, alpha_is_upper, K_prev,
+    return bucket_row<THREADS, ITEMS, NB, CAP, LISTS>(lds, x, n, f, alpha, beta, Kout, thr_val, thr_idx, alpha_is_upper, K_prev,
                                                upper_prev, max_change);
 }
 

@@ -28,7 +28,8 @@ struct Out {
     std::vector<float> alpha, beta, thr_val;
     std::vector<int32_t> K, thr_idx;
     std::vector<uint8_t> upper, done;
-    explicit Out(int F) : alpha(F), beta(F), thr_val(F), K(F), thr_idx(F), upper(F), done(F, 1) {}
+    std::vector<int> barriers;                             // that a row's first thread passed
+    explicit Out(int F) : alpha(F), beta(F), thr_val(F), K(F), thr_idx(F), upper(F), done(F, 1), barriers(F, 0) {}
 };
 
 // One workgroup: `threads` OS threads that all run body(), blockIdx.x = f.
@@ -72,7 +73,10 @@ void run_bucket(const std::vector<float>& W, int F, int n, Out& o) {
             const bool done = dab::bucket_row<THREADS, ITEMS, NB, CAP>(x, n, f, o.alpha.data(), o.beta.data(), o.K.data(),
                                                                        o.thr_val.data(), o.thr_idx.data(), o.upper.data(),
                                                                        nullptr, nullptr, 0);
-            if (threadIdx.x == 0) o.done[static_cast<size_t>(f)] = done ? 1 : 0;
+            if (threadIdx.x == 0) {
+                o.done[static_cast<size_t>(f)] = done ? 1 : 0;
+                o.barriers[static_cast<size_t>(f)] = emu::t_barriers;
+            }
         });
 }
 
@@ -156,6 +160,31 @@ int fill(const std::string& kind, int n, std::vector<float>& W) {
             }
         return F;
     }
+    if (kind == "scattered") {
+        // Rows whose candidates lie far apart: heavy tails (Laplace, then symmetric with splits i and n - i of the same score)
+        // and, with outliers that leave the rest few and full buckets, more of them than the list holds.
+        for (int k = 0; k < 4; ++k) {
+            float* w = row();
+            for (int j = 0; j < n; ++j) {
+                const double u = uniform() - 0.5;
+                w[j] = static_cast<float>(0.004 - 0.03 * std::copysign(std::log(1.0 - 2.0 * std::fabs(u) + 1e-300), u));
+            }
+        }
+        for (int k = 0; k < 2; ++k) {
+            float* w = row();
+            for (int j = 0; j < n; ++j) {
+                double chi = 0.0;
+                for (int d = 0; d < 2; ++d) { const double g = gaussian(); chi += g * g; }
+                w[j] = j < n / 2 ? static_cast<float>(gaussian() / std::sqrt(chi / 2)) : (j < 2 * (n / 2) ? -w[j - n / 2] : 0.0f);
+            }
+        }
+        for (int k = 0; k < 8; ++k) {
+            float* w = row();
+            for (int j = 0; j < n; ++j) w[j] = static_cast<float>(gaussian());
+            w[n / 5] = static_cast<float>(12.0 * std::pow(1.6, k) * (k % 2 ? -1 : 1));
+        }
+        return 14;
+    }
     return 0;
 }
 
@@ -213,8 +242,8 @@ int main(int argc, char** argv) {
         const bool same = gi == r.i && o.thr_idx[static_cast<size_t>(f)] == r.thr_idx && o.thr_val[static_cast<size_t>(f)] == r.thr_val &&
                           (o.upper[static_cast<size_t>(f)] != 0) == r.upper;
         const bool close = got >= r.D * (1.0 - 1e-12) && std::fabs(o.alpha[static_cast<size_t>(f)] - r.alpha) <= 1e-5 * std::fabs(r.alpha) + 1e-12;
-        std::printf("row %d: split %d (reference %d) D %.17g (reference %.17g) %s\n", f, gi, r.i, got, r.D,
-                    same ? "identical" : (close ? "equal score" : "WRONG"));
+        std::printf("row %d: %d barriers split %d (reference %d) D %.17g (reference %.17g) %s\n", f,
+                    o.barriers[static_cast<size_t>(f)], gi, r.i, got, r.D, same ? "identical" : (close ? "equal score" : "WRONG"));
         if (!same && !close) ++bad;
     }
     return bad ? 1 : 0;

@@ -17,7 +17,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 EMU = os.path.join(ROOT, "tests", "emu")
 CSRC = os.path.join(ROOT, "paper_1804_02941_amd", "csrc")
 CLANG = "/opt/rocm/llvm/bin/clang++"
-CASES = ["sort64x3", "sort256x7", "sort512x7", "sort1024x7", "sort1024x13", "bucket256x9", "bucket512x9", "bucket512x26", "bucket256x36"]
+CASES = ["sort64x3", "sort256x7", "sort512x7", "sort1024x7", "sort1024x13", "bucket256x9", "bucket512x9", "bucket512x26", "bucket256x36",
+         "bucket256x52"]
+SEARCHES = ["bucket256x3", "bucket256x7", "bucket256x9", "bucket512x9", "bucket256x18", "bucket256x36", "bucket512x26", "bucket256x52"]
 
 
 def build(tmp, name, compiler, flags):
@@ -73,8 +75,31 @@ def test_no_read_of_unwritten_memory(builds, case):
     assert "LDS section marked uninitialised" in p.stdout
 
 
-@pytest.mark.parametrize("case", ["bucket256x3", "bucket256x7", "bucket256x9", "bucket512x9", "bucket256x18", "bucket256x36",
-                                  "bucket512x26", "bucket256x52"])
+# Barriers of a row: 7; one more where several wavefronts hold the candidates, one more where every bucket has a part of the
+# list to itself; three more for every further list.
+@pytest.mark.parametrize("case", SEARCHES)
+def test_scattered_candidates(plain, case):
+    """Candidates far apart, skipped buckets between them, more of them than the list holds: the definition's split.
+    Laplacian rows of up to 2304 weights take one list."""
+    p = run(plain, case, rows="scattered")
+    assert p.returncode == 0 and p.stdout.count("identical") + p.stdout.count("left to the sort") == 14, p.stdout
+    assert p.stdout.count("identical") >= 13, p.stdout
+    barriers = [int(line.split()[2]) for line in p.stdout.splitlines() if "barriers" in line]
+    if case in ("bucket256x3", "bucket256x7", "bucket256x9"):
+        assert max(barriers[:4]) <= 9, p.stdout
+    if case not in ("bucket256x3", "bucket256x9"):
+        assert max(barriers) >= 11, p.stdout                       # (more than one list)
+
+
+@pytest.mark.parametrize("case", ["bucket256x7", "bucket256x18", "bucket256x52"])
+def test_several_lists_under_sanitizers(builds, case):
+    for name in ("tsan", "asan", "msan"):
+        if name in builds:
+            p = run(builds[name], case, rows="scattered")
+            assert "Sanitizer" not in p.stderr and p.returncode == 0, p.stdout[-2000:] + p.stderr[-3000:]
+
+
+@pytest.mark.parametrize("case", SEARCHES)
 def test_smallest_weight_below_the_others_last_bit(plain, case):
     """A row's only weights that are rounded when it is scaled to integers; at the row's minimum the rounding decides its bucket."""
     p = run(plain, case, rows="tiny_minimum")
