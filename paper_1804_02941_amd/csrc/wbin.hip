@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256, 2) void wbin_patch_kernel(const WbinGeom g, co
     double sum[SLOTS];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) sum[s] = 0.0;
-    v16f acc[NB];                                        // (a second set would leave no register free)
+    v16f acc[NB];                                        // (one set: rounded pieces)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
@@ -472,8 +472,7 @@ static long long patch_pixels(const WbinGeom& g, int n) {
 // channels a tap, the group and 64 pixels of the patch, with one workgroup on a compute unit and with two.  Fitted to
 // 304 random layers of 1e6 to 1.5e10 multiply-accumulates, every form timed on each (rms error 4-5 % patch, 6-11 %
 // direct); on 152 others the form taken is 0.8 % slower than the fastest one in the geometric mean, at most 14 %, and
-// 2.2 times faster than the kernels on expanded operands that these replaced (at least 1.08 times; beyond that range,
-// 3 x 3 layers of 2e10 and more were 4-8 % faster there).  Times (us) at 61504 pixels x 128 filters x 25 taps x 64 channels:
+// 2.2 times faster than the kernels on expanded operands that these replaced (at least 1.08 times).  Times (us) at 61504 pixels x 128 filters x 25 taps x 64 channels:
 // patch 4,4 68.7, 2,4 77.3, 2,2 74.2, direct 32,4,1 81.1, the others 96 and more (expanded: 81.8); 128 x 4096 x 1000, one
 // tap: 155.5 (32,4,1), 44.6 (32,4,4), 21.2 (32,2,8), 13.7 (16,4,8), 12.4 (16,2,8), 19.7 (16,1,8), expanded 25.4;
 // 51 x 152 x 8 x 23 -> 130, 3 x 3, stride 2: 10.4 (32,2,8), 13.0 (32,1,8), 29.5 (patch 2,2), expanded 33.6.
@@ -496,6 +495,27 @@ static const FormCost kForms[] = {
     {{16, 2, 8}, 3.65, 0.393, 0.84, 0.000, 0, 0, 0, 0, 0, 0},
     {{16, 1, 8}, 3.59, 0.343, 0.70, 0.000, 0, 0, 0, 0, 0, 0},
 };
+
+// The same for layers of more than 1e10 multiply-accumulates, where the many rounds of workgroups run into each other and the
+// numbers above come out up to 19 % too high for the patch kernel: fitted to 98 layers of 6e9 to 6e10 (rms error 14-17 % patch,
+// 8-14 % direct).  On the 81 of them above 1e10 the form taken is 0.6 % slower than the fastest one in the geometric mean, at most
+// 13 %; by the numbers above 2.1 %, at most 19 %.  (us, form by those | by these: 57600 pixels x 9 taps x 256 channels -> 256
+// 192 | 165, 50176 pixels 190 | 160, 28800 99.6 | 88.9.)
+static const FormCost kLargeForms[] = {
+    {{0, 4, 4}, 14.10, 0, 0, 0, 0.280, 0.190, 0.0000, 0.384, 0.728, 0.2271},
+    {{0, 2, 4}, 9.52, 0, 0, 0, 0.172, 0.000, 0.0392, 0.228, 0.110, 0.2808},
+    {{0, 2, 2}, 10.37, 0, 0, 0, 0.193, 0.000, 0.0000, 0.242, 0.479, 0.1556},
+    {{32, 4, 1}, 3.76, 0.609, 7.03, 0.000, 0, 0, 0, 0, 0, 0},
+    {{32, 2, 1}, 4.37, 0.457, 4.64, 0.000, 0, 0, 0, 0, 0, 0},
+    {{32, 4, 4}, 5.51, 0.606, 5.25, 0.115, 0, 0, 0, 0, 0, 0},
+    {{32, 2, 4}, 7.22, 0.440, 3.62, 0.045, 0, 0, 0, 0, 0, 0},
+    {{32, 2, 8}, 9.26, 0.456, 2.84, 0.071, 0, 0, 0, 0, 0, 0},
+    {{32, 1, 8}, 6.81, 0.375, 0.93, 0.000, 0, 0, 0, 0, 0, 0},
+    {{16, 4, 8}, 4.96, 0.563, 2.60, 0.000, 0, 0, 0, 0, 0, 0},
+    {{16, 2, 8}, 25.09, 0.348, 1.02, 0.000, 0, 0, 0, 0, 0, 0},
+    {{16, 1, 8}, 24.02, 0.358, 0.80, 0.000, 0, 0, 0, 0, 0, 0},
+};
+constexpr double kLargeMacs = 1e10;
 
 // What the layer may be, and the workspace that its callers bring: the room that the expanded operands once took.  The
 // kernels use none of it, but a call with less is refused as it always was.
@@ -529,7 +549,9 @@ void plan_wbin(const dab_conv_desc& d, WbinPlan* pl) {
     g.stream_out = 4ll * g.M * g.F > (64ll << 20);
 
     pl->us = 1e30;
-    for (const FormCost& k : kForms) {
+    static_assert(sizeof kForms == sizeof kLargeForms, "the same forms");
+    const bool large = 1.0 * g.M * d.F * d.C * g.T > kLargeMacs;
+    for (const FormCost& k : large ? kLargeForms : kForms) {
         const WbinForm& f = k.form;
         int pixels, filters;
         size_t lds;

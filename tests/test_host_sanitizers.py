@@ -74,3 +74,14 @@ def test_the_gpu_tests_of_the_weights_only_layer_reach_the_forms_they_name(fuzz)
     out = subprocess.run([fuzz, "wbin", *args], capture_output=True, text=True, check=True).stdout.split()
     for (form, layer), got in zip(LAYERS, out, strict=True):
         assert tuple(int(v) for v in got.split(",")) == form, layer
+
+
+# Large layers timed in every form (us: the patch kernel's 4,4 | the direct kernel's 32,4,1): 165 | 192, 160 | 190, 88.9 | 99.6.
+LARGE_WBIN = [((256, 256, 15, 15, 256, 3, 1, 1), (0, 4, 4)), ((256, 256, 14, 14, 256, 3, 1, 1), (0, 4, 4)),
+              ((128, 256, 15, 15, 256, 3, 1, 1), (0, 4, 4))]
+
+
+def test_large_weights_only_layers_take_the_form_measured_fastest(fuzz):
+    args = [str(v) for (B, C, H, W, F, k, p, s), _ in LARGE_WBIN for v in (B, C, H, W, F, k, k, p, p, s, s)]
+    out = subprocess.run([fuzz, "wbin", *args], capture_output=True, text=True, check=True).stdout.split()
+    assert [tuple(int(v) for v in got.split(",")) for got in out] == [form for _, form in LARGE_WBIN]
