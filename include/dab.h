@@ -118,7 +118,7 @@ int dab_init(void);
  *   alpha_is_upper [F] uint8 out: 1 if the alpha group is the upper group
  *   ws, ws_bytes   scratch of at least dab_estimate_workspace_bytes(F, n) bytes (one flag per
  *                  filter for rows of 4096 weights and more, nothing for shorter rows).
- *                  Rows of more than 256 weights are estimated without a full sort: value
+ *                  Most rows are estimated without a full sort: value
  *                  buckets with exact integer sums give D at every bucket end and an
  *                  upper bound inside every bucket, and only the few elements of the
  *                  buckets that can hold the arg-max are ranked exactly; rows where that
@@ -277,8 +277,8 @@ int dab_pack_activations_multi(const dab_pack_job* jobs /* host */, int32_t n_jo
  * dab_binarize_weights_multi(wjobs) and dab_pack_activations_multi(pjobs) in the launches of the
  * former.  The weight side (Section 4.3.1, Corollary 1) and the binarization of the inputs (Section 4)
  * do not depend on each other and load different parts of the chip (vector instructions and LDS
- * against memory), so every workgroup of the weight-side launches also packs a share of the
- * activations, and the two overlap inside one launch.  Results are, bit for bit, those of the two
+ * against memory), so some workgroups of the weight-side launches pack the activations beside
+ * the others, which take the filters, and the two overlap inside one launch.  Results are, bit for bit, those of the two
  * separate calls; arguments, workspace and errors are theirs.  In addition: fewer filters in all
  * wjobs together than tensors in pjobs -> DAB_ERR_UNSUPPORTED (call the two separately).
  */
