@@ -6,7 +6,7 @@
 // s1 is a dense contraction, so it runs on the MFMA units: both operands are expanded from
 // their packed bits to 4-bit floats (E2M1: +1 = 0x2, -1 = 0xA, 0 = 0x0 for padding), which
 // every product and, in the fp32 accumulator, every sum below 2^24 represents exactly, and
-// multiplied with v_mfma_scale_f32_32x32x64_f8f6f4 (unit scales).  Measured on MI355X this
+// multiplied with v_mfma_f32_32x32x64_f8f6f4.  Measured on MI355X this
 // instruction sustains 4.2e15 multiply-accumulates/s at 4 bits per operand element, 6.7 times
 // the AND + BCNT ceiling of the vector ALU on the same bits, which is why the popcount form
 // of the product is not the one that ships.

@@ -615,7 +615,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
             const v4i a = expand_a(x, va[set][d / LW] ? k8 : 0u, va[set][d / LW] ? k2 : 0u);
             const uint4 e = expand_e(xe[set][d]);
             const v4i bv = {static_cast<int>(e.x), static_cast<int>(e.y), static_cast<int>(e.z), static_cast<int>(e.w)};
-            acc = mfma_fp4(a, bv, acc);                            // (a k-step past k1 multiplies zeros)
+            acc = mfma_fp4<true>(a, bv, acc);                      // (a k-step past k1 multiplies zeros)
         }
     };
     fetch(0, k0);
