@@ -31,7 +31,8 @@ def compile_to_isa(source: str, out: str, extra=()) -> None:
     """hipcc -S of one translation unit of csrc/ for gfx950 (the flags of build.py that shape the code)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fno-gpu-rdc", "-ffp-contract=off",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC,
            *extra, "-S", "--cuda-device-only", os.path.join(CSRC, source), "-o", out]
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if proc.returncode != 0:
