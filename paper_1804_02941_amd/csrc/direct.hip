@@ -118,6 +118,17 @@ template <int N, typename T>
 __device__ __forceinline__ void wait_words(T& a, T& b) {
     asm volatile("s_waitcnt vmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N));
 }
+// a = 4 a + 2 [a0 >= t0] + [a1 >= t1], and b likewise: a compare and an add with carry per bit.  (In C++ the compiler makes a
+// select, half a shift and half an or of every bit.)  A carry is read three instructions behind its compare; two are required.
+__device__ __forceinline__ void append_bits(uint32_t& a, uint32_t& b, float a0, float b0, float t0, float a1, float b1, float t1) {
+    unsigned long long c0, c1, c2, c3;
+    asm("v_cmp_ge_f32_e64 %2, %6, %8\n\tv_cmp_ge_f32_e64 %3, %7, %8\n\tv_cmp_ge_f32_e64 %4, %9, %11\n\tv_cmp_ge_f32_e64 %5, %10, %11\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\tv_addc_co_u32_e64 %1, vcc, %1, %1, %3\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4\n\tv_addc_co_u32_e64 %1, vcc, %1, %1, %5"
+        : "+v"(a), "+v"(b), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
+        : "v"(a0), "v"(b0), "v"(t0), "v"(a1), "v"(b1), "v"(t1)
+        : "vcc");
+}
 template <int LW>
 __device__ __forceinline__ uint32_t word_of(const typename WordsOf<LW>::type& x, int u) {
     if constexpr (LW == 1) return x;
@@ -158,13 +169,12 @@ __device__ __forceinline__ void locate_windows(const DirectGeom& g, int m_base, 
 // PAD   the layer has zero padding: taps are tested against the image per lane
 // BITS  re-binarized output (packed signs) instead of fp32
 template <int LW, int PF, bool PAD, bool BITS>
-__global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g, const uint32_t* __restrict__ A,
-                                                             const uint32_t* __restrict__ E,
+__global__ __launch_bounds__(512) void binconv_direct_kernel(const uint32_t* __restrict__ E, const uint32_t* __restrict__ A,
                                                              const float* __restrict__ alpha,
-                                                             const float* __restrict__ beta, float* __restrict__ Y,
-                                                             int32_t* __restrict__ dbg_s1,
-                                                             const float* __restrict__ tau_out,
-                                                             uint32_t* __restrict__ out_bits) {
+                                                             const float* __restrict__ beta,
+                                                             const float* __restrict__ tau_out, const FastDiv d_wgs,
+                                                             const DirectGeom g, float* __restrict__ Y,
+                                                             int32_t* __restrict__ dbg_s1, uint32_t* __restrict__ out_bits) {
     constexpr int NFP = 4;                                         // 32-filter column blocks of a tile
     extern __shared__ __align__(16) uint4 panel[];                 // [n_ent][4][64 lanes] 16-byte groups; entries from nk on are zero
     __shared__ __align__(16) float sA_lds[8][64];                  // row sums of each wavefront's 64 pixels
@@ -179,64 +189,90 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = static_cast<int>(blockDim.x >> 6);
     const int p = lane & 31, h = lane >> 5;
-    const int ntile = blockIdx.x / g.wg_per_ntile;
-    const int mt_first = blockIdx.x - ntile * g.wg_per_ntile;
+    const int ntile = fdiv(static_cast<int>(blockIdx.x), d_wgs);
+    const int mt_first = static_cast<int>(blockIdx.x) - ntile * g.wg_per_ntile;
     const int f0 = ntile * kDirNTile;
+
+    // ---- the B panel: bits -> fp4, once per workgroup.  Which filter sits in column n of column
+    // block j is free to choose; it is filter 4n + j.  With fp32 output a lane then holds four
+    // neighbouring filters of an output row in its four blocks and writes them with one 16-byte
+    // store, a half-wavefront a whole 512-byte row segment; with bit output it holds sixteen neighbouring
+    // bits of each of a pixel's words.  Item = (k-step, half): lane n reads the mask words of its four
+    // filters, sixteen contiguous bytes.
+    // Five entries of a wavefront at a time: their loads are in flight together (with eight
+    // wavefronts that is the whole panel in one round trip).  The first five are requested before anything else is
+    // worked out.
+    constexpr int kBatch = 5;
+    const int n_items = g.n_ent;
+    uint32_t bits[kBatch][4];
+    auto request_masks = [&](int ks0) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int ks = ks0 + u * waves;
+            const int tap = fdiv(min(ks, n_items - 1), g.d_WH);
+            const int wd = h * g.WH + (ks - tap * g.WH);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bits[u][j] = 0u;
+            if (ks < g.nk && wd < g.Cw && f0 + 4 * p < g.Fp) {       // (Fp is a multiple of 64: all four or none)
+                const uint4 v = *reinterpret_cast<const uint4*>(E + static_cast<size_t>(tap * g.Cw + wd) * g.Fp + f0 + 4 * p);
+                bits[u][0] = v.x; bits[u][1] = v.y; bits[u][2] = v.z; bits[u][3] = v.w;
+            }
+        }
+    };
+    auto expand_masks = [&](int ks0) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int ks = ks0 + u * waves;
+            if (ks < n_items) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) panel[(ks * 4 + j) * 64 + lane] = expand_e(bits[u][j]);
+            }
+        }
+    };
+    request_masks(wave);
+    // scalars of the tile's 128 columns
+    const int f_col = min(f0 + (tid & (kDirNTile - 1)), g.F - 1);
+    const float al = alpha[f_col], be = beta[f_col], ta = BITS && tau_out ? tau_out[f_col] : 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
 
     // the packed activations as a raw buffer: offsets past its end read as zero
     const uint64_t a_addr = reinterpret_cast<uint64_t>(A);
     const v4s arsrc = {static_cast<int>(static_cast<uint32_t>(a_addr)), static_cast<int>(static_cast<uint32_t>(a_addr >> 32) & 0xFFFFu),
                        static_cast<int>(g.a_bytes), 0x00020000};
+    // Load cursor: the windows whose words are being requested, and a group's two loads into a slot of the queue.
+    // off, tap: where the group lies in the window; last_odd: its upper half's word does not exist (the last
+    // group of a tap with an odd number of words per pixel)
     uint32_t base[2], tbits[2];
     locate_windows<PAD>(g, (mt_first * waves + wave) * 64, p, h * g.WH * 4, base, tbits);
-    // the first tap's words on their way into the caches while the panel is built (their round trip to
-    // memory would otherwise follow it); the values are not used
-    uint32_t warm[2];
+    typename WordsOf<LW>::type xq[PF][2];
+    auto request = [&](int slot, uint32_t off, uint32_t tap, bool last_odd) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-        warm[i] = __builtin_amdgcn_raw_buffer_load_b32(
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(A), 0, static_cast<int>(g.a_bytes), 0x00020000),
-            static_cast<int>(base[i]), 0, 0);
-
-    // ---- the B panel: bits -> fp4, once per workgroup.  Which filter sits in column n of column
-    // block j is free to choose.  With fp32 output it is filter 4n + j: a lane then holds four
-    // neighbouring filters of an output row in its four blocks and writes them with one 16-byte
-    // store, a half-wavefront a whole 512-byte row segment.  With bit output it is filter 32j + n,
-    // so that a block's filters are the bits of a packed word.  Item = (k-step, half): lane n reads the mask
-    // words of its four filters (fp32 output: sixteen contiguous bytes).
+        for (int i = 0; i < 2; ++i) {
+            uint32_t voff = base[i] + off;
+            if (PAD) voff = ((tbits[i] >> (tap & 31u)) & 1u) ? voff : kOob;
+            if (LW == 1) voff = (h == 1 && last_odd) ? kOob : voff;
+            load_words<LW>(xq[slot][i], arsrc, voff);
+        }
+    };
+    // The first tile's first groups are requested before the panel is built, and every later tile's before the epilogue
+    // of the tile in front, so that no tile begins with a round trip to memory.  With the mask words requested before
+    // the windows are worked out and the sums cleared in front of the barrier, what comes before the first multiply went from
+    // 3.9 to 3.2 us: with the epilogue below, the six layers that hand bits on, batch 256, 102.7 -> 97.1 us, with fp32 output
+    // 165.6 -> 163.8, 64 x 56 x 56 x 64 -> 64, 3 x 3, 25.6 -> 25.1.
     {
-        // five entries of a wavefront at a time: their loads are in flight together (with eight
-        // wavefronts that is the whole panel in one round trip)
-        constexpr int kBatch = 5;
-        const int n_items = g.n_ent;
-        for (int ks0 = wave; ks0 < n_items; ks0 += kBatch * waves) {
-            uint32_t bits[kBatch][4];
+        int jg = 0, kx = 0;
+        uint32_t tap = 0, off = 0, row = 0;                        // row: offset of the window row's first tap
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int ks = ks0 + u * waves;
-                const int tap = fdiv(min(ks, n_items - 1), g.d_WH);
-                const int wd = h * g.WH + (ks - tap * g.WH);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) bits[u][j] = 0u;
-                if (ks < g.nk && wd < g.Cw) {
-                    const uint32_t* row = E + static_cast<size_t>(tap * g.Cw + wd) * g.Fp;
-                    if (BITS) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) bits[u][j] = f0 + j * 32 + p < g.Fp ? row[f0 + j * 32 + p] : 0u;
-                    } else if (f0 + 4 * p < g.Fp) {                  // (Fp is a multiple of 64: all four or none)
-                        const uint4 v = *reinterpret_cast<const uint4*>(row + f0 + 4 * p);
-                        bits[u][0] = v.x; bits[u][1] = v.y; bits[u][2] = v.z; bits[u][3] = v.w;
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int ks = ks0 + u * waves;
-                if (ks < n_items) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) panel[(ks * 4 + j) * 64 + lane] = expand_e(bits[u][j]);
-                }
-            }
+        for (int d = 0; d < PF - 1; ++d) {
+            request(d, d < g.NG ? off : kOob, tap, g.odd && jg == g.G - 1);
+            const bool next_tap = ++jg == g.G;
+            jg = next_tap ? 0 : jg;
+            tap += next_tap ? 1 : 0;
+            kx += next_tap ? 1 : 0;
+            const bool next_row = kx == g.kw;
+            kx = next_row ? 0 : kx;
+            row += next_row ? static_cast<uint32_t>(g.W * g.pix_bytes) : 0u;
+            off = row + static_cast<uint32_t>(kx * g.pix_bytes + jg * LW * 4);
         }
     }
 
@@ -250,13 +286,17 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
         }
         gtab[tid] = e;
     }
-    // scalars of the tile's 128 columns, kept in LDS (not in registers through the reduction loop)
+    expand_masks(wave);
+    for (int ks0 = wave + kBatch * waves; ks0 < n_items; ks0 += kBatch * waves) {
+        request_masks(ks0);
+        expand_masks(ks0);
+    }
+    // the columns' scalars are kept in LDS (not in registers through the reduction loop), in filter order; the epilogues
+    // index accordingly
     if (tid < kDirNTile) {
-        const int f = min(f0 + tid, g.F - 1);                      // (in filter order; the epilogues index accordingly)
-        const float al = alpha[f], be = beta[f];
         col_lds[0][tid] = be - al;                                 // the accumulators hold -s1
         col_lds[1][tid] = be;
-        col_lds[2][tid] = f0 + tid >= g.F ? __builtin_nanf("") : (BITS && tau_out) ? tau_out[f] : 0.0f;
+        col_lds[2][tid] = f0 + tid >= g.F ? __builtin_nanf("") : ta;
     }
     // the outputs as raw buffers (stores past their end are dropped)
     auto as_buffer = [](const void* ptr, uint32_t bytes) {
@@ -266,8 +306,18 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     };
     const v4s yrsrc = as_buffer(Y, g.y_bytes);
     const v4s drsrc = as_buffer(dbg_s1, dbg_s1 ? g.y_bytes : 0u);
+    // the first tile's sums start before the barrier, every later tile's behind the epilogue of the tile in front
+    v16f acc[2][NFP];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NFP; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    };
+    clear();
     __syncthreads();                                               // the panel is complete
-    asm volatile("" : : "v"(warm[0]), "v"(warm[1]));
 
     // the two masks of the expansion in registers (as literals they would split the and-or in two)
     uint32_t k8, k2;
@@ -276,42 +326,22 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
     const uint4* bp = panel + lane;
     for (int mt = mt_first; mt < g.n_mtiles; mt += g.wg_per_ntile) {
         const int m_base = (mt * waves + wave) * 64;
-        if (m_base >= g.M) continue;
-        if (mt != mt_first) locate_windows<PAD>(g, m_base, p, h * g.WH * 4, base, tbits);
+        if (m_base >= g.M) break;                                  // (nor has a later tile pixels for this wavefront)
         int ones[2] = {0, 0};
         {
-            v16f acc[2][NFP];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < NFP; ++j)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
             // ---- the reduction.  Load groups run over (tap, word group); group gi covers k-steps
-            // gi*LW .. gi*LW + LW-1.  PF groups are in flight; the slot emptied by the previous
-            // group is refilled during this one.  Groups past the end load nothing (zeros) and
-            // meet zero entries of the panel.  Where a group lies comes from the table in LDS; the
-            // consume cursor is wavefront-uniform and advances by selects, so a round of PF groups
-            // is one basic block.
-            typename WordsOf<LW>::type xq[PF][2];
-            int l_g = 0;
-            uint2 nxt = gtab[0];                                   // the entry of group l_g
+            // gi*LW .. gi*LW + LW-1.  PF groups are in flight (the first PF - 1 of a tile when it begins);
+            // the slot emptied by the previous group is refilled during this one.  Groups between the last one and
+            // the end of the round load nothing (zeros) and meet zero entries of the panel.  Where a group
+            // lies comes from the table in LDS; the consume cursor is wavefront-uniform and advances by
+            // selects, so a round of PF groups is one basic block.
+            int l_g = PF - 1;
+            uint2 nxt = gtab[l_g];                                 // the entry of group l_g
             auto issue = [&](int slot) {
-                const uint2 e = nxt;
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    uint32_t voff = base[i] + e.x;
-                    if (PAD) voff = ((tbits[i] >> (e.y & 31u)) & 1u) ? voff : kOob;
-                    // an odd number of words per pixel: the upper half's last word does not exist
-                    if (LW == 1) voff = (h == 1 && (e.y & 256u)) ? kOob : voff;
-                    load_words<LW>(xq[slot][i], arsrc, voff);
-                }
+                request(slot, nxt.x, nxt.y, (nxt.y & 256u) != 0u);
                 ++l_g;
                 nxt = gtab[l_g];
             };
-#pragma unroll
-            for (int d = 0; d < PF - 1; ++d) issue(d);
             const uint4* bptr = bp;                                // B fragments of the round's first k-step
             // B fragments: one register set; a fragment is reloaded for the next k-step right behind the
             // two multiplies that read it, a whole k-step before its next use
@@ -410,44 +440,60 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
             // lane l holds row l of the 64 (row block l / 32, pixel l % 32); a wavefront reads back only
             // what it wrote itself: no workgroup barrier needed
             if (!BITS) sA_lds[wave][lane] = h ? sAv[1] : sAv[0];
+            const int m_next = ((mt + g.wg_per_ntile) * waves + wave) * 64;
+            if (mt + g.wg_per_ntile < g.n_mtiles && m_next < g.M) {
+                locate_windows<PAD>(g, m_next, p, h * g.WH * 4, base, tbits);
+#pragma unroll
+                for (int d = 0; d < PF - 1; ++d) {
+                    const uint2 e = gtab[d];
+                    request(d, e.x, e.y, (e.y & 256u) != 0u);
+                }
+            }
 
             // ---- epilogue.  Register v of a 32x32 block is row (v/4)*8 + (lane/32)*4 + v%4, column
             // lane%32.  y = (beta - alpha)*(-s1) + beta*sA.
             if constexpr (BITS) {
-                // The blocks are transposed here: register v of block j is filter 32j + (v/4)*8 + (lane/32)*4
-                // + v%4, the lane's pixel is column lane%32, so a lane gathers half of a word's bits by
-                // itself (a compare, a select and an or each) and one exchange with the lane that has the
-                // same pixel's other filters completes the words.  (Pixels in rows, a ballot per
-                // register and two lane writes to drop it into its row took 3.3-4.3 us per tile, more
-                // than a third of the reduction; this form measured 1.6-2.)  Columns past F compare
-                // against NaN.
+                // The blocks are transposed here: register 4q + t of block j is filter 4(8q + 4(lane/32) + t) + j, which
+                // is bit 16(lane/32) + 4t + j of word q, and the lane's pixel is column lane%32.  So a lane gathers
+                // half of each word by itself, a bit a time from the highest down (the compare's carry is added to twice
+                // the bits so far), and an exchange with the lane that has the same pixel's other filters completes
+                // the words.  What bounds this is vector instructions, four a value.  (Pixels in rows, a ballot per register
+                // and two lane writes to drop it into its row took 3.3-4.3 us per tile, more than a third of the
+                // reduction; a select and an or per bit, a word's bits scattered over the lane's nibbles, 2.2-3.1; this
+                // form 1.8-2.5.)  Columns past F compare against NaN.
                 uint32_t half[2][NFP];
 #pragma unroll
-                for (int j = 0; j < NFP; ++j) {
-                    half[0][j] = half[1][j] = 0u;
+                for (int q = 0; q < NFP; ++q) {
+                    half[0][q] = half[1][q] = 0u;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int c0 = j * 32 + q * 8 + h * 4;
+                    for (int t = 3; t >= 0; --t) {
+                        const int c0 = q * 32 + h * 16 + t * 4;
                         const float4 d4 = *reinterpret_cast<const float4*>(&col_lds[0][c0]);
                         const float4 b4 = *reinterpret_cast<const float4*>(&col_lds[1][c0]);
                         const float4 t4 = *reinterpret_cast<const float4*>(&col_lds[2][c0]);
                         const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, bv[4] = {b4.x, b4.y, b4.z, b4.w}, tv[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
+                        for (int j = 3; j >= 0; j -= 2) {
+                            float y[2][2];
 #pragma unroll
-                            for (int i = 0; i < 2; ++i) {
-                                const float y = fmaf(dv[t], acc[i][j][q * 4 + t], bv[t] * sAv[i]);
-                                half[i][j] |= y >= tv[t] ? 1u << (q * 8 + t) : 0u;
-                            }
+                            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                                for (int k = 0; k < 2; ++k) y[i][k] = fmaf(dv[j - k], acc[i][j - k][q * 4 + t], bv[j - k] * sAv[i]);
+                            append_bits(half[0][q], half[1][q], y[0][0], y[1][0], tv[j], y[0][1], y[1][1], tv[j - 1]);
+                        }
                     }
                 }
-                // lane l stores row l of the 64: block i = h of its own pixel
+                // lane l stores row l of the 64: block i = h of its own pixel; two halves of words per exchange
                 uint32_t wb[NFP];
 #pragma unroll
-                for (int j = 0; j < NFP; ++j) {
-                    const uint32_t mine = (h ? half[1][j] : half[0][j]) << (4 * h);
-                    const uint32_t gives = (h ? half[0][j] : half[1][j]) << (4 * h);
-                    wb[j] = mine | static_cast<uint32_t>(__shfl_xor(static_cast<int>(gives), 32, 64));
+                for (int q = 0; q < NFP; q += 2) {
+                    const uint32_t gives = (h ? half[0][q] : half[1][q]) | ((h ? half[0][q + 1] : half[1][q + 1]) << 16);
+                    const uint32_t gets = static_cast<uint32_t>(__shfl_xor(static_cast<int>(gives), 32, 64));
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const uint32_t mine = h ? half[1][q + k] : half[0][q + k], other = k ? gets >> 16 : gets & 0xFFFFu;
+                        wb[q + k] = h ? other | (mine << 16) : mine | (other << 16);
+                    }
                 }
                 const int row = m_base + lane;
                 const int Fw = (g.F + 31) >> 5;
@@ -461,6 +507,7 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
                             if ((f0 >> 5) + j < Fw) store_u32(dst + j, wb[j]);
                     }
                 }
+                clear();
                 continue;
             }
             // fp32 output.  Column n of block j is filter 4n + j, so the four
@@ -519,8 +566,12 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const DirectGeom g,
             };
             if (g.stream_out) store_tile(std::true_type{});
             else store_tile(std::false_type{});
+            clear();
         }
     }
+    // (a wavefront without a tile leaves with its first requests answered)
+#pragma unroll
+    for (int d = 0; d < PF - 1; ++d) asm volatile("s_waitcnt vmcnt(0)" : "+v"(xq[d][0]), "+v"(xq[d][1]));
 }
 
 // ---------------------------------------------------------------- small products
@@ -1154,8 +1205,8 @@ int launch_split(const SplitPlan& pl, hipStream_t st, const uint32_t* A, const u
 template <int LW, int PF, bool PAD, bool BITS>
 static int launch_direct_as(const DirectPlan& pl, hipStream_t st, const uint32_t* A, const uint32_t* E, const float* alpha,
                             const float* beta, float* Y, int32_t* dbg_s1, const float* tau_out, uint32_t* out_bits) {
-    return launch(binconv_direct_kernel<LW, PF, PAD, BITS>, dim3(pl.grid), dim3(64 * pl.waves), pl.lds_bytes, st, pl.g, A, E,
-                  alpha, beta, Y, dbg_s1, tau_out, out_bits);
+    return launch(binconv_direct_kernel<LW, PF, PAD, BITS>, dim3(pl.grid), dim3(64 * pl.waves), pl.lds_bytes, st, E, A, alpha, beta,
+                  tau_out, make_fastdiv(pl.g.wg_per_ntile), pl.g, Y, dbg_s1, out_bits);
 }
 
 // The instantiations in use: (words per load, groups per round) x padding x (fp32 | bits).
