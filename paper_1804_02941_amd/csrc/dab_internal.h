@@ -117,6 +117,7 @@ struct BlockPlan {
 struct SplitGeom {
     int log_ks, groups_per_share;  // shares of the reduction per pixel block (a power of two), load groups per share
     int n_mtiles, units, per_xcd;  // pixel tiles, workgroups with work, those of one XCD
+    int narrow;                    // the shares exchange their sums as 16-bit numbers
     uint32_t e_bytes;
     FastDiv d_mtiles, d_G, d_kw;
 };

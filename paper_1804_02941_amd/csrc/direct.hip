@@ -726,7 +726,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
 // instructions beside eight multiplies, which hide them (two wavefronts per SIMD: the multiplies are
 // 60 % of the issue time).  The eight wavefronts of a workgroup are 8 / KS pixel blocks x KS shares of
 // the reduction; the shares' exact partial sums are added through LDS, each wavefront finishing a
-// KS-th of the rows.  Nothing is staged, no workspace, one launch; the only barriers are around that
+// KS-th of the rows.  Nothing is staged, no workspace, one launch; the only barrier is that of the
 // exchange.  (The form it replaces expanded both operands into a workspace, multiplied from there and
 // added the shares in a third launch: 1024 x 9216 x 4096 took 9.8 + 29.5 + 18.5 us.)
 constexpr int kSplitWaves = 8;
@@ -745,6 +745,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
     constexpr int STEPS = 8;                                       // k-steps per round, and weight loads in the queue
     constexpr int PF = STEPS / LW;                                 // activation load groups per round and in the queue
     extern __shared__ __align__(16) float4 red[];                  // [wave][register row e of a block row][lane]: the exchange
+    uint4* const red16 = reinterpret_cast<uint4*>(red);            // the same of both block rows, 16 bits a sum
     __shared__ int ones_lds[2][kSplitWaves][64];
     __shared__ __align__(16) float sA_lds[kSplitWaves][64];
     __shared__ __align__(16) float col_lds[3][kDirNTile];
@@ -764,13 +765,17 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
     const int g_first = min(share * sg.groups_per_share, g.NG);
     const int g_end = m_base < g.M ? min(g_first + sg.groups_per_share, g.NG) : g_first;
 
-    if (tid < kDirNTile) {
-        const int f = min(f0 + tid, g.F - 1);
-        const float al = alpha[f], be = beta[f];
-        col_lds[0][tid] = be - al;                                 // the accumulators hold -s1
-        col_lds[1][tid] = be;
-        col_lds[2][tid] = f0 + tid >= g.F ? __builtin_nanf("") : (BITS && tau_out) ? tau_out[f] : 0.0f;
-    }
+    // scalars of the tile's columns: requested in front of the operands and put into LDS behind the operands' requests
+    const int f_col = min(f0 + (tid & (kDirNTile - 1)), g.F - 1);
+    const float al = alpha[f_col], be = beta[f_col], ta = BITS && tau_out ? tau_out[f_col] : 0.0f;
+    auto keep_columns = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        if (tid < kDirNTile) {
+            col_lds[0][tid] = be - al;                             // the accumulators hold -s1
+            col_lds[1][tid] = be;
+            col_lds[2][tid] = f0 + tid >= g.F ? __builtin_nanf("") : ta;
+        }
+    };
     const __amdgpu_buffer_rsrc_t arsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(A), 0, static_cast<int>(g.a_bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t ersrc =
@@ -832,13 +837,17 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
         }
     };
 
+    // Partial sums that the shares exchange as 16-bit numbers count from 1.5 * 2^23: the low half of such a float is the
+    // sum's, modulo 2^16.  (Register by register: eight equal initial values in C++ are made by copying one tuple, which
+    // costs scratch memory here.)
+    const float start = sg.narrow ? 12582912.0f : 0.0f;
     v16f acc[2][NFP];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < NFP; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) asm volatile("v_mov_b32 %0, %1" : "=v"(acc[i][j][v]) : "s"(start));
     int ones[2] = {0, 0};
 
     if (g_first < g_end) {
@@ -848,6 +857,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
             if constexpr (q % LW == 0) request_a(q / LW);
             request_b(q, q % LW == LW - 1);
         });
+        keep_columns();
         uint32_t k8, k2;
         asm volatile("s_mov_b32 %0, 0x88888888" : "=s"(k8));
         asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(k2));
@@ -911,25 +921,21 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
         int left = steps;
         for (; left > STEPS / 2; left -= STEPS) for_each_column<STEPS>([&](auto qc) { step(qc, std::true_type{}); });
         if (left > 0) for_each_column<STEPS / 2>([&](auto qc) { step(qc, std::false_type{}); });
+    } else {
+        keep_columns();
     }
 
-    // ---- sA of the pixel block: ones of both halves and all shares, taps inside the image
-    const int ks = 1 << sg.log_ks;
+    // ---- what the workgroup's wavefronts hand each other: counts of ones and, in 16-bit numbers, the sums
     ones_lds[0][wave][lane] = ones[0];
     ones_lds[1][wave][lane] = ones[1];
-    __syncthreads();
-    {
-        int both = 0;
-        for (int k = 0; k < ks; ++k) both += ones_lds[h][mw * ks + k][p] + ones_lds[h][mw * ks + k][p + 32];
-        const int taps = PAD ? __builtin_popcount(h ? tbits[1] : tbits[0]) : g.T;
-        sA_lds[wave][lane] = static_cast<float>(2 * both - taps * g.C);     // lane l: row l of the block (read back by this wavefront only)
-    }
-
     // ---- epilogue.  Register row e = 4q + t of block row i is output row i*32 + q*8 + (lane/32)*4 + t,
     // column n of block j is filter 4n + j.  y = (beta - alpha)*(-s1) + beta*sA.
-    const float4 d4 = *reinterpret_cast<const float4*>(&col_lds[0][4 * p]);
-    const float4 b4 = *reinterpret_cast<const float4*>(&col_lds[1][4 * p]);
-    const float4 t4 = *reinterpret_cast<const float4*>(&col_lds[2][4 * p]);
+    float4 d4, b4, t4;
+    auto read_columns = [&]() {                                    // (behind a barrier)
+        d4 = *reinterpret_cast<const float4*>(&col_lds[0][4 * p]);
+        b4 = *reinterpret_cast<const float4*>(&col_lds[1][4 * p]);
+        t4 = *reinterpret_cast<const float4*>(&col_lds[2][4 * p]);
+    };
     const int fl = f0 + 4 * p;
     const int Fw = (g.F + 31) >> 5;
     auto finish = [&](int i, int e, float4 ns1) {
@@ -967,6 +973,66 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
             }
         }
     };
+    // ones of a pixel: both halves, all shares.  lane l: row l of the block (read back by this wavefront only)
+    auto row_sums = [&](int both) {
+        const int taps = PAD ? __builtin_popcount(h ? tbits[1] : tbits[0]) : g.T;
+        sA_lds[wave][lane] = static_cast<float>(2 * both - taps * g.C);
+    };
+    // Sums of 16-bit numbers: the exact sum of at most 2^15 - 1 terms is what it is modulo 2^16, whatever the shares' own.
+    // Half the bytes of an exchange of fp32 sums, so both block rows fit in LDS at once, one barrier in place of
+    // four, and with the number of shares known all reads of a wavefront are in flight together.  With the columns'
+    // scalars requested instead of waited for in front of the operands: 7200 pixels x 36 steps x 256, eight shares, 10.4 ->
+    // 7.5 us, 12312 x 50 x 150 (signs), four shares, 15.7 -> 13.6, 1024 x 9216 x 4096, four shares, 23.7 -> 21.6.
+    auto exchange16 = [&](auto lk) {
+        constexpr int KS = 1 << decltype(lk)::value, PER = 16 / KS;
+        int both = 0;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) both += ones_lds[h][mw * KS + k][p] + ones_lds[h][mw * KS + k][p + 32];
+        row_sums(both);
+        typedef short v2s __attribute__((ext_vector_type(2)));
+        v2s s[PER][4];
+#pragma unroll
+        for (int n = 0; n < PER; ++n)
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const uint4 v = red16[((mw * KS + k) * 16 + share * PER + n) * 64 + lane];
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const v2s t = __builtin_bit_cast(v2s, w[c]);
+                    s[n][c] = k ? s[n][c] + t : t;
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int n = 0; n < PER; ++n) {
+                finish(i, share * PER + n, make_float4(s[n][2 * i].x, s[n][2 * i].y, s[n][2 * i + 1].x, s[n][2 * i + 1].y));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    if (sg.narrow) {
+        // low halves of two registers in a word
+        auto low_halves = [](float lo, float hi) { return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x05040100u); };
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            red16[(wave * 16 + e) * 64 + lane] =
+                make_uint4(low_halves(acc[0][0][e], acc[0][1][e]), low_halves(acc[0][2][e], acc[0][3][e]),
+                           low_halves(acc[1][0][e], acc[1][1][e]), low_halves(acc[1][2][e], acc[1][3][e]));
+        __syncthreads();
+        read_columns();
+        if (sg.log_ks == 3) exchange16(std::integral_constant<int, 3>{});
+        else if (sg.log_ks == 2) exchange16(std::integral_constant<int, 2>{});
+        else exchange16(std::integral_constant<int, 1>{});
+        return;
+    }
+    // One share, or sums that 16 bits do not hold.
+    __syncthreads();
+    read_columns();
+    const int ks = 1 << sg.log_ks;
+    int both = 0;
+    for (int k = 0; k < ks; ++k) both += ones_lds[h][mw * ks + k][p] + ones_lds[h][mw * ks + k][p + 32];
+    row_sums(both);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         if (ks == 1) {
@@ -1181,6 +1247,7 @@ bool plan_split(const dab_conv_desc& d, SplitPlan* pl) {
     sg.d_mtiles = make_fastdiv(sg.n_mtiles);
     pl->grid = static_cast<unsigned>(sg.per_xcd * kNumXCD);
     pl->lds_bytes = sg.log_ks ? kSplitLds : 0;
+    sg.narrow = sg.log_ks && 1ll * d.C * g.T < (1 << 15) ? 1 : 0;
     return true;
 }
 
