@@ -72,10 +72,9 @@ int init_pack();
 int init_estimate(int dev);
 
 // The product kernel that reads both operands as packed bits (direct.hip).
-// (The places of its fields decide how the compiler groups a kernel's scalar loads.  Without the two steps in front of
-// n_mtiles the padded block kernels of two wavefronts come out with 56-72 registers instead of 88-104, one burst of
-// loads waited for before the next: 64 x 192 x 7 x 7 -> 64, 3 x 3, padding 1, 7.7 us with them, 8.1 without; over 90
-// padded layers between 15 % faster and 8 % slower without.)
+// (The places of its fields decide how the compiler groups a kernel's scalar loads, and with it how many of the block kernels'
+// loads are in flight: without the two steps in front of n_mtiles their padded forms came out with a third fewer registers, one
+// burst of loads waited for before the next, between 15 % faster and 8 % slower over 90 padded layers.)
 struct DirectGeom {
     int H, W, C, Cw, WH, F, Fp, kh, kw, ph, pw, sh, sw;   // WH: words per half of a pixel = ceil(Cw / 2)
     int HoWo, Wo, M, T;

@@ -595,7 +595,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
                                                                    uint32_t* __restrict__ out_bits) {
     __shared__ float red[WAVES][16][64];
     __shared__ int ones_lds[WAVES][64];
-    __shared__ float sA_blk[32];
+    DAB_RESERVE_VGPRS();
     const int lane = threadIdx.x & 63, p = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // block of this workgroup: consecutive workgroups go to consecutive XCDs, and an XCD keeps its filter blocks
@@ -604,16 +604,16 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
     const int fb = xcd + kNumXCD * (r - mb * bg.fb_per_xcd);
     if (fb >= bg.n_fblocks) return;                                // (the whole workgroup)
 
-    // this lane's pixel: byte offset of word h*WH of the window's first tap, taps inside the image
-    uint32_t base1[1], tbits1[1];
-    locate_windows<PAD>(g, mb * 32, p, h * g.WH * 4, base1, tbits1);
-    const uint32_t base = base1[0], tbits = tbits1[0];
     const __amdgpu_buffer_rsrc_t arsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(A), 0, static_cast<int>(g.a_bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t ersrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(E), 0, static_cast<int>(bg.e_bytes), 0x00020000);
     const int fcol = fb * 32 + p;                                  // this lane's filter (as the B operand's column)
     const uint32_t ecol = fcol < g.Fp ? static_cast<uint32_t>(fcol * 4) : kOob;
+    // the filter's scalars, which the epilogue would otherwise wait for behind the barrier (with the mask words requested
+    // before the windows are worked out and one barrier in place of two: conv4 of the sketch network, one image, 4.4 -> 4.0 us)
+    const int f = min(fcol, g.F - 1);
+    const float al = alpha[f], be = beta[f], tcol = (BITS && tau_out) ? tau_out[f] : 0.0f;
 
     // this wavefront's k-steps [k0, k1): k-step ks = tap * WH + j multiplies word h*WH + j of the tap.
     // A lane's activation words of a tap are neighbours in memory: with LW = 4 (WH a multiple of four)
@@ -626,7 +626,8 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
     typename WordsOf<LW>::type xa[2][NL];
     uint32_t xe[2][DEPTH];
     bool va[2][NL];
-    auto fetch = [&](int set, int first) {
+    uint32_t base1[1], tbits1[1];
+    auto fetch = [&](int set, int first, bool masks, bool words) {
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
             const int ks = first + l * LW;                         // (wavefront-uniform; a multiple of LW)
@@ -636,17 +637,21 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
             const int kx = tap - ky * g.kw;
             const int wd = h * g.WH + j;
             const bool live = ks < k1 && wd < g.Cw;                // (LW = 4: Cw = 2 WH, all four words or none)
+            if (masks) {
+#pragma unroll
+                for (int u = 0; u < LW; ++u) {
+                    const uint32_t eoff = ecol + static_cast<uint32_t>((tap * g.Cw + wd + u) * g.Fp * 4);
+                    xe[set][l * LW + u] = __builtin_amdgcn_raw_buffer_load_b32(ersrc, static_cast<int>(live ? eoff : kOob), 0, 0);
+                }
+            }
+            if (!words) continue;
+            const uint32_t base = base1[0], tbits = tbits1[0];
             const bool in = live && (!PAD || ((tbits >> (tap & 31)) & 1u));
             const uint32_t aoff = base + static_cast<uint32_t>(((ky * g.W + kx) * g.Cw + j) * 4);
             if constexpr (LW == 1) {
                 xa[set][l] = __builtin_amdgcn_raw_buffer_load_b32(arsrc, static_cast<int>(in ? aoff : kOob), 0, 0);
             } else {
                 xa[set][l] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(arsrc, static_cast<int>(in ? aoff : kOob), 0, 0));
-            }
-#pragma unroll
-            for (int u = 0; u < LW; ++u) {
-                const uint32_t eoff = ecol + static_cast<uint32_t>((tap * g.Cw + wd + u) * g.Fp * 4);
-                xe[set][l * LW + u] = __builtin_amdgcn_raw_buffer_load_b32(ersrc, static_cast<int>(live ? eoff : kOob), 0, 0);
             }
             va[set][l] = in;
         }
@@ -669,32 +674,31 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
             acc = mfma_fp4<true>(a, bv, acc);                      // (a k-step past k1 multiplies zeros)
         }
     };
-    fetch(0, k0);
+    // the first mask words are requested before the windows are worked out: byte offset of word h*WH of the window's
+    // first tap, taps inside the image
+    fetch(0, k0, true, false);
+    locate_windows<PAD>(g, mb * 32, p, h * g.WH * 4, base1, tbits1);
+    fetch(0, k0, false, true);
     for (int st = k0; st < k1; st += 2 * DEPTH) {
-        fetch(1, st + DEPTH);
+        fetch(1, st + DEPTH, true, true);
         multiply(0);
-        fetch(0, st + 2 * DEPTH);
+        fetch(0, st + 2 * DEPTH, true, true);
         multiply(1);
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
     ones_lds[wave][lane] = ones;
     __syncthreads();
-    if (threadIdx.x < 32) {
-        // sA of the block's pixels: ones of both halves and all wavefronts, taps inside the image
-        int both = 0;
+    // sA of pixel p, in every wavefront: ones of both halves and all wavefronts, taps inside the image
+    int both = 0;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) both += ones_lds[w][p] + ones_lds[w][p + 32];
-        const int taps = PAD ? __builtin_popcount(tbits) : g.T;
-        sA_blk[p] = static_cast<float>(2 * both - taps * g.C);
-    }
-    __syncthreads();
+    for (int w = 0; w < WAVES; ++w) both += ones_lds[w][lane];
+    both += __shfl_xor(both, 32, 64);
+    const int taps = PAD ? __builtin_popcount(tbits1[0]) : g.T;
+    const float sA = static_cast<float>(2 * both - taps * g.C);
 
     // register v of lane l is row (v/4)*8 + (l/32)*4 + v%4 of the block, column l%32; wavefront w
     // finishes registers w, w + WAVES, ...  The accumulators hold -s1.
-    const int f = min(fcol, g.F - 1);
-    const float al = alpha[f], be = beta[f];
-    const float tcol = (BITS && tau_out) ? tau_out[f] : 0.0f;
     const bool fvalid = fcol < g.F;
     const float dcol = be - al;
     const int Fw = (g.F + 31) >> 5;
@@ -705,7 +709,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
         float ns1 = 0.0f;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) ns1 += red[w][v][lane];
-        const float y = fmaf(dcol, ns1, be * sA_blk[rl]);
+        const float y = fmaf(dcol, ns1, be * __shfl(sA, rl, 64));
         if (BITS) {
             const unsigned long long mask = __ballot(fvalid && y >= tcol);
             const uint32_t word = static_cast<uint32_t>(lane < 32 ? mask : mask >> 32);
@@ -1160,8 +1164,11 @@ bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large) {
     if (large ? (blocks > 8192 || blocks * nk > 400000) : (tiles256 * 2 > kNumCU || blocks > 512)) return false;
     pl->grid = static_cast<unsigned>(ceil_div(g.M, 32) * bg.fb_per_xcd * kNumXCD);
     // enough wavefronts per block that each keeps a few k-steps of the reduction; the burst such that
-    // two of them hold a wavefront's whole share where that is short (one round trip to memory)
-    pl->waves = g.nk >= 32 ? 8 : 2;
+    // two of them hold a wavefront's whole share where that is short (one round trip to memory).  From 17 k-steps four
+    // wavefronts are faster than two for any number of blocks, below that while a compute unit has two of them at most (us,
+    // two | four wavefronts, 110 random layers: 124 blocks x 25 steps 5.4 | 4.0, 306 x 18 6.3 | 4.6, 1760 x 18 9.5 | 8.4,
+    // 480 x 8 4.9 | 4.7; 800 x 9 5.2 | 5.8, 2032 x 6 7.6 | 9.6).  Sixteen instead of eight gain 3 % at most and lose up to half.
+    pl->waves = g.nk >= 32 ? 8 : (g.nk >= 17 || pl->grid <= 2 * kNumCU ? 4 : 2);
     pl->lw = (g.Cw % 2 == 0 && g.WH % 4 == 0) ? 4 : 1;
     const int share = ceil_div(g.nk, pl->waves * pl->lw) * pl->lw;
     if (pl->lw == 4) pl->depth = share <= 8 ? 4 : (share > 16 && share <= 32 ? 16 : 8);
@@ -1193,8 +1200,8 @@ int launch_block(const BlockPlan& pl, hipStream_t st, const uint32_t* A, const u
         return bits ? launch_block_as<false, true, WAVES, DEPTH, LW>(pl, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits)      \
                     : launch_block_as<false, false, WAVES, DEPTH, LW>(pl, st, A, E, alpha, beta, Y, dbg_s1, tau_out, out_bits);    \
     }
-    DAB_X(8, 4, 1) DAB_X(8, 8, 1) DAB_X(8, 13, 1) DAB_X(2, 4, 1) DAB_X(2, 8, 1)
-    DAB_X(8, 4, 4) DAB_X(8, 8, 4) DAB_X(8, 16, 4) DAB_X(2, 4, 4) DAB_X(2, 8, 4)
+    DAB_X(8, 4, 1) DAB_X(8, 8, 1) DAB_X(8, 13, 1) DAB_X(4, 4, 1) DAB_X(2, 4, 1)
+    DAB_X(8, 4, 4) DAB_X(8, 8, 4) DAB_X(8, 16, 4) DAB_X(4, 4, 4) DAB_X(2, 4, 4)
 #undef DAB_X
     return DAB_ERR_UNSUPPORTED;
 }

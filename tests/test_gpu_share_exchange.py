@@ -1,6 +1,7 @@
 """Products whose reduction is split over the wavefronts of a workgroup: the exchange of the shares' partial sums.
 
-Reductions of at most 2^15 - 1 terms are exchanged as 16-bit numbers, longer ones in fp32.  Sums of whole numbers are exact, so
+A workgroup per 32 x 32 block has two, four or eight wavefronts, by the k-steps and the number of blocks.  In blocks of 64 x 128
+reductions of at most 2^15 - 1 terms are exchanged as 16-bit numbers, longer ones in fp32.  Sums of whole numbers are exact, so
 the integers have to agree with a float32 product of the same signs (exact below 2^24), up to rows and filters whose sum is
 the whole reduction, of either sign."""
 import pytest
@@ -24,6 +25,9 @@ def _signs(words, n):
     (2050, 4096, 1280), (2048, 2400, 1284),                # four
     (8192, 2400, 640), (8191, 2336, 515),                  # two; a row short, a filter count that is no multiple of four
     (19, 9216, 4096), (40000, 2368, 40),                   # few rows; one share
+    # a workgroup per 32 x 32 block: the k-steps and numbers of blocks where its wavefronts change, one and four words a load
+    (33, 960, 70), (33, 1024, 33), (33, 1088, 40), (31, 1984, 64), (31, 2048, 64), (2, 33, 1), (9, 256, 65),
+    (2048, 960, 100), (2049, 960, 100), (2049, 768, 37), (2049, 1088, 100),
 ])
 def test_sums_of_shares(B, K, F):
     g = torch.Generator(device=DEV)
