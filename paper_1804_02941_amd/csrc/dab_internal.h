@@ -100,9 +100,9 @@ struct DirectPlan {
 // The kernel for layers of few output blocks (one workgroup per 32 x 32 block, the reduction split
 // over its wavefronts); it shares DirectGeom's description of the layer.
 struct BlockGeom {
-    int n_fblocks, fb_per_xcd;     // 32-filter blocks in all and per XCD
+    int n_mblocks, units, per_xcd; // 32-pixel blocks, workgroups with work, those of one XCD
     uint32_t e_bytes;              // bytes of the packed weight tensor
-    FastDiv d_kw;
+    FastDiv d_kw, d_mblocks;
 };
 struct BlockPlan {
     DirectGeom g;

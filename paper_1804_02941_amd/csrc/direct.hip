@@ -581,8 +581,8 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const uint32_t* __r
 // wavefronts take consecutive shares of the reduction.  Both operands are read as packed bits
 // straight from memory (L2), DEPTH k-steps per burst into two register sets, expanded in
 // registers and multiplied; the wavefronts' exact partial sums (and their counts of ones for
-// sA) are added through LDS.  Workgroups that share a block of filters run on the same XCD, so
-// the filter words are fetched into one L2 only.
+// sA) are added through LDS.  Workgroups that share a block of filters are neighbours on an XCD, so
+// the filter words are fetched into few L2s.
 
 template <bool PAD, bool BITS, int WAVES, int DEPTH, int LW>
 __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectGeom g, const BlockGeom bg,
@@ -598,11 +598,14 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
     DAB_RESERVE_VGPRS();
     const int lane = threadIdx.x & 63, p = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // block of this workgroup: consecutive workgroups go to consecutive XCDs, and an XCD keeps its filter blocks
-    const int xcd = blockIdx.x % kNumXCD, r = blockIdx.x / kNumXCD;
-    const int mb = r / bg.fb_per_xcd;
-    const int fb = xcd + kNumXCD * (r - mb * bg.fb_per_xcd);
-    if (fb >= bg.n_fblocks) return;                                // (the whole workgroup)
+    // Block of this workgroup: consecutive workgroups go to consecutive XCDs, and an XCD takes a contiguous run of blocks,
+    // pixel blocks of one filter block next to each other.  (A filter block to one XCD left XCDs without work where
+    // there are fewer than eight, or not a multiple of eight: 14175 pixels x 144 steps x 21 59 us, now
+    // 12.3; 13454 x 95 x 20 41 and 9.0.)
+    const int unit = static_cast<int>(blockIdx.x % kNumXCD) * bg.per_xcd + static_cast<int>(blockIdx.x / kNumXCD);
+    if (unit >= bg.units) return;                                  // (the whole workgroup)
+    const int fb = fdiv(unit, bg.d_mblocks);
+    const int mb = unit - fb * bg.n_mblocks;
 
     const __amdgpu_buffer_rsrc_t arsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(A), 0, static_cast<int>(g.a_bytes), 0x00020000);
@@ -1155,19 +1158,21 @@ bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large) {
     g.nk = static_cast<int>(nk);
     g.d_HoWo = make_fastdiv(g.HoWo); g.d_Wo = make_fastdiv(g.Wo); g.d_WH = make_fastdiv(g.WH);
     BlockGeom& bg = pl->bg;
-    bg.n_fblocks = ceil_div(d.F, 32);
-    bg.fb_per_xcd = ceil_div(bg.n_fblocks, kNumXCD);
+    bg.n_mblocks = ceil_div(g.M, 32);
+    bg.d_mblocks = make_fastdiv(bg.n_mblocks);
     bg.e_bytes = static_cast<uint32_t>(e_bytes);
     bg.d_kw = make_fastdiv(d.kw);
-    const long long blocks = 1ll * ceil_div(g.M, 32) * bg.n_fblocks;
+    const long long blocks = 1ll * bg.n_mblocks * ceil_div(d.F, 32);
     const int tiles256 = ceil_div(g.M, 256) * ceil_div(d.F, kDirNTile);
     if (large ? (blocks > 8192 || blocks * nk > 400000) : (tiles256 * 2 > kNumCU || blocks > 512)) return false;
-    pl->grid = static_cast<unsigned>(ceil_div(g.M, 32) * bg.fb_per_xcd * kNumXCD);
+    bg.units = static_cast<int>(blocks);
+    bg.per_xcd = ceil_div(bg.units, kNumXCD);
+    pl->grid = static_cast<unsigned>(bg.per_xcd * kNumXCD);
     // enough wavefronts per block that each keeps a few k-steps of the reduction; the burst such that
     // two of them hold a wavefront's whole share where that is short (one round trip to memory).  From 17 k-steps four
     // wavefronts are faster than two for any number of blocks, below that while a compute unit has two of them at most (us,
-    // two | four wavefronts, 110 random layers: 124 blocks x 25 steps 5.4 | 4.0, 306 x 18 6.3 | 4.6, 1760 x 18 9.5 | 8.4,
-    // 480 x 8 4.9 | 4.7; 800 x 9 5.2 | 5.8, 2032 x 6 7.6 | 9.6).  Sixteen instead of eight gain 3 % at most and lose up to half.
+    // two | four wavefronts, 300 random layers: 126 blocks x 25 steps 5.9 | 4.3, 306 x 18 6.2 | 4.4, 1568 x 18 10.9 | 10.1,
+    // 480 x 9 4.9 | 4.6; 728 x 9 5.8 | 6.2, 2044 x 8 6.9 | 9.7).  Sixteen instead of eight gain 3 % at most and lose up to half.
     pl->waves = g.nk >= 32 ? 8 : (g.nk >= 17 || pl->grid <= 2 * kNumCU ? 4 : 2);
     pl->lw = (g.Cw % 2 == 0 && g.WH % 4 == 0) ? 4 : 1;
     const int share = ceil_div(g.nk, pl->waves * pl->lw) * pl->lw;
@@ -1176,7 +1181,7 @@ bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large) {
     // Time of a launch, fitted to 2500 random layers of more than 36 k-steps (rms error 5 %): workgroups per compute
     // unit of the XCD with the most filter blocks, and in each the k-steps of its wavefronts in whole bursts, at
     // sixteen and four bytes of a pixel per load; dearer where neighbouring taps share no cache lines.
-    const double per_cu = static_cast<double>(ceil_div(g.M, 32)) * bg.fb_per_xcd * kNumXCD / kNumCU;
+    const double per_cu = static_cast<double>(pl->grid) / kNumCU;
     const double step_us = pl->lw == 4 ? (g.T > 1 ? 0.0081 : 0.0093) : (g.T > 1 ? 0.015 : 0.0165);
     pl->us = 1.9 + (per_cu + 1.65) * ((pl->pad ? 0.57 : 0.42) + pl->waves * ceil_div(share, pl->depth) * pl->depth * step_us);
     return true;
