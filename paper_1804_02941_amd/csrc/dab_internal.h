@@ -87,9 +87,10 @@ struct DirectGeom {
     int pix_bytes;                 // bytes of a pixel's packed words
     uint32_t a_bytes;              // bytes of the packed activation tensor
     uint32_t y_bytes;              // bytes of the fp32 output (below 2^31)
-    int stream_out;                // the fp32 output is far larger than the chip's caches: streaming stores
+    int store_policy;              // of the fp32 output's 16-byte stores
     FastDiv d_HoWo, d_Wo, d_WH;
 };
+enum { kStorePlain = 0, kStoreThrough = 1, kStoreStream = 2 };
 struct DirectPlan {
     DirectGeom g;
     int lw, pf, waves;             // words per load, load groups per round, wavefronts per workgroup

@@ -69,16 +69,23 @@ __device__ __forceinline__ void for_each_column(Fn&& f) {
     }
 }
 // Cache policy of the output stores (measured on MI355X; a policy changes only where the data waits
-// on its way to memory): streaming ("nt") is the fastest for an output of more than a hundred
-// megabytes (conv2 of the Sketch-A-Net trunk at batch 256: 126 MB), device-scope write-through
-// ("sc1") for the smaller ones, which the memory-side cache absorbs: their stores otherwise pile up
-// behind the end of the kernel (conv3: 17.7 us instead of 19-23, conv4 21.9 instead of 22.9).
-template <bool STREAM>
+// on its way to memory).  Streaming ("nt") for outputs above 48 MB in whole lines of 128 bytes: they reach memory while the
+// multiplies leave it idle, where written through they are still on their way when the next layers' inputs are read (the
+// six layers of the Sketch-A-Net trunk at batch 256, outputs of 59 and 126 MB: 162.4 -> 154.3 us with the 59 MB ones streamed
+// too, 2.5 % more with none; a kernel that reads such an output right away loses 0.7 us of 30 at 59 MB, 3.8 of 49 at 126).
+// Device-scope write-through ("sc1") for the smaller ones, which the memory-side cache absorbs: their stores otherwise pile up
+// behind the end of the kernel (12 to 16 % with the default policy at 15 to 60 MB).  Rows that are not whole
+// lines leave both ends of a tile's row in parts: streamed, such outputs above 96 MB took 1.2 to 1.9 times as long as with
+// the default policy, written through 0.9 to 1.2 times; where the stores are not even aligned to their 16 bytes, writing
+// through takes up to 4 times as long, so those keep the default (1286 random layers).
+template <int POLICY>
 __device__ __forceinline__ void store_buffer_x4(v4f v, uint32_t voff, v4s rsrc, uint32_t soff) {
-    if constexpr (STREAM) {
+    if constexpr (POLICY == kStoreStream) {
         asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen nt\n\ts_nop 1" : : "v"(v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-    } else {
+    } else if constexpr (POLICY == kStoreThrough) {
         asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen sc1\n\ts_nop 1" : : "v"(v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    } else {
+        asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen\n\ts_nop 1" : : "v"(v), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
     }
 }
 __device__ __forceinline__ void store_buffer(float v, uint32_t voff, v4s rsrc, uint32_t soff) {
@@ -515,8 +522,7 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const uint32_t* __r
             // 16-byte store per lane, 512 contiguous bytes per half-wavefront, two rows per
             // instruction.  Y (and the optional integer dump) are raw buffers: the lane's offset
             // (first row of its half, its four filters) plus a scalar row offset; rows past M fall
-            // outside the buffer and are dropped by the range check.  When F is not a multiple of
-            // four, or for the integer dump, one store per value with columns past F masked.
+            // outside the buffer and are dropped by the range check.
             static_assert(NFP == 4, "the epilogues store all four column blocks of a row together");
             float4 s4[2][4];
 #pragma unroll
@@ -529,17 +535,20 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const uint32_t* __r
             const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, bv[4] = {b4.x, b4.y, b4.z, b4.w};
             const int fl = f0 + 4 * p;                             // first of this lane's four filters
             const uint32_t lane_off = static_cast<uint32_t>(((m_base + h * 4) * g.F + fl) * 4);
-            // Offsets of the lane's four values, kept in registers: worked out again in front of every store, into a
-            // register that the store before it still reads, they slowed narrow tiles (F = 15 to 63, not a multiple of
-            // four) by up to 13 %.
-            uint32_t off[4];
+            // Offsets of the lane's stores, kept in registers (worked out again in front of every store, into a register that
+            // the store before it still reads, they slowed narrow tiles by up to 13 %): of the four values together, and, in
+            // the one lane whose four filters the last one is among, of each by itself.  A 16-byte store needs 4-byte alignment
+            // only, so rows of any number of filters take it.  (As single
+            // values: 111475 pixels x 9 steps x 175 filters 44.0 us, now 23.0; 78608 x 18 x 182 45.7 and 23.7.)
+            uint32_t off4 = fl + 4 <= g.F ? lane_off : kOob, off1[3];
+            asm volatile("" : "+v"(off4));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                off[j] = fl + j < g.F ? lane_off + 4 * j : kOob;
-                asm volatile("" : "+v"(off[j]));
+            for (int j = 0; j < 3; ++j) {
+                off1[j] = fl + 4 > g.F && fl + j < g.F ? lane_off + 4 * j : kOob;
+                asm volatile("" : "+v"(off1[j]));
             }
-            const bool wide = (g.F & 3) == 0 && !dbg_s1;
-            auto store_tile = [&](auto stream) {
+            const bool tail = (g.F & 3) != 0 && f0 + kDirNTile > g.F;
+            auto store_tile = [&](auto policy) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
 #pragma unroll
@@ -551,21 +560,29 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const uint32_t* __r
                             float y[4];
 #pragma unroll
                             for (int j = 0; j < 4; ++j) y[j] = fmaf(dv[j], acc[i][j][q * 4 + t], bv[j] * sv[t]);
-                            if (wide) {
-                                store_buffer_x4<decltype(stream)::value>(v4f{y[0], y[1], y[2], y[3]}, off[0], yrsrc, row_off);
-                            } else {
+                            store_buffer_x4<decltype(policy)::value>(v4f{y[0], y[1], y[2], y[3]}, off4, yrsrc, row_off);
+                            if constexpr (decltype(policy)::value == kStorePlain) {
+                                if (tail) {
 #pragma unroll
-                                for (int j = 0; j < 4; ++j) {
-                                    store_buffer(y[j], off[j], yrsrc, row_off);
-                                    if (dbg_s1) store_buffer(__int_as_float(-static_cast<int>(acc[i][j][q * 4 + t])), off[j], drsrc, row_off);
+                                    for (int j = 0; j < 3; ++j) store_buffer(y[j], off1[j], yrsrc, row_off);
+                                }
+                                if (dbg_s1) {
+                                    float n[4];
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j) n[j] = __int_as_float(-static_cast<int>(acc[i][j][q * 4 + t]));
+                                    store_buffer_x4<kStorePlain>(v4f{n[0], n[1], n[2], n[3]}, off4, drsrc, row_off);
+#pragma unroll
+                                    for (int j = 0; j < 3; ++j) store_buffer(n[j], off1[j], drsrc, row_off);
                                 }
                             }
                         }
                     }
                 }
             };
-            if (g.stream_out) store_tile(std::true_type{});
-            else store_tile(std::false_type{});
+            // (rows of whole 16-byte stores, and nothing else to store, outside the default policy)
+            if (g.store_policy == kStoreStream && !dbg_s1) store_tile(std::integral_constant<int, kStoreStream>{});
+            else if (g.store_policy == kStoreThrough && !dbg_s1) store_tile(std::integral_constant<int, kStoreThrough>{});
+            else store_tile(std::integral_constant<int, kStorePlain>{});
             clear();
         }
     }
@@ -966,9 +983,13 @@ __global__ __launch_bounds__(64 * kSplitWaves) void binconv_split_kernel(const D
             }
             if (p < 4 && row < g.M && (f0 >> 5) + p < Fw) out_bits[static_cast<size_t>(row) * Fw + (f0 >> 5) + p] = word;
         } else if (row < g.M) {
+            // (rows of any number of filters: a 16-byte store needs 4-byte alignment only; 10300 x 25 x 202 16.4 -> 14.0 us)
+            typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
             const size_t o = static_cast<size_t>(row) * g.F + fl;
             if ((g.F & 3) == 0 && !dbg_s1) {
                 if (fl < g.F) *reinterpret_cast<float4*>(Y + o) = make_float4(y[0], y[1], y[2], y[3]);
+            } else if (fl + 4 <= g.F && !dbg_s1) {
+                *reinterpret_cast<v4f_any*>(Y + o) = v4f_any{y[0], y[1], y[2], y[3]};
             } else {
                 const float n[4] = {ns1.x, ns1.y, ns1.z, ns1.w};
 #pragma unroll
@@ -1094,7 +1115,7 @@ static bool describe(const dab_conv_desc& d, DirectGeom* pg, bool* pad, int* lw)
     g.M = static_cast<int>(M);
     g.a_bytes = static_cast<uint32_t>(a_bytes);
     g.y_bytes = static_cast<uint32_t>(M * d.F * 4);
-    g.stream_out = g.y_bytes > (96u << 20) ? 1 : 0;
+    g.store_policy = d.F % 4 ? kStorePlain : (g.y_bytes > (48u << 20) && d.F % 32 == 0 ? kStoreStream : kStoreThrough);
     g.pix_bytes = g.Cw * 4;
     g.nk = static_cast<int>(nk);
     g.odd = g.Cw & 1;

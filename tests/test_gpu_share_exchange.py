@@ -28,6 +28,10 @@ def _signs(words, n):
     # a workgroup per 32 x 32 block: the k-steps and numbers of blocks where its wavefronts change, one and four words a load
     (33, 960, 70), (33, 1024, 33), (33, 1088, 40), (31, 1984, 64), (31, 2048, 64), (2, 33, 1), (9, 256, 65),
     (2048, 960, 100), (2049, 960, 100), (2049, 768, 37), (2049, 1088, 100),
+    # many rows, the mask panel in LDS: last filters alone, in twos and in threes, whole and part tiles; 16-byte stores of rows
+    # of any length, streamed above 48 MB in rows of 128-byte lines
+    (70001, 320, 125), (70001, 320, 126), (70001, 320, 127), (70001, 320, 129), (70001, 320, 130), (70001, 320, 131),
+    (70001, 320, 132), (70001, 320, 1), (100001, 320, 160),
 ])
 def test_sums_of_shares(B, K, F):
     g = torch.Generator(device=DEV)
