@@ -834,9 +834,9 @@ static double expanded_us(const MfmaPlan& pl, bool bits) {
     return us;
 }
 
-// Estimated times (us) of the kernels that read bits, for reductions of at most 36 k-steps.  Fitted to 573 random layers
-// and batches of the trunk that are too large for plan_block's first rule, both outputs, every kernel timed on each (rms
-// error 12 % persistent, 7 % blocks, 12 % split).
+// Estimated times (us) of the kernels that read bits, for reductions of at most 36 k-steps.  Fitted to random layers of more
+// than 256 blocks, both outputs, every kernel timed on each (persistent and blocks 573 layers, rms error 12 and 9 %; split 2100
+// layers, 9 %).
 static double short_out(const DirectGeom& g, bool bits, double whole, double single) {
     return bits ? 0.0 : 4.0e-6 * g.M * g.F * (g.F % 4 ? single : whole);    // stores of four values, of one
 }
@@ -844,7 +844,7 @@ static double short_direct_us(const DirectPlan& pl, bool bits) {
     const DirectGeom& g = pl.g;
     const int n_ntiles = ceil_div(g.F, kNTile), tiles = ceil_div(g.n_mtiles, g.wg_per_ntile) * ceil_div(n_ntiles, kNumCU);
     const double step = (pl.waves == 4 ? 0.114 : 0.151) * (pl.pad ? 1.485 : 1.0) * (pl.lw == 1 ? 1.477 : pl.lw == 2 ? 1.062 : 1.0);
-    return 3.64 + 0.0385 * g.n_ent + tiles * ((g.n_ent - 1) * step + (pl.waves == 4 ? 2.08 : 3.72)) + short_out(g, bits, 0.033, 0.494);
+    return 3.64 + 0.0385 * g.n_ent + tiles * ((g.n_ent - 1) * step + (pl.waves == 4 ? 2.08 : 3.72)) + short_out(g, bits, 0.033, 0.12);
 }
 static double short_block_us(const BlockPlan& pl, bool bits) {
     const DirectGeom& g = pl.g;
@@ -855,10 +855,8 @@ static double short_block_us(const BlockPlan& pl, bool bits) {
 }
 static double short_split_us(const SplitPlan& pl, bool bits) {
     const DirectGeom& g = pl.g;
-    const int steps = pl.sg.groups_per_share * pl.lw;
-    const int steps_run = steps % 8 == 0 ? steps : steps / 8 * 8 + (steps % 8 <= 4 ? 4 : 8);
-    const double step = (pl.lw == 1 ? 0.643 : pl.lw == 2 ? 0.506 : 0.421) * (1.0 + (pl.pad ? 0.158 : 0.0) + 0.018 / g.T);
-    return 3.65 + ceil_div(pl.sg.units, kNumCU) * (2.92 + steps_run * step) + short_out(g, bits, 0.018, 0.342);
+    const double step = (pl.lw == 1 ? 0.381 : pl.lw == 2 ? 0.276 : 0.165) + (pl.pad ? 0.108 : 0.0) + 0.074 / g.T + 0.231 * pl.filled;
+    return 4.86 + pl.rounds * (pl.sg.log_ks ? -0.06 : 1.43) + pl.rounds * pl.steps_run * step + short_out(g, bits, 0.064, 0.121);
 }
 
 // Which kernel computes a layer, with its plan.
@@ -875,36 +873,36 @@ static int plan_product(const dab_conv_desc& d, bool bits, ProductPlans* p, Prod
     *which = Product::kBlock;
     if (plan_block(d, &p->block, false)) return DAB_OK;
     // A reduction whose B fragments fit in LDS: the persistent kernel, which builds them once per workgroup.  With too few
-    // tiles for the compute units, or where its stores are of single values, a workgroup per 32 x 32 block or the split
-    // kernel are faster: taken where their estimates are under 0.9 and 0.85 of the persistent one's (the split kernel from
-    // eight k-steps and up to two rounds of workgroups, as far as it was timed).  Over 295 other layers that makes fp32
-    // outputs 15.2 % and packed signs 8.1 % faster in the geometric mean, at most 2.5 times faster and 4 % slower.  (us,
-    // persistent | blocks | split, fp32:) 3600 pixels x 36 steps x 256 12.1 | 7.3 | 9.4, 7200 12.3 | 11.2 | 10.0,
-    // 10800 12.4 | 14.7 | 12.8; 15376 x 25 x 128 10.2 | 17.2 | 9.8; 4104 x 18 x 205 16.8 | 8.7 | 10.1.
+    // tiles for the compute units, a workgroup per 32 x 32 block or the split kernel are faster: taken where their estimates
+    // are under 0.95 and 0.85 of the persistent one's, the split kernel's also under 0.9 of the blocks' (from
+    // eight k-steps and up to two rounds of workgroups, as far as it was timed).  Over 2137 random layers the form taken
+    // is 0.7 % slower than the fastest in the geometric mean.  (us, persistent | blocks | split, fp32:) 7290 pixels x 18
+    // steps x 519 filters 10.7 | 16.6 | 12.4, 52200 x 20 x 88 11.6 | 21.1 | 14.3; 864 x 25 x 382 12.6 | 4.9 | 7.3, 16473 x 12 x 19
+    // 7.8 | 4.0 | 7.3; 3648 x 25 x 487 14.0 | 11.0 | 8.6, 12544 x 36 x 115 13.0 | 9.9 | 7.7.
     if (plan_direct(d, &p->direct)) {
         *which = Product::kDirect;
         const double direct = short_direct_us(p->direct, bits);
         double best = direct;
-        if (plan_block(d, &p->block, true) && short_block_us(p->block, bits) < 0.9 * direct) {
+        if (plan_block(d, &p->block, true) && short_block_us(p->block, bits) < 0.95 * direct) {
             best = short_block_us(p->block, bits);
             *which = Product::kBlock;
         }
         if (p->direct.g.nk >= 8 && plan_split(d, &p->split) && p->split.sg.units <= 2 * kNumCU) {
             const double split = short_split_us(p->split, bits);
-            if (split < best && split < 0.85 * direct) *which = Product::kSplit;
+            if (split < (*which == Product::kBlock ? 0.9 * best : 0.85 * direct) && split < 0.85 * direct) *which = Product::kSplit;
         }
         return DAB_OK;
     }
     // Longer reductions: shares of it per wavefront over blocks of 64 x 128 where that is the faster form.  Otherwise a
     // workgroup per 32 x 32 block up to a few thousand blocks, and past those the operands expanded into the workspace:
     // a multiply has less work beside it there (nothing is expanded again for each filter tile and tap), which pays for
-    // the launch and the bytes more on large layers.  Chosen by estimated times, which are within 5 % (blocks), 6 %
-    // (split) and 7 % rms (workspace) of the measured ones over 3300 random layers of 37 to 1100 k-steps, both outputs;
-    // over 1750 others the form taken is 0.3 % slower than the faster one in the geometric mean, at most 23 %.  (Split
-    // up to 3 % above the other estimate: of the factors 0.9 to 1.1 this made the fewest choices that cost over 3 %.)
-    // (us, split | blocks | workspace, fp32 output:) 1024 x 9216 x 4096 21.4 | - | 55.8, 80142 pixels x 144 steps x 33
-    // 52.3 | - | 135, 92 x 10^3 pixels x 400 steps x 512 635 | - | 413, 24480 pixels x 637 steps x 640 310 | - | 216,
-    // 2025 pixels x 108 steps x 384 11.8 | 9.5 | -, 3136 x 72 x 512 12.1 | 15.2 | -, 789 x 8296 x 928 13.6 | 21.5 | -.
+    // the launch and the bytes more on large layers.  Chosen by estimated times, which are within 9 % (blocks), 7 %
+    // (split) and 7 % rms (workspace) of the measured ones over random layers of 37 to 1100 k-steps, both outputs;
+    // over 1900 others the form taken is 0.5 % slower than the fastest one in the geometric mean.  (Split where its estimate
+    // is 5 % below the blocks', up to 3 % above the workspace's: of the factors 0.9 to 1.1 these made the best choices.)
+    // (us, split | blocks | workspace, fp32 output:) 5819 pixels x 66 steps x 542 filters 15.2 |
+    // 39.3 | 42.4, 19044 x 50 x 290 19.7 | 35.9 | 25.8; 5408 x 50 x 40 9.5 | 6.0 | -, 624 x 60 x 446 9.3 | 5.8 | 13.4;
+    // 58190 x 117 x 144 71.9 | - | 57.7, 98315 x 325 x 35 152 | - | 120.
     // (The workspace is asked for, as dab_binconv2d_workspace_bytes says, whichever of split and workspace is taken.)
     const bool few_blocks = plan_block(d, &p->block, true);
     if (!few_blocks) {
@@ -913,7 +911,7 @@ static int plan_product(const dab_conv_desc& d, bool bits, ProductPlans* p, Prod
     }
     const bool splits = plan_split(d, &p->split);
     const double other_us = few_blocks ? p->block.us : expanded_us(p->expanded, bits);
-    if (splits && (bits ? p->split.us_bits : p->split.us) < 1.03 * other_us) *which = Product::kSplit;
+    if (splits && (bits ? p->split.us_bits : p->split.us) < (few_blocks ? 0.95 : 1.03) * other_us) *which = Product::kSplit;
     else *which = few_blocks ? Product::kBlock : Product::kExpanded;
     return DAB_OK;
 }

@@ -125,6 +125,8 @@ struct SplitPlan {
     DirectGeom g;
     SplitGeom sg;
     double us, us_bits;            // estimated time of a launch with fp32 and with packed-sign output
+    int steps_run, rounds;         // k-steps a wavefront runs, rounds of workgroups
+    double filled;                 // part of the compute units at work in a round
     int lw;
     bool pad;
     unsigned grid;

@@ -1247,14 +1247,15 @@ bool plan_split(const dab_conv_desc& d, SplitPlan* pl) {
     sg.d_G = make_fastdiv(g.G);
     sg.d_kw = make_fastdiv(d.kw);
     // Shares of the reduction per pixel block: the number that minimises rounds of workgroups times the
-    // time of one, as measured (0.4 us a k-step of two wavefronts per SIMD: 1024 x 9216 x 4096, 36 steps of
-    // four shares, 23.7 us, 1024 x 4096 x 4096, 16 steps, 16.2; set-up and epilogue 4, the exchange 4).
+    // time of one: 0.4 us a k-step of two wavefronts per SIMD, set-up and epilogue 4.5, the exchange 0.5 (2.5 in fp32).
+    // (Over 3587 random layers for which this is the kernel, 0.4 % slower than the best number of shares.)
+    const bool narrow = 1ll * d.C * g.T < (1 << 15);
     const int n_ntiles = ceil_div(d.F, kDirNTile);
     double best = 0.0;
     for (int lk = 0; lk <= 3; ++lk) {
         const int per = ceil_div(g.NG, 1 << lk);
         const long long units = 1ll * ceil_div(g.M, 64 * (kSplitWaves >> lk)) * n_ntiles;
-        const double us = static_cast<double>((units + kNumCU - 1) / kNumCU) * (per * pl->lw * 0.4 + 4.5 + (lk ? 4.0 : 0.0));
+        const double us = static_cast<double>((units + kNumCU - 1) / kNumCU) * (per * pl->lw * 0.4 + 4.5 + (lk ? (narrow ? 0.5 : 2.5) : 0.0));
         if (lk == 0 || us < best) {
             best = us;
             sg.log_ks = lk;
@@ -1264,23 +1265,23 @@ bool plan_split(const dab_conv_desc& d, SplitPlan* pl) {
     sg.n_mtiles = ceil_div(g.M, 64 * (kSplitWaves >> sg.log_ks));
     const long long units = 1ll * sg.n_mtiles * n_ntiles;
     if (units >= (1ll << 30)) return false;
-    // Time of a launch, to compare with the other kernels' (fitted to 3300 random layers with the shares chosen above,
-    // rms error 6 %): per round of workgroups the k-steps, which come in whole and then half rounds of eight, by the
+    // Time of a launch, to compare with the other kernels' (fitted to 1900 random layers with the shares chosen above,
+    // rms error 7 %): per round of workgroups the k-steps, which come in whole and then half rounds of eight, by the
     // words per load; dearer with padding, with fewer taps that share their cache lines and with more compute units at
-    // work.  What the fp32 stores add is six times as much where they are of single values.
+    // work.  What the fp32 stores add is more where rows are no whole number of 16-byte stores.
     const int steps = sg.groups_per_share * pl->lw;
-    const int steps_run = steps % 8 == 0 ? steps : steps / 8 * 8 + (steps % 8 <= 4 ? 4 : 8);
-    const double rounds = static_cast<double>((units + kNumCU - 1) / kNumCU);
-    const double step_us = (pl->lw == 1 ? 0.324 : (pl->lw == 2 ? 0.241 : 0.21)) *
-                           (1.0 + (pl->pad ? 0.32 : 0.0) + 0.39 / g.T + 0.34 * units / (rounds * kNumCU));
-    pl->us_bits = 2.2 + rounds * (5.9 + steps_run * step_us);
-    pl->us = pl->us_bits + (d.F % 4 ? 2.9 : 0.51) * 4.0 * g.M * d.F / 10.0e6;
+    pl->steps_run = steps % 8 == 0 ? steps : steps / 8 * 8 + (steps % 8 <= 4 ? 4 : 8);
+    pl->rounds = static_cast<int>((units + kNumCU - 1) / kNumCU);
+    pl->filled = static_cast<double>(units) / (1.0 * pl->rounds * kNumCU);
+    const double step_us = (pl->lw == 1 ? 0.334 : (pl->lw == 2 ? 0.23 : 0.189)) + (pl->pad ? 0.078 : 0.0) + 0.088 / g.T + 0.112 * pl->filled;
+    pl->us_bits = 2.75 + pl->rounds * (3.62 + (sg.log_ks ? (narrow ? -0.85 : 1.75) : 0.0) + pl->steps_run * step_us);
+    pl->us = pl->us_bits + (d.F % 4 ? 0.14 : 0.057) * 4.0e-6 * g.M * d.F;
     sg.units = static_cast<int>(units);
     sg.per_xcd = ceil_div(sg.units, kNumXCD);
     sg.d_mtiles = make_fastdiv(sg.n_mtiles);
     pl->grid = static_cast<unsigned>(sg.per_xcd * kNumXCD);
     pl->lds_bytes = sg.log_ks ? kSplitLds : 0;
-    sg.narrow = sg.log_ks && 1ll * d.C * g.T < (1 << 15) ? 1 : 0;
+    sg.narrow = sg.log_ks && narrow ? 1 : 0;
     return true;
 }
 
