@@ -4,7 +4,8 @@ Every function here has the name of the C entry point it calls (see
 ``include/dab.h``) and does nothing but check tensor dtype / device /
 contiguity, allocate the output tensors with ``torch.empty`` and pass raw
 device pointers plus the current HIP stream.  The calls of single layers do that
-in native code (``csrc/binding_call.cpp``, the module ``_dab_call``); the grouped
+in native code (``csrc/binding_call.cpp``, the module ``_dab_call``), plain ones whole,
+others from the Python below on; the grouped
 calls, whose jobs are marshalled once and kept, go through ctypes.  All arithmetic
 of the path runs in the HIP kernels.  There is no CPU fallback: if the library is
 not built, or a tensor is not on the GPU, the call raises.
@@ -266,6 +267,9 @@ def dab_pack_weights(W, thr_val, thr_idx, alpha_is_upper, out=None):
 
 def dab_pack_activations(X, layout=DAB_LAYOUT_NHWC, tau=None, out=None):
     """X fp32 NHWC [B,H,W,C] (or NCHW [B,C,H,W]; a 2-D [B,C] is H=W=1) -> int32 [B,H,W,Cw]."""
+    A = (_native or native()).pack_activations(X, layout, tau, out)
+    if A is not None:
+        return A
     if X.dim() == 2:
         B, C = X.shape
         H = W = 1
@@ -362,6 +366,10 @@ def dab_prepare_layers(wjobs, pjobs, ws=None):
 
 def dab_binconv2d(desc, A_packed, E_packed, alpha, beta, want_s1=False, out=None, ws=None):
     """Binarized convolution; returns Y fp32 [B,Ho,Wo,F] (and int32 s1 of the same shape if asked)."""
+    if not want_s1:
+        Y = (_native or native()).binconv2d(desc, A_packed, E_packed, alpha, beta, out, ws)
+        if Y is not None:
+            return Y
     dev = A_packed.device
     shape = (desc.B, desc.Ho, desc.Wo, desc.F) if out is None or want_s1 else None
     Y = out if out is not None else torch.empty(shape, dtype=torch.float32, device=dev)
@@ -375,6 +383,10 @@ def dab_binconv2d(desc, A_packed, E_packed, alpha, beta, want_s1=False, out=None
 
 def dab_binfc(A_packed, E_packed, alpha, beta, Kin, want_s1=False, out=None, ws=None):
     """Binarized fully-connected layer; A_packed [B, Kw], returns Y fp32 [B, F]."""
+    if not want_s1:
+        Y = (_native or native()).binfc(A_packed, E_packed, alpha, beta, Kin, out, ws)
+        if Y is not None:
+            return Y
     dev = A_packed.device
     B = A_packed.shape[0]
     F = alpha.shape[0]
@@ -389,6 +401,9 @@ def dab_binfc(A_packed, E_packed, alpha, beta, Kin, want_s1=False, out=None, ws=
 
 def dab_binconv2d_bits(desc, A_packed, E_packed, alpha, beta, tau_out=None, out=None, ws=None):
     """Binarized convolution with the re-binarizing epilogue; returns int32 [B,Ho,Wo,ceil(F/32)]."""
+    A_next = (_native or native()).binconv2d_bits(desc, A_packed, E_packed, alpha, beta, tau_out, out, ws)
+    if A_next is not None:
+        return A_next
     dev = A_packed.device
     A_next = out if out is not None else torch.empty((desc.B, desc.Ho, desc.Wo, words_per_pixel(desc.F)), dtype=torch.int32,
                                                      device=dev)
@@ -413,6 +428,9 @@ def dab_binfc_bits(A_packed, E_packed, alpha, beta, Kin, tau_out=None, out=None,
 
 def dab_pool_bits(A_packed, C, kh, kw, stride_h, stride_w, out=None):
     """OR-pooling of packed signs: int32 [B,H,W,Cw] -> [B,Ho,Wo,Cw] (windows inside the image)."""
+    A_pooled = (_native or native()).pool_bits(A_packed, C, kh, kw, stride_h, stride_w, out)
+    if A_pooled is not None:
+        return A_pooled
     B, H, W, Cw = A_packed.shape
     Ho, Wo = (H - kh) // stride_h + 1, (W - kw) // stride_w + 1
     A_pooled = out if out is not None else torch.empty((B, max(Ho, 0), max(Wo, 0), Cw), dtype=torch.int32,
@@ -468,6 +486,9 @@ def dab_estimate_alpha_beta_bounded(W, K_prev, alpha_is_upper_prev, max_change, 
 
 def dab_wbin_conv2d(desc, X, E_packed, alpha, beta, out=None, ws=None):
     """Weights-only binarized convolution: X fp32 NHWC [B,H,W,C] -> Y fp32 [B,Ho,Wo,F]."""
+    Y = (_native or native()).wbin_conv2d(desc, X, E_packed, alpha, beta, out, ws)
+    if Y is not None:
+        return Y
     dev = X.device
     Y = out if out is not None else torch.empty((desc.B, desc.Ho, desc.Wo, desc.F), dtype=torch.float32, device=dev)
     call = _native or native()
@@ -479,6 +500,9 @@ def dab_wbin_conv2d(desc, X, E_packed, alpha, beta, out=None, ws=None):
 
 def dab_wbin_fc(X, E_packed, alpha, beta, out=None, ws=None):
     """Weights-only binarized fully-connected layer: X fp32 [B,Kin] -> Y fp32 [B,F]."""
+    Y = (_native or native()).wbin_fc(X, E_packed, alpha, beta, out, ws)
+    if Y is not None:
+        return Y
     dev = X.device
     B, Kin = X.shape
     F = alpha.shape[0]
