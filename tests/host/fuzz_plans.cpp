@@ -53,17 +53,18 @@ int check_one(const dab_conv_desc& d) {
     for (int large = 0; large < 2; ++large) {
         BlockPlan bp;
         if (plan_block(d, &bp, large != 0)) {
-            REQUIRE(bp.waves == 2 || bp.waves == 8);
+            REQUIRE(bp.waves == 2 || bp.waves == 4 || bp.waves == 8);
             REQUIRE(bp.g.M == M);
-            REQUIRE(bp.bg.n_fblocks == (d.F + 31) / 32 && bp.bg.fb_per_xcd * 8 >= bp.bg.n_fblocks);
-            REQUIRE(1ull * bp.grid == 1ull * ((M + 31) / 32) * bp.bg.fb_per_xcd * 8);
-            const long long blocks = 1ll * ((M + 31) / 32) * bp.bg.n_fblocks;
+            const long long blocks = 1ll * ((M + 31) / 32) * ((d.F + 31) / 32);
+            REQUIRE(bp.bg.n_mblocks == (M + 31) / 32 && bp.bg.units == blocks);
+            REQUIRE(8ll * bp.bg.per_xcd >= blocks && 8ll * (bp.bg.per_xcd - 1) < blocks);
+            REQUIRE(1ull * bp.grid == 8ull * bp.bg.per_xcd);
             REQUIRE(blocks <= (large ? 8192 : 512) && (!large || blocks * bp.g.nk <= 400000));
             // the load burst: whole loads, and a kernel exists for the combination
             REQUIRE(bp.lw == 1 || (bp.lw == 4 && bp.g.Cw % 8 == 0));
             REQUIRE(bp.depth % bp.lw == 0);
-            REQUIRE((bp.lw == 1 && (bp.depth == 4 || bp.depth == 8 || (bp.depth == 13 && bp.waves == 8))) ||
-                    (bp.lw == 4 && (bp.depth == 4 || bp.depth == 8 || (bp.depth == 16 && bp.waves == 8))));
+            REQUIRE((bp.lw == 1 && (bp.depth == 4 || ((bp.depth == 8 || bp.depth == 13) && bp.waves == 8))) ||
+                    (bp.lw == 4 && (bp.depth == 4 || ((bp.depth == 8 || bp.depth == 16) && bp.waves == 8))));
             REQUIRE(1ll * d.C * d.kh * d.kw < (1ll << 24));
         }
     }

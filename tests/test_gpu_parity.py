@@ -441,8 +441,8 @@ def test_sign_split_estimate_and_layer(n):
 
 # (name, B, C, H, W, F, k, pad, stride): padding as wide as the kernel or wider, on each of the product kernels
 # (that a layer takes the kernel it is named after is checked on the CPU, test_host_sanitizers.py)
-BORDER_LAYERS = [("persistent k1p1", 120, 64, 12, 13, 64, 1, 1, 1), ("persistent k2p2", 100, 64, 12, 13, 64, 2, 2, 1),
-                 ("persistent k3p3", 90, 96, 9, 8, 100, 3, 3, 1), ("persistent k1p2s2", 200, 128, 9, 9, 130, 1, 2, 2),
+BORDER_LAYERS = [("persistent k1p1", 120, 64, 12, 13, 64, 1, 1, 1), ("persistent k2p2", 150, 64, 12, 13, 64, 2, 2, 1),
+                 ("persistent k3p3", 150, 96, 9, 8, 100, 3, 3, 1), ("persistent k1p2s2", 200, 128, 9, 9, 130, 1, 2, 2),
                  ("block k1p1", 1, 64, 6, 6, 32, 1, 1, 1), ("block k2p3", 2, 33, 5, 5, 7, 2, 3, 1),
                  ("block k1p1, 40 blocks", 6, 64, 12, 13, 64, 1, 1, 1), ("block k2p2", 6, 64, 12, 13, 64, 2, 2, 1),
                  ("block k3p3", 5, 96, 9, 8, 100, 3, 3, 1), ("block k1p2s2", 40, 128, 9, 9, 130, 1, 2, 2),

@@ -97,16 +97,16 @@ def test_filter_counts_that_end_inside_a_word_in_the_persistent_kernel(C, F):
 SPLIT_LAYERS = [
     # name, B, C, H, W, F, k, pad, stride.  Words per load (w1, w2, w4; odd: an odd number of words per pixel) and
     # shares of the reduction (s1 to s8), with and without padding; last tiles of 1 to 128 filters and 1 to 64 pixels
-    ("w1_s1", 245, 576, 21, 21, 20, 3, 0, 1), ("w1_s2_odd_pad", 211, 352, 26, 26, 38, 3, 1, 2), ("w1_s4", 247, 320, 12, 12, 33, 3, 0, 1),
-    ("w1_s8_odd_fc", 2802, 3463, 1, 1, 312, 1, 0, 1), ("w2_s1_pad", 491, 640, 11, 11, 58, 2, 1, 1), ("w2_s2", 356, 631, 12, 12, 64, 2, 0, 1),
-    ("w2_s4_pad", 375, 105, 15, 15, 28, 5, 2, 2), ("w2_s8_fc", 1021, 4736, 1, 1, 1030, 1, 0, 1), ("w4_s1_pad", 262, 512, 16, 16, 84, 3, 1, 1),
+    ("w1_s1", 245, 576, 21, 21, 40, 3, 0, 1), ("w1_s2_odd_pad", 211, 352, 26, 26, 70, 3, 1, 2), ("w1_s4", 247, 320, 12, 12, 33, 3, 0, 1),
+    ("w1_s8_odd_fc", 2802, 3463, 1, 1, 480, 1, 0, 1), ("w2_s1_pad", 491, 640, 11, 11, 58, 2, 1, 1), ("w2_s2", 356, 631, 12, 12, 64, 2, 0, 1),
+    ("w2_s4_pad", 375, 105, 15, 15, 33, 5, 2, 2), ("w2_s8_fc", 1021, 4736, 1, 1, 1030, 1, 0, 1), ("w4_s1_pad", 262, 512, 16, 16, 84, 3, 1, 1),
     ("w4_s2", 494, 482, 8, 8, 133, 3, 0, 1), ("w4_s4_fc", 1021, 9216, 1, 1, 2050, 1, 0, 1), ("w4_s8_pad", 83, 512, 9, 9, 129, 5, 2, 1),
 ]
 EXPANDED_LAYERS = [
     # name, B, C, H, W, F, k, pad, stride: through the workspace, by a padded window of more than 32 taps and by time
     ("eight_wavefronts", 32, 64, 48, 48, 200, 7, 3, 1), ("four_wavefronts", 16, 64, 48, 48, 200, 7, 3, 1),
     ("split_reduction", 4, 64, 48, 48, 200, 7, 3, 1), ("split_reduction_tails", 5, 70, 41, 37, 131, 7, 3, 1),
-    ("odd_words_by_time", 16, 80, 32, 48, 385, 5, 2, 1),
+    ("odd_words_by_time", 24, 80, 48, 48, 385, 5, 2, 1),
 ]
 LONG_REDUCTIONS = SPLIT_LAYERS + EXPANDED_LAYERS + [
     # name, B, C, H, W, F, k, pad, stride: other reductions of more than 36 steps over many blocks, on whichever

@@ -91,7 +91,7 @@ def test_the_padded_block_kernels_hold_both_bursts_of_loads_like_the_plain_ones(
     """Each burst has registers of its own; a padded form with fewer registers than the plain one waits for one burst before it
     requests the next (seen with 56 and 72 registers instead of 88 and 104)."""
     regs = dict(re.findall(r"\.amdhsa_kernel \S*binconv_block_kernelI(\w+?)EEv.*?\.amdhsa_next_free_vgpr (\d+)", direct_isa, re.S))
-    padded = [k for k in regs if k.startswith("Lb1E") and "ELi2E" in k]
+    padded = [k for k in regs if re.match(r"Lb1ELb[01]ELi[24]E", k)]
     assert len(padded) == 8
     for k in padded:
         assert int(regs[k]) >= int(regs["Lb0E" + k[4:]]), k
