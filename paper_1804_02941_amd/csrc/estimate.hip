@@ -106,11 +106,18 @@ __device__ __forceinline__ const EstJob& find_job(const EstJobs& jobs, unsigned 
 // Rows of up to THREADS * ITEMS weights, one per workgroup: buckets first; where they cannot finish
 // the row, the sort by the same workgroup (SORT_HERE) or a flag for the sort kernel launched
 // behind; then the packing.
-template <int THREADS, int ITEMS, int NB, int CAP, bool SORT_HERE>
+// (The pool is declared in a function of its own, so that two classes of rows in one kernel share it.)
+template <int THREADS, int ITEMS, int NB, int CAP>
+constexpr size_t kRowPool = sizeof(BucketLds<THREADS, NB, CAP>) > THREADS * ITEMS ? sizeof(BucketLds<THREADS, NB, CAP>) : THREADS * ITEMS;
+template <size_t BYTES>
+__device__ __forceinline__ unsigned char* row_pool() {
+    __shared__ __align__(16) unsigned char pool[BYTES];
+    return pool;
+}
+template <int THREADS, int ITEMS, int NB, int CAP, bool SORT_HERE, size_t POOL = kRowPool<THREADS, ITEMS, NB, CAP>>
 __device__ __forceinline__ void binarize_row_of_block(const EstJobs& jobs, unsigned block) {
     using Lds = BucketLds<THREADS, NB, CAP>;
-    constexpr size_t kPool = sizeof(Lds) > THREADS * ITEMS ? sizeof(Lds) : THREADS * ITEMS;
-    __shared__ __align__(16) unsigned char pool[kPool];            // the search's arrays, then the mask, a byte per weight
+    unsigned char* const pool = row_pool<POOL>();                  // the search's arrays, then the mask, a byte per weight
     __shared__ SplitInfo info;
     unsigned blk0;
     const EstJob& q = find_job(jobs, block, &blk0);
@@ -159,6 +166,19 @@ __global__ __launch_bounds__(THREADS, MIN_WAVES) void prepare_rows_kernel(const 
     DAB_RESERVE_VGPRS();
     if (blockIdx.x < n_pack) pack_share<THREADS / 64>(packs, blockIdx.x);
     else binarize_row_of_block<THREADS, ITEMS, NB, CAP, SORT_HERE>(jobs, blockIdx.x - n_pack);
+}
+
+// Long rows, a row of up to 2304 weights each for the workgroups behind them, and in front of both the packing, in one launch:
+// the short rows run where long ones leave compute units, instead of before them.  The long rows' registers leave
+// room for four workgroups on a compute unit where the short ones alone would have seven, which pays while those are few.  (The trunk of the
+// sketch network with its packing: batch 1 36.0 -> 30.5 us, 32 39.9 -> 33.5, 128 48.4 -> 41.5, 192 (180 MB) 51.7 -> 48.3; at 256, 240 MB, memory decides: 56.1 and 56.2, two launches.)
+template <int ITEMS, int NB, int CAP>
+__global__ __launch_bounds__(256, 4) void prepare_two_kernel(const EstJobs jobs, const PackJobs packs, unsigned n_pack, unsigned n_long) {
+    DAB_RESERVE_VGPRS();
+    constexpr size_t kLong = kRowPool<256, ITEMS, NB, CAP>, kShort = kRowPool<256, 9, 512, 256>, kPool = kLong > kShort ? kLong : kShort;
+    if (blockIdx.x < n_pack) pack_share<4>(packs, blockIdx.x);
+    else if (blockIdx.x < n_pack + n_long) binarize_row_of_block<256, ITEMS, NB, CAP, false, kPool>(jobs, blockIdx.x - n_pack);
+    else binarize_row_of_block<256, 9, 512, 256, false, kPool>(jobs, blockIdx.x - n_pack);
 }
 
 // The rows the kernels above have flagged, kSortRowsPerGroup per workgroup.  Their flags are one aligned 8-byte
@@ -368,6 +388,8 @@ static double rows_us(int c, long long rows) {
 }
 
 constexpr double kWidePackBytes = 8e7;
+constexpr int kTogetherRows = 20 * kNumCU;         // short and long rows, up to these many, in one launch,
+constexpr double kTogetherPackBytes = 2e8;         // beside up to this much packing
 
 static int run_weight_jobs(const dab_weight_job* jobs, int n_jobs, void* ws, size_t ws_bytes, hipStream_t st,
                            const dab_pack_job* packs = nullptr, int n_packs = 0) {
@@ -406,22 +428,39 @@ static int run_weight_jobs(const dab_weight_job* jobs, int n_jobs, void* ws, siz
         }
     }
     (void)ws_bytes;
+    // Short rows beside long ones: in the long ones' launch while they are few (both hand rows over to the sort kernel then).
+    // (us, two launches | one: 512 rows of 1152 weights and 256 of 8192 22.6 | 14.9, 1536 of 2304 and 512 of 12544 37.0 | 32.2, 512 of
+    // 1152 and 2048 of 9216 45.9 | 40.3, 4096 of 288 and 512 of 12544 44.7 | 44.2; 2048 of 1152 and 4096 of 5000 64.4 | 65.2,
+    // 4096 of 2304 and 4096 of 5000 77.9 | 80.2.)
+    const int longest = rows[3] ? 3 : 2;
+    const unsigned n_long = end[longest];
+    double pack_bytes = 0.0;
+    for (int i = 0; i < n_packs; ++i) pack_bytes += 4.0 * packs[i].B * packs[i].H * packs[i].W * packs[i].C;
+    const bool together = rows[0] > 0 && rows[longest] > 0 && rows[0] + rows[longest] <= kTogetherRows && pack_bytes < kTogetherPackBytes;
+    if (together) {
+        for (int i = 0; i < cls[0].n; ++i) {
+            EstJob q = cls[0].job[i];
+            q.blk_end += end[longest];
+            cls[longest].job[cls[longest].n++] = q;
+        }
+        end[longest] += end[0];
+        cls[0].n = 0;
+    }
     // the activation packing, dealt out over the launches in proportion to their duration: every tensor's
     // pixels are cut at the same fractions
     PackJobs pk[kClasses];
     unsigned n_pack[kClasses] = {0, 0, 0, 0};
-    double us[kClasses], total = 0.0, pack_bytes = 0.0;
+    double us[kClasses], total = 0.0;
     for (int c = 0; c < kClasses; ++c) {
         pk[c].n = 0;
-        us[c] = rows_us(c, rows[c]);
+        us[c] = together && c == 0 ? 0.0 : rows_us(c, rows[c]);
         total += us[c];
     }
-    for (int i = 0; i < n_packs; ++i) pack_bytes += 4.0 * packs[i].B * packs[i].H * packs[i].W * packs[i].C;
     // Rows of 9217 .. 13312 weights: 512 threads finish a row sooner, 256 finish more rows in the same time and leave
     // room for packing workgroups: 512 rows 18.5 us and 19.3, 1024 rows 30.5 and 28.4, 4096 rows 83.8 and 75.3; the
     // rows of config 3 with its packing at batch 32 (30 MB) 40.1 and 41.9, at 96 45.6 and 46.0, at 128 (120 MB) 50.7 and
     // 48.2, at 256 62.7 and 55.8.
-    const bool wide = rows[3] <= 2 * kNumCU && pack_bytes < kWidePackBytes;
+    const bool wide = rows[3] <= 2 * kNumCU && pack_bytes < kWidePackBytes && !together;
     const int class_waves[kClasses] = {4, hand.medium ? 4 : 8, 4, wide ? 8 : 4};   // (wavefronts of the class's workgroups)
     double done = 0.0;
     for (int c = 0; c < kClasses && n_packs > 0; ++c) {
@@ -445,6 +484,14 @@ static int run_weight_jobs(const dab_weight_job* jobs, int n_jobs, void* ws, siz
         if (int rc = hand.small ? DAB_ROWS(0, 256, 9, 512, 256, false, 7) : DAB_ROWS(0, 256, 9, 512, 256, true, 4)) return rc;
     if (cls[1].n)
         if (int rc = hand.medium ? DAB_ROWS(1, 256, 18, 1024, 256, false, 6) : DAB_ROWS(1, 512, 9, 2048, 256, true, 4)) return rc;
+    if (together) {
+        const int c = longest;
+        const dim3 grid(end[c] + n_pack[c]);
+        if (int rc = c == 3 ? launch(prepare_two_kernel<52, 2048, 256>, grid, dim3(256), 0, st, cls[c], pk[c], n_pack[c], n_long)
+                            : launch(prepare_two_kernel<36, 2048, 256>, grid, dim3(256), 0, st, cls[c], pk[c], n_pack[c], n_long))
+            return rc;
+        cls[c].n = 0;
+    }
     if (cls[2].n)
         if (int rc = DAB_ROWS(2, 256, 36, 2048, 256, false, 4)) return rc;
     if (cls[3].n)
