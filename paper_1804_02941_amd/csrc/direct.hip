@@ -104,7 +104,8 @@ __device__ __forceinline__ void for_each_column(Fn&& f) {
 // on its way to memory).  Streaming ("nt") for outputs above 48 MB in whole lines of 128 bytes: they reach memory while the
 // multiplies leave it idle, where written through they are still on their way when the next layers' inputs are read (the
 // six layers of the Sketch-A-Net trunk at batch 256, outputs of 59 and 126 MB: 162.4 -> 154.3 us with the 59 MB ones streamed
-// too, 2.5 % more with none; a kernel that reads such an output right away loses 0.7 us of 30 at 59 MB, 3.8 of 49 at 126).
+// too, 2.5 % more with none; a kernel that reads such an output right away loses 0.7 us of 30 at 59 MB, 3.8 of 49 at 126,
+// and a step replayed over one set of buffers, which the memory-side cache then partly holds, 151 -> 156).
 // Device-scope write-through ("sc1") for the smaller ones, which the memory-side cache absorbs: their stores otherwise pile up
 // behind the end of the kernel (12 to 16 % with the default policy at 15 to 60 MB).  Rows that are not whole
 // lines leave both ends of a tile's row in parts: streamed, such outputs above 96 MB took 1.2 to 1.9 times as long as with

@@ -142,7 +142,7 @@ def main():
              "prepare_rows_kernel<256, 52,...> (conv6's weight side + the rest of the packing), binarize_sort_kernel (the rows they flag: none here), then",
              "the six products: binconv_direct_kernel<1, 5, false, false> grid 131072 is conv2, <2, 3, true, false> conv3,",
              "<4, 3, true, false> grid 115712 conv4 and conv5, binconv_block_kernel<false, false, 8, 16, 4> grid 65536 conv6 and",
-             "<false, false, 2, 4, 4> grid 16384 fc7.  The other rows belong to the measurements beside the headline: the separate",
+             "<false, false, 4, 4, 4> grid 32768 fc7.  The other rows belong to the measurements beside the headline: the separate",
              "calls of the stage table, the chain that hands bits on (product kernels whose BITS argument is true), the training side, the",
              "weights-only layers (wbin_patch_kernel, wbin_direct_kernel), configurations 2, 4 and 5 (config 5's",
              "weight sides are the binarize_rows_kernel launches with grids 2097152 and 1048576), batch 32, and the popcount-rate probe.", "",
