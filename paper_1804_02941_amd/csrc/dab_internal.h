@@ -90,6 +90,9 @@ struct DirectGeom {
     int store_policy;              // of the fp32 output's 16-byte stores
     FastDiv d_HoWo, d_Wo, d_WH;
 };
+// Buffer offsets past every tensor of these kernels: a load from there returns 0, a store to there is dropped.  Operands
+// are below 2^30 bytes (and two such offsets may be added: the sum has to stay past them too), fp32 outputs below 2^31.
+constexpr uint32_t kOob = 0x7FFFFFF0u, kOobStore = 0x80000000u;
 enum { kStorePlain = 0, kStoreThrough = 1, kStoreStream = 2 };
 struct DirectPlan {
     DirectGeom g;

@@ -32,7 +32,6 @@ namespace dab {
 
 constexpr int kDirNTile = 128;              // filters per workgroup
 constexpr int kDirGroupTable = 64;          // >= load groups of a tile (36) + two rounds of lookahead
-constexpr uint32_t kOob = 0x7FFFFFF0u;      // a buffer offset past every tensor: such loads return 0
 
 // bit 4i + d of x -> sign bit of nibble i of dword d, magnitude 1.0: the A fragment of 32 channels.
 // m8 / m2 are 0x88888888 / 0x22222222, or zero for a tap outside the image.
@@ -573,11 +572,11 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const uint32_t* __r
             // the one lane whose four filters the last one is among, of each by itself.  A 16-byte store needs 4-byte alignment
             // only, so rows of any number of filters take it.  (As single
             // values: 111475 pixels x 9 steps x 175 filters 44.0 us, now 23.0; 78608 x 18 x 182 45.7 and 23.7.)
-            uint32_t off4 = fl + 4 <= g.F ? lane_off : kOob, off1[3];
+            uint32_t off4 = fl + 4 <= g.F ? lane_off : kOobStore, off1[3];
             asm volatile("" : "+v"(off4));
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                off1[j] = fl + 4 > g.F && fl + j < g.F ? lane_off + 4 * j : kOob;
+                off1[j] = fl + 4 > g.F && fl + j < g.F ? lane_off + 4 * j : kOobStore;
                 asm volatile("" : "+v"(off1[j]));
             }
             const bool tail = (g.F & 3) != 0 && f0 + kDirNTile > g.F;

@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 
 #include "dab_internal.h"
 #include "wbin.h"
@@ -49,6 +50,8 @@ int check_one(const dab_conv_desc& d) {
         REQUIRE(1ull * g.y_bytes == 4ull * static_cast<unsigned long long>(M) * static_cast<unsigned long long>(d.F));
         REQUIRE(1ull * g.a_bytes == 4ull * d.B * d.H * d.W * g.Cw);
         REQUIRE(!dp.pad || g.T <= 32);
+        // the offsets that drop a load or a store lie past the tensors
+        REQUIRE(g.y_bytes <= kOobStore && g.a_bytes <= (1u << 30));
     }
     for (int large = 0; large < 2; ++large) {
         BlockPlan bp;
@@ -79,6 +82,7 @@ int check_one(const dab_conv_desc& d) {
         REQUIRE(1ll * sg.units == 1ll * sg.n_mtiles * ((d.F + 127) / 128));
         REQUIRE(sp.grid == 8u * static_cast<unsigned>(sg.per_xcd) && 8ll * sg.per_xcd >= sg.units);
         REQUIRE(1ull * sg.e_bytes == 4ull * sp.g.T * sp.g.Cw * sp.g.Fp && sg.e_bytes < (1u << 30));
+        REQUIRE(sp.g.a_bytes <= (1u << 30));
         REQUIRE(sp.lds_bytes == (ks > 1 ? 131072u : 0u));
         REQUIRE(!sp.pad || sp.g.T <= 32);
         REQUIRE(1ll * d.C * d.kh * d.kw < (1ll << 24));
@@ -169,6 +173,13 @@ int main(int argc, char** argv) {
             }
         }
         return 0;
+    }
+    // outputs of 2^29 - 1, - 2 and - 4 values, the largest that the persistent kernel takes, and one that it does not
+    for (const auto& [B, F] : {std::pair{2304167, 233}, {4227330, 127}, {4194303, 128}, {4194304, 128}}) {
+        const dab_conv_desc d{B, 32, 1, 1, F, 1, 1, 0, 0, 1, 1};
+        dab::DirectPlan dp;
+        REQUIRE(dab::plan_direct(d, &dp) == (1ll * B * F < (1ll << 29)));
+        if (check_one(d)) return 1;
     }
     const int cases = argc > 1 ? std::atoi(argv[1]) : 20000;
     g_state = argc > 2 ? static_cast<uint64_t>(std::atoll(argv[2])) * 2 + 1 : 1;

@@ -32,6 +32,8 @@ def _signs(words, n):
     # of any length, streamed above 48 MB in rows of 128-byte lines
     (70001, 320, 125), (70001, 320, 126), (70001, 320, 127), (70001, 320, 129), (70001, 320, 130), (70001, 320, 131),
     (70001, 320, 132), (70001, 320, 1), (100001, 320, 160),
+    # outputs of 2^29 - 1 and 2^29 - 2 values: nothing that a lane must not store lands on the last ones
+    (2304167, 32, 233), (4227330, 32, 127),
 ])
 def test_sums_of_shares(B, K, F):
     g = torch.Generator(device=DEV)
