@@ -100,11 +100,14 @@ __device__ __forceinline__ void for_each_column(Fn&& f) {
     }
 }
 // Cache policy of the output stores (measured on MI355X; a policy changes only where the data waits
-// on its way to memory).  Streaming ("nt") for outputs above 48 MB in whole lines of 128 bytes: they reach memory while the
-// multiplies leave it idle, where written through they are still on their way when the next layers' inputs are read (the
-// six layers of the Sketch-A-Net trunk at batch 256, outputs of 59 and 126 MB: 162.4 -> 154.3 us with the 59 MB ones streamed
-// too, 2.5 % more with none; a kernel that reads such an output right away loses 0.7 us of 30 at 59 MB, 3.8 of 49 at 126,
-// and a step replayed over one set of buffers, which the memory-side cache then partly holds, 151 -> 156).
+// on its way to memory).  Streaming ("nt") for outputs above 96 MB in whole lines of 128 bytes: they reach memory while the
+// multiplies leave it idle, and leave the memory-side cache to the operands.  Smaller ones are read from that cache by what comes
+// behind the layer, which streaming takes away.  (us, written through | streamed; the product alone over outputs in turn, over
+// one output, with packing of the output behind it, with an in-place ReLU: 56 MB of 256 filters 21.4 | 22.5, 18.9 | 22.4,
+// 29.4 | 32.0, 37.9 | 43.7; 80 MB of 64 25.8 | 25.3, 22.0 | 22.7, 35.8 | 37.1, 52.0 | 56.9; 128 MB of 64 38.7 | 36.0, 31.5 | 32.2,
+// 51.0 | 52.9, 77.5 | 83.4; 160 MB of 128 48.3 | 44.0, 39.8 | 39.5, 63.7 | 66.4, 100.5 | 104.2.  The six layers of the Sketch-A-Net
+// trunk at batch 256, outputs of 59 and 126 MB, with their weight sides, streamed above 48 MB | above 96 MB | never: outputs in
+// turn 154.7 | 158.9 | 161.9, one set of them 153.8 | 147.9 | 159.2, each packed 209.4 | 203.9 | 202.9, behind a ReLU 284 | 266 | 261.)
 // Device-scope write-through ("sc1") for the smaller ones, which the memory-side cache absorbs: their stores otherwise pile up
 // behind the end of the kernel (12 to 16 % with the default policy at 15 to 60 MB).  Rows that are not whole
 // lines leave both ends of a tile's row in parts: streamed, such outputs above 96 MB took 1.2 to 1.9 times as long as with
@@ -1141,7 +1144,7 @@ static bool describe(const dab_conv_desc& d, DirectGeom* pg, bool* pad, int* lw)
     g.M = static_cast<int>(M);
     g.a_bytes = static_cast<uint32_t>(a_bytes);
     g.y_bytes = static_cast<uint32_t>(M * d.F * 4);
-    g.store_policy = d.F % 4 ? kStorePlain : (g.y_bytes > (48u << 20) && d.F % 32 == 0 ? kStoreStream : kStoreThrough);
+    g.store_policy = d.F % 4 ? kStorePlain : (g.y_bytes > (96u << 20) && d.F % 32 == 0 ? kStoreStream : kStoreThrough);
     g.pix_bytes = g.Cw * 4;
     g.nk = static_cast<int>(nk);
     g.odd = g.Cw & 1;

@@ -3,6 +3,7 @@
 // ABI (with placeholder pointers; without a GPU every call ends before a launch).  Checks the
 // invariants the kernels rely on.  Usage: fuzz_plans [cases] [seed]; or fuzz_plans route followed by the
 // eleven numbers of a layer's descriptor, any number of times: which kernel computes it, fp32 and packed-sign output;
+// or plan and the same numbers: the kernel of the fp32 form and what its plan chose;
 // or wbin and the same numbers: the form of the weights-only layer.
 #include <cstdio>
 #include <cstdlib>
@@ -171,6 +172,20 @@ int main(int argc, char** argv) {
                 if (dab::product_of(d, bits, &which) != DAB_OK) return 1;
                 std::printf("%s%c", names[static_cast<int>(which)], bits ? '\n' : ' ');
             }
+        }
+        return 0;
+    }
+    if (argc > 1 && std::strcmp(argv[1], "plan") == 0) {
+        static const char* const stores[] = {"plain", "through", "streamed"};
+        for (int a = 2; a + 11 <= argc; a += 11) {
+            int32_t v[11];
+            for (int i = 0; i < 11; ++i) v[i] = std::atoi(argv[a + i]);
+            const dab_conv_desc d{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10]};
+            dab::Product which;
+            dab::DirectPlan dp;
+            if (dab::product_of(d, false, &which) != DAB_OK) return 1;
+            if (which == dab::Product::kDirect && dab::plan_direct(d, &dp)) std::printf("direct %s\n", stores[dp.g.store_policy]);
+            else std::printf("other\n");
         }
         return 0;
     }

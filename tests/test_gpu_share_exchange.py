@@ -29,9 +29,9 @@ def _signs(words, n):
     (33, 960, 70), (33, 1024, 33), (33, 1088, 40), (31, 1984, 64), (31, 2048, 64), (2, 33, 1), (9, 256, 65),
     (2048, 960, 100), (2049, 960, 100), (2049, 768, 37), (2049, 1088, 100),
     # many rows, the mask panel in LDS: last filters alone, in twos and in threes, whole and part tiles; 16-byte stores of rows
-    # of any length, streamed above 48 MB in rows of 128-byte lines
+    # of any length, streamed above 96 MB in rows of 128-byte lines
     (70001, 320, 125), (70001, 320, 126), (70001, 320, 127), (70001, 320, 129), (70001, 320, 130), (70001, 320, 131),
-    (70001, 320, 132), (70001, 320, 1), (100001, 320, 160),
+    (70001, 320, 132), (70001, 320, 1), (100001, 320, 160), (170001, 320, 160),
     # outputs of 2^29 - 1 and 2^29 - 2 values: nothing that a lane must not store lands on the last ones
     (2304167, 32, 233), (4227330, 32, 127),
 ])

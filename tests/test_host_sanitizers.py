@@ -34,10 +34,10 @@ def test_random_geometries_through_the_host_code(fuzz, seed):
     assert "geometries checked" in p.stdout
 
 
-def routes(fuzz, layers):
+def routes(fuzz, layers, mode="route"):
     """[(kernel of the fp32 form, of the packed-sign form)] of layers (B, C, H, W, F, k, pad, stride)."""
     args = [str(v) for B, C, H, W, F, k, p, s in layers for v in (B, C, H, W, F, k, k, p, p, s, s)]
-    out = subprocess.run([fuzz, "route", *args], capture_output=True, text=True, check=True).stdout
+    out = subprocess.run([fuzz, mode, *args], capture_output=True, text=True, check=True).stdout
     return [tuple(line.split()) for line in out.splitlines()]
 
 
@@ -52,6 +52,20 @@ def test_long_reductions_take_the_kernel_that_measured_faster(fuzz):
     }
     for kernel, ls in layers.items():
         assert routes(fuzz, ls) == [(kernel, kernel)] * len(ls)
+
+
+# The persistent kernel's outputs: what reads one of up to 96 MB finds it in the memory-side cache.
+STORES = {
+    "through": [(64, 64, 56, 56, 64, 3, 1, 1), (255, 256, 15, 15, 256, 3, 1, 1), (200, 64, 35, 35, 128, 5, 0, 1), (52, 128, 28, 28, 512, 1, 0, 1),
+                (98303, 320, 1, 1, 256, 1, 0, 1), (98304, 320, 1, 1, 256, 1, 0, 1), (200000, 320, 1, 1, 132, 1, 0, 1)],
+    "streamed": [(98305, 320, 1, 1, 256, 1, 0, 1), (256, 64, 35, 35, 128, 5, 0, 1), (170001, 320, 1, 1, 160, 1, 0, 1)],
+    "plain": [(19044, 320, 1, 1, 290, 1, 0, 1), (200000, 320, 1, 1, 133, 1, 0, 1)],
+}
+
+
+@pytest.mark.parametrize("policy", STORES)
+def test_outputs_that_the_memory_side_cache_holds_are_not_streamed(fuzz, policy):
+    assert routes(fuzz, STORES[policy], "plan") == [("direct", policy)] * len(STORES[policy])
 
 
 def test_the_gpu_tests_of_the_long_reduction_kernels_reach_them(fuzz):
