@@ -163,7 +163,7 @@ struct Entry<Fn> {
 };
 
 // ---------------------------------------------------------------- whole calls
-// A layer's call with nothing unusual about it, sizes, output and workspace check included: the tensors plain fp32 / int32
+// A layer's call with nothing unusual about it, sizes, output and workspace included: the tensors plain fp32 / int32
 // ones on the GPU, contiguous and not empty, numbers Python ints, no mode active.  Whatever is not so is left to the binding's
 // Python, which does the same by the entry points above or raises: the functions then return None, before anything is
 // launched.  Sizes read, the output allocated and the checks done in Python were 1.7 us of a call of 5.9: 16 x 4096 -> 4096,
@@ -211,49 +211,68 @@ int64_t extent(int32_t in, int32_t pad, int32_t k, int32_t stride) {
 }
 int64_t words(int64_t n) { return (n + 31) / 32; }
 
-// The output: the caller's, or a new one.
-struct Output {
+// The buffers of a call: the output and the workspace (if one is needed) are the caller's, or new ones.  (A missing workspace left
+// to Python cost an exception and the output allocated twice: 8192 x 2400 -> 1284 without one 7.9 us of host time, 10.2 with a new
+// output, by Python alone 6.4 and 7.9, now 5.8 and 6.3.)
+struct Buffers {
     PyObject* given;
-    at::Tensor made;
-    void* ptr;
-    Output(PyObject* out, at::ScalarType type, at::IntArrayRef shape, const at::Tensor& beside) : given(out) {
-        if (out != Py_None) {
-            ptr = plain(out, type).data_ptr();
-            return;
-        }
-        made = at::empty(shape, at::TensorOptions().dtype(type).device(beside.device()));
-        ptr = made.data_ptr();
+    at::ScalarType type;
+    c10::SmallVector<int64_t, 4> shape;
+    c10::Device device;
+    size_t ws_bytes = 0;
+    at::Tensor made, scratch;
+    void *out = nullptr, *ws = nullptr;
+
+    Buffers(PyObject* o, at::ScalarType t, std::initializer_list<int64_t> s, const at::Tensor& beside)
+        : given(o), type(t), shape(s), device(beside.device()) {
+        if (o != Py_None) out = plain(o, t).data_ptr();
     }
-    template <typename T>
-    T* as() const { return static_cast<T*>(ptr); }
+    Buffers& workspace(size_t nbytes, PyObject* o) {
+        ws_bytes = nbytes;
+        if (nbytes == 0 || o == Py_None) return *this;
+        if (!THPVariable_CheckExact(o)) throw Unusual{};
+        const at::Tensor& t = THPVariable_Unpack(o);
+        if (!t.is_cuda()) throw Unusual{};
+        if (t.nbytes() >= nbytes) ws = t.data_ptr();
+        return *this;
+    }
+    void allocate() {
+        if (out == nullptr) {
+            made = at::empty(shape, at::TensorOptions().dtype(type).device(device));
+            out = made.data_ptr();
+        }
+        if (ws_bytes != 0 && ws == nullptr) {
+            scratch = at::empty({static_cast<int64_t>(ws_bytes)}, at::TensorOptions().dtype(at::kByte).device(device));
+            ws = scratch.data_ptr();
+        }
+    }
     PyObject* result() {
         if (given == Py_None) return THPVariable_Wrap(std::move(made));
         Py_INCREF(given);
         return given;
     }
 };
-void* workspace(size_t nbytes, PyObject* ws) {
-    if (nbytes == 0) return nullptr;
-    if (!THPVariable_CheckExact(ws)) throw Unusual{};
-    const at::Tensor& t = THPVariable_Unpack(ws);
-    if (!t.is_cuda() || t.nbytes() < nbytes) throw Unusual{};
-    return t.data_ptr();
-}
+struct WithoutGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
 
-// Sizes and pointers by `prepare` (which may find the call unusual), then the launch.
+// Sizes and pointers by `prepare` (which may find the call unusual), then the new buffers and the launch, without the
+// interpreter's lock: an allocation may wait for the device, and other threads run on meanwhile, as during torch.empty.
 template <size_t N, typename Prepare>
 PyObject* whole_call(const char* name, Py_ssize_t n, Prepare&& prepare) {
     if (n != static_cast<Py_ssize_t>(N)) return PyErr_Format(PyExc_TypeError, "%s takes %zu arguments, got %zd", name, N, n);
     try {
         if (at::impl::torch_function_mode_enabled() || c10::impl::dispatch_mode_enabled()) Py_RETURN_NONE;
-        auto [output, enqueue] = prepare();
-        void* stream = c10::hip::getCurrentHIPStream().stream();
+        auto [buffers, enqueue] = prepare();
         int rc;
-        Py_BEGIN_ALLOW_THREADS
-        rc = enqueue(stream);
-        Py_END_ALLOW_THREADS
+        {
+            WithoutGil released;
+            buffers.allocate();
+            rc = enqueue(buffers, c10::hip::getCurrentHIPStream().stream());
+        }
         if (rc != 0) return PyObject_CallFunction(g_failed, "si", name, rc);
-        return output.result();
+        return buffers.result();
     } catch (...) {
         // not a plain call, or torch has refused something: Python meets the same and reports it
         Py_RETURN_NONE;
@@ -270,9 +289,9 @@ PyObject* pack_activations(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int32_t B = whole(X.size(0)), C = whole(flat ? X.size(1) : X.size(nhwc ? 3 : 1));
         const int32_t H = flat ? 1 : whole(X.size(nhwc ? 1 : 2)), W = flat ? 1 : whole(X.size(nhwc ? 2 : 3));
         const float *x = address<const float>(a[0]), *tau = address_or_none<const float>(a[2]);
-        Output A(a[3], at::kInt, {B, H, W, words(C)}, X);
-        uint32_t* out = A.as<uint32_t>();
-        return std::pair(std::move(A), [=](void* st) { return ::dab_pack_activations(x, layout, B, C, H, W, tau, out, st); });
+        return std::pair(Buffers(a[3], at::kInt, {B, H, W, words(C)}, X), [=](const Buffers& b, void* st) {
+            return ::dab_pack_activations(x, layout, B, C, H, W, tau, static_cast<uint32_t*>(b.out), st);
+        });
     });
 }
 // (desc, A_packed, E_packed, alpha, beta, out, ws)
@@ -282,11 +301,11 @@ PyObject* binconv2d(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& A = plain(a[1], at::kInt);
         const auto *bits = reinterpret_cast<const uint32_t*>(A.data_ptr()), *E = reinterpret_cast<const uint32_t*>(address<int32_t>(a[2]));
         const float *alpha = address<const float>(a[3]), *beta = address<const float>(a[4]);
-        Output Y(a[5], at::kFloat, {whole(d.B), extent(d.H, d.pad_h, d.kh, d.stride_h), extent(d.W, d.pad_w, d.kw, d.stride_w), whole(d.F)}, A);
-        float* out = Y.as<float>();
-        const size_t nbytes = ::dab_binconv2d_workspace_bytes(&d);
-        void* ws = workspace(nbytes, a[6]);
-        return std::pair(std::move(Y), [=](void* st) { return ::dab_binconv2d(&d, bits, E, alpha, beta, out, nullptr, ws, nbytes, st); });
+        Buffers Y(a[5], at::kFloat, {whole(d.B), extent(d.H, d.pad_h, d.kh, d.stride_h), extent(d.W, d.pad_w, d.kw, d.stride_w), whole(d.F)}, A);
+        Y.workspace(::dab_binconv2d_workspace_bytes(&d), a[6]);
+        return std::pair(std::move(Y), [=](const Buffers& b, void* st) {
+            return ::dab_binconv2d(&d, bits, E, alpha, beta, static_cast<float*>(b.out), nullptr, b.ws, b.ws_bytes, st);
+        });
     });
 }
 // (desc, A_packed, E_packed, alpha, beta, tau_out, out, ws)
@@ -296,12 +315,12 @@ PyObject* binconv2d_bits(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& A = plain(a[1], at::kInt);
         const auto *bits = reinterpret_cast<const uint32_t*>(A.data_ptr()), *E = reinterpret_cast<const uint32_t*>(address<int32_t>(a[2]));
         const float *alpha = address<const float>(a[3]), *beta = address<const float>(a[4]), *tau = address_or_none<const float>(a[5]);
-        Output next(a[6], at::kInt,
-                    {whole(d.B), extent(d.H, d.pad_h, d.kh, d.stride_h), extent(d.W, d.pad_w, d.kw, d.stride_w), words(whole(d.F))}, A);
-        uint32_t* out = next.as<uint32_t>();
-        const size_t nbytes = ::dab_binconv2d_workspace_bytes(&d);
-        void* ws = workspace(nbytes, a[7]);
-        return std::pair(std::move(next), [=](void* st) { return ::dab_binconv2d_bits(&d, bits, E, alpha, beta, tau, out, ws, nbytes, st); });
+        Buffers next(a[6], at::kInt,
+                     {whole(d.B), extent(d.H, d.pad_h, d.kh, d.stride_h), extent(d.W, d.pad_w, d.kw, d.stride_w), words(whole(d.F))}, A);
+        next.workspace(::dab_binconv2d_workspace_bytes(&d), a[7]);
+        return std::pair(std::move(next), [=](const Buffers& b, void* st) {
+            return ::dab_binconv2d_bits(&d, bits, E, alpha, beta, tau, static_cast<uint32_t*>(b.out), b.ws, b.ws_bytes, st);
+        });
     });
 }
 // (A_packed, E_packed, alpha, beta, Kin, out, ws)
@@ -312,12 +331,11 @@ PyObject* binfc(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int32_t B = whole(A.size(0)), F = whole(al.size(0)), Kin = small_int(a[4]);
         const auto *bits = reinterpret_cast<const uint32_t*>(A.data_ptr()), *E = reinterpret_cast<const uint32_t*>(address<int32_t>(a[1]));
         const float *alpha = address<const float>(a[2]), *beta = address<const float>(a[3]);
-        Output Y(a[5], at::kFloat, {B, F}, A);
-        float* out = Y.as<float>();
-        const size_t nbytes = ::dab_binfc_workspace_bytes(B, Kin, F);
-        void* ws = workspace(nbytes, a[6]);
-        return std::pair(std::move(Y),
-                         [=](void* st) { return ::dab_binfc(B, Kin, F, bits, E, alpha, beta, out, nullptr, ws, nbytes, st); });
+        Buffers Y(a[5], at::kFloat, {B, F}, A);
+        Y.workspace(::dab_binfc_workspace_bytes(B, Kin, F), a[6]);
+        return std::pair(std::move(Y), [=](const Buffers& b, void* st) {
+            return ::dab_binfc(B, Kin, F, bits, E, alpha, beta, static_cast<float*>(b.out), nullptr, b.ws, b.ws_bytes, st);
+        });
     });
 }
 // (A_packed, C, kh, kw, stride_h, stride_w, out)
@@ -328,9 +346,9 @@ PyObject* pool_bits(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int32_t B = whole(A.size(0)), H = whole(A.size(1)), W = whole(A.size(2));
         const int32_t C = small_int(a[1]), kh = small_int(a[2]), kw = small_int(a[3]), sh = whole(small_int(a[4])), sw = whole(small_int(a[5]));
         const auto* bits = reinterpret_cast<const uint32_t*>(A.data_ptr());
-        Output pooled(a[6], at::kInt, {B, extent(H, 0, kh, sh), extent(W, 0, kw, sw), A.size(3)}, A);
-        uint32_t* out = pooled.as<uint32_t>();
-        return std::pair(std::move(pooled), [=](void* st) { return ::dab_pool_bits(bits, B, C, H, W, kh, kw, sh, sw, out, st); });
+        return std::pair(Buffers(a[6], at::kInt, {B, extent(H, 0, kh, sh), extent(W, 0, kw, sw), A.size(3)}, A), [=](const Buffers& b, void* st) {
+            return ::dab_pool_bits(bits, B, C, H, W, kh, kw, sh, sw, static_cast<uint32_t*>(b.out), st);
+        });
     });
 }
 // (desc, X, E_packed, alpha, beta, out, ws)
@@ -341,11 +359,11 @@ PyObject* wbin_conv2d(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const float* x = address<const float>(a[1]);
         const auto* E = reinterpret_cast<const uint32_t*>(address<int32_t>(a[2]));
         const float *alpha = address<const float>(a[3]), *beta = address<const float>(a[4]);
-        Output Y(a[5], at::kFloat, {whole(d.B), extent(d.H, d.pad_h, d.kh, d.stride_h), extent(d.W, d.pad_w, d.kw, d.stride_w), whole(d.F)}, X);
-        float* out = Y.as<float>();
-        const size_t nbytes = ::dab_wbin_conv2d_workspace_bytes(&d);
-        void* ws = workspace(nbytes, a[6]);
-        return std::pair(std::move(Y), [=](void* st) { return ::dab_wbin_conv2d(&d, x, E, alpha, beta, out, ws, nbytes, st); });
+        Buffers Y(a[5], at::kFloat, {whole(d.B), extent(d.H, d.pad_h, d.kh, d.stride_h), extent(d.W, d.pad_w, d.kw, d.stride_w), whole(d.F)}, X);
+        Y.workspace(::dab_wbin_conv2d_workspace_bytes(&d), a[6]);
+        return std::pair(std::move(Y), [=](const Buffers& b, void* st) {
+            return ::dab_wbin_conv2d(&d, x, E, alpha, beta, static_cast<float*>(b.out), b.ws, b.ws_bytes, st);
+        });
     });
 }
 // (X, E_packed, alpha, beta, out, ws)
@@ -357,11 +375,11 @@ PyObject* wbin_fc(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const float* x = address<const float>(a[0]);
         const auto* E = reinterpret_cast<const uint32_t*>(address<int32_t>(a[1]));
         const float *alpha = address<const float>(a[2]), *beta = address<const float>(a[3]);
-        Output Y(a[4], at::kFloat, {B, F}, X);
-        float* out = Y.as<float>();
-        const size_t nbytes = ::dab_wbin_fc_workspace_bytes(B, Kin, F);
-        void* ws = workspace(nbytes, a[5]);
-        return std::pair(std::move(Y), [=](void* st) { return ::dab_wbin_fc(B, Kin, F, x, E, alpha, beta, out, ws, nbytes, st); });
+        Buffers Y(a[4], at::kFloat, {B, F}, X);
+        Y.workspace(::dab_wbin_fc_workspace_bytes(B, Kin, F), a[5]);
+        return std::pair(std::move(Y), [=](const Buffers& b, void* st) {
+            return ::dab_wbin_fc(B, Kin, F, x, E, alpha, beta, static_cast<float*>(b.out), b.ws, b.ws_bytes, st);
+        });
     });
 }
 PyMethodDef whole_def(const char* name, PyObject* (*fn)(PyObject*, PyObject* const*, Py_ssize_t)) {

@@ -98,3 +98,38 @@ def test_refusals_are_those_of_the_entry_points(call):
         dab.dab_binfc(A.view(2, -1), A, X[0].contiguous(), X[0].contiguous(), 1)
     with pytest.raises(dab.DabError, match="dab_pool_bits failed"):
         dab.dab_pool_bits(A, 64, 3, 3, 1, 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("own", [False, True])
+def test_calls_that_need_a_workspace_are_done_whole(call, own, monkeypatch):
+    """Without a workspace, or with one that is too small, the call makes one itself: one allocation for it and one for the output,
+    and what Python returns."""
+    dev = "cuda:0"
+    g = torch.Generator(device=dev)
+    g.manual_seed(6)
+    words = lambda *shape: torch.randint(-2**31, 2**31 - 1, shape, generator=g, device=dev).to(torch.int32)
+    al, be = torch.rand(1284, generator=g, device=dev), -torch.rand(1284, generator=g, device=dev)
+    d = dab.dab_conv_desc(160, 320, 12, 12, 640, 3, 3, 0, 0, 1, 1)
+    A, E, Af, Ef = words(160, 12, 12, 10), words(90, 640), words(8192, 75), words(75, 1344)
+    Ef[:, 1284:] = 0
+    X, V = torch.randn(2, 12, 12, 320, generator=g, device=dev), torch.randn(9, 2400, generator=g, device=dev)
+    dw = dab.dab_conv_desc(2, 320, 12, 12, 640, 3, 3, 0, 0, 1, 1)
+    assert dab.lib().dab_binconv2d_workspace_bytes(d) > 1 < dab.lib().dab_binfc_workspace_bytes(8192, 2400, 1284)
+    ws = torch.empty(1, dtype=torch.uint8, device=dev) if own else None
+    for name, f in (("binconv2d", lambda: dab.dab_binconv2d(d, A, E, al, be, ws=ws)),
+                    ("binconv2d_bits", lambda: dab.dab_binconv2d_bits(d, A, E, al, be, al, ws=ws)),
+                    ("binfc", lambda: dab.dab_binfc(Af, Ef, al, be, 2400, ws=ws)),
+                    ("wbin_conv2d", lambda: dab.dab_wbin_conv2d(dw, X, E, al, be, ws=ws)),
+                    ("wbin_fc", lambda: dab.dab_wbin_fc(V, Ef, al, be, ws=ws))):
+        taken = []
+        whole = getattr(call, name)
+        proxy = type("Counting", (), {k: staticmethod(getattr(call, k)) for k in dir(call) if not k.startswith("__")})
+        setattr(proxy, name, staticmethod(lambda *a: taken.append(whole(*a)) or taken[-1]))
+        monkeypatch.setattr(dab, "_native", proxy)
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        got = f()
+        assert taken[-1] is got and torch.cuda.memory_stats()["allocation.all.allocated"] - before == 2, name
+        setattr(proxy, name, staticmethod(lambda *a: None))
+        assert torch.equal(f(), got), name
+        monkeypatch.setattr(dab, "_native", call)
