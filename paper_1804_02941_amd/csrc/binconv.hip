@@ -879,7 +879,7 @@ static int plan_product(const dab_conv_desc& d, bool bits, ProductPlans* p, Prod
     // is 0.7 % slower than the fastest in the geometric mean.  (us, persistent | blocks | split, fp32:) 7290 pixels x 18
     // steps x 519 filters 10.7 | 16.6 | 12.4, 52200 x 20 x 88 11.6 | 21.1 | 14.3; 864 x 25 x 382 12.6 | 4.9 | 7.3, 16473 x 12 x 19
     // 7.8 | 4.0 | 7.3; 3648 x 25 x 487 14.0 | 11.0 | 8.6, 12544 x 36 x 115 13.0 | 9.9 | 7.7.
-    if (plan_direct(d, &p->direct)) {
+    if ((bits || d.F <= kDirMaxFilters) && plan_direct(d, &p->direct)) {
         *which = Product::kDirect;
         const double direct = short_direct_us(p->direct, bits);
         double best = direct;
@@ -1022,7 +1022,7 @@ size_t dab_binconv2d_workspace_bytes(const dab_conv_desc* d) {
     dab::DirectPlan dp;
     if (!d || dab::check_desc(d) != DAB_OK) return 0;
     dab::BlockPlan bp;
-    if (dab::plan_block(*d, &bp, false) || dab::plan_direct(*d, &dp) || dab::plan_block(*d, &bp, true)) return 0;
+    if (dab::plan_block(*d, &bp, false) || (d->F <= dab::kDirMaxFilters && dab::plan_direct(*d, &dp)) || dab::plan_block(*d, &bp, true)) return 0;
     if (dab::plan_binconv(*d, &pl) != DAB_OK) return 0;
     return pl.ws_bytes;
 }

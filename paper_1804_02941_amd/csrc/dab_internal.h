@@ -93,6 +93,9 @@ struct DirectGeom {
 // Buffer offsets past every tensor of these kernels: a load from there returns 0, a store to there is dropped.  Operands
 // are below 2^30 bytes (and two such offsets may be added: the sum has to stay past them too), fp32 outputs below 2^31.
 constexpr uint32_t kOob = 0x7FFFFFF0u, kOobStore = 0x80000000u;
+// Filters up to which the persistent kernel writes fp32: the offsets of the 64 rows of a tile, those past the last pixel
+// among them, have to fit in 32 bits.
+constexpr int kDirMaxFilters = 1 << 24;
 enum { kStorePlain = 0, kStoreThrough = 1, kStoreStream = 2 };
 struct DirectPlan {
     DirectGeom g;

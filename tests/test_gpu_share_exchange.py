@@ -34,6 +34,8 @@ def _signs(words, n):
     (70001, 320, 132), (70001, 320, 1), (100001, 320, 160), (170001, 320, 160),
     # outputs of 2^29 - 1 and 2^29 - 2 values: nothing that a lane must not store lands on the last ones
     (2304167, 32, 233), (4227330, 32, 127),
+    # rows so long that 64 of them take more than 32 bits of offset
+    (2, 64, 18400001),
 ])
 def test_sums_of_shares(B, K, F):
     g = torch.Generator(device=DEV)

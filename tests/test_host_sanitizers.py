@@ -54,6 +54,11 @@ def test_long_reductions_take_the_kernel_that_measured_faster(fuzz):
         assert routes(fuzz, ls) == [(kernel, kernel)] * len(ls)
 
 
+def test_fp32_outputs_of_more_filters_than_its_row_offsets_reach_leave_the_persistent_kernel(fuzz):
+    wide = [(B, 64, 1, 1, F, 1, 0, 1) for B, F in ((1, 1 << 24), (1, (1 << 24) + 1), (2, 18400000), (29, 18400000))]
+    assert routes(fuzz, wide) == [("direct", "direct")] + [("split", "direct")] * 3
+
+
 # The persistent kernel's outputs: what reads one of up to 96 MB finds it in the memory-side cache.
 STORES = {
     "through": [(64, 64, 56, 56, 64, 3, 1, 1), (255, 256, 15, 15, 256, 3, 1, 1), (200, 64, 35, 35, 128, 5, 0, 1), (52, 128, 28, 28, 512, 1, 0, 1),
