@@ -84,6 +84,7 @@ int check_one(const dab_conv_desc& d) {
         REQUIRE(sp.grid == 8u * static_cast<unsigned>(sg.per_xcd) && 8ll * sg.per_xcd >= sg.units);
         REQUIRE(1ull * sg.e_bytes == 4ull * sp.g.T * sp.g.Cw * sp.g.Fp && sg.e_bytes < (1u << 30));
         REQUIRE(sp.g.a_bytes <= (1u << 30));
+        REQUIRE((sg.narrow != 0) == (ks > 1 && 1ll * d.C * d.kh * d.kw < (1 << 15)));    // (a sum of 2^15 terms has no 16 bits)
         REQUIRE(sp.lds_bytes == (ks > 1 ? 131072u : 0u));
         REQUIRE(!sp.pad || sp.g.T <= 32);
         REQUIRE(1ll * d.C * d.kh * d.kw < (1ll << 24));
@@ -183,9 +184,15 @@ int main(int argc, char** argv) {
             const dab_conv_desc d{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10]};
             dab::Product which;
             dab::DirectPlan dp;
+            dab::SplitPlan sp;
+            dab::BlockPlan bp;
             if (dab::product_of(d, false, &which) != DAB_OK) return 1;
             if (which == dab::Product::kDirect && dab::plan_direct(d, &dp)) std::printf("direct %s\n", stores[dp.g.store_policy]);
-            else std::printf("other\n");
+            else if (which == dab::Product::kSplit && dab::plan_split(d, &sp))
+                std::printf("split w%d s%d %s\n", sp.lw, 1 << sp.sg.log_ks, !sp.sg.log_ks ? "alone" : sp.sg.narrow ? "16-bit" : "fp32");
+            else if (which == dab::Product::kBlock && dab::plan_block(d, &bp, true))
+                std::printf("block w%d s%d depth%d\n", bp.lw, bp.waves, bp.depth);
+            else std::printf("expanded\n");
         }
         return 0;
     }

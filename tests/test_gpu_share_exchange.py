@@ -19,24 +19,32 @@ def _signs(words, n):
     return bits.reshape(words.shape[0], -1)[:, :n].float()
 
 
-# rows, terms, filters: two, four and eight shares at most; 2^15 - 1 terms are the last in 16 bits
-@pytest.mark.parametrize("B,K,F", [
-    (2048, 32767, 641), (2048, 32768, 641),                # eight shares, a last filter tile of one
-    (2050, 4096, 1280), (2048, 2400, 1284),                # four
-    (8192, 2400, 640), (8191, 2336, 515),                  # two; a row short, a filter count that is no multiple of four
-    (19, 9216, 4096), (40000, 2368, 40),                   # few rows; one share
-    # a workgroup per 32 x 32 block: the k-steps and numbers of blocks where its wavefronts change, one and four words a load
-    (33, 960, 70), (33, 1024, 33), (33, 1088, 40), (31, 1984, 64), (31, 2048, 64), (2, 33, 1), (9, 256, 65),
-    (2048, 960, 100), (2049, 960, 100), (2049, 768, 37), (2049, 1088, 100),
+# (rows, terms, filters) by kernel and what its plan chose, which test_host_sanitizers.py checks on the CPU: shares of the
+# reduction (s1 to s8) in tiles of 64 x 128 and how they are exchanged, wavefronts of a 32 x 32 block, stores of fp32 outputs
+CASES = {
+    "split s8 16-bit": [(2048, 32767, 641)],                # 2^15 - 1 terms are the last in 16 bits; a last filter tile of one
+    "split s8 fp32": [(2048, 32768, 641)],
+    "split s4 16-bit": [(2050, 4096, 1280), (2048, 2400, 1284)],
+    "split s4 fp32": [(2049, 33000, 1285)],
+    "split s2 16-bit": [(8192, 2400, 640), (8191, 2336, 515), (40000, 2368, 40)],      # a row short, a filter count that is no multiple of four
+    "split s2 fp32": [(8190, 32800, 1023)],
+    "split s1 alone": [(81920, 2400, 40), (16300, 2368, 515),
+                       (2, 64, 18400001)],                  # rows so long that 64 of them take more than 32 bits of offset
+    # the k-steps and numbers of blocks where the wavefronts of a block change, one and four words a load
+    "block s8": [(19, 9216, 4096), (31, 2048, 64)],
+    "block s4": [(33, 960, 70), (33, 1024, 33), (33, 1088, 40), (31, 1984, 64), (2, 33, 1), (9, 256, 65), (2048, 960, 100),
+                 (2049, 960, 100), (2049, 768, 37), (2049, 1088, 100)],
+    "block s2": [(70001, 320, 1)],
     # many rows, the mask panel in LDS: last filters alone, in twos and in threes, whole and part tiles; 16-byte stores of rows
-    # of any length, streamed above 96 MB in rows of 128-byte lines
-    (70001, 320, 125), (70001, 320, 126), (70001, 320, 127), (70001, 320, 129), (70001, 320, 130), (70001, 320, 131),
-    (70001, 320, 132), (70001, 320, 1), (100001, 320, 160), (170001, 320, 160),
-    # outputs of 2^29 - 1 and 2^29 - 2 values: nothing that a lane must not store lands on the last ones
-    (2304167, 32, 233), (4227330, 32, 127),
-    # rows so long that 64 of them take more than 32 bits of offset
-    (2, 64, 18400001),
-])
+    # of any length
+    "direct plain": [(70001, 320, 125), (70001, 320, 126), (70001, 320, 127), (70001, 320, 129), (70001, 320, 130), (70001, 320, 131), (300001, 320, 1),
+                     (2304167, 32, 233), (4227330, 32, 127)],          # 2^29 - 1 and 2^29 - 2 values: nothing lands on the last ones
+    "direct through": [(70001, 320, 132), (100001, 320, 160)],
+    "direct streamed": [(170001, 320, 160)],                # above 96 MB in rows of 128-byte lines
+}
+
+
+@pytest.mark.parametrize("B,K,F", [c for cases in CASES.values() for c in cases])
 def test_sums_of_shares(B, K, F):
     g = torch.Generator(device=DEV)
     g.manual_seed(B + K + F)

@@ -80,6 +80,18 @@ def test_the_gpu_tests_of_the_long_reduction_kernels_reach_them(fuzz):
             assert r == (kernel, kernel), layer[0]
 
 
+def test_the_gpu_tests_of_shares_reach_the_exchanges_they_name(fuzz):
+    """Every kernel of the case lists with the shares, the exchange and the stores that the list is for."""
+    from test_gpu_rebinarize import SPLIT_LAYERS
+    from test_gpu_share_exchange import CASES
+    for name, cases in CASES.items():
+        for case, plan in zip(cases, routes(fuzz, [(B, K, 1, 1, F, 1, 0, 1) for B, K, F in cases], "plan")):
+            assert set(name.split()) <= set(plan), case
+    for layer, plan in zip(SPLIT_LAYERS, routes(fuzz, [c[1:] for c in SPLIT_LAYERS], "plan")):
+        words, shares = layer[0].split("_")[:2]
+        assert plan[:3] == ("split", words, shares) and plan[3] == ("alone" if shares == "s1" else "16-bit"), layer[0]
+
+
 def test_the_gpu_tests_of_wide_padding_reach_the_kernels_they_name(fuzz):
     from test_gpu_parity import BORDER_LAYERS
     kernels = {"persistent": "direct", "block": "block", "split": "split", "workspace": "expanded"}
