@@ -837,8 +837,8 @@ static double expanded_us(const MfmaPlan& pl, bool bits) {
 // Estimated times (us) of the kernels that read bits, for reductions of at most 36 k-steps.  Fitted to random layers of more
 // than 256 blocks, both outputs, every kernel timed on each (persistent and blocks 573 layers, rms error 12 and 9 %; split 2100
 // layers, 9 %).
-static double short_out(const DirectGeom& g, bool bits, double whole, double single) {
-    return bits ? 0.0 : 4.0e-6 * g.M * g.F * (g.F % 4 ? single : whole);    // stores of four values, of one
+static double short_out(const DirectGeom& g, bool bits, double whole, double part) {
+    return bits ? 0.0 : 4.0e-6 * g.M * g.F * (g.F % 4 ? part : whole);    // rows of whole 16-byte stores, other rows
 }
 static double short_direct_us(const DirectPlan& pl, bool bits) {
     const DirectGeom& g = pl.g;

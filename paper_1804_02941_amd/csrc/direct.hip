@@ -84,10 +84,11 @@ __device__ __forceinline__ v4i expand_a_in_place(uint32_t x, const SignMasks& m)
 // complete out of order with respect to each other, so a compiler that sees both pending waits for
 // the counter to reach zero before every use of a loaded activation word, once per round of the
 // reduction loop: the prefetch distance is gone and the loop runs at memory latency.  With the
-// stores out of its sight it counts the loads alone, which is still safe: the stores of a tile are
-// older than every load it waits for, loads complete in order among themselves, so "at most n
-// operations outstanding" with n the loads issued later implies the awaited load has landed (with
-// stores still in flight the wait is merely longer).  Stores read their operands when they issue;
+// stores out of its sight it counts the loads alone, which is safe wherever the stores lie: loads complete
+// in order among themselves, so while the awaited load is pending, so are the n loads requested behind it,
+// and more than n operations are outstanding.  Stores in flight only make a wait longer: the first loads of a
+// tile are requested in front of the stores of the tile before, so its first wait is also one for all but a few
+// of those stores.  Stores read their operands when they issue;
 // a store of more than eight bytes is followed by a wait state before its data may be overwritten.
 typedef int v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -297,7 +298,8 @@ __global__ __launch_bounds__(512) void binconv_direct_kernel(const uint32_t* __r
         }
     };
     // The first tile's first groups are requested before the panel is built, and every later tile's before the epilogue
-    // of the tile in front, so that no tile begins with a round trip to memory.  With the mask words requested before
+    // of the tile in front, so that no tile begins with a round trip of its loads (with fp32 output its first wait counts
+    // the stores of that epilogue too, so the gain there is small).  With the mask words requested before
     // the windows are worked out and the sums cleared in front of the barrier, what comes before the first multiply went from
     // 3.9 to 3.2 us: with the epilogue below, the six layers that hand bits on, batch 256, 102.7 -> 97.1 us, with fp32 output
     // 165.6 -> 163.8, 64 x 56 x 56 x 64 -> 64, 3 x 3, 25.6 -> 25.1.
@@ -781,7 +783,7 @@ __global__ __launch_bounds__(64 * WAVES) void binconv_block_kernel(const DirectG
 // windows over many channels.  A wavefront computes 64 pixels x 128 filters over a share of the
 // reduction, with both operands read as packed bits and expanded in registers: per k-step 34 vector
 // instructions beside eight multiplies, which hide them (two wavefronts per SIMD: the multiplies are
-// 60 % of the issue time).  The eight wavefronts of a workgroup are 8 / KS pixel blocks x KS shares of
+// 65 % of the issue time).  The eight wavefronts of a workgroup are 8 / KS pixel blocks x KS shares of
 // the reduction; the shares' exact partial sums are added through LDS, each wavefront finishing a
 // KS-th of the rows.  Nothing is staged, no workspace, one launch; the only barrier is that of the
 // exchange.  (The form it replaces expanded both operands into a workspace, multiplied from there and
@@ -1228,8 +1230,8 @@ bool plan_block(const dab_conv_desc& d, BlockPlan* pl, bool large) {
     const int share = ceil_div(g.nk, pl->waves * pl->lw) * pl->lw;
     if (pl->lw == 4) pl->depth = share <= 8 ? 4 : (share > 16 && share <= 32 ? 16 : 8);
     else pl->depth = share <= 8 ? 4 : (share > 16 && share <= 26 ? 13 : 8);
-    // Time of a launch, fitted to 2500 random layers of more than 36 k-steps (rms error 5 %): workgroups per compute
-    // unit of the XCD with the most filter blocks, and in each the k-steps of its wavefronts in whole bursts, at
+    // Time of a launch, fitted to random layers of more than 36 k-steps (rms error 9 %): workgroups per compute unit (they are
+    // dealt evenly over the XCDs), and in each the k-steps of its wavefronts in whole bursts, at
     // sixteen and four bytes of a pixel per load; dearer where neighbouring taps share no cache lines.
     const double per_cu = static_cast<double>(pl->grid) / kNumCU;
     const double step_us = pl->lw == 4 ? (g.T > 1 ? 0.0081 : 0.0093) : (g.T > 1 ? 0.015 : 0.0165);
