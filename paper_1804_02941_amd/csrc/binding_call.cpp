@@ -167,8 +167,7 @@ struct Entry<Fn> {
 // ones on the GPU, contiguous and not empty, numbers Python ints, no mode active.  Whatever is not so is left to the binding's
 // Python, which does the same by the entry points above or raises: the functions then return None, before anything is
 // launched.  Sizes read, the output allocated and the checks done in Python were 1 us of a call of 5: 16 x 4096 -> 4096,
-// packing and product with new outputs, 12.6 -> 10.3 us; one sketch through six layers, nine calls into kept buffers, stays where
-// its kernels are (39.1 and 40.0, runs of one side 8 % apart).
+// packing and product with new outputs, 12.6 -> 10.3 us; one sketch through six layers, nine calls into kept buffers, 38.6 -> 37.3.
 struct Unusual {};
 
 const at::Tensor& plain(PyObject* o, at::ScalarType type) {
